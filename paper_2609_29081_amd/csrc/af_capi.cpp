@@ -1091,8 +1091,8 @@ af_status af_mlp_train(const float* X, const float* y, long n, float* params, fl
     // over from the first row
     long nb = batch < n ? batch : n;
     if (row + nb > n) row = 0;
-    AF_HIP(afi::mlp_grad(X + row * afi::kMlpIn, y + row, nb, params, grad, loss_out, gws, s));
-    AF_HIP(afi::mlp_adam(params, grad, m, v, step0 + k + 1, lr, s));
+    AF_HIP(afi::mlp_step(X + row * afi::kMlpIn, y + row, nb, params, grad, m, v, step0 + k + 1, lr,
+                         loss_out, gws, s));
     row += nb;
   }
   return AF_OK;

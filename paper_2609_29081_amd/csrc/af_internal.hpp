@@ -158,6 +158,9 @@ hipError_t blend_infer(const Geo& g, const afd::Phys& ph, const double* U, const
 size_t mlp_grad_workspace(long n);
 hipError_t mlp_grad(const float* X, const float* y, long n, const float* params, float* grad,
                     float* loss, void* ws, hipStream_t s);
+// gradient and one Adam update (step counted from 1)
+hipError_t mlp_step(const float* X, const float* y, long n, float* params, float* grad, float* m,
+                    float* v, long step, float lr, float* loss, void* ws, hipStream_t s);
 hipError_t mlp_adam(float* params, const float* grad, float* m, float* v, long step, float lr,
                     hipStream_t s);
 

@@ -414,178 +414,226 @@ __global__ void k_pack(const float* __restrict__ p, unsigned char* __restrict__ 
 }
 
 // ---------------------------------------------------------------------------
-// training: gradient of the mean squared error over n samples, FP32.  Each
-// workgroup takes chunks of 64 samples, runs forward and backward through
-// LDS and accumulates its share of the gradient in registers; partial
-// gradients are then summed in a fixed order (deterministic).
+// training: gradient of the mean squared error over n samples, FP32.  A
+// workgroup (four wave64s) takes chunks of 16 samples through the forward
+// and backward pass with MFMA 16x16x4 FP32 (FP32 products and sums, as the
+// vector units form them): wave w owns hidden units 16w .. 16w+15 of every
+// layer, its slices of W1, W2 and W2^T stay in registers, and only the
+// activations and their derivatives pass through LDS.  Its share of the
+// gradient accumulates in registers; partial gradients are summed in a fixed
+// order (deterministic).
+//
+// What bounds a minibatch of 1024 rows is latency, not arithmetic (41 MFLOP,
+// 0.3 us at the matrix rate): hence chunks of the smallest matrix tile, 64
+// workgroups, and 70 matrix instructions in a row per wave (1 us).  Chunks of
+// 64 samples on the vector units, with weight rows read from LDS 64 banks
+// apart by the lanes of a wave, took 194 us per minibatch.
 // ---------------------------------------------------------------------------
-constexpr int GC = 64;          // samples per chunk
-constexpr int GT = 256;         // threads per workgroup
-constexpr int kGradBlocks = 128;
+constexpr int GC = 16;             // samples per chunk
+constexpr int GT = 256;            // threads per workgroup
+constexpr int kGradBlocks = 256;   // partial gradients at most
+// LDS rows: sample rows of 68 (activations) and 44 (inputs) floats put the 16
+// rows x 4 columns a matrix operand reads into 64 different banks
+constexpr int HS = NH + 4, XS = NIN + 4;
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 struct GradShared {
-  float W1[NH * NIN], W2[NH * NH], w3[NH], b1[NH], b2[NH];
-  float X[GC * NIN], H1[GC * NH], H2[GC * NH], A[GC * NH], dz[GC], red[GT];
+  float X[GC * XS], H1[GC * HS], A2[GC * HS], A1[GC * HS], zp[4][GC], y[GC];
 };
+
+__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// sum over the 16 lanes of each quarter of a wave
+__device__ __forceinline__ float sum16(float v) {
+#pragma unroll
+  for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+// sum over the four quarters of a wave
+__device__ __forceinline__ float sum_quarters(float v) {
+  v += __shfl_xor(v, 16, 64);
+  return v + __shfl_xor(v, 32, 64);
+}
 
 __global__ void __launch_bounds__(GT) k_grad(const float* __restrict__ X,
                                              const float* __restrict__ y, long n,
                                              const float* __restrict__ p,
                                              float* __restrict__ part, float inv_n) {
   __shared__ GradShared S;
-  const int t = threadIdx.x;
-  for (int e = t; e < NH * NIN; e += GT) S.W1[e] = p[OFF_W1 + e];
-  for (int e = t; e < NH * NH; e += GT) S.W2[e] = p[OFF_W2 + e];
-  if (t < NH) {
-    S.w3[t] = p[OFF_W3 + t];
-    S.b1[t] = p[OFF_B1 + t];
-    S.b2[t] = p[OFF_B2 + t];
+  const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+  // operand coordinates of the lane: A[c][q], B[q][c], D[4 q + r][c]
+  const int c = lane & 15, q = lane >> 4;
+  const int u = 16 * w + c;  // this lane's unit (column) in every layer
+  // B operands: W1^T and W2^T (forward) and W2 (backward), column u
+  float bW1[NIN / 4], bW2[NH / 4], bW2t[NH / 4];
+#pragma unroll
+  for (int s = 0; s < NIN / 4; ++s) bW1[s] = p[OFF_W1 + u * NIN + 4 * s + q];
+#pragma unroll
+  for (int s = 0; s < NH / 4; ++s) {
+    bW2[s] = p[OFF_W2 + u * NH + 4 * s + q];
+    bW2t[s] = p[OFF_W2 + (4 * s + q) * NH + u];
   }
-  const float b3 = p[OFF_B3];
-  float gW1[10], gW2[16], gb1 = 0.f, gb2 = 0.f, gw3 = 0.f, gb3 = 0.f, loss = 0.f;
+  const float b1 = p[OFF_B1 + u], b2 = p[OFF_B2 + u], w3 = p[OFF_W3 + u], b3 = p[OFF_B3];
+  f32x4 gW2[4], gW1[3];
 #pragma unroll
-  for (int r = 0; r < 10; ++r) gW1[r] = 0.f;
+  for (int k = 0; k < 4; ++k) gW2[k] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int r = 0; r < 16; ++r) gW2[r] = 0.f;
-  const int nu = t & 63, mg = t >> 6;  // unit and sample group of this thread
+  for (int k = 0; k < 3; ++k) gW1[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float gb1 = 0.f, gb2 = 0.f, gw3 = 0.f, gb3 = 0.f, loss = 0.f;
   const long nchunk = (n + GC - 1) / GC;
-  for (long c = blockIdx.x; c < nchunk; c += gridDim.x) {
-    const long base = c * GC;
+  for (long ch = blockIdx.x; ch < nchunk; ch += gridDim.x) {
+    const long base = ch * GC;
+    __syncthreads();  // the previous chunk is done with the LDS
+    for (int e = t; e < GC * XS; e += GT) {
+      const long row = base + e / XS;
+      S.X[e] = (row < n && e % XS < NIN) ? X[row * NIN + e % XS] : 0.f;
+    }
+    if (t < GC) S.y[t] = base + t < n ? y[base + t] : 0.f;
     __syncthreads();
-    for (int e = t; e < GC * NIN; e += GT) {
-      const long row = base + e / NIN;
-      S.X[e] = row < n ? X[row * NIN + e % NIN] : 0.f;
+    // layer 1: H1 = tanh(X W1^T + b1)
+    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < NIN / 4; ++s) acc = mfma4(S.X[c * XS + 4 * s + q], bW1[s], acc);
+    float h1[4], h2[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      h1[r] = tanhf(acc[r] + b1);
+      S.H1[(4 * q + r) * HS + u] = h1[r];
     }
     __syncthreads();
-    // layer 1
-#pragma unroll 1
-    for (int r = 0; r < 16; ++r) {
-      const int m = 16 * mg + r;
-      float a = S.b1[nu];
-#pragma unroll 8
-      for (int k = 0; k < NIN; ++k) a += S.W1[nu * NIN + k] * S.X[m * NIN + k];
-      S.H1[m * NH + nu] = tanhf(a);
+    // layer 2, and this wave's units' share of z = w3 . H2 + b3
+    acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < NH / 4; ++s) acc = mfma4(S.H1[c * HS + 4 * s + q], bW2[s], acc);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      h2[r] = tanhf(acc[r] + b2);
+      const float zs = sum16(w3 * h2[r]);
+      if (c == 0) S.zp[w][4 * q + r] = zs;
     }
     __syncthreads();
-    // layer 2
-#pragma unroll 1
-    for (int r = 0; r < 16; ++r) {
-      const int m = 16 * mg + r;
-      float a = S.b2[nu];
-#pragma unroll 8
-      for (int k = 0; k < NH; ++k) a += S.W2[nu * NH + k] * S.H1[m * NH + k];
-      S.H2[m * NH + nu] = tanhf(a);
-    }
-    __syncthreads();
-    // output, residual, dL/dz
-    if (t < GC) {
-      float z = b3;
-      for (int k = 0; k < NH; ++k) z += S.w3[k] * S.H2[t * NH + k];
-      const bool valid = base + t < n;
-      const float res = valid ? z - y[base + t] : 0.f;
+    // residuals, dL/d(layer-2 pre-activation)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = 4 * q + r;
+      const float z = ((S.zp[0][m] + S.zp[1][m]) + (S.zp[2][m] + S.zp[3][m])) + b3;
+      const float res = base + m < n ? z - S.y[m] : 0.f;
+      const float dz = 2.f * res * inv_n;
+      const float a2 = dz * w3 * (1.f - h2[r] * h2[r]);
+      gw3 += dz * h2[r];
+      gb2 += a2;
+      gb3 += dz;
       loss += res * res;
-      S.dz[t] = 2.f * res * inv_n;
+      S.A2[m * HS + u] = a2;
     }
     __syncthreads();
-    // dL/d(layer-2 pre-activation)
-#pragma unroll 1
-    for (int r = 0; r < 16; ++r) {
-      const int m = 16 * mg + r;
-      const float h2 = S.H2[m * NH + nu];
-      S.A[m * NH + nu] = S.dz[m] * S.w3[nu] * (1.f - h2 * h2);
+    // dL/d(layer-1 pre-activation) = (A2 W2) (1 - H1^2)
+    acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < NH / 4; ++s) acc = mfma4(S.A2[c * HS + 4 * s + q], bW2t[s], acc);
+    // gradient of W2, rows 16w .. 16w+15: A2^T H1 over the samples
+#pragma unroll
+    for (int s = 0; s < GC / 4; ++s) {
+      const float a = S.A2[(4 * s + q) * HS + u];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) gW2[k] = mfma4(a, S.H1[(4 * s + q) * HS + 16 * k + c], gW2[k]);
     }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float a1 = acc[r] * (1.f - h1[r] * h1[r]);
+      gb1 += a1;
+      S.A1[(4 * q + r) * HS + u] = a1;
+    }
+    // gradient of W1, rows 16w ..: A1^T X; only this wave's own columns of
+    // A1 are read, so its own LDS order suffices, but the compiler is told
     __syncthreads();
-    if (t < NH) {
-      float s3 = 0.f, s2 = 0.f;
-      for (int m = 0; m < GC; ++m) {
-        s3 += S.dz[m] * S.H2[m * NH + t];
-        s2 += S.A[m * NH + t];
+#pragma unroll
+    for (int s = 0; s < GC / 4; ++s) {
+      const float a = S.A1[(4 * s + q) * HS + u];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const int col = 16 * k + c;
+        const float x = S.X[(4 * s + q) * XS + (col < XS ? col : XS - 1)];  // columns 40.. are 0
+        gW1[k] = mfma4(a, x, gW1[k]);
       }
-      gw3 += s3;
-      gb2 += s2;
-    }
-    if (t == 0) {
-      float s = 0.f;
-#pragma unroll 8
-      for (int m = 0; m < GC; ++m) s += S.dz[m];
-      gb3 += s;
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int e = t + GT * r, o = e / NH, k = e % NH;
-      float s = 0.f;
-#pragma unroll 8
-      for (int m = 0; m < GC; ++m) s += S.A[m * NH + o] * S.H1[m * NH + k];
-      gW2[r] += s;
-    }
-    // dL/d(layer-1 pre-activation), into H2 (no longer needed)
-#pragma unroll 1
-    for (int r = 0; r < 16; ++r) {
-      const int m = 16 * mg + r;
-      float s = 0.f;
-#pragma unroll 8
-      for (int o = 0; o < NH; ++o) s += S.A[m * NH + o] * S.W2[o * NH + nu];
-      const float h1 = S.H1[m * NH + nu];
-      S.H2[m * NH + nu] = s * (1.f - h1 * h1);
-    }
-    __syncthreads();
-    if (t < NH) {
-      float s1 = 0.f;
-      for (int m = 0; m < GC; ++m) s1 += S.H2[m * NH + t];
-      gb1 += s1;
-    }
-#pragma unroll
-    for (int r = 0; r < 10; ++r) {
-      const int e = t + GT * r, o = e / NIN, k = e % NIN;
-      float s = 0.f;
-#pragma unroll 8
-      for (int m = 0; m < GC; ++m) s += S.H2[m * NH + o] * S.X[m * NIN + k];
-      gW1[r] += s;
     }
   }
   // this workgroup's partial gradient and loss sum
-  float* q = part + (long)blockIdx.x * (afi::kMlpParams + 1);
+  float* o = part + (long)blockIdx.x * (afi::kMlpParams + 1);
 #pragma unroll
-  for (int r = 0; r < 10; ++r) q[OFF_W1 + t + GT * r] = gW1[r];
+  for (int r = 0; r < 4; ++r) {
+    const int row = 16 * w + 4 * q + r;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) q[OFF_W2 + t + GT * r] = gW2[r];
-  if (t < NH) {
-    q[OFF_B1 + t] = gb1;
-    q[OFF_B2 + t] = gb2;
-    q[OFF_W3 + t] = gw3;
+    for (int k = 0; k < 4; ++k) o[OFF_W2 + row * NH + 16 * k + c] = gW2[k][r];
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      if (16 * k + c < NIN) o[OFF_W1 + row * NIN + 16 * k + c] = gW1[k][r];
   }
-  if (t == 0) q[OFF_B3] = gb3;
-  S.red[t] = t < GC ? loss : 0.f;
-  __syncthreads();
+  gb1 = sum_quarters(gb1);
+  gb2 = sum_quarters(gb2);
+  gw3 = sum_quarters(gw3);
+  gb3 = sum_quarters(gb3);  // the same sum in every lane of every wave
+  loss = sum_quarters(loss);
+  if (q == 0) {
+    o[OFF_B1 + u] = gb1;
+    o[OFF_B2 + u] = gb2;
+    o[OFF_W3 + u] = gw3;
+  }
   if (t == 0) {
-    float s = 0.f;
-    for (int k = 0; k < GC; ++k) s += S.red[k];
-    q[afi::kMlpParams] = s;
+    o[OFF_B3] = gb3;
+    o[afi::kMlpParams] = loss;
   }
 }
 
-__global__ void k_grad_sum(const float* __restrict__ part, int nparts, float* __restrict__ grad,
-                           float* __restrict__ loss, float inv_n) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e > afi::kMlpParams) return;
-  float s = 0.f;
-  for (int b = 0; b < nparts; ++b) s += part[(long)b * (afi::kMlpParams + 1) + e];
-  if (e < afi::kMlpParams)
-    grad[e] = s;
-  else if (loss)
-    *loss = s * inv_n;
-}
-
-__global__ void k_adam(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
-                       float* __restrict__ v, float lr, float c1, float c2) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= afi::kMlpParams) return;
-  const float ge = g[e];
+// one Adam update of parameter e
+__device__ __forceinline__ void adam_one(float* p, float ge, float* m, float* v, int e, float lr,
+                                         float c1, float c2) {
   const float me = 0.9f * m[e] + 0.1f * ge;
   const float ve = 0.999f * v[e] + 0.001f * ge * ge;
   m[e] = me;
   v[e] = ve;
   p[e] -= lr * (me * c1) / (sqrtf(ve * c2) + 1e-8f);
+}
+
+// Sum of the partial gradients, and (ADAM) the update that uses it: 64
+// elements a workgroup, a quarter of the partials per wave (one thread per
+// element over all 16 partials of a minibatch of 1024 took 5.3 us, and the
+// update another launch of 4.7 us)
+template <bool ADAM>
+__global__ void __launch_bounds__(256) k_grad_sum(const float* __restrict__ part, int nparts,
+                                                  float* __restrict__ grad,
+                                                  float* __restrict__ loss, float inv_n,
+                                                  float* __restrict__ p, float* __restrict__ m,
+                                                  float* __restrict__ v, float lr, float c1,
+                                                  float c2) {
+  __shared__ float sh[4][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int e = blockIdx.x * 64 + lane;
+  const int b0 = w * nparts / 4, b1 = (w + 1) * nparts / 4;
+  float s = 0.f;
+  if (e <= afi::kMlpParams) {
+#pragma unroll 8
+    for (int b = b0; b < b1; ++b) s += part[(long)b * (afi::kMlpParams + 1) + e];
+  }
+  sh[w][lane] = s;
+  __syncthreads();
+  if (w != 0 || e > afi::kMlpParams) return;
+  s = (sh[0][lane] + sh[1][lane]) + (sh[2][lane] + sh[3][lane]);
+  if (e == afi::kMlpParams) {
+    if (loss) *loss = s * inv_n;
+    return;
+  }
+  grad[e] = s;
+  if constexpr (ADAM) adam_one(p, s, m, v, e, lr, c1, c2);
+}
+
+__global__ void k_adam(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
+                       float* __restrict__ v, float lr, float c1, float c2) {
+  const int e = blockIdx.x * blockDim.x + threadIdx.x;
+  if (e < afi::kMlpParams) adam_one(p, g[e], m, v, e, lr, c1, c2);
 }
 
 }  // namespace
@@ -653,24 +701,50 @@ size_t mlp_grad_workspace(long n) {
   return sizeof(float) * (size_t)kGradBlocks * (kMlpParams + 1);
 }
 
-hipError_t mlp_grad(const float* X, const float* y, long n, const float* params, float* grad,
-                    float* loss, void* ws, hipStream_t s) {
+// bias corrections of Adam's moments after `step` updates
+static void adam_coefs(long step, float& c1, float& c2) {
+  c1 = float(1.0 / (1.0 - pow(0.9, (double)step)));
+  c2 = float(1.0 / (1.0 - pow(0.999, (double)step)));
+}
+
+// the partial gradients of the n rows; returns their number
+static int grad_parts(const float* X, const float* y, long n, const float* params, float* part,
+                      hipStream_t s) {
   const long nchunk = (n + GC - 1) / GC;
   const int nb = (int)(nchunk < kGradBlocks ? nchunk : kGradBlocks);
+  hipLaunchKernelGGL(k_grad, dim3(nb), dim3(GT), 0, s, X, y, n, params, part, 1.0f / float(n));
+  return nb;
+}
+
+constexpr int kSumBlocks = (int)((kMlpParams + 1 + 63) / 64);
+
+hipError_t mlp_grad(const float* X, const float* y, long n, const float* params, float* grad,
+                    float* loss, void* ws, hipStream_t s) {
   float* part = (float*)ws;
-  const float inv_n = 1.0f / float(n);
-  hipLaunchKernelGGL(k_grad, dim3(nb), dim3(GT), 0, s, X, y, n, params, part, inv_n);
-  hipLaunchKernelGGL(k_grad_sum, dim3((kMlpParams + 1 + 255) / 256), dim3(256), 0, s,
-                     (const float*)part, nb, grad, loss, inv_n);
+  const int nb = grad_parts(X, y, n, params, part, s);
+  hipLaunchKernelGGL((k_grad_sum<false>), dim3(kSumBlocks), dim3(256), 0, s, (const float*)part,
+                     nb, grad, loss, 1.0f / float(n), (float*)nullptr, (float*)nullptr,
+                     (float*)nullptr, 0.f, 0.f, 0.f);
+  return hipGetLastError();
+}
+
+hipError_t mlp_step(const float* X, const float* y, long n, float* params, float* grad, float* m,
+                    float* v, long step, float lr, float* loss, void* ws, hipStream_t s) {
+  float* part = (float*)ws;
+  const int nb = grad_parts(X, y, n, params, part, s);
+  float c1, c2;
+  adam_coefs(step, c1, c2);
+  hipLaunchKernelGGL((k_grad_sum<true>), dim3(kSumBlocks), dim3(256), 0, s, (const float*)part, nb,
+                     grad, loss, 1.0f / float(n), params, m, v, lr, c1, c2);
   return hipGetLastError();
 }
 
 hipError_t mlp_adam(float* params, const float* grad, float* m, float* v, long step, float lr,
                     hipStream_t s) {
-  const double c1 = 1.0 / (1.0 - pow(0.9, (double)step));
-  const double c2 = 1.0 / (1.0 - pow(0.999, (double)step));
+  float c1, c2;
+  adam_coefs(step, c1, c2);
   hipLaunchKernelGGL(k_adam, dim3((kMlpParams + 255) / 256), dim3(256), 0, s, params, grad, m, v,
-                     lr, float(c1), float(c2));
+                     lr, c1, c2);
   return hipGetLastError();
 }
 
