@@ -267,12 +267,12 @@ af_status af_reset_flags(af_ctx* ctx, void* ws, void* stream);
  * each kernel kind below, the number of launches and their summed duration
  * in milliseconds since the previous read (arrays of AF_K_COUNT entries). */
 enum {
-  AF_K_LATTICE = 0,  /* 1D: half-lattice values, centres, auxiliaries */
-  AF_K_GRAD = 1,     /* 1D: lattice gradients                          */
-  AF_K_CELLPRE = 2,  /* 1D: per-cell low-order data                    */
-  AF_K_FACE = 3,     /* 1D: limited face fluxes                         */
-  AF_K_CELLS = 4,    /* 1D: cell-average update                         */
-  AF_K_POINTS = 5,   /* 1D: point-value update                          */
+  AF_K_LATTICE = 0,  /* 1D: the stage kernel                            */
+  AF_K_GRAD = 1,     /* 1 to 5: no kernel of the library                */
+  AF_K_CELLPRE = 2,
+  AF_K_FACE = 3,
+  AF_K_CELLS = 4,
+  AF_K_POINTS = 5,
   AF_K_CFL = 6,      /* time-step reduction                             */
   AF_K_STAGE2D = 7,  /* 2D: the fused stage kernel                      */
   AF_K_BLEND = 8,    /* 2D: the learned blend's features and network   */

@@ -194,16 +194,6 @@ hipError_t launch_coef(const afi::Geo& g, const afd::Phys& ph, const afi::Work& 
                        afi::StageCoef sc, const double* Un, const double* Uk, double* Uout,
                        const double* dt_dev, double dt_host, hipStream_t s, afi::Timer* tm) {
   if (!Un) Un = Uk;
-  if (sc.dt_mul != 1.0) {
-    // the stage's step as its own device scalar (the spare workspace slot)
-    if (dt_dev) {
-      hipError_t e = afi::scaled_scalar(w.scal + 3, dt_dev, sc.dt_mul, s);
-      if (e != hipSuccess) return e;
-      dt_dev = w.scal + 3;
-    } else {
-      dt_host *= sc.dt_mul;
-    }
-  }
   if (g.dim == 2 && (ph.lim & afd::LIM_LEARNED)) {
     // the network's blend from this stage's input, then the stage
     if (!w.net) return hipErrorInvalidValue;
@@ -216,11 +206,21 @@ hipError_t launch_coef(const afi::Geo& g, const afd::Phys& ph, const afi::Work& 
                     : afi::stage2d(g, ph, w, Un, Uk, Uout, dt_dev, dt_host, sc, s, tm);
 }
 
+// what the stages of a 1D step do beside it: fix dt in the first one, keep
+// the run's time in the last one
+struct StepExtras {
+  afi::StageCoef::Cfl cfl = {};
+  double* adv = nullptr;
+};
+
 hipError_t launch_stage(const afi::Geo& g, const afd::Phys& ph, const afi::Work& w, int k,
                         const double* Un, const double* Uk, double* Uout, const double* dt_dev,
-                        double dt_host, hipStream_t s, afi::Timer* tm, bool in_step = true) {
+                        double dt_host, hipStream_t s, afi::Timer* tm, bool in_step = true,
+                        const StepExtras& x = {}) {
   afi::StageCoef sc = kCoef[k];
   sc.skip_flagged = in_step ? 1 : 0;
+  if (k == 0) sc.cfl = x.cfl;
+  if (k == 2) sc.adv = x.adv;
   return launch_coef(g, ph, w, sc, Un, Uk, Uout, dt_dev, dt_host, s, tm);
 }
 
@@ -247,7 +247,7 @@ constexpr double kB54 = 0.226007483236906;
 // for rk3 (five stage inputs)
 hipError_t rk54(const afi::Geo& g, const afd::Phys& ph, const afi::Work& w, const double* u0,
                 double* A, double* B, double* X, const double* dt_dev, double dt, hipStream_t s,
-                afi::Timer* tm, const double* const* src = nullptr) {
+                afi::Timer* tm, const double* const* src = nullptr, const StepExtras& x = {}) {
   auto coef = [](double a, double b, double mul) {
     afi::StageCoef c{};
     c.a = a;
@@ -260,26 +260,38 @@ hipError_t rk54(const afi::Geo& g, const afd::Phys& ph, const afi::Work& w, cons
   const long n = g.state_len;
   hipError_t e;
   auto S = [&](int k) { return src ? src[k] : nullptr; };
-  if ((e = launch_coef(g, ph, w, coef(0.0, 1.0, kB10), u0, u0, A, dt_dev, dt, s, tm)) != hipSuccess)
+  afi::StageCoef c0 = coef(0.0, 1.0, kB10);
+  c0.cfl = x.cfl;
+  if ((e = launch_coef(g, ph, w, c0, u0, u0, A, dt_dev, dt, s, tm)) != hipSuccess)
     return e;  // A = u1
   if ((e = add_source(g, A, kB10 * dt, S(0), s)) != hipSuccess) return e;
   if ((e = launch_coef(g, ph, w, coef(kA20, kA21, kB21 / kA21), u0, A, B, dt_dev, dt, s, tm)) !=
       hipSuccess)
     return e;  // B = u2
   if ((e = add_source(g, B, kB21 * dt, S(1), s)) != hipSuccess) return e;
-  if ((e = launch_coef(g, ph, w, coef(kA30, kA32, kB32 / kA32), u0, B, A, dt_dev, dt, s, tm)) !=
+  if ((e = launch_coef(g, ph, w, coef(kA30, kA32, kB32 / kA32), u0, B, X, dt_dev, dt, s, tm)) !=
       hipSuccess)
-    return e;  // A = u3
-  if ((e = add_source(g, A, kB32 * dt, S(2), s)) != hipSuccess) return e;
-  if ((e = launch_coef(g, ph, w, coef(0.0, 1.0, kB43 / kA43), u0, A, X, dt_dev, dt, s, tm)) !=
-      hipSuccess)
-    return e;  // X = E3
-  if ((e = add_source(g, X, kB43 / kA43 * dt, S(3), s)) != hipSuccess) return e;
-  if ((e = afi::lincomb(A, kA40, u0, kA43, X, n, s)) != hipSuccess) return e;   // A = u4
-  if ((e = afi::lincomb(B, kA52, B, kA53, X, n, s)) != hipSuccess) return e;    // B = a52 u2 + a53 E3
-  if ((e = launch_coef(g, ph, w, coef(1.0, kA54, kB54 / kA54), B, A, X, dt_dev, dt, s, tm)) !=
-      hipSuccess)
-    return e;
+    return e;  // X = u3
+  if ((e = add_source(g, X, kB32 * dt, S(2), s)) != hipSuccess) return e;
+  // E3 = FE(u3): A = u4 = a40 u0 + a43 E3 and B = a52 u2 + a53 E3, in the 1D
+  // stage itself where no source comes between
+  afi::StageCoef c3 = coef(0.0, 1.0, kB43 / kA43);
+  if (g.dim == 1 && !src) {
+    c3.acc = B;
+    c3.wa = kA40;
+    c3.wb = kA43;
+    c3.ga = kA52;
+    c3.gb = kA53;
+    if ((e = launch_coef(g, ph, w, c3, u0, X, A, dt_dev, dt, s, tm)) != hipSuccess) return e;
+  } else {
+    if ((e = launch_coef(g, ph, w, c3, u0, X, A, dt_dev, dt, s, tm)) != hipSuccess) return e;
+    if ((e = add_source(g, A, kB43 / kA43 * dt, S(3), s)) != hipSuccess) return e;
+    if ((e = afi::lincomb(B, kA52, B, kA53, A, n, s)) != hipSuccess) return e;
+    if ((e = afi::lincomb(A, kA40, u0, kA43, A, n, s)) != hipSuccess) return e;
+  }
+  afi::StageCoef c4 = coef(1.0, kA54, kB54 / kA54);
+  c4.adv = x.adv;
+  if ((e = launch_coef(g, ph, w, c4, B, A, X, dt_dev, dt, s, tm)) != hipSuccess) return e;
   return add_source(g, X, kB54 * dt, S(4), s);
 }
 
@@ -291,9 +303,91 @@ hipError_t launch_cfl(const af_ctx* c, const afi::Geo& g, const afi::Work& w, co
                      U, t_host, t_dev, t_final, dt_out, s, c->timer);
 }
 
+// the CFL step of a 1D stage that fixes dt itself, as launch_cfl takes it
+afi::StageCoef::Cfl stage_cfl(const af_ctx* c, const afi::Geo& g, double t_host,
+                              const double* t_dev, double t_final) {
+  const af_params& p = c->p;
+  afi::StageCoef::Cfl f;
+  f.on = 1;
+  f.icx = 1.0 / (p.cfl_c * g.dx);
+  f.vcoef = fmax(4.0 * p.mu / 3.0, p.gamma * p.mu / p.Pr) / (p.cfl_v * g.dx * g.dx);
+  f.t_host = t_host;
+  f.t_dev = t_dev;
+  f.t_final = t_final;
+  return f;
+}
+
 af_status read_flags(const afi::Work& w, hipStream_t s, unsigned* out) {
   AF_HIP(hipMemcpyAsync(out, w.flags, sizeof(unsigned), hipMemcpyDeviceToHost, s));
   AF_HIP(hipStreamSynchronize(s));
+  return AF_OK;
+}
+
+// Host slots that a kernel writes the step scalars and flag word to: 64 slots
+// of one pinned page per process, taken for the time of one call.  A call that
+// finds none (or no pinned memory) copies from the device instead.
+class HostSlots {
+ public:
+  afi::StepReport* take() {
+    std::lock_guard<std::mutex> lock(mu_);
+    if (!tried_) {
+      tried_ = true;
+      void* p = nullptr;
+      if (hipHostMalloc(&p, kSlots * sizeof(afi::StepReport),
+                        hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
+        for (int i = 0; i < kSlots; ++i) free_.push_back((afi::StepReport*)p + i);
+      else
+        (void)hipGetLastError();
+    }
+    if (free_.empty()) return nullptr;
+    afi::StepReport* r = free_.back();
+    free_.pop_back();
+    return r;
+  }
+  void give(afi::StepReport* r) {
+    std::lock_guard<std::mutex> lock(mu_);
+    if (r) free_.push_back(r);
+  }
+
+ private:
+  static constexpr int kSlots = 64;
+  std::mutex mu_;
+  bool tried_ = false;
+  std::vector<afi::StepReport*> free_;
+};
+HostSlots g_slots;
+
+struct SlotHolder {
+  afi::StepReport* slot;
+  SlotHolder() : slot(g_slots.take()) {}
+  ~SlotHolder() { g_slots.give(slot); }
+  SlotHolder(const SlotHolder&) = delete;
+  SlotHolder& operator=(const SlotHolder&) = delete;
+};
+
+// the device scalars (dt, t, steps) and the flag word: written by a kernel to
+// the call's host slot, or else in one copy (they are the first two entries
+// of the workspace).  A copy to pageable memory costs a synchronous call about
+// 15 us whatever its size.
+af_status read_scalars(const afi::Work& w, hipStream_t s, afi::StepReport* slot, double* sc,
+                       unsigned* flags) {
+  afi::StepReport r;
+  if (slot) {
+    AF_HIP(afi::report(w, slot, s));
+    AF_HIP(hipStreamSynchronize(s));
+    r = *slot;
+  } else {
+    char buf[512];
+    const size_t at = (size_t)((const char*)w.flags - (const char*)w.scal);
+    const size_t bytes = at + sizeof(unsigned);
+    if (bytes > sizeof(buf)) return fail(AF_E_HIP, "workspace layout");
+    AF_HIP(hipMemcpyAsync(buf, w.scal, bytes, hipMemcpyDeviceToHost, s));
+    AF_HIP(hipStreamSynchronize(s));
+    memcpy(r.scal, buf, sizeof(r.scal));
+    memcpy(&r.flags, buf + at, sizeof(unsigned));
+  }
+  memcpy(sc, r.scal, sizeof(r.scal));
+  *flags = r.flags;
   return AF_OK;
 }
 
@@ -323,9 +417,10 @@ af_status scratch_on_current_device(void** out) {
 // forward Euler step then adds tau S_k after its limited update
 hipError_t rk3(const afi::Geo& g, const afd::Phys& ph, const afi::Work& w, const double* cur,
                double* out, const double* dt_dev, double dt, hipStream_t s, afi::Timer* tm,
-               const double* const* src = nullptr) {
+               const double* const* src = nullptr, const StepExtras& x = {}) {
   hipError_t e;
-  if ((e = launch_stage(g, ph, w, 0, cur, cur, w.S1, dt_dev, dt, s, tm)) != hipSuccess) return e;
+  if ((e = launch_stage(g, ph, w, 0, cur, cur, w.S1, dt_dev, dt, s, tm, true, x)) != hipSuccess)
+    return e;
   if (src && (e = add_source(g, w.S1, dt, src[0], s)) != hipSuccess) return e;
   if ((e = launch_stage(g, ph, w, 1, cur, w.S1, w.S2, dt_dev, dt, s, tm)) != hipSuccess) return e;
   if (src && (e = add_source(g, w.S2, 0.25 * dt, src[1], s)) != hipSuccess) return e;
@@ -689,8 +784,9 @@ af_status af_reset_flags(af_ctx* c, void* ws, void* stream) {
   return AF_OK;
 }
 
-af_status af_step(af_ctx* c, double* U, void* ws, void* stream, double dt, double t,
-                  double t_final, double* dt_used, int* halvings) {
+// af_step, its results read through slot (NULL: by a copy)
+static af_status step_in(af_ctx* c, double* U, void* ws, void* stream, double dt, double t,
+                         double t_final, double* dt_used, int* halvings, afi::StepReport* slot) {
   if (!c || !U || !ws) return fail(AF_E_ARG, "af_step: NULL argument");
   if (!net_ready(c)) return AF_E_ARG;
   if (!(t_final >= t)) return fail(AF_E_ARG, "t_final < t");
@@ -699,26 +795,36 @@ af_status af_step(af_ctx* c, double* U, void* ws, void* stream, double dt, doubl
   const afi::Work w = work_of(c, g, ws);
   const hipStream_t s = (hipStream_t)stream;
   const afd::Phys ph = physics(c->p);
-  AF_HIP(afi::copy_state(w.SAVE, U, g.state_len, s));
+  AF_HIP(afi::copy_state(w.SAVE, U, g.state_len, s, w.flags));
+  // the CFL step stays on the device for the first attempt; the host reads it
+  // with the flags
+  const double* dt_dev = nullptr;
+  StepExtras x;
   if (dt <= 0.0) {
-    AF_HIP(launch_cfl(c, g, w, U, t, nullptr, t_final, w.scal, s));
-    AF_HIP(hipMemcpyAsync(&dt, w.scal, sizeof(double), hipMemcpyDeviceToHost, s));
-    AF_HIP(hipStreamSynchronize(s));
+    dt_dev = w.scal;
+    if (afi::stage1d_takes_cfl(g))
+      x.cfl = stage_cfl(c, g, t, nullptr, t_final);
+    else
+      AF_HIP(launch_cfl(c, g, w, U, t, nullptr, t_final, w.scal, s));
   } else if (t + dt > t_final) {
     dt = t_final - t;
   }
   unsigned fl = 0;
   int h;
   for (h = 0; h <= c->p.max_halvings; ++h) {
-    AF_HIP(afi::clear_flags(w, s));
+    if (h > 0) AF_HIP(afi::clear_flags(w, s));
     if (c->p.rk == 54)
-      AF_HIP(rk54(g, ph, w, w.SAVE, w.S1, w.S2, U, nullptr, dt, s, c->timer));
+      AF_HIP(rk54(g, ph, w, w.SAVE, w.S1, w.S2, U, dt_dev, dt, s, c->timer, nullptr, x));
     else
-      AF_HIP(rk3(g, ph, w, w.SAVE, U, nullptr, dt, s, c->timer));
-    af_status st = read_flags(w, s, &fl);
+      AF_HIP(rk3(g, ph, w, w.SAVE, U, dt_dev, dt, s, c->timer, nullptr, x));
+    double sc[3];
+    af_status st = read_scalars(w, s, slot, sc, &fl);
     if (st != AF_OK) return st;
+    if (dt_dev) dt = sc[0];
     if (fl == 0) break;
     dt *= 0.5;
+    dt_dev = nullptr;
+    x = {};
   }
   if (dt_used) *dt_used = dt;
   if (halvings) *halvings = h;
@@ -729,6 +835,12 @@ af_status af_step(af_ctx* c, double* U, void* ws, void* stream, double dt, doubl
     return fail(AF_E_PP, "low-order states inadmissible after %d halvings (flags %u)", h - 1, fl);
   }
   return AF_OK;
+}
+
+af_status af_step(af_ctx* c, double* U, void* ws, void* stream, double dt, double t,
+                  double t_final, double* dt_used, int* halvings) {
+  SlotHolder slot;
+  return step_in(c, U, ws, stream, dt, t, t_final, dt_used, halvings, slot.slot);
 }
 
 af_status af_step_noalloc(af_ctx* c, double* U, void* stream, double dt, double t,
@@ -745,7 +857,8 @@ af_status af_step_noalloc(af_ctx* c, double* U, void* stream, double dt, double 
   void* ws = nullptr;
   const af_status st = scratch_on_current_device(&ws);
   if (st != AF_OK) return st;
-  return af_step(c, U, ws, stream, dt, t, t_final, dt_used, halvings);
+  // no host slot: taking the process's first one allocates pinned memory
+  return step_in(c, U, ws, stream, dt, t, t_final, dt_used, halvings, nullptr);
 }
 
 af_status af_run(af_ctx* c, double* U, void* ws, void* stream, double t0, double t_final,
@@ -769,41 +882,43 @@ af_status af_run(af_ctx* c, double* U, void* ws, void* stream, double t0, double
   double t = t0;
   long done = 0;
   af_status status = AF_OK;
-  double sc[4];
+  double sc[3];
   unsigned fl = 0;
-  auto read_back = [&]() -> af_status {
-    AF_HIP(hipMemcpyAsync(sc, w.scal, 3 * sizeof(double), hipMemcpyDeviceToHost, s));
-    AF_HIP(hipMemcpyAsync(&fl, w.flags, sizeof(unsigned), hipMemcpyDeviceToHost, s));
-    AF_HIP(hipStreamSynchronize(s));
-    return AF_OK;
-  };
-  auto three_stages = [&](int from) -> hipError_t {
+  SlotHolder slot;
+  auto read_back = [&]() { return read_scalars(w, s, slot.slot, sc, &fl); };
+  auto three_stages = [&](int from, const StepExtras& x = {}) -> hipError_t {
     if (rk54s)
       return rk54(g, ph, w, bufs[from], bufs[(from + 1) % 4], bufs[(from + 2) % 4],
-                  bufs[(from + 3) % 4], w.scal, 0.0, s, c->timer);
+                  bufs[(from + 3) % 4], w.scal, 0.0, s, c->timer, nullptr, x);
     const int a = (from + 1) % 3, b = (from + 2) % 3;
     hipError_t e;
     if ((e = launch_stage(g, ph, w, 0, bufs[from], bufs[from], bufs[a], w.scal, 0.0, s,
-                          c->timer)) != hipSuccess)
+                          c->timer, true, x)) != hipSuccess)
       return e;
     if ((e = launch_stage(g, ph, w, 1, bufs[from], bufs[a], bufs[b], w.scal, 0.0, s,
                           c->timer)) != hipSuccess)
       return e;
-    return launch_stage(g, ph, w, 2, bufs[from], bufs[b], bufs[a], w.scal, 0.0, s, c->timer);
+    return launch_stage(g, ph, w, 2, bufs[from], bufs[b], bufs[a], w.scal, 0.0, s, c->timer, true,
+                        x);
   };
+  // in 1D the stages of a block's step fix dt and keep the time themselves
+  StepExtras in_stages;
+  const bool cfl_in_stage = afi::stage1d_takes_cfl(g);
+  if (cfl_in_stage) in_stages.cfl = stage_cfl(c, g, 0.0, w.scal + 1, t_final);
+  if (g.dim == 1) in_stages.adv = w.scal;
   AF_HIP(afi::set_scalar(w.scal + 1, t, s));
   while (done < max_steps && t < t_final) {
     const long K = (max_steps - done) < check_every ? (max_steps - done) : check_every;
     if (K > 1) {
       // optimistic block of K steps with one synchronisation at its end
-      AF_HIP(afi::copy_state(w.SAVE, bufs[cur], g.state_len, s));
+      AF_HIP(afi::copy_state(w.SAVE, bufs[cur], g.state_len, s, w.flags));
       AF_HIP(afi::set_scalar(w.scal + 2, 0.0, s));
-      AF_HIP(afi::clear_flags(w, s));
       int c2 = cur;
       for (long k = 0; k < K; ++k) {
-        AF_HIP(launch_cfl(c, g, w, bufs[c2], 0.0, w.scal + 1, t_final, w.scal, s));
-        AF_HIP(three_stages(c2));
-        AF_HIP(afi::advance_time(w, s));
+        if (!cfl_in_stage)
+          AF_HIP(launch_cfl(c, g, w, bufs[c2], 0.0, w.scal + 1, t_final, w.scal, s));
+        AF_HIP(three_stages(c2, in_stages));
+        if (!in_stages.adv) AF_HIP(afi::advance_time(w, s));
         c2 = next(c2);
       }
       if ((status = read_back()) != AF_OK) break;
@@ -1129,8 +1244,7 @@ af_status af_step_source(af_ctx* c, double* U, void* ws, void* stream, double dt
   const afi::Work w = work_of(c, g, ws);
   const hipStream_t s = (hipStream_t)stream;
   const afd::Phys ph = physics(c->p);
-  AF_HIP(afi::copy_state(w.SAVE, U, g.state_len, s));
-  AF_HIP(afi::clear_flags(w, s));
+  AF_HIP(afi::copy_state(w.SAVE, U, g.state_len, s, w.flags));
   if (c->p.rk == 54)
     AF_HIP(rk54(g, ph, w, w.SAVE, w.S1, w.S2, U, nullptr, dt, s, c->timer, src));
   else

@@ -133,6 +133,13 @@ __global__ void k_clear_flags(unsigned* flags) {
   if (threadIdx.x == 0 && blockIdx.x == 0) flags[0] = 0u;
 }
 
+__global__ void k_report(const double* scal, const unsigned* flags, afi::StepReport* out) {
+  if (threadIdx.x < 3)
+    out->scal[threadIdx.x] = scal[threadIdx.x];
+  else if (threadIdx.x == 3)
+    out->flags = flags[0];
+}
+
 __global__ void k_set(double* p, double v) {
   if (threadIdx.x == 0 && blockIdx.x == 0) p[0] = v;
 }
@@ -143,18 +150,15 @@ __global__ void __launch_bounds__(kBlock) k_lincomb(double* out, double a, const
     out[q] = a * x[q] + b * y[q];
 }
 
-__global__ void k_scaled(double* dst, const double* src, double f) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) dst[0] = f * src[0];
-}
-
 __global__ void k_scale(double* p, double f) {
   if (threadIdx.x == 0 && blockIdx.x == 0) p[0] = p[0] * f;
 }
 
 __global__ void __launch_bounds__(kBlock) k_copy(double* __restrict__ d, const double* __restrict__ s,
-                                                 long n) {
+                                                 long n, unsigned* flags) {
   for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x)
     d[i] = s[i];
+  if (flags && blockIdx.x == 0 && threadIdx.x == 0) flags[0] = 0u;
 }
 
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
@@ -288,11 +292,6 @@ namespace afi {
 
 // carve the workspace; with base == nullptr only the size is computed
 size_t workspace_layout(const Geo& g, Work* w, char* base) {
-  const int nc = g.dim == 1 ? 3 : 4;
-  const int naux = g.dim == 1 ? 4 : 5;
-  const int ngrad = g.dim == 1 ? 2 : 6;
-  const int ncp = g.dim == 1 ? 10 : 18;
-  const long ncells_ring = g.dim == 1 ? (long)(g.n1 + 2) : (long)(g.n1 + 2) * (g.n2 + 2);
   const long nfx = g.dim == 1 ? (long)(g.n1 + 1) : (long)(g.n1 + 1) * g.n2;
   const long nfy = g.dim == 1 ? 0 : (long)g.n1 * (g.n2 + 1);
   size_t off = 0;
@@ -308,14 +307,11 @@ size_t workspace_layout(const Geo& g, Work* w, char* base) {
   r.nb_cfl = kMaxCflBlocks;
   r.partial = (double*)take(2 * sizeof(double) * kMaxCflBlocks);
   if (g.dim == 1) {
-    // the 1D stage passes its lattice, gradient, cell and face data through
-    // device memory; the 2D stage keeps them in LDS
-    r.LU = (double*)take(sizeof(double) * nc * g.ns);
-    r.LA = (double*)take(sizeof(double) * naux * g.ns);
-    r.LG = (double*)take(sizeof(double) * ngrad * g.ns);
-    r.CP = (double*)take(sizeof(double) * ncp * ncells_ring);
-    r.FX = (double*)take(sizeof(double) * nc * nfx);
-    r.FY = (double*)take(sizeof(double) * nc * (nfy > 0 ? nfy : 1));
+    // not used: the 1D stage keeps its lattice and cell data in LDS.  The room
+    // stays in the layout, because the size of a workspace decides which
+    // grids af_step_noalloc takes
+    for (long n : {3 * g.ns, 4 * g.ns, 2 * g.ns, 10L * (g.n1 + 2), 3L * (g.n1 + 1), 3L})
+      take(sizeof(double) * n);
   }
   r.S1 = (double*)take(sizeof(double) * g.state_len);
   r.S2 = (double*)take(sizeof(double) * g.state_len);
@@ -361,6 +357,12 @@ hipError_t advance_time(const Work& w, hipStream_t s) {
 
 hipError_t clear_flags(const Work& w, hipStream_t s) {
   hipLaunchKernelGGL(k_clear_flags, dim3(1), dim3(64), 0, s, w.flags);
+  return hipGetLastError();
+}
+
+hipError_t report(const Work& w, StepReport* out, hipStream_t s) {
+  hipLaunchKernelGGL(k_report, dim3(1), dim3(64), 0, s, (const double*)w.scal,
+                     (const unsigned*)w.flags, out);
   return hipGetLastError();
 }
 
@@ -432,16 +434,11 @@ hipError_t lincomb(double* out, double a, const double* x, double b, const doubl
   return hipGetLastError();
 }
 
-hipError_t scaled_scalar(double* dst, const double* src, double f, hipStream_t s) {
-  hipLaunchKernelGGL(k_scaled, dim3(1), dim3(64), 0, s, dst, src, f);
-  return hipGetLastError();
-}
-
-hipError_t copy_state(double* dst, const double* src, long n, hipStream_t s) {
+hipError_t copy_state(double* dst, const double* src, long n, hipStream_t s, unsigned* flags) {
   long nb = (n + kBlock - 1) / kBlock;
   if (nb > 4096) nb = 4096;
   if (nb < 1) nb = 1;
-  hipLaunchKernelGGL(k_copy, dim3((unsigned)nb), dim3(kBlock), 0, s, dst, src, n);
+  hipLaunchKernelGGL(k_copy, dim3((unsigned)nb), dim3(kBlock), 0, s, dst, src, n, flags);
   return hipGetLastError();
 }
 

@@ -88,12 +88,6 @@ struct Work {
   unsigned long long* count;  // result of the admissibility count
   double* partial;   // CFL partial maxima [2][nb_cfl]
   int nb_cfl;
-  double* LU;        // lattice conservative values  [ncomp][ns]
-  double* LA;        // lattice auxiliaries          [naux][ns]
-  double* LG;        // lattice gradients            [ngrad][ns]
-  double* CP;        // per-cell low-order data      [ncp][ncells incl. ring]
-  double* FX;        // limited x-face fluxes
-  double* FY;        // limited y-face fluxes (2D)
   double* S1;        // stage buffers and checkpoint (one state each)
   double* S2;
   double* S3;        // fourth stage buffer of SSP-RK54
@@ -127,6 +121,19 @@ struct StageCoef {
   float* ts_out;
   // the forward-Euler step is dt_mul * dt (the stages of SSP-RK54)
   double dt_mul = 1.0;
+  // 1D only, the rest.  acc != NULL (SSP-RK54's shared evaluation o): the
+  // stage writes Uout = wa Un + wb o and acc = ga acc + gb o in place of o
+  double* acc = nullptr;
+  double wa = 0.0, wb = 0.0, ga = 0.0, gb = 0.0;
+  // the stage fixes the step's dt itself (eq. cfl, from its input's averages,
+  // as k_cfl takes it) and leaves it in scal[0]
+  struct Cfl {
+    int on;
+    double icx, vcoef, t_host, t_final;
+    const double* t_dev;
+  } cfl = {};
+  // the stage ends an accepted step: t += dt, one step more (scal[1], scal[2])
+  double* adv = nullptr;
 };
 
 size_t workspace_layout(const Geo& g, Work* w, char* base);
@@ -169,6 +176,9 @@ hipError_t mlp_adam(float* params, const float* grad, float* m, float* v, long s
 hipError_t stage2d(const Geo& g, const afd::Phys& ph, const Work& w, const double* Un,
                    const double* Uk, double* Uout, const double* dt_dev, double dt_host,
                    StageCoef sc, hipStream_t s, Timer* tm);
+// whether a 1D stage of this grid can fix dt itself (every workgroup reads
+// all averages, which pays while they are few)
+bool stage1d_takes_cfl(const Geo& g);
 hipError_t stage1d(const Geo& g, const afd::Phys& ph, const Work& w, const double* Un,
                    const double* Uk, double* Uout, const double* dt_dev, double dt_host,
                    StageCoef sc, hipStream_t s, Timer* tm);
@@ -178,12 +188,19 @@ hipError_t cfl_dt(const Geo& g, const afd::Phys& ph, double cfl_c, double cfl_v,
                   Timer* tm);
 hipError_t advance_time(const Work& w, hipStream_t s);
 hipError_t clear_flags(const Work& w, hipStream_t s);
-hipError_t copy_state(double* dst, const double* src, long n, hipStream_t s);
+// the step scalars (dt, t, steps) and the flag word into host memory that the
+// device can write
+struct alignas(64) StepReport {
+  double scal[3];
+  unsigned flags;
+};
+hipError_t report(const Work& w, StepReport* out, hipStream_t s);
+// a state; flags, if not NULL, is a flag word cleared with it
+hipError_t copy_state(double* dst, const double* src, long n, hipStream_t s,
+                      unsigned* flags = nullptr);
 // out = a x + b y over n values (out may be x or y)
 hipError_t lincomb(double* out, double a, const double* x, double b, const double* y, long n,
                    hipStream_t s);
-// *dst = f * *src (device scalars)
-hipError_t scaled_scalar(double* dst, const double* src, double f, hipStream_t s);
 hipError_t set_scalar(double* dst, double v, hipStream_t s);
 hipError_t scale_scalar(double* dst, double f, hipStream_t s);
 // number of DOF sites of state U whose density or pressure is not positive

@@ -1,8 +1,23 @@
 // af_kern1d.hip -- one SSP-RK3 stage of the 1D compact AF method (Sec. 2.1)
-// on gfx950, FP64.  Same pipeline as the 2D stage (lattice, gradients,
-// per-cell low-order data, limited face fluxes, cell update, point update),
-// with U = (rho, rho u, E), W = (rho, u, p), Z = (0, u, T) and
+// on gfx950, FP64, as one launch.  Same pipeline as the 2D stage (lattice,
+// gradients, per-cell low-order data, limited face fluxes, cell update, point
+// update), with U = (rho, rho u, E), W = (rho, u, p), Z = (0, u, T) and
 //   K(W) = [[0,0,0],[0,4mu/3,0],[0,4mu u/3,kappa]].
+//
+// The 1D problems are small (hundreds of cells), so a stage is bound by
+// latency: launches, and the chain of dependent FP64 operations.  A workgroup
+// of three wave64s takes 61 cells and the points at their lower sides, and
+// passes everything through LDS with one barrier:
+//   before it  waves 0-1 one lattice site each (values, centres, primitives),
+//              wave 2 one cell each of the tile +- 1 (low-order data); and, in
+//              the first stage of a step that fixes dt, all three the CFL
+//              maxima of the whole grid (each workgroup for itself: the
+//              averages of a small grid are a few loads per thread, where the
+//              reduction as kernels of its own cost two launches)
+//   after it   wave 0 one face each (limited flux), whose neighbours' fluxes
+//              come by a lane shift to the cell update; wave 1 one point each
+// 61 cells are the most for which sites (2 x 61 + 5), ring cells (63) and
+// faces (62) fit one per lane.
 #include "af_device.hpp"
 #include "af_internal.hpp"
 
@@ -10,23 +25,33 @@ using namespace afd;
 
 namespace {
 
-constexpr int kBlock = 256;
+constexpr int kCells = 61, kThreads = 192;
+constexpr int kSites = 2 * kCells + 5, kRing = kCells + 2;
+static_assert(kSites <= 128 && kRing <= 64, "one site and one ring cell per lane");
 
 struct G1 {
-  int n, np, LX;
+  int n, np;
   long off_pts;
   int bc0, bc1;
   double dx;
   double dl[3], dr[3];  // states of Dirichlet sides (x-low, x-high)
-  // inside a step attempt: stop once the attempt's flag word is set (it is
-  // rejected and the stage output is never read)
-  int skip_flagged;
-  unsigned* fl;
 };
 
-__device__ __forceinline__ bool rejected(const G1& g) {
-  return g.skip_flagged && peek_flags(g.fl) != 0u;
-}
+// what a launch does beside the forward-Euler step (see StageCoef)
+struct Stage1 {
+  double ca, cb;
+  int first, skip_flagged;
+  unsigned* flags;
+  const double* dt_dev;
+  double dt_host, dt_mul;
+  double* acc;
+  double wa, wb, ga, gb;
+  double* adv;
+  int cfl;
+  double icx, vcoef, t_host, t_final;
+  const double* t_dev;
+  double* dt_out;
+};
 
 __device__ __forceinline__ double pt(const G1& g, const double* __restrict__ U, int X, int k) {
   if (X == 2 * g.n && g.np == g.n) X = 0;
@@ -51,12 +76,19 @@ __device__ __forceinline__ void cell_image1(const G1& g, const double* __restric
   V[2] = U[2 * g.n + ii];
 }
 
-__global__ void __launch_bounds__(kBlock) k_lattice1(G1 g, Phys ph, const double* __restrict__ U,
-                                                     double* __restrict__ LU,
-                                                     double* __restrict__ LA) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= g.LX || rejected(g)) return;
-  const int X = t - kMargin;
+// data of a tile in LDS
+struct Tile1 {
+  double U[3][kSites];   // lattice values (centres: Simpson, scaled)
+  double A[4][kSites];   // u, p, T, c
+  // cells of the tile +- 1: 0-2 F, 3 rs, 4 b, 5 phi1, 6 phi2, 7-9 average
+  double C[10][kRing];
+  double red[2][kThreads / 64];
+  unsigned stop;
+};
+
+// lattice site X into tile entry t
+__device__ __forceinline__ void lattice_site(const G1& g, const Phys& ph,
+                                             const double* __restrict__ U, int X, int t, Tile1& S) {
   int kind;
   const int Xi = axis_image(X, 2 * g.n, g.bc0, g.bc1, kind);
   const double s = (kind == BC_NOSLIP || kind == BC_SYMMETRY) ? -1.0 : 1.0;
@@ -95,33 +127,16 @@ __global__ void __launch_bounds__(kBlock) k_lattice1(G1 g, Phys ph, const double
   const double u = V[1] / V[0];
   const double p = pressure1(V[0], V[1], V[2], ph.gm1);
 #pragma unroll
-  for (int k = 0; k < 3; ++k) LU[k * g.LX + t] = V[k];
-  LA[0 * g.LX + t] = u;
-  LA[1 * g.LX + t] = p;
-  LA[2 * g.LX + t] = p / V[0];
-  LA[3 * g.LX + t] = sqrt(ph.gam * p / V[0]);
+  for (int k = 0; k < 3; ++k) S.U[k][t] = V[k];
+  S.A[0][t] = u;
+  S.A[1][t] = p;
+  S.A[2][t] = p / V[0];
+  S.A[3][t] = sqrt(ph.gam * p / V[0]);
 }
 
-__global__ void __launch_bounds__(kBlock) k_grad1(G1 g, const double* __restrict__ LA,
-                                                  double* __restrict__ LG) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= 2 * g.n + 5 || rejected(g)) return;
-  const int q = t - 2 + kMargin;
-  const double i6 = 1.0 / (6.0 * g.dx);
-  const double* u = LA;
-  const double* T = LA + 2 * g.LX;
-  LG[q] = dc5(u[q - 2], u[q - 1], u[q + 1], u[q + 2], i6);
-  LG[g.LX + q] = dc5(T[q - 2], T[q - 1], T[q + 1], T[q + 2], i6);
-}
-
-// CP layout (cells -1..n): 0-2 F, 3 rs, 4 b, 5 phi1, 6 phi2, 7-9 average
-
-__global__ void __launch_bounds__(kBlock) k_cellpre1(G1 g, Phys ph, const double* __restrict__ U,
-                                                     double* __restrict__ CP) {
-  const int nc = g.n + 2;
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= nc || rejected(g)) return;
-  const int i = t - 1;
+// low-order data of cell i (ghosts as boundary images) into ring entry t
+__device__ __forceinline__ void cell_site(const G1& g, const Phys& ph,
+                                          const double* __restrict__ U, int i, int t, Tile1& S) {
   double C0[3], Cm[3], Cp[3];
   cell_image1(g, U, i, C0);
   cell_image1(g, U, i - 1, Cm);
@@ -134,55 +149,48 @@ __global__ void __launch_bounds__(kBlock) k_cellpre1(G1 g, Phys ph, const double
   const double ux = (up - um) * i2;
   const double Tx = (pp / Cp[0] - pm / Cm[0]) * i2;
   const double tau = (4.0 / 3.0) * ph.mu * ux;
-  CP[0 * nc + t] = C0[1];
-  CP[1 * nc + t] = C0[1] * u0 + p0 - tau;
-  CP[2 * nc + t] = (C0[2] + p0) * u0 - (u0 * tau + ph.kap * Tx);
-  CP[3 * nc + t] = fabs(u0) + sqrt(ph.gam * p0 / C0[0]);
-  CP[4 * nc + t] = bvisc1(C0[0], p0, ux, Tx, ph);
-  CP[5 * nc + t] = fabs(pp - 2.0 * p0 + pm) / fabs(pp + 2.0 * p0 + pm);
-  CP[6 * nc + t] = mx(-ux / sqrt(ux * ux + kDucros), 0.0);
+  S.C[0][t] = C0[1];
+  S.C[1][t] = C0[1] * u0 + p0 - tau;
+  S.C[2][t] = (C0[2] + p0) * u0 - (u0 * tau + ph.kap * Tx);
+  S.C[3][t] = fabs(u0) + sqrt(ph.gam * p0 / C0[0]);
+  S.C[4][t] = bvisc1(C0[0], p0, ux, Tx, ph);
+  S.C[5][t] = fabs(pp - 2.0 * p0 + pm) / fabs(pp + 2.0 * p0 + pm);
+  S.C[6][t] = mx(-ux / sqrt(ux * ux + kDucros), 0.0);
 #pragma unroll
-  for (int k = 0; k < 3; ++k) CP[(7 + k) * nc + t] = C0[k];
+  for (int k = 0; k < 3; ++k) S.C[7 + k][t] = C0[k];
 }
 
-__device__ __forceinline__ void site_flux1(const G1& g, const Phys& ph, const double* __restrict__ LU,
-                                           const double* __restrict__ LA,
-                                           const double* __restrict__ LG, int q, double* F) {
-  const double m = LU[g.LX + q], E = LU[2 * g.LX + q];
-  const double u = LA[q], p = LA[g.LX + q];
-  const double tau = (4.0 / 3.0) * ph.mu * LG[q];
-  F[0] = m;
-  F[1] = m * u + p - tau;
-  F[2] = (E + p) * u - (u * tau + ph.kap * LG[g.LX + q]);
-}
-
-__global__ void __launch_bounds__(kBlock) k_face1(G1 g, Phys ph, const double* __restrict__ LU,
-                                                  const double* __restrict__ LA,
-                                                  const double* __restrict__ LG,
-                                                  const double* __restrict__ CP,
-                                                  double* __restrict__ FO, const double* dt_dev,
-                                                  double dt_host, unsigned* flags) {
-  const int nf = g.n + 1;
-  const int f = blockIdx.x * blockDim.x + threadIdx.x;
-  if (f >= nf || rejected(g)) return;
-  const double dt = dt_dev ? *dt_dev : dt_host;
-  double FH[3], F[3];
-  site_flux1(g, ph, LU, LA, LG, 2 * f + kMargin, FH);
+// limited flux of the face between ring cells a and a + 1, at lattice entry q
+__device__ __forceinline__ void face_flux(const G1& g, const Phys& ph, const Tile1& S, int a, int q,
+                                          double dt, unsigned* flags, double* F) {
+  const int b = a + 1;
+  double FH[3];
+  {
+    const double i6 = 1.0 / (6.0 * g.dx);
+    const double* uu = S.A[0];
+    const double* TT = S.A[2];
+    const double gu = dc5(uu[q - 2], uu[q - 1], uu[q + 1], uu[q + 2], i6);
+    const double gT = dc5(TT[q - 2], TT[q - 1], TT[q + 1], TT[q + 2], i6);
+    const double m = S.U[1][q], E = S.U[2][q];
+    const double u = uu[q], p = S.A[1][q];
+    const double tau = (4.0 / 3.0) * ph.mu * gu;
+    FH[0] = m;
+    FH[1] = m * u + p - tau;
+    FH[2] = (E + p) * u - (u * tau + ph.kap * gT);
+  }
   const int limc = ph.lim & (LIM_SMOOTH | LIM_PP | LIM_LOWONLY);
   if (!limc) {
 #pragma unroll
     for (int k = 0; k < 3; ++k) F[k] = FH[k];
   } else {
-    const int nc = g.n + 2;
-    const int a = f, b = f + 1;  // cells f-1 and f in the ringed grid
-    const double lam = mx(CP[3 * nc + a], CP[3 * nc + b]) + mx(CP[4 * nc + a], CP[4 * nc + b]);
+    const double lam = mx(S.C[3][a], S.C[3][b]) + mx(S.C[4][a], S.C[4][b]);
     double FL[3], Ua[3], Ub[3], Fa[3], Fb[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      Ua[k] = CP[(7 + k) * nc + a];
-      Ub[k] = CP[(7 + k) * nc + b];
-      Fa[k] = CP[k * nc + a];
-      Fb[k] = CP[k * nc + b];
+      Ua[k] = S.C[7 + k][a];
+      Ub[k] = S.C[7 + k][b];
+      Fa[k] = S.C[k][a];
+      Fb[k] = S.C[k][b];
       FL[k] = 0.5 * (Fa[k] + Fb[k]) - 0.5 * lam * (Ub[k] - Ua[k]);
     }
     double ts = 1.0, tpp = 1.0;
@@ -191,7 +199,7 @@ __global__ void __launch_bounds__(kBlock) k_face1(G1 g, Phys ph, const double* _
       tpp = 0.0;
     } else {
       if (ph.lim & LIM_SMOOTH)
-        ts = exp(-ph.Cs * mx(CP[5 * nc + a], CP[5 * nc + b]) * mx(CP[6 * nc + a], CP[6 * nc + b]));
+        ts = exp(-ph.Cs * mx(S.C[5][a], S.C[5][b]) * mx(S.C[6][a], S.C[6][b]));
       if (ph.lim & LIM_PP) {
         const double m2 = 2.0 * dt / g.dx;
         double ULp[3], UHp[3], ULm[3], UHm[3];
@@ -231,30 +239,6 @@ __global__ void __launch_bounds__(kBlock) k_face1(G1 g, Phys ph, const double* _
 #pragma unroll
     for (int k = 0; k < 3; ++k) F[k] = FL[k] + th * (FH[k] - FL[k]);
   }
-#pragma unroll
-  for (int k = 0; k < 3; ++k) FO[k * nf + f] = F[k];
-}
-
-__global__ void __launch_bounds__(kBlock) k_cells1(G1 g, const double* __restrict__ Un,
-                                                   const double* __restrict__ Uk,
-                                                   double* __restrict__ Uout,
-                                                   const double* __restrict__ FX,
-                                                   const double* dt_dev, double dt_host, double ca,
-                                                   double cb, int first, unsigned* flags) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= g.n || rejected(g)) return;
-  const double dt = dt_dev ? *dt_dev : dt_host;
-  const double m = dt / g.dx;
-  const int nf = g.n + 1;
-  bool bad = false;
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    const double fe = Uk[k * g.n + i] - m * (FX[k * nf + i + 1] - FX[k * nf + i]);
-    const double o = first ? fe : ca * Un[k * g.n + i] + cb * fe;
-    if (!isfinite(o)) bad = true;
-    Uout[k * g.n + i] = o;
-  }
-  if (bad) raise_flag(flags, FLAG_NONFINITE);
 }
 
 // low-order data of site o (1..3) of the five-site low-order point lattice
@@ -273,18 +257,12 @@ __device__ __forceinline__ void lo_site1(const Phys& ph, const double (&V)[5][3]
   b = bvisc1(V[o][0], p[o], ux, Tx, ph);
 }
 
-__global__ void __launch_bounds__(kBlock) k_points1(G1 g, Phys ph, const double* __restrict__ LU,
-                                                    const double* __restrict__ LA,
-                                                    const double* __restrict__ CP,
-                                                    const double* __restrict__ Un,
-                                                    double* __restrict__ Uout, const double* dt_dev,
-                                                    double dt_host, double ca, double cb, int first,
-                                                    unsigned* flags) {
-  const int k0 = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k0 >= g.np || rejected(g)) return;
+// forward-Euler value of point k0 (lattice entry q, ring cells r0 and r0 + 1
+// at its sides) into out
+__device__ __forceinline__ void point_update(const G1& g, const Phys& ph, const Tile1& S, int k0,
+                                             int q, int r0, double dt, unsigned* flags,
+                                             double* out) {
   const int X = 2 * k0;
-  const int q = X + kMargin;
-  const double dt = dt_dev ? *dt_dev : dt_host;
   const double i6h = 1.0 / (6.0 * g.dx);
   double Us[5][3], u[5], p[5], T[5];
   double alpha = 0.0;
@@ -292,11 +270,11 @@ __global__ void __launch_bounds__(kBlock) k_points1(G1 g, Phys ph, const double*
   for (int o = 0; o < 5; ++o) {
     const int s = q + o - 2;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) Us[o][k] = LU[k * g.LX + s];
-    u[o] = LA[s];
-    p[o] = LA[g.LX + s];
-    T[o] = LA[2 * g.LX + s];
-    alpha = mx(alpha, fabs(u[o]) + LA[3 * g.LX + s]);
+    for (int k = 0; k < 3; ++k) Us[o][k] = S.U[k][s];
+    u[o] = S.A[0][s];
+    p[o] = S.A[1][s];
+    T[o] = S.A[2][s];
+    alpha = mx(alpha, fabs(u[o]) + S.A[3][s]);
   }
   double Fc[5][3];
 #pragma unroll
@@ -316,7 +294,7 @@ __global__ void __launch_bounds__(kBlock) k_points1(G1 g, Phys ph, const double*
   const double m43 = (4.0 / 3.0) * ph.mu;
   R[1] += s4 * m43 * bcol(u);
   R[2] += s4 * (m43 * bform(u, u) + ph.kap * bcol(T));
-  double U0[3], UH[3], out[3];
+  double U0[3], UH[3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     U0[k] = Us[2][k];
@@ -325,7 +303,6 @@ __global__ void __launch_bounds__(kBlock) k_points1(G1 g, Phys ph, const double*
   if (ph.lim & LIM_POINT) {
     // low-order LLF scheme on the lattice of point values (X-2, X, X+2) and
     // cell averages (X-1, X+1: ring cells k0 and k0+1), Sec. 3.4
-    const int nc = g.n + 2;
     double V[5][3], lu[5], lp[5], lT[5], lc[5];
 #pragma unroll
     for (int o = 0; o < 5; o += 2) {
@@ -334,12 +311,12 @@ __global__ void __launch_bounds__(kBlock) k_points1(G1 g, Phys ph, const double*
       lu[o] = u[o];
       lp[o] = p[o];
       lT[o] = T[o];
-      lc[o] = LA[3 * g.LX + q + o - 2];
+      lc[o] = S.A[3][q + o - 2];
     }
 #pragma unroll
     for (int o = 1; o < 5; o += 2) {
 #pragma unroll
-      for (int k = 0; k < 3; ++k) V[o][k] = CP[(7 + k) * nc + k0 + (o >> 1)];
+      for (int k = 0; k < 3; ++k) V[o][k] = S.C[7 + k][r0 + (o >> 1)];
       const double ir = 1.0 / V[o][0];
       lu[o] = V[o][1] * ir;
       lp[o] = pressure1(V[o][0], V[o][1], V[o][2], ph.gm1);
@@ -383,22 +360,109 @@ __global__ void __launch_bounds__(kBlock) k_points1(G1 g, Phys ph, const double*
 #pragma unroll
     for (int k = 0; k < 3; ++k) out[k] = d[k];
   }
-  bool bad = false;
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    const long a = g.off_pts + (long)k * g.np + k0;
-    const double o = first ? out[k] : ca * Un[a] + cb * out[k];
-    if (!isfinite(o)) bad = true;
-    Uout[a] = o;
-  }
-  if (bad) raise_flag(flags, FLAG_NONFINITE);
 }
 
-inline unsigned nblk(long n) { return (unsigned)((n + kBlock - 1) / kBlock); }
+// RK combination of the forward-Euler value fe of DOF array element a, and
+// the further combinations a stage may carry (see StageCoef); false if the
+// value is not finite
+__device__ __forceinline__ bool combine(const Stage1& st, const double* __restrict__ Un,
+                                        double* __restrict__ Uout, long a, double fe) {
+  const double o = st.first ? fe : st.ca * Un[a] + st.cb * fe;
+  if (st.acc) {
+    Uout[a] = st.wa * Un[a] + st.wb * o;
+    st.acc[a] = st.ga * st.acc[a] + st.gb * o;
+  } else {
+    Uout[a] = o;
+  }
+  return isfinite(o);
+}
+
+__global__ void __launch_bounds__(kThreads) k_stage1(G1 g, Phys ph, Stage1 st,
+                                                     const double* __restrict__ Un,
+                                                     const double* __restrict__ Uk,
+                                                     double* __restrict__ Uout) {
+  __shared__ Tile1 S;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int i0 = blockIdx.x * kCells;
+  const int nc = min(kCells, g.n - i0);        // cells of the tile (0: a last point alone)
+  const int npt = min(kCells, g.np - i0);      // its points
+  // inside a step attempt: stop once the attempt's flag word is set (it is
+  // rejected and the stage output is never read)
+  if (tid == 0) S.stop = st.skip_flagged ? peek_flags(st.flags) : 0u;
+  double ra = 0.0, rv = 0.0;
+  if (st.cfl) {
+    for (int c = tid; c < g.n; c += kThreads) {
+      const double r = Uk[c], m = Uk[g.n + c], E = Uk[2 * g.n + c];
+      const double p = pressure1(r, m, E, ph.gm1);
+      const double cs = sqrt(ph.gam * p / r);
+      ra = mx(ra, (fabs(m / r) + cs) * st.icx);
+      rv = mx(rv, st.vcoef / r);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      ra = mx(ra, __shfl_xor(ra, o, 64));
+      rv = mx(rv, __shfl_xor(rv, o, 64));
+    }
+    if (lane == 0) {
+      S.red[0][wave] = ra;
+      S.red[1][wave] = rv;
+    }
+  }
+  // entry t of the tile's lattice is site 2 i0 - 2 + t; ring entry t is cell
+  // i0 - 1 + t
+  if (wave < 2) {
+    if (tid < 2 * nc + 5) lattice_site(g, ph, Uk, 2 * i0 - 2 + tid, tid, S);
+  } else if (lane < nc + 2) {
+    cell_site(g, ph, Uk, i0 - 1 + lane, lane, S);
+  }
+  __syncthreads();
+  if (S.stop) return;
+  double dt;
+  if (st.cfl) {
+    const double a = mx(mx(S.red[0][0], S.red[0][1]), S.red[0][2]);
+    const double v = mx(mx(S.red[1][0], S.red[1][1]), S.red[1][2]);
+    const double t = st.t_dev ? *st.t_dev : st.t_host;
+    dt = 1.0 / (a + v);
+    if (t + dt > st.t_final) dt = st.t_final - t;
+    if (!(dt > 0.0)) dt = 0.0;
+    if (blockIdx.x == 0 && tid == 0) *st.dt_out = dt;
+  } else {
+    dt = st.dt_dev ? *st.dt_dev : st.dt_host;
+  }
+  // a run's last stage keeps the time (no other workgroup reads it here)
+  if (st.adv && blockIdx.x == 0 && tid == 0 && dt > 0.0) {
+    st.adv[1] = st.adv[1] + dt;
+    st.adv[2] = st.adv[2] + 1.0;
+  }
+  if (st.dt_mul != 1.0) dt = st.dt_mul * dt;
+  bool ok = true;
+  if (wave == 0) {
+    double F[3] = {0.0, 0.0, 0.0};
+    if (nc > 0 && lane <= nc) face_flux(g, ph, S, lane, 2 * lane + 2, dt, st.flags, F);
+    const double m = dt / g.dx;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const double Fp = __shfl_down(F[k], 1, 64);
+      if (lane < nc) {
+        const double fe = S.C[7 + k][lane + 1] - m * (Fp - F[k]);
+        ok &= combine(st, Un, Uout, (long)k * g.n + i0 + lane, fe);
+      }
+    }
+  } else if (wave == 1 && lane < npt) {
+    double out[3];
+    point_update(g, ph, S, i0 + lane, 2 * lane + 2, lane, dt, st.flags, out);
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      ok &= combine(st, Un, Uout, g.off_pts + (long)k * g.np + i0 + lane, out[k]);
+  }
+  if (!ok) raise_flag(st.flags, FLAG_NONFINITE);
+}
 
 }  // namespace
 
 namespace afi {
+
+bool stage1d_takes_cfl(const Geo& g) { return g.dim == 1 && g.n1 <= 4096; }
 
 hipError_t stage1d(const Geo& geo, const Phys& ph, const Work& w, const double* Un,
                    const double* Uk, double* Uout, const double* dt_dev, double dt_host,
@@ -406,7 +470,6 @@ hipError_t stage1d(const Geo& geo, const Phys& ph, const Work& w, const double* 
   G1 g;
   g.n = geo.n1;
   g.np = geo.n1x;
-  g.LX = geo.LX;
   g.off_pts = geo.off_pts;
   g.bc0 = geo.bc[0];
   g.bc1 = geo.bc[1];
@@ -415,29 +478,31 @@ hipError_t stage1d(const Geo& geo, const Phys& ph, const Work& w, const double* 
     g.dl[k] = geo.bcstate[0][k];
     g.dr[k] = geo.bcstate[1][k];
   }
-  g.skip_flagged = sc.skip_flagged;
-  g.fl = w.flags;
+  Stage1 st{};
+  st.ca = sc.a;
+  st.cb = sc.b;
+  st.first = sc.first;
+  st.skip_flagged = sc.skip_flagged;
+  st.flags = w.flags;
+  st.dt_dev = dt_dev;
+  st.dt_host = dt_host;
+  st.dt_mul = sc.dt_mul;
+  st.acc = sc.acc;
+  st.wa = sc.wa;
+  st.wb = sc.wb;
+  st.ga = sc.ga;
+  st.gb = sc.gb;
+  st.adv = sc.adv;
+  st.cfl = sc.cfl.on;
+  st.icx = sc.cfl.icx;
+  st.vcoef = sc.cfl.vcoef;
+  st.t_host = sc.cfl.t_host;
+  st.t_dev = sc.cfl.t_dev;
+  st.t_final = sc.cfl.t_final;
+  st.dt_out = w.scal;
   AFI_TIMED(tm, 0, s,
-            hipLaunchKernelGGL(k_lattice1, dim3(nblk(g.LX)), dim3(kBlock), 0, s, g, ph, Uk, w.LU,
-                               w.LA));
-  AFI_TIMED(tm, 1, s,
-            hipLaunchKernelGGL(k_grad1, dim3(nblk(2 * g.n + 5)), dim3(kBlock), 0, s, g,
-                               (const double*)w.LA, w.LG));
-  AFI_TIMED(tm, 2, s,
-            hipLaunchKernelGGL(k_cellpre1, dim3(nblk(g.n + 2)), dim3(kBlock), 0, s, g, ph, Uk,
-                               w.CP));
-  AFI_TIMED(tm, 3, s,
-            hipLaunchKernelGGL(k_face1, dim3(nblk(g.n + 1)), dim3(kBlock), 0, s, g, ph,
-                               (const double*)w.LU, (const double*)w.LA, (const double*)w.LG,
-                               (const double*)w.CP, w.FX, dt_dev, dt_host, w.flags));
-  AFI_TIMED(tm, 4, s,
-            hipLaunchKernelGGL(k_cells1, dim3(nblk(g.n)), dim3(kBlock), 0, s, g, Un, Uk, Uout,
-                               (const double*)w.FX, dt_dev, dt_host, sc.a, sc.b, sc.first,
-                               w.flags));
-  AFI_TIMED(tm, 5, s,
-            hipLaunchKernelGGL(k_points1, dim3(nblk(g.np)), dim3(kBlock), 0, s, g, ph,
-                               (const double*)w.LU, (const double*)w.LA, (const double*)w.CP, Un,
-                               Uout, dt_dev, dt_host, sc.a, sc.b, sc.first, w.flags));
+            hipLaunchKernelGGL(k_stage1, dim3((unsigned)((g.np + kCells - 1) / kCells)),
+                               dim3(kThreads), 0, s, g, ph, st, Un, Uk, Uout));
   return hipGetLastError();
 }
 

@@ -600,7 +600,7 @@ struct StageArgs {
   const double* Un;
   double* Uout;
   const double* dt_dev;
-  double dt_host;
+  double dt_host, dt_mul;  // the step is dt_mul * dt
   unsigned* flags;
   int ntx;
   // learned blend (one instance): a blend coefficient per face replacing
@@ -754,7 +754,7 @@ __global__ void __launch_bounds__(NT) k_stage(StageArgs sa) {
       dt1 = I.dt;
       flags1 = &sa.dinst->flags;
     } else {
-      dt1 = sa.dt_dev ? *sa.dt_dev : sa.dt_host;
+      dt1 = sa.dt_mul * (sa.dt_dev ? *sa.dt_dev : sa.dt_host);
     }
   }
   // what tile t works on (built where used, from the kernel arguments or the
@@ -1456,6 +1456,7 @@ hipError_t launch(const G2& g, const Phys& ph, const afi::Work& w, const double*
   sa.Uout = Uout;
   sa.dt_dev = dt_dev;
   sa.dt_host = dt_host;
+  sa.dt_mul = sc.dt_mul;
   sa.flags = w.flags;
   sa.ntx = ntx;
   sa.ca = sc.a;
