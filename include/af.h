@@ -368,7 +368,7 @@ af_status af_blend_features(af_ctx* ctx, const double* U, float* feat, void* str
 af_status af_set_blend_net(af_ctx* ctx, const float* params);
 
 /* theta_nn of every face of U into theta (af_face_count floats, device),
- * asynchronous; uses the workspace for the packed weights. */
+ * asynchronous (the workspace is not used). */
 af_status af_blend_infer(af_ctx* ctx, const double* U, float* theta, void* ws, void* stream);
 
 /* af_rk_stage (2D) with explicit blend arrays: theta (af_face_count floats,

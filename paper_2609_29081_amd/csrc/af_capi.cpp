@@ -198,8 +198,7 @@ hipError_t launch_coef(const afi::Geo& g, const afd::Phys& ph, const afi::Work& 
     // the network's blend from this stage's input, then the stage
     if (!w.net) return hipErrorInvalidValue;
     hipError_t e;
-    if ((e = afi::mlp_pack(w.net, w.mlp, s)) != hipSuccess) return e;
-    if ((e = afi::blend_infer(g, ph, Uk, w.mlp, w.blend, s, tm)) != hipSuccess) return e;
+    if ((e = afi::blend_infer(g, ph, Uk, w.net, w.blend, s, tm)) != hipSuccess) return e;
     sc.blend = w.blend;
   }
   return g.dim == 1 ? afi::stage1d(g, ph, w, Un, Uk, Uout, dt_dev, dt_host, sc, s, tm)
@@ -1136,10 +1135,7 @@ af_status af_blend_infer(af_ctx* c, const double* U, float* theta, void* ws, voi
   if (!c->net) return fail(AF_E_ARG, "af_blend_infer: no network set (af_set_blend_net)");
   afi::Geo g;
   if (!geometry(c, &g)) return AF_E_ARG;
-  const afi::Work w = work_of(c, g, ws);
-  const hipStream_t s = (hipStream_t)stream;
-  AF_HIP(afi::mlp_pack(c->net, w.mlp, s));
-  AF_HIP(afi::blend_infer(g, physics(c->p), U, w.mlp, theta, s, c->timer));
+  AF_HIP(afi::blend_infer(g, physics(c->p), U, c->net, theta, (hipStream_t)stream, c->timer));
   return AF_OK;
 }
 
@@ -1166,8 +1162,7 @@ af_status af_rk_stage_blend(af_ctx* c, int k, const double* dt_dev, double dt_ho
   if (theta) {
     sc.blend = theta;
   } else if (ph.lim & afd::LIM_LEARNED) {
-    AF_HIP(afi::mlp_pack(c->net, w.mlp, s));
-    AF_HIP(afi::blend_infer(g, ph, Uk, w.mlp, w.blend, s, c->timer));
+    AF_HIP(afi::blend_infer(g, ph, Uk, c->net, w.blend, s, c->timer));
     sc.blend = w.blend;
   }
   AF_HIP(afi::stage2d(g, ph, w, Un, Uk, Uout, dt_dev, dt_host, sc, s, c->timer));

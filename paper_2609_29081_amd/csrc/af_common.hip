@@ -319,7 +319,7 @@ size_t workspace_layout(const Geo& g, Work* w, char* base) {
   r.SAVE = (double*)take(sizeof(double) * g.state_len);
   if (g.dim == 2) {
     r.blend = (float*)take(sizeof(float) * (nfx + nfy));
-    r.mlp = (void*)take(kMlpPackedBytes);
+    take(14336);  // not used (packed network weights once); see the 1D room above
     r.binst = (BatchInst*)take(sizeof(BatchInst));
     r.bpartial = (double*)take(2 * sizeof(double) * kSingleCflBlocks);
     r.bnact = (int*)take(sizeof(int));

@@ -92,10 +92,8 @@ struct Work {
   double* S2;
   double* S3;        // fourth stage buffer of SSP-RK54
   double* SAVE;
-  // 2D learned blend: one coefficient per face, and the network's weights as
-  // the inference kernel reads them (bfloat16 W1, W2, w3; FP32 biases)
+  // 2D learned blend: one coefficient per face
   float* blend;
-  void* mlp;
   // 2D: one batch descriptor, its CFL partial maxima and active count, for
   // the single instance's device-resident step loop (af_run_graph)
   struct BatchInst* binst;
@@ -156,11 +154,9 @@ struct Timer {
 constexpr int kMlpIn = 40, kMlpHidden = 64;
 constexpr long kMlpParams = (long)kMlpHidden * kMlpIn + kMlpHidden + (long)kMlpHidden * kMlpHidden +
                             kMlpHidden + kMlpHidden + 1;
-constexpr size_t kMlpPackedBytes = 14336;
 hipError_t blend_features(const Geo& g, const afd::Phys& ph, const double* U, float* feat,
                           hipStream_t s);
-hipError_t mlp_pack(const float* params, void* packed, hipStream_t s);
-hipError_t blend_infer(const Geo& g, const afd::Phys& ph, const double* U, const void* packed,
+hipError_t blend_infer(const Geo& g, const afd::Phys& ph, const double* U, const float* params,
                        float* theta, hipStream_t s, Timer* tm);
 size_t mlp_grad_workspace(long n);
 hipError_t mlp_grad(const float* X, const float* y, long n, const float* params, float* grad,

@@ -36,35 +36,10 @@ constexpr int OFF_W1 = 0, OFF_B1 = NH * NIN, OFF_W2 = OFF_B1 + NH, OFF_B2 = OFF_
               OFF_W3 = OFF_B2 + NH, OFF_B3 = OFF_W3 + NH;
 static_assert(OFF_B3 + 1 == afi::kMlpParams, "parameter layout");
 
-// packed inference weights: bfloat16 W1 [64][40], W2 [64][64], w3 [64], then
-// FP32 b1 [64], b2 [64], b3
-constexpr int PK_W1 = 0, PK_W2 = PK_W1 + 2 * NH * NIN, PK_W3 = PK_W2 + 2 * NH * NH,
-              PK_B1 = PK_W3 + 2 * NH, PK_B2 = PK_B1 + 4 * NH, PK_B3 = PK_B2 + 4 * NH;
-static_assert(PK_B3 + 4 <= (int)afi::kMlpPackedBytes, "packed weights");
-
 // round to nearest even (one hardware conversion on gfx950)
 __device__ __forceinline__ unsigned short to_bf16(float x) {
   return __builtin_bit_cast(unsigned short, (__bf16)x);
 }
-__device__ __forceinline__ float from_bf16(unsigned short h) {
-  return __uint_as_float((unsigned)h << 16);
-}
-
-// face f -> direction d, face (i, j); x-faces [n2][n1+1] first
-__device__ __forceinline__ void face_of(const G2& g, long f, int& d, int& i, int& j) {
-  const long nfx = (long)g.n2 * (g.n1 + 1);
-  if (f < nfx) {
-    d = 0;
-    j = (int)(f / (g.n1 + 1));
-    i = (int)(f % (g.n1 + 1));
-  } else {
-    d = 1;
-    const long r = f - nfx;
-    j = (int)(r / g.n1);
-    i = (int)(r % g.n1);
-  }
-}
-
 // (rho, u, v, p) as FP32 from a cell average (FP64 arithmetic)
 __device__ __forceinline__ void prims_of(double gm1, const double* V, float* P) {
   const double ir = 1.0 / V[0], u = V[1] * ir, v = V[2] * ir;
@@ -72,14 +47,6 @@ __device__ __forceinline__ void prims_of(double gm1, const double* V, float* P) 
   P[1] = float(u);
   P[2] = float(v);
   P[3] = float(gm1 * (V[3] - 0.5 * V[0] * (u * u + v * v)));
-}
-
-// (rho, u, v, p) of the cell average of cell (ci, cj), ci in [-2, n1+1]
-__device__ __forceinline__ void cell_prims(const G2& g, double gm1, const double* U, int ci, int cj,
-                                           float* P) {
-  double V[4];
-  raw_value(g, U, 2 * ci + 1, 2 * cj + 1, V);
-  prims_of(gm1, V, P);
 }
 
 __device__ __forceinline__ float pos_or_tiny(float v) { return v > 1e-30f ? v : 1e-30f; }
@@ -143,31 +110,136 @@ __device__ __forceinline__ void stencil_cell(int d, int i, int j, int s, int q, 
 }
 
 // ---------------------------------------------------------------------------
-// features of every face (training data), one thread per face
+// Blocks of faces: a workgroup of 256 threads takes up to 128 consecutive
+// faces of each of up to eight rows of one direction and holds the primitives
+// of their stencil cells in LDS (ten rows of cells for eight rows of x-faces,
+// eleven for y-faces, where one face row at a time needed three or four).
 // ---------------------------------------------------------------------------
+constexpr int IB = 128;                 // faces per row of a block
+constexpr int RB = 8;                   // face rows per block, at most
+constexpr int CW = IB + 4;              // stencil cells per row
+typedef float CellBlock[4][RB + 3][CW]; // [component][row][column]
+
+// how the faces of a grid are cut into blocks of rb rows
+struct FaceBlocks {
+  int nsegx, nsegy, rb;
+  long nbx, nblocks;  // blocks of x-faces, all blocks
+};
+
+// block blk: direction, first row and row count, first face along the
+// rows, face count per row, and its stencil cells: x-faces need columns
+// i0-2 .. i0+cnt and rows row0-1 .. row0+nr, y-faces columns i0-1 ..
+// i0+cnt and rows row0-2 .. row0+nr-1
+struct FaceBlock {
+  int d, row0, nr, i0, cnt, ncol, nrow, c0, r0;
+};
+__device__ __forceinline__ FaceBlock block_of(const G2& g, const FaceBlocks& fb, long blk) {
+  FaceBlock b;
+  if (blk < fb.nbx) {
+    b.d = 0;
+    b.row0 = (int)(blk / fb.nsegx) * fb.rb;
+    b.nr = min(fb.rb, g.n2 - b.row0);
+    b.i0 = (int)(blk % fb.nsegx) * IB;
+    b.cnt = min(IB, g.n1 + 1 - b.i0);
+  } else {
+    b.d = 1;
+    const long r = blk - fb.nbx;
+    b.row0 = (int)(r / fb.nsegy) * fb.rb;
+    b.nr = min(fb.rb, g.n2 + 1 - b.row0);
+    b.i0 = (int)(r % fb.nsegy) * IB;
+    b.cnt = min(IB, g.n1 - b.i0);
+  }
+  b.ncol = b.d == 0 ? b.cnt + 3 : b.cnt + 2;
+  b.nrow = (b.d == 0 ? 2 : 3) + b.nr;
+  b.c0 = b.d == 0 ? b.i0 - 2 : b.i0 - 1;
+  b.r0 = b.d == 0 ? b.row0 - 1 : b.row0 - 2;
+  return b;
+}
+
+// the primitives of block b's stencil cells into LDS, by all 256 threads: the
+// loads of the FP64 averages are all issued, then a barrier (the previous
+// block's readers are done), then the stores
+__device__ __forceinline__ void stage_cells(const G2& g, double gm1, const double* __restrict__ U,
+                                            const FaceBlock& b, CellBlock& cell) {
+  constexpr int CPT = ((RB + 3) * (IB + 2) + 255) / 256;
+  static_assert((RB + 2) * (IB + 3) <= CPT * 256 && (RB + 3) * (IB + 2) <= CPT * 256,
+                "cells per thread");
+  const int tid = threadIdx.x;
+  double pre[CPT][4];
+#pragma unroll
+  for (int r = 0; r < CPT; ++r) {
+    const int e = tid + 256 * r;
+    if (e < b.ncol * b.nrow)
+      raw_value(g, U, 2 * (b.c0 + e % b.ncol) + 1, 2 * (b.r0 + e / b.ncol) + 1, pre[r]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < CPT; ++r) {
+    const int e = tid + 256 * r;
+    if (e < b.ncol * b.nrow) {
+      float P[4];
+      prims_of(gm1, pre[r], P);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) cell[k][e / b.ncol][e % b.ncol] = P[k];
+    }
+  }
+}
+
+// half h of the features of face (i0 + fl, row) of block b
+template <typename PutFn>
+__device__ __forceinline__ void block_features(const FaceBlock& b, const CellBlock& cell, float gam,
+                                               int fl, int row, int h, PutFn put) {
+  const int i = b.i0 + fl;
+  features_of(b.d, gam,
+              [&](int s, int q, float* P) {
+                int ci, cj;
+                stencil_cell(b.d, i, row, s, q, ci, cj);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) P[k] = cell[k][cj - b.r0][ci - b.c0];
+              },
+              put, h);
+}
+
+// index of the first face of a block's row
+__device__ __forceinline__ long first_face(const G2& g, const FaceBlock& b, int row) {
+  return b.d == 0 ? (long)row * (g.n1 + 1) + b.i0
+                  : (long)g.n2 * (g.n1 + 1) + (long)row * g.n1 + b.i0;
+}
+
+// ---------------------------------------------------------------------------
+// features of every face (training data).  The output, 160 bytes a face, is
+// what the kernel has to move: two threads form a face's features, a row of
+// 128 faces passes through LDS and is written as one contiguous run.  (One
+// thread per face with its own 40 stores, 160 bytes apart between lanes, and
+// its 18 cells' primitives formed again for every face, took 64 us at
+// 500 x 250, 0.7 TB/s; the copy rate is 5.1 TB/s.)
+// ---------------------------------------------------------------------------
+constexpr int OROW = NIN + 1;  // LDS row (floats): lanes 41 apart fall on different banks
+
 __global__ void __launch_bounds__(256) k_features(G2 g, double gm1, float gam,
                                                   const double* __restrict__ U,
-                                                  float* __restrict__ out, long nf) {
-  for (long f = blockIdx.x * (long)blockDim.x + threadIdx.x; f < nf;
-       f += (long)gridDim.x * blockDim.x) {
-    int d, i, j;
-    face_of(g, f, d, i, j);
-    features_of(d, gam,
-                [&](int s, int q, float* P) {
-                  int ci, cj;
-                  stencil_cell(d, i, j, s, q, ci, cj);
-                  cell_prims(g, gm1, U, ci, cj, P);
-                },
-                [&](int n, float v) { out[f * NIN + n] = v; });
+                                                  float* __restrict__ out, FaceBlocks fb) {
+  __shared__ CellBlock cell;
+  __shared__ float feat[IB * OROW];
+  const int tid = threadIdx.x, fl = tid & (IB - 1), half = tid / IB;
+  for (long blk = blockIdx.x; blk < fb.nblocks; blk += gridDim.x) {
+    const FaceBlock B = block_of(g, fb, blk);
+    stage_cells(g, gm1, U, B, cell);
+    for (int rr = 0; rr < B.nr; ++rr) {
+      const int row = B.row0 + rr;
+      __syncthreads();  // the cells are in; the previous row is written
+      if (fl < B.cnt)
+        block_features(B, cell, gam, fl, row, half, [&](int n, float v) { feat[fl * OROW + n] = v; });
+      __syncthreads();
+      float* o = out + first_face(g, B, row) * NIN;
+      for (int e = tid; e < B.cnt * NIN; e += 256) o[e] = feat[e / NIN * OROW + e % NIN];
+    }
   }
 }
 
 // ---------------------------------------------------------------------------
-// inference.  A workgroup (four wave64s) takes 128 consecutive faces of
-// each of eight rows of one direction: it stages the primitives of their
-// stencil cells in LDS once (ten rows of cells for eight rows of x-faces,
-// eleven for y-faces, where one face row at a time needed three or four),
-// and for each face row writes the features as bfloat16 rows; each wave
+// inference.  For each face row of a block (above) the four wave64s of a
+// workgroup write the features as bfloat16 rows; each wave
 // then runs the network on 32 faces with MFMA 32x32x16 bf16 in the
 // transposed form H^T = W X^T: the weights are the A operand (units x
 // inputs, in registers), the faces the columns.  A 32 x 32 accumulator holds
@@ -180,17 +252,15 @@ __global__ void __launch_bounds__(256) k_features(G2 g, double gm1, float gam,
 // registers, and the output layer's sum over units ends with one exchange
 // between the two halves of the wave.
 // ---------------------------------------------------------------------------
-constexpr int IB = 128;                 // faces per row of a block
-constexpr int RB = 8;                   // face rows per block, at most
 constexpr int KIN = 48;                 // inputs padded to three K steps of 16
 constexpr int FROW = KIN + 8;           // feature row (bf16; 16-byte aligned)
-constexpr int CW = IB + 4;              // stencil cells per row
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 struct InferShared {
-  float cell[4][RB + 3][CW];            // [component][row][column]
+  CellBlock cell;
   unsigned short feat[IB * FROW];
   float b1[NH], b2[NH], w3[NH];         // biases, and the output weights (bf16 values)
   // layer 2's A operands, per lane (in LDS rather than registers: with them
@@ -199,10 +269,10 @@ struct InferShared {
   bf16x8 a2[2][4][64];
 };
 
-__device__ __forceinline__ bf16x8 bf16x8_of(const unsigned short* p, int n) {
-  bf16x8 v;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) v[e] = __builtin_bit_cast(__bf16, e < n ? p[e] : (unsigned short)0);
+// four floats, which need no more than a float's alignment
+__device__ __forceinline__ f32x4 load4(const float* p) {
+  f32x4 v;
+  __builtin_memcpy(&v, p, sizeof(v));
   return v;
 }
 
@@ -216,106 +286,57 @@ __device__ __forceinline__ int hidden_unit(int kb, int h, int e) {
 // at least three waves per SIMD (at most 168 VGPRs)
 __global__ void __launch_bounds__(256, 3) k_infer(G2 g, double gm1, float gam,
                                                const double* __restrict__ U,
-                                               const unsigned char* __restrict__ pk,
-                                               float* __restrict__ theta, int nsegx, int nsegy,
-                                               int rb, long nblocks) {
+                                               const float* __restrict__ p,
+                                               float* __restrict__ theta, FaceBlocks fb) {
   __shared__ InferShared S;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int h = lane >> 5, c32 = lane & 31;
-  const unsigned short* W1 = (const unsigned short*)(pk + PK_W1);
-  const unsigned short* W2 = (const unsigned short*)(pk + PK_W2);
-  const unsigned short* w3 = (const unsigned short*)(pk + PK_W3);
-  const float* b1 = (const float*)(pk + PK_B1);
-  const float* b2 = (const float*)(pk + PK_B2);
-  const float b3 = *(const float*)(pk + PK_B3);
+  const float b3 = p[OFF_B3];
   // A operands: lane (m = c32, h) holds row 32 nb + m, inputs 16 kb + 8 h + e
-  // (layer 2's written to LDS by the first wave, read after the first barrier)
+  // (layer 2's written to LDS by the first wave, read after the first
+  // barrier), from the FP32 parameters: each workgroup rounds them for itself
+  // (27 KB from L2), which spares a packing launch of 4.7 us per inference
   bf16x8 A1[2][3];
 #pragma unroll
   for (int nb = 0; nb < 2; ++nb) {
 #pragma unroll
     for (int kb = 0; kb < 3; ++kb) {
-      const int k0 = 16 * kb + 8 * h;
-      A1[nb][kb] = bf16x8_of(W1 + (32 * nb + c32) * NIN + (k0 < NIN ? k0 : 0),
-                             k0 < NIN ? NIN - k0 : 0);
-    }
+      const int k0 = 16 * kb + 8 * h;  // 40: past the inputs
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb) {
-      bf16x8 v;
+      for (int a = 0; a < 2; ++a) {
+        const f32x4 x = load4(p + OFF_W1 + (32 * nb + c32) * NIN + (k0 < NIN ? k0 : 0) + 4 * a);
 #pragma unroll
-      for (int e = 0; e < 8; ++e)
-        v[e] = __builtin_bit_cast(__bf16, W2[(32 * nb + c32) * NH + hidden_unit(kb, h, e)]);
-      if (wave == 0) S.a2[nb][kb][lane] = v;
-    }
-  }
-  for (int e = tid; e < NH; e += 256) {
-    S.b1[e] = b1[e];
-    S.b2[e] = b2[e];
-    S.w3[e] = from_bf16(w3[e]);
-  }
-  const long nfx = (long)g.n2 * (g.n1 + 1);
-  const long ngx = (g.n2 + rb - 1) / rb;  // row groups of the x-faces
-  const long nbx = ngx * nsegx;
-  // block blk: direction, first row and row count, first face along the
-  // rows, face count per row, and its stencil cells: x-faces need columns
-  // i0-2 .. i0+cnt and rows row0-1 .. row0+nr, y-faces columns i0-1 ..
-  // i0+cnt and rows row0-2 .. row0+nr-1
-  struct Blk {
-    int d, row0, nr, i0, cnt, ncol, nrow, c0, r0;
-  };
-  auto block_of = [&](long blk) {
-    Blk b;
-    if (blk < nbx) {
-      b.d = 0;
-      b.row0 = (int)(blk / nsegx) * rb;
-      b.nr = min(rb, g.n2 - b.row0);
-      b.i0 = (int)(blk % nsegx) * IB;
-      b.cnt = min(IB, g.n1 + 1 - b.i0);
-    } else {
-      b.d = 1;
-      const long r = blk - nbx;
-      b.row0 = (int)(r / nsegy) * rb;
-      b.nr = min(rb, g.n2 + 1 - b.row0);
-      b.i0 = (int)(r % nsegy) * IB;
-      b.cnt = min(IB, g.n1 - b.i0);
-    }
-    b.ncol = b.d == 0 ? b.cnt + 3 : b.cnt + 2;
-    b.nrow = (b.d == 0 ? 2 : 3) + b.nr;
-    b.c0 = b.d == 0 ? b.i0 - 2 : b.i0 - 1;
-    b.r0 = b.d == 0 ? b.row0 - 1 : b.row0 - 2;
-    return b;
-  };
-  // the FP64 averages of a block's stencil cells, up to (RB + 3) x 130 cells,
-  // loaded at the start of the block (held one block ahead, they took more
-  // registers than three workgroups per CU leave; the other workgroups on the
-  // CU hide the wait)
-  constexpr int CPT = ((RB + 3) * (IB + 2) + 255) / 256;
-  static_assert((RB + 2) * (IB + 3) <= CPT * 256 && (RB + 3) * (IB + 2) <= CPT * 256,
-                "cells per thread");
-  double pre[CPT][4];
-  auto fetch = [&](const Blk& b) {
-#pragma unroll
-    for (int r = 0; r < CPT; ++r) {
-      const int e = tid + 256 * r;
-      if (e < b.ncol * b.nrow) raw_value(g, U, 2 * (b.c0 + e % b.ncol) + 1, 2 * (b.r0 + e / b.ncol) + 1, pre[r]);
-    }
-  };
-  long blk = blockIdx.x;
-  for (; blk < nblocks; blk += gridDim.x) {
-    const Blk B = block_of(blk);
-    fetch(B);
-    const int d = B.d, i0 = B.i0, cnt = B.cnt, c0 = B.c0, r0 = B.r0;
-    __syncthreads();  // the previous block is done with the cell and feature arrays
-#pragma unroll
-    for (int r = 0; r < CPT; ++r) {
-      const int e = tid + 256 * r;
-      if (e < B.ncol * B.nrow) {
-        float P[4];
-        prims_of(gm1, pre[r], P);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) S.cell[k][e / B.ncol][e % B.ncol] = P[k];
+        for (int i = 0; i < 4; ++i) A1[nb][kb][4 * a + i] = (__bf16)(k0 < NIN ? x[i] : 0.0f);
       }
     }
+    if (wave == 0) {
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb) {
+        bf16x8 v;
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+          // four consecutive units (see hidden_unit)
+          const f32x4 x = load4(p + OFF_W2 + (32 * nb + c32) * NH + hidden_unit(kb, h, 4 * a));
+#pragma unroll
+          for (int i = 0; i < 4; ++i) v[4 * a + i] = (__bf16)x[i];
+        }
+        S.a2[nb][kb][lane] = v;
+      }
+    }
+  }
+  static_assert(NIN % 8 == 0, "whole groups of eight inputs");
+  if (tid < NH) {
+    S.b1[tid] = p[OFF_B1 + tid];
+    S.b2[tid] = p[OFF_B2 + tid];
+    S.w3[tid] = (float)(__bf16)p[OFF_W3 + tid];
+  }
+  for (long blk = blockIdx.x; blk < fb.nblocks; blk += gridDim.x) {
+    // (held one block ahead, the loads of the averages took more registers
+    // than three workgroups per CU leave; the other workgroups on the CU hide
+    // the wait)
+    const FaceBlock B = block_of(g, fb, blk);
+    stage_cells(g, gm1, U, B, S.cell);
+    const int cnt = B.cnt;
     for (int rr = 0; rr < B.nr; ++rr) {
       const int row = B.row0 + rr;
       __syncthreads();  // the cells are in; the previous row is done with the features
@@ -325,15 +346,8 @@ __global__ void __launch_bounds__(256, 3) k_infer(G2 g, double gm1, float gam,
         const int fl = tid & (IB - 1), half = tid / IB;
         unsigned short* fo = S.feat + fl * FROW;
         if (fl < cnt) {
-          const int i = i0 + fl;
-          features_of(d, gam,
-                      [&](int s, int q, float* P) {
-                        int ci, cj;
-                        stencil_cell(d, i, row, s, q, ci, cj);
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) P[k] = S.cell[k][cj - r0][ci - c0];
-                      },
-                      [&](int n, float v) { fo[n] = to_bf16(v); }, half);
+          block_features(B, S.cell, gam, fl, row, half,
+                         [&](int n, float v) { fo[n] = to_bf16(v); });
         } else {
           for (int n = half; n < NIN; n += 2) fo[n] = 0;
         }
@@ -394,23 +408,11 @@ __global__ void __launch_bounds__(256, 3) k_infer(G2 g, double gm1, float gam,
       z += __shfl_xor(z, 32, 64);
       const int m = 32 * wave + c32;
       if (h == 0 && m < cnt) {
-        const long f = (d == 0 ? 0 : nfx) + (long)row * (d == 0 ? g.n1 + 1 : g.n1) + i0 + m;
+        const long f = first_face(g, B, row) + m;
         theta[f] = fminf(fmaxf(z + b3, 0.0f), 1.0f);
       }
     }
   }
-}
-
-__global__ void k_pack(const float* __restrict__ p, unsigned char* __restrict__ pk) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < NH * NIN) ((unsigned short*)(pk + PK_W1))[t] = to_bf16(p[OFF_W1 + t]);
-  if (t < NH * NH) ((unsigned short*)(pk + PK_W2))[t] = to_bf16(p[OFF_W2 + t]);
-  if (t < NH) {
-    ((unsigned short*)(pk + PK_W3))[t] = to_bf16(p[OFF_W3 + t]);
-    ((float*)(pk + PK_B1))[t] = p[OFF_B1 + t];
-    ((float*)(pk + PK_B2))[t] = p[OFF_B2 + t];
-  }
-  if (t == 0) *(float*)(pk + PK_B3) = p[OFF_B3];
 }
 
 // ---------------------------------------------------------------------------
@@ -435,8 +437,6 @@ constexpr int kGradBlocks = 256;   // partial gradients at most
 // LDS rows: sample rows of 68 (activations) and 44 (inputs) floats put the 16
 // rows x 4 columns a matrix operand reads into 64 different banks
 constexpr int HS = NH + 4, XS = NIN + 4;
-
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 struct GradShared {
   float X[GC * XS], H1[GC * HS], A2[GC * HS], A1[GC * HS], zp[4][GC], y[GC];
@@ -640,26 +640,9 @@ __global__ void k_adam(float* __restrict__ p, const float* __restrict__ g, float
 
 namespace afi {
 
-hipError_t blend_features(const Geo& geo, const Phys& ph, const double* U, float* feat,
-                          hipStream_t s) {
-  const G2 g = stage_geo(geo);
-  const long nf = (long)g.n2 * (g.n1 + 1) + (long)(g.n2 + 1) * g.n1;
-  long nb = (nf + 255) / 256;
-  if (nb > 65536) nb = 65536;
-  hipLaunchKernelGGL(k_features, dim3((unsigned)nb), dim3(256), 0, s, g, ph.gm1, float(ph.gam), U,
-                     feat, nf);
-  return hipGetLastError();
-}
-
-hipError_t mlp_pack(const float* params, void* packed, hipStream_t s) {
-  hipLaunchKernelGGL(k_pack, dim3((NH * NH + 255) / 256), dim3(256), 0, s, params,
-                     (unsigned char*)packed);
-  return hipGetLastError();
-}
-
-// persistent workgroups of the inference kernel: as many as are resident
-static int infer_workgroups() {
-  static int cache[64] = {0};
+// persistent workgroups of kernel K (256 threads): as many as are resident
+template <typename K>
+static int resident(K kernel, int (&cache)[64]) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
   if (cache[dev] == 0) {
@@ -667,7 +650,7 @@ static int infer_workgroups() {
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         cus <= 0)
       cus = 256;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_infer, 256, 0) != hipSuccess ||
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, 256, 0) != hipSuccess ||
         per <= 0)
       per = 1;
     cache[dev] = cus * per;
@@ -675,24 +658,43 @@ static int infer_workgroups() {
   return cache[dev];
 }
 
-hipError_t blend_infer(const Geo& geo, const Phys& ph, const double* U, const void* packed,
-                       float* theta, hipStream_t s, Timer* tm) {
+// the blocks of a grid's faces for nwg workgroups.  Rows per block: the most
+// (up to RB) that still leave every resident workgroup two blocks, so that a
+// small grid keeps the device busy
+static FaceBlocks face_blocks(const G2& g, long nwg) {
+  FaceBlocks fb;
+  fb.nsegx = (g.n1 + 1 + IB - 1) / IB;
+  fb.nsegy = (g.n1 + IB - 1) / IB;
+  auto bx = [&](int rb) { return (long)((g.n2 + rb - 1) / rb) * fb.nsegx; };
+  auto all = [&](int rb) { return bx(rb) + (long)((g.n2 + 1 + rb - 1) / rb) * fb.nsegy; };
+  fb.rb = RB;
+  while (fb.rb > 1 && all(fb.rb) < 2 * nwg) fb.rb /= 2;
+  fb.nbx = bx(fb.rb);
+  fb.nblocks = all(fb.rb);
+  return fb;
+}
+
+hipError_t blend_features(const Geo& geo, const Phys& ph, const double* U, float* feat,
+                          hipStream_t s) {
+  static int cache[64] = {0};
   const G2 g = stage_geo(geo);
-  const int nsegx = (g.n1 + 1 + IB - 1) / IB, nsegy = (g.n1 + IB - 1) / IB;
-  const long nwg = infer_workgroups();
-  // rows per block: the most (up to RB) that still leave every resident
-  // workgroup two blocks, so that a small grid keeps the device busy
-  auto blocks = [&](int rb) {
-    return (long)((g.n2 + rb - 1) / rb) * nsegx + (long)((g.n2 + 1 + rb - 1) / rb) * nsegy;
-  };
-  int rb = RB;
-  while (rb > 1 && blocks(rb) < 2 * nwg) rb /= 2;
-  const long nblocks = blocks(rb);
-  const long grid = nblocks < nwg ? nblocks : nwg;
+  const long nwg = resident(k_features, cache);
+  const FaceBlocks fb = face_blocks(g, nwg);
+  hipLaunchKernelGGL(k_features, dim3((unsigned)(fb.nblocks < nwg ? fb.nblocks : nwg)), dim3(256),
+                     0, s, g, ph.gm1, float(ph.gam), U, feat, fb);
+  return hipGetLastError();
+}
+
+hipError_t blend_infer(const Geo& geo, const Phys& ph, const double* U, const float* params,
+                       float* theta, hipStream_t s, Timer* tm) {
+  static int cache[64] = {0};
+  const G2 g = stage_geo(geo);
+  const long nwg = resident(k_infer, cache);
+  const FaceBlocks fb = face_blocks(g, nwg);
   AFI_TIMED(tm, 8, s,
-            hipLaunchKernelGGL(k_infer, dim3((unsigned)grid), dim3(256), 0, s, g, ph.gm1,
-                               float(ph.gam), U, (const unsigned char*)packed, theta, nsegx,
-                               nsegy, rb, nblocks));
+            hipLaunchKernelGGL(k_infer, dim3((unsigned)(fb.nblocks < nwg ? fb.nblocks : nwg)),
+                               dim3(256), 0, s, g, ph.gm1, float(ph.gam), U,
+                               params, theta, fb));
   return hipGetLastError();
 }
 
