@@ -301,7 +301,8 @@ size_t af_batch_workspace_bytes(const af_batch* b);
  * opens a step (fresh CFL dt) for every instance that is between steps and
  * runs one RK3 attempt of every instance inside a step; the attempt is then
  * accepted or redone with dt/2 in the next round (af_run's halving rule).
- * use_graph != 0 captures one slot in a HIP graph and replays it.  steps[i], t[i], status[i] (AF_OK, AF_E_PP, AF_E_NONFINITE: the state
+ * use_graph != 0 captures one slot in a HIP graph and replays it, where
+ * max_steps needs more than two slots.  steps[i], t[i], status[i] (AF_OK, AF_E_PP, AF_E_NONFINITE: the state
  * is then the one before the failed step) and attempts[i] (RK3 attempts,
  * accepted and rejected) receive per-instance results; any may be NULL. */
 af_status af_batch_run(af_batch* b, double* const* U, void* ws, void* stream, double t0,

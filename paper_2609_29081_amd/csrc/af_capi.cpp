@@ -10,6 +10,7 @@
 #include <stdio.h>
 
 #include <string.h>
+#include <algorithm>
 #include <memory>
 #include <mutex>
 #include <new>
@@ -497,18 +498,20 @@ hipError_t batch_slot(const afi::StageVariant* v, afi::BatchInst* dinst, int n, 
 // Enqueue step slots (slot(stream) enqueues one) for the n instances whose
 // descriptors (host copies h, already on the device at dinst) are set, on
 // stream s: captured once in a HIP graph (use_graph) or launched directly,
-// in chunks of `chunk` slots with a read-back of the descriptors after each; stops
+// in chunks of up to `chunk` slots (`rounds` rounds each) with a read-back of the descriptors after each; stops
 // once no instance is active or may open a step.  h receives the final
 // descriptors.
 // keep (cache != NULL): the instantiated graph is taken from *cache if set
 // there, else built and left in *cache for the caller to reuse and destroy.
 template <typename Slot>
-af_status run_slots(Slot slot, afi::BatchInst* dinst, int n, int use_graph, hipStream_t s,
+af_status run_slots(Slot slot, int rounds, afi::BatchInst* dinst, int n, int use_graph, hipStream_t s,
                     long max_steps, double t_final, std::vector<afi::BatchInst>& h,
                     const char* who, hipGraphExec_t* cache = nullptr, long chunk = 8) {
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = cache ? *cache : nullptr;
-  if (use_graph && !exec) {
+  // a graph kept by no cache pays from its third replay on (capturing and
+  // instantiating a slot costs the host about what launching it twice does)
+  if (use_graph && !exec && (cache || max_steps > 2L * rounds)) {
     // the slot is captured on a private stream (the caller's may be the null
     // stream, which cannot be captured) and replayed on the caller's
     hipStream_t cs = nullptr;
@@ -534,8 +537,13 @@ af_status run_slots(Slot slot, afi::BatchInst* dinst, int n, int use_graph, hipS
   }
   af_status st = AF_OK;
   long progress = -1;  // sum of steps and attempts: it grows while any instance works
+  long left = max_steps;  // most steps any instance may still take
   for (;;) {
-    for (long c = 0; c < chunk; ++c) {
+    // no more slots than those steps need when every attempt is accepted: a
+    // round with nothing left to do still costs its launches (32 rounds for 3
+    // steps of a batch: 750 of its 2460 us)
+    const long slots = std::max(1L, std::min(chunk, (left + rounds - 1) / rounds));
+    for (long c = 0; c < slots; ++c) {
       const hipError_t e = exec ? hipGraphLaunch(exec, s) : slot(s);
       if (e != hipSuccess) {
         st = fail(AF_E_HIP, "%s: launch: %s", who, hipGetErrorString(e));
@@ -551,9 +559,13 @@ af_status run_slots(Slot slot, afi::BatchInst* dinst, int n, int use_graph, hipS
     }
     bool busy = false;
     long prog = 0;
+    left = 0;
     for (int i = 0; i < n; ++i) {
       const afi::BatchInst& I = h[i];
-      if (I.active || (I.status == 0 && I.steps < max_steps && I.t < t_final)) busy = true;
+      if (I.active || (I.status == 0 && I.steps < max_steps && I.t < t_final)) {
+        busy = true;
+        left = std::max(left, max_steps - I.steps);
+      }
       prog += I.steps + I.attempts;
     }
     if (!busy) break;
@@ -1029,7 +1041,7 @@ af_status af_batch_run(af_batch* b, double* const* U, void* ws, void* stream, do
     return batch_slot(b->var, dinst, n, total_tiles, partial, nact, attempts_per_slot, q);
   };
   const af_status st =
-      run_slots(slot, dinst, n, use_graph, s, max_steps, t_final, h, "af_batch_run");
+      run_slots(slot, attempts_per_slot, dinst, n, use_graph, s, max_steps, t_final, h, "af_batch_run");
   if (st != AF_OK) return st;
   // the current state of every instance back into its U
   for (int i = 0; i < n; ++i)
@@ -1089,7 +1101,7 @@ af_status af_run_graph(af_ctx* c, double* U, void* ws, void* stream, double t0, 
     }
     return hipSuccess;
   };
-  const af_status st = run_slots(slot, w.binst, 1, 1, s, max_steps, t_final, h, "af_run_graph",
+  const af_status st = run_slots(slot, attempts_per_slot, w.binst, 1, 1, s, max_steps, t_final, h, "af_run_graph",
                                  &c->run_exec, 4);
   if (st != AF_OK) return st;
   if (h[0].cur != 0) AF_HIP(afi::copy_state(U, h[0].buf[h[0].cur], g.state_len, s));
