@@ -21,7 +21,8 @@ SOURCES = [("af_capi.cpp", "af_capi.o", []),
            ("af_variants.cpp", "af_variants.o", ["--cuda-host-only"]),
            ("af_common.hip", "af_common.o", []),
            ("af_kern1d.hip", "af_kern1d.o", []),
-           ("af_learn.hip", "af_learn.o", [])] + [
+           ("af_learn.hip", "af_learn.o", []),
+           ("af_strip2d.hip", "af_strip2d.o", [])] + [
     ("af_stage2d.hip", f"{name}.o",
      [f"-DAF_STAGE_REAL={real}", f"-DAF_STAGE_TY={ty}", f"-DAF_STAGE_ENTRY={name}",
       # no hoisting of loop-invariant values out of the persistent tile

@@ -1071,7 +1071,8 @@ af_status af_run_graph(af_ctx* c, double* U, void* ws, void* stream, double t0, 
   const afi::StageVariant* v = afi::default_variant(g.mixed);
   std::vector<afi::BatchInst> h(1);
   h[0] = instance_of(c, g, v, U, w.S1, w.S2, t0, t_final, max_steps);
-  h[0].stage_nwg = v->dev_nwg(g);
+  const int nwg = afi::stage2d_dev_nwg(g);
+  h[0].stage_nwg = nwg;
   AF_HIP(hipMemcpyAsync(w.binst, h.data(), sizeof(afi::BatchInst), hipMemcpyHostToDevice, s));
   // the first step's CFL maxima; every later step opens from those its
   // predecessor's last stage left (the dt reduction fused into that stage)
@@ -1092,11 +1093,13 @@ af_status af_run_graph(af_ctx* c, double* U, void* ws, void* stream, double t0, 
   auto slot = [&](hipStream_t q) {
     hipError_t e;
     for (int a = 0; a < attempts_per_slot; ++a) {
+      if (!nwg && (e = afi::batch_cfl(w.binst, 1, w.bpartial, afi::kSingleCflBlocks, q)) != hipSuccess)
+        return e;
       if ((e = afi::batch_open(w.binst, 1, w.bpartial, afi::kSingleCflBlocks, w.bnact, q)) !=
           hipSuccess)
         return e;
       for (int k = 0; k < 3; ++k)
-        if ((e = v->dev(g, ph, w.binst, w.bpartial, k, q)) != hipSuccess) return e;
+        if ((e = afi::stage2d_dev(g, ph, w.binst, w.bpartial, k, q)) != hipSuccess) return e;
       if ((e = afi::batch_decide(w.binst, 1, w.bnact, q)) != hipSuccess) return e;
     }
     return hipSuccess;

@@ -168,7 +168,7 @@ hipError_t mlp_adam(float* params, const float* grad, float* m, float* v, long s
                     hipStream_t s);
 
 // launchers (enqueue on stream; return the first HIP error)
-// the 2D stage of one instance, with its precision's default variant
+// the 2D stage of one instance (af_strip2d.hip)
 hipError_t stage2d(const Geo& g, const afd::Phys& ph, const Work& w, const double* Un,
                    const double* Uk, double* Uout, const double* dt_dev, double dt_host,
                    StageCoef sc, hipStream_t s, Timer* tm);
@@ -216,23 +216,22 @@ hipError_t batch_cfl(BatchInst* inst, int n, double* partial, int nb, hipStream_
 hipError_t batch_open(BatchInst* inst, int n, const double* partial, int nb, int* n_active,
                       hipStream_t s);
 hipError_t batch_decide(BatchInst* inst, int n, int* n_active, hipStream_t s);
-// Compiled variants of the 2D stage (af_stage2d.hip, one object each): the
-// single-instance stage, the batch stage and the tile count of a grid.
+// stage k of the current attempt of one instance whose step machinery is on
+// the device (descriptor dinst).  Its last stage writes the CFL maxima of the
+// new state per workgroup into cfl_partial (stride kSingleCflBlocks);
+// stage2d_dev_nwg: the number of its workgroups, or 0 where they are more and
+// leave no maxima (grids over 61440 cells wide)
+hipError_t stage2d_dev(const Geo& g, const afd::Phys& ph, BatchInst* dinst, double* cfl_partial,
+                       int k, hipStream_t s);
+int stage2d_dev_nwg(const Geo& g);
+// Compiled variants of the 2D stage of a batch (af_stage2d.hip, one object
+// each): the stage, and the tile count of a grid.
 struct StageVariant {
   const char* name;
   int mixed;  // 1: FP32 stencils
   int ty;     // tile height (cells)
-  hipError_t (*single)(const Geo&, const afd::Phys&, const Work&, const double*, const double*,
-                       double*, const double*, double, StageCoef, hipStream_t, Timer*);
   hipError_t (*batch)(BatchInst*, int, int, const int*, int, hipStream_t, Timer*);
   int (*tiles)(const Geo&);
-  // stage k of the current attempt of one instance whose step machinery is on
-  // the device (descriptor dinst): the single-instance kernel; its last stage
-  // writes the CFL maxima of the new state per workgroup into cfl_partial
-  // (stride kSingleCflBlocks); dev_nwg: its number of workgroups
-  hipError_t (*dev)(const Geo&, const afd::Phys&, BatchInst*, double* cfl_partial, int,
-                    hipStream_t);
-  int (*dev_nwg)(const Geo&);
 };
 // all variants; the first of each precision is its default
 extern const StageVariant kStageVariants[];

@@ -1,0 +1,306 @@
+// af_scheme2d.hpp -- the pieces of the 2D stage that its kernels share: site
+// and cell data, the limited face flux, the wall projection, and the launch
+// arguments.  Kernels that evaluate the same expression of the same values
+// round alike (multiply-adds are fused within one expression only), so all of
+// them give the same bits.
+#pragma once
+
+#include <type_traits>
+
+#include "af_device.hpp"
+#include "af_internal.hpp"
+#include "af_lattice.hpp"
+
+namespace afd {
+
+// (u, v, p, T, c) of state V, given 1/rho
+template <typename R>
+__device__ __forceinline__ void aux_of(const PhysT<R>& ph, const R* V, R ir, R* w) {
+  const R p = ph.gm1 * (V[3] - R(0.5) * (V[1] * V[1] + V[2] * V[2]) * ir);
+  w[0] = V[1] * ir;
+  w[1] = V[2] * ir;
+  w[2] = p;
+  w[3] = p * ir;
+  w[4] = sqrt(ph.gam * w[3]);
+}
+
+// Simpson centre value from the cell average, the sum of the four edge
+// points and the sum of the four corners (Sec. 2.2), scaled toward the
+// average with the density-then-pressure rule when the centre limiter is on,
+// and its (u, v, p, T, c).  A centre whose density and pressure are already
+// at least eps keeps its value: the rule's parameter is 1 there (the rule is
+// continuous at that threshold, so only round-off separates the two
+// evaluations of the test).  The rule itself runs in FP64.
+template <typename R>
+__device__ __forceinline__ void centre_value(const PhysT<R>& ph, const Phys& phd, const R* Ub,
+                                             const R* e, const R* c, R* V, R* w) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) V[k] = (R(36.0) * Ub[k] - R(4.0) * e[k] - c[k]) / R(16.0);
+  R ir = rcp(V[0]);
+  const R p = ph.gm1 * (V[3] - R(0.5) * (V[1] * V[1] + V[2] * V[2]) * ir);
+  if ((ph.lim & LIM_CENTRE) && !(Ub[0] > R(0.0) && V[0] >= R(kPPEps) && p >= R(kPPEps))) {
+    if (!(Ub[0] > R(0.0))) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) V[k] = Ub[k];
+    } else {
+      double Ud[4], Vd[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        Ud[k] = Ub[k];
+        Vd[k] = V[k];
+      }
+      bool bad = false;
+      const double th = theta_pair2(Ud, Vd, phd.gm1, bad, ph.lim & LIM_PEXACT);
+      if (th < 1.0) {
+        double Wd[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          Wd[k] = Ud[k] + th * (Vd[k] - Ud[k]);
+          V[k] = R(Wd[k]);
+        }
+        if constexpr (!std::is_same<R, double>::value) {
+          // FP32 stencils: the scaled centre's pressure may sit at eps, far
+          // below the rounding of E - |m|^2 / (2 rho) in FP32, so its
+          // (u, v, p, T, c) are taken from the FP64 value
+          const double ird = rcp(Wd[0]);
+          const double pd = phd.gm1 * (Wd[3] - 0.5 * (Wd[1] * Wd[1] + Wd[2] * Wd[2]) * ird);
+          w[0] = R(Wd[1] * ird);
+          w[1] = R(Wd[2] * ird);
+          w[2] = R(pd);
+          w[3] = R(pd * ird);
+          w[4] = R(sqrt(phd.gam * (pd * ird)));
+          return;
+        }
+      }
+    }
+    ir = rcp(V[0]);
+  }
+  aux_of(ph, V, ir, w);
+}
+
+// (u, v, p, T, c) in R of the FP64 value V
+template <typename R>
+__device__ __forceinline__ void aux_of_fp64(const PhysT<double>& pd, const double* V, R* w) {
+  const double ir = rcp(V[0]);
+  const double p = pd.gm1 * (V[3] - 0.5 * (V[1] * V[1] + V[2] * V[2]) * ir);
+  const double Tt = p * ir;
+  w[0] = R(V[1] * ir);
+  w[1] = R(V[2] * ir);
+  w[2] = R(p);
+  w[3] = R(Tt);
+  w[4] = R(sqrt(pd.gam * Tt));
+}
+
+// pressure of state V, given 1/rho
+template <typename R>
+__device__ __forceinline__ R pressure_r(const PhysT<R>& ph, const R* V, R ir) {
+  return ph.gm1 * (V[3] - R(0.5) * (V[1] * V[1] + V[2] * V[2]) * ir);
+}
+
+// per-cell low-order data (Sec. 3.1-3.2):
+//   o[0..3] F_x, o[4..7] F_y (total fluxes with S = central differences of
+//   Z(average)), o[8] |u|+c, o[9] |v|+c, o[10] b_x, o[11] b_y, o[12] phi1,
+//   o[13] phi2, o[14..17] the cell average, o[18..22] its (u, v, p, T, c);
+//   from the averages of the cell and of its four neighbours (ghost cells as
+//   boundary images)
+// A cell average with its reciprocal density and pressure: neighbours enter
+// by their momenta, 1/rho and p.
+template <typename R>
+struct CellAvg {
+  R U[4], r, p;
+};
+template <typename R>
+__device__ __forceinline__ void cell_low(const G2& g, const PhysT<R>& ph, const CellAvg<R>& a0,
+                                         const CellAvg<R>& xm, const CellAvg<R>& xp,
+                                         const CellAvg<R>& ym, const CellAvg<R>& yp, R* o) {
+  const R *C0 = a0.U, *Cxm = xm.U, *Cxp = xp.U, *Cym = ym.U, *Cyp = yp.U;
+  const R r0 = a0.r, rxm = xm.r, rxp = xp.r, rym = ym.r, ryp = yp.r;
+  const R p0 = a0.p, pxm = xm.p, pxp = xp.p, pym = ym.p, pyp = yp.p;
+  const R u0 = C0[1] * r0, v0 = C0[2] * r0;
+  const R i2x = R(1.0 / (2.0 * g.dx)), i2y = R(1.0 / (2.0 * g.dy));
+  const R ux = (Cxp[1] * rxp - Cxm[1] * rxm) * i2x;
+  const R vx = (Cxp[2] * rxp - Cxm[2] * rxm) * i2x;
+  const R Tx = (pxp * rxp - pxm * rxm) * i2x;
+  const R uy = (Cyp[1] * ryp - Cym[1] * rym) * i2y;
+  const R vy = (Cyp[2] * ryp - Cym[2] * rym) * i2y;
+  const R Ty = (pyp * ryp - pym * rym) * i2y;
+  const R c0 = sqrt(ph.gam * p0 * r0);
+  R Fv[4];
+  visc_flux2(0, u0, v0, ux, vx, Tx, uy, vy, Ty, ph, Fv);
+  o[0] = C0[1] - Fv[0];
+  o[1] = C0[1] * u0 + p0 - Fv[1];
+  o[2] = C0[2] * u0 - Fv[2];
+  o[3] = (C0[3] + p0) * u0 - Fv[3];
+  visc_flux2(1, u0, v0, ux, vx, Tx, uy, vy, Ty, ph, Fv);
+  o[4] = C0[2] - Fv[0];
+  o[5] = C0[1] * v0 - Fv[1];
+  o[6] = C0[2] * v0 + p0 - Fv[2];
+  o[7] = (C0[3] + p0) * v0 - Fv[3];
+  o[8] = fabs(u0) + c0;
+  o[9] = fabs(v0) + c0;
+  o[18] = u0;
+  o[19] = v0;
+  o[20] = p0;
+  o[21] = p0 * r0;
+  o[22] = c0;
+  bvisc2_xy(p0, p0 * r0, ux, vx, Tx, uy, vy, Ty, ph, o[10], o[11]);
+  const R jx = fabs(pxp - R(2.0) * p0 + pxm) / fabs(pxp + R(2.0) * p0 + pxm);
+  const R jy = fabs(pyp - R(2.0) * p0 + pym) / fabs(pyp + R(2.0) * p0 + pym);
+  o[12] = mx(jx, jy);
+  const R div = ux + vy, curl = vx - uy;
+  o[13] = mx(-div / sqrt(div * div + curl * curl + R(kDucros)), R(0.0));
+#pragma unroll
+  for (int k = 0; k < 4; ++k) o[14 + k] = C0[k];
+}
+
+// total flux F_d = F^c_d - F^v_d of state (m1, m2, E) with velocity (u, v),
+// pressure p and gradients gr = (u_x, v_x, T_x, u_y, v_y, T_y)
+template <typename R>
+__device__ __forceinline__ void tot_flux(int d, const R* U, R u, R v, R p, const R* gr,
+                                         const PhysT<R>& ph, R* F) {
+  R Fv[4];
+  visc_flux2(d, u, v, gr[0], gr[1], gr[2], gr[3], gr[4], gr[5], ph, Fv);
+  const R ud = d == 0 ? u : v;
+  F[0] = U[1 + d] - Fv[0];
+  F[1] = U[1] * ud + (d == 0 ? p : R(0.0)) - Fv[1];
+  F[2] = U[2] * ud + (d == 1 ? p : R(0.0)) - Fv[2];
+  F[3] = (U[3] + p) * ud - Fv[3];
+}
+
+// wall projection of a point value (no-slip: zero momentum; symmetry: zero
+// normal momentum; density and internal energy kept)
+__device__ __forceinline__ void project(int kind, int ax, double* V) {
+  if (kind == BC_NOSLIP) {
+    V[3] -= (V[1] * V[1] + V[2] * V[2]) / (2.0 * V[0]);
+    V[1] = 0.0;
+    V[2] = 0.0;
+  } else if (kind == BC_SYMMETRY) {
+    V[3] -= V[1 + ax] * V[1 + ax] / (2.0 * V[0]);
+    V[1 + ax] = 0.0;
+  }
+}
+
+__device__ __forceinline__ int wall_of(int bc) {
+  return (bc == BC_NOSLIP || bc == BC_SYMMETRY) ? bc : -1;
+}
+
+// what the limiter of a face reads of its cells a (minus) and b (plus): the
+// FP64 averages, the low-order cell fluxes along the face's axis, the LLF
+// flux, and the larger of the two cells' sensors
+template <typename R>
+struct FaceCells {
+  double Ua[4], Ub[4];
+  R Fa[4], Fb[4], FL[4], phi1, phi2;
+};
+
+// limited flux of face (i, j) of direction d (Sec. 3.2, 3.3) from its
+// high-order flux FH.  blend: a coefficient per face that takes the place of
+// theta^s, or NULL; ts_out: receives the coefficient used in its place per
+// face, or NULL.  own: the face belongs to this workgroup (others are computed
+// along, raise no flag and write nothing).
+template <typename R>
+__device__ __forceinline__ void limit_face(const G2& g, const PhysT<R>& ph, const Phys& phd, int d,
+                                           int i, int j, double dt, const FaceCells<R>& c,
+                                           const R* FH, const float* blend, float* ts_out, bool own,
+                                           unsigned* flags, R* F) {
+  R ts = R(1.0);
+  double tpp = 1.0;
+  // the face's entries in per-face arrays: x-faces [n2][n1+1], then
+  // y-faces [n2+1][n1]; a periodic axis's last face is its first again
+  const bool use_blend = blend != nullptr;
+  if (ph.lim & LIM_LOWONLY) {
+    ts = R(0.0);
+    tpp = 0.0;
+  } else {
+    if (use_blend) {
+      // the given coefficient takes the place of theta^s
+      const long nfx = (long)g.n2 * (g.n1 + 1);
+      const int fi = (d == 0 && i == g.n1 && g.n1x == g.n1) ? 0 : i;
+      const int fj = (d == 1 && j == g.n2 && g.n2y == g.n2) ? 0 : j;
+      if (own) ts = R(blend[d == 0 ? (long)fj * (g.n1 + 1) + fi : nfx + (long)fj * g.n1 + fi]);
+    } else if (ph.lim & LIM_SMOOTH) {
+      ts = exp(-ph.Cs * c.phi1 * c.phi2);
+    }
+    if (ph.lim & LIM_PP) {
+      // the density and pressure blend in FP64 (Sec. 3.3)
+      const double m4 = 4.0 * dt / (d == 0 ? g.dx : g.dy);
+      double ULp[4], UHp[4], ULm[4], UHm[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const double fl = c.FL[k], fh = FH[k], fca = c.Fa[k], fcb = c.Fb[k];
+        const double Fs = fl + double(ts) * (fh - fl);
+        ULp[k] = c.Ua[k] - m4 * (fl - fca);
+        UHp[k] = c.Ua[k] - m4 * (Fs - fca);
+        ULm[k] = c.Ub[k] - m4 * (fcb - fl);
+        UHm[k] = c.Ub[k] - m4 * (fcb - Fs);
+      }
+      tpp = 0.0;
+      bool bad = false;
+      if (!(ULp[0] > 0.0) || !(ULm[0] > 0.0)) {
+        bad = true;
+      } else {
+        const double pLp = pressure2(ULp[0], ULp[1], ULp[2], ULp[3], phd.gm1);
+        const double pLm = pressure2(ULm[0], ULm[1], ULm[2], ULm[3], phd.gm1);
+        if (!(pLp > 0.0) || !(pLm > 0.0)) bad = true;
+        const double tr = mn(theta_lin(ULp[0], UHp[0], mn(kPPEps, ULp[0])),
+                             theta_lin(ULm[0], UHm[0], mn(kPPEps, ULm[0])));
+        double Tp[4], Tm[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          Tp[k] = ULp[k] + tr * (UHp[k] - ULp[k]);
+          Tm[k] = ULm[k] + tr * (UHm[k] - ULm[k]);
+        }
+        const bool ex = ph.lim & LIM_PEXACT;
+        const double tp = mn(theta_p2(ULp, pLp, Tp, mn(kPPEps, pLp), phd.gm1, ex),
+                             theta_p2(ULm, pLm, Tm, mn(kPPEps, pLm), phd.gm1, ex));
+        tpp = tr * tp;
+      }
+      if (bad && own) raise_flag(flags, FLAG_CELL_LOW);
+    }
+  }
+  const double th = double(ts) * tpp;
+  if (ts_out && own) {
+    const long nfx = (long)g.n2 * (g.n1 + 1);
+    ts_out[d == 0 ? (long)j * (g.n1 + 1) + i : nfx + (long)j * g.n1 + i] = float(ts);
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const double fl = c.FL[k], fh = FH[k];
+    F[k] = R(fl + th * (fh - fl));
+  }
+}
+
+// launch arguments of a stage: one instance, or a batch of 2D instances
+constexpr int kMaxBatch = 512;
+struct StageArgs {
+  // one instance
+  G2 g;
+  Phys ph;
+  const double* Uk;
+  const double* Un;
+  double* Uout;
+  const double* dt_dev;
+  double dt_host, dt_mul;  // the step is dt_mul * dt
+  unsigned* flags;
+  int ntx;
+  // learned blend (one instance): a blend coefficient per face replacing
+  // theta^s, or NULL; and where to write theta^s per face, or NULL
+  const float* blend;
+  float* ts_out;
+  // a batch: its instances (stage k reads and writes their rotating buffers)
+  afi::BatchInst* inst;
+  int ninst, k;
+  const int* n_active;
+  // one instance whose step machinery lives on the device (a single
+  // descriptor; stage k of its current attempt, nothing once it is
+  // inactive), or NULL: then Uk, Un, Uout, dt and flags above are used.
+  // Its last stage leaves the CFL maxima of the new state in cfl_partial
+  // (a at [wg], v at [kSingleCflBlocks + wg]), for the next step's dt
+  afi::BatchInst* dinst;
+  double* cfl_partial;
+  // both
+  double ca, cb;
+  int first, skip_flagged, ntiles;
+};
+
+}  // namespace afd

@@ -31,11 +31,7 @@
 // update, the point-value update and the low-order point value stay FP64 on
 // FP64 data read from the state, and the point sites' (u, v, p, T, c) are
 // taken from their FP64 values; the state itself is FP64 in both.
-#include <type_traits>
-
-#include "af_device.hpp"
-#include "af_internal.hpp"
-#include "af_lattice.hpp"
+#include "af_scheme2d.hpp"
 
 using namespace afd;
 
@@ -78,148 +74,11 @@ constexpr int NSX = SW * 2 * TY, NSY = 2 * TX * SH;
 template <typename R>
 constexpr bool kFP64 = std::is_same<R, double>::value;
 
-// (u, v, p, T, c) of state V, given 1/rho
-template <typename R>
-__device__ __forceinline__ void aux_of(const PhysT<R>& ph, const R* V, R ir, R* w) {
-  const R p = ph.gm1 * (V[3] - R(0.5) * (V[1] * V[1] + V[2] * V[2]) * ir);
-  w[0] = V[1] * ir;
-  w[1] = V[2] * ir;
-  w[2] = p;
-  w[3] = p * ir;
-  w[4] = sqrt(ph.gam * w[3]);
-}
-
-// Simpson centre value from the cell average, the sum of the four edge
-// points and the sum of the four corners (Sec. 2.2), scaled toward the
-// average with the density-then-pressure rule when the centre limiter is on,
-// and its (u, v, p, T, c).  A centre whose density and pressure are already
-// at least eps keeps its value: the rule's parameter is 1 there (the rule is
-// continuous at that threshold, so only round-off separates the two
-// evaluations of the test).  The rule itself runs in FP64.
-template <typename R>
-__device__ __forceinline__ void centre_value(const PhysT<R>& ph, const Phys& phd, const R* Ub,
-                                             const R* e, const R* c, R* V, R* w) {
-#pragma unroll
-  for (int k = 0; k < 4; ++k) V[k] = (R(36.0) * Ub[k] - R(4.0) * e[k] - c[k]) / R(16.0);
-  R ir = rcp(V[0]);
-  const R p = ph.gm1 * (V[3] - R(0.5) * (V[1] * V[1] + V[2] * V[2]) * ir);
-  if ((ph.lim & LIM_CENTRE) && !(Ub[0] > R(0.0) && V[0] >= R(kPPEps) && p >= R(kPPEps))) {
-    if (!(Ub[0] > R(0.0))) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) V[k] = Ub[k];
-    } else {
-      double Ud[4], Vd[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        Ud[k] = Ub[k];
-        Vd[k] = V[k];
-      }
-      bool bad = false;
-      const double th = theta_pair2(Ud, Vd, phd.gm1, bad, ph.lim & LIM_PEXACT);
-      if (th < 1.0) {
-        double Wd[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          Wd[k] = Ud[k] + th * (Vd[k] - Ud[k]);
-          V[k] = R(Wd[k]);
-        }
-        if constexpr (!std::is_same<R, double>::value) {
-          // FP32 stencils: the scaled centre's pressure may sit at eps, far
-          // below the rounding of E - |m|^2 / (2 rho) in FP32, so its
-          // (u, v, p, T, c) are taken from the FP64 value
-          const double ird = rcp(Wd[0]);
-          const double pd = phd.gm1 * (Wd[3] - 0.5 * (Wd[1] * Wd[1] + Wd[2] * Wd[2]) * ird);
-          w[0] = R(Wd[1] * ird);
-          w[1] = R(Wd[2] * ird);
-          w[2] = R(pd);
-          w[3] = R(pd * ird);
-          w[4] = R(sqrt(phd.gam * (pd * ird)));
-          return;
-        }
-      }
-    }
-    ir = rcp(V[0]);
-  }
-  aux_of(ph, V, ir, w);
-}
-
 // whether the centre site (X, Y) of the lattice is a ghost beyond a wall or
 // outflow side (not a periodic one)
 __device__ __forceinline__ bool ghost_centre(const G2& g, int X, int Y) {
   return ((X < 0 || X > 2 * g.n1) && g.bc0 != BC_PERIODIC) ||
          ((Y < 0 || Y > 2 * g.n2) && g.bc2 != BC_PERIODIC);
-}
-
-// per-cell low-order data (Sec. 3.1-3.2):
-//   o[0..3] F_x, o[4..7] F_y (total fluxes with S = central differences of
-//   Z(average)), o[8] |u|+c, o[9] |v|+c, o[10] b_x, o[11] b_y, o[12] phi1,
-//   o[13] phi2, o[14..17] the cell average, o[18..22] its (u, v, p, T, c);
-//   from the averages of the cell and of its four neighbours (ghost cells as
-//   boundary images)
-template <typename R>
-__device__ __forceinline__ void cell_low(const G2& g, const PhysT<R>& ph, const R* C0,
-                                         const R* Cxm, const R* Cxp, const R* Cym, const R* Cyp,
-                                         R* o) {
-  // one reciprocal density per cell
-  const R r0 = rcp(C0[0]), rxm = rcp(Cxm[0]), rxp = rcp(Cxp[0]),
-          rym = rcp(Cym[0]), ryp = rcp(Cyp[0]);
-  auto pr = [&](const R* V, R ir) {
-    return ph.gm1 * (V[3] - R(0.5) * (V[1] * V[1] + V[2] * V[2]) * ir);
-  };
-  const R p0 = pr(C0, r0), pxm = pr(Cxm, rxm), pxp = pr(Cxp, rxp), pym = pr(Cym, rym),
-          pyp = pr(Cyp, ryp);
-  const R u0 = C0[1] * r0, v0 = C0[2] * r0;
-  const R i2x = R(1.0 / (2.0 * g.dx)), i2y = R(1.0 / (2.0 * g.dy));
-  const R ux = (Cxp[1] * rxp - Cxm[1] * rxm) * i2x;
-  const R vx = (Cxp[2] * rxp - Cxm[2] * rxm) * i2x;
-  const R Tx = (pxp * rxp - pxm * rxm) * i2x;
-  const R uy = (Cyp[1] * ryp - Cym[1] * rym) * i2y;
-  const R vy = (Cyp[2] * ryp - Cym[2] * rym) * i2y;
-  const R Ty = (pyp * ryp - pym * rym) * i2y;
-  const R c0 = sqrt(ph.gam * p0 * r0);
-  R Fv[4];
-  visc_flux2(0, u0, v0, ux, vx, Tx, uy, vy, Ty, ph, Fv);
-  o[0] = C0[1] - Fv[0];
-  o[1] = C0[1] * u0 + p0 - Fv[1];
-  o[2] = C0[2] * u0 - Fv[2];
-  o[3] = (C0[3] + p0) * u0 - Fv[3];
-  visc_flux2(1, u0, v0, ux, vx, Tx, uy, vy, Ty, ph, Fv);
-  o[4] = C0[2] - Fv[0];
-  o[5] = C0[1] * v0 - Fv[1];
-  o[6] = C0[2] * v0 + p0 - Fv[2];
-  o[7] = (C0[3] + p0) * v0 - Fv[3];
-  o[8] = fabs(u0) + c0;
-  o[9] = fabs(v0) + c0;
-  o[18] = u0;
-  o[19] = v0;
-  o[20] = p0;
-  o[21] = p0 * r0;
-  o[22] = c0;
-  bvisc2_xy(p0, p0 * r0, ux, vx, Tx, uy, vy, Ty, ph, o[10], o[11]);
-  const R jx = fabs(pxp - R(2.0) * p0 + pxm) / fabs(pxp + R(2.0) * p0 + pxm);
-  const R jy = fabs(pyp - R(2.0) * p0 + pym) / fabs(pyp + R(2.0) * p0 + pym);
-  o[12] = mx(jx, jy);
-  const R div = ux + vy, curl = vx - uy;
-  o[13] = mx(-div / sqrt(div * div + curl * curl + R(kDucros)), R(0.0));
-#pragma unroll
-  for (int k = 0; k < 4; ++k) o[14 + k] = C0[k];
-}
-
-// wall projection of a point value (no-slip: zero momentum; symmetry: zero
-// normal momentum; density and internal energy kept)
-__device__ __forceinline__ void project(int kind, int ax, double* V) {
-  if (kind == BC_NOSLIP) {
-    V[3] -= (V[1] * V[1] + V[2] * V[2]) / (2.0 * V[0]);
-    V[1] = 0.0;
-    V[2] = 0.0;
-  } else if (kind == BC_SYMMETRY) {
-    V[3] -= V[1 + ax] * V[1 + ax] / (2.0 * V[0]);
-    V[1 + ax] = 0.0;
-  }
-}
-
-__device__ __forceinline__ int wall_of(int bc) {
-  return (bc == BC_NOSLIP || bc == BC_SYMMETRY) ? bc : -1;
 }
 
 // LDS-resident tile data
@@ -262,14 +121,10 @@ static_assert(4 * NSY <= 14 * NC, "the y-direction site data fit in rows 0-13 of
 template <typename R>
 __device__ __forceinline__ void store_aux(Tile<R>& T, const PhysT<double>& pd, int s,
                                           const double* V) {
-  const double ir = rcp(V[0]);
-  const double p = pd.gm1 * (V[3] - 0.5 * (V[1] * V[1] + V[2] * V[2]) * ir);
-  const double Tt = p * ir;
-  T.A[0][s] = R(V[1] * ir);
-  T.A[1][s] = R(V[2] * ir);
-  T.A[2][s] = R(p);
-  T.A[3][s] = R(Tt);
-  T.A[4][s] = R(sqrt(pd.gam * Tt));
+  R w[5];
+  aux_of_fp64(pd, V, w);
+#pragma unroll
+  for (int k = 0; k < 5; ++k) T.A[k][s] = w[k];
 }
 
 // total flux F_d = F^c_d - F^v_d at an LDS site (a: block+-4 index, q: block+-2 index)
@@ -285,20 +140,6 @@ __device__ __forceinline__ void site_flux(const Tile<R>& T, const PhysT<R>& ph, 
   F[1] = m1 * ud + (d == 0 ? p : R(0.0)) - Fv[1];
   F[2] = m2 * ud + (d == 1 ? p : R(0.0)) - Fv[2];
   F[3] = (E + p) * ud - Fv[3];
-}
-
-// total flux F_d = F^c_d - F^v_d of state (m1, m2, E) with velocity (u, v),
-// pressure p and gradients gr = (u_x, v_x, T_x, u_y, v_y, T_y)
-template <typename R>
-__device__ __forceinline__ void tot_flux(int d, const R* U, R u, R v, R p, const R* gr,
-                                         const PhysT<R>& ph, R* F) {
-  R Fv[4];
-  visc_flux2(d, u, v, gr[0], gr[1], gr[2], gr[3], gr[4], gr[5], ph, Fv);
-  const R ud = d == 0 ? u : v;
-  F[0] = U[1 + d] - Fv[0];
-  F[1] = U[1] * ud + (d == 0 ? p : R(0.0)) - Fv[1];
-  F[2] = U[2] * ud + (d == 1 ? p : R(0.0)) - Fv[2];
-  F[3] = (U[3] + p) * ud - Fv[3];
 }
 
 // The low-order point scheme works on the half lattice whose point sites hold
@@ -590,39 +431,6 @@ struct TileIter {
   }
 };
 
-// launch arguments of a stage: one instance, or a batch of 2D instances
-constexpr int kMaxBatch = 512;
-struct StageArgs {
-  // one instance
-  G2 g;
-  Phys ph;
-  const double* Uk;
-  const double* Un;
-  double* Uout;
-  const double* dt_dev;
-  double dt_host, dt_mul;  // the step is dt_mul * dt
-  unsigned* flags;
-  int ntx;
-  // learned blend (one instance): a blend coefficient per face replacing
-  // theta^s, or NULL; and where to write theta^s per face, or NULL
-  const float* blend;
-  float* ts_out;
-  // a batch: its instances (stage k reads and writes their rotating buffers)
-  afi::BatchInst* inst;
-  int ninst, k;
-  const int* n_active;
-  // one instance whose step machinery lives on the device (a single
-  // descriptor; stage k of its current attempt, nothing once it is
-  // inactive), or NULL: then Uk, Un, Uout, dt and flags above are used.
-  // Its last stage leaves the CFL maxima of the new state in cfl_partial
-  // (a at [wg], v at [kSingleCflBlocks + wg]), for the next step's dt
-  afi::BatchInst* dinst;
-  double* cfl_partial;
-  // both
-  double ca, cb;
-  int first, skip_flagged, ntiles;
-};
-
 // what one tile of a stage works on.  Geometry and physics are referenced,
 // not copied: a copy would hold some thirty uniform values live across the
 // whole tile (register pressure of a kernel that is at its VGPR limit), while
@@ -676,11 +484,7 @@ __device__ __forceinline__ TileArgs batch_tile(const StageArgs& sa, const int* t
   return A;
 }
 
-// BLEND: the single-instance kernel with per-face blend input/output arrays
-// (its own instance, so that the plain stage carries none of that code)
-// DEV: the single-instance kernel of a device-resident step loop, whose
-// buffers, dt and flag word come from the descriptor sa.dinst
-template <typename R, bool BATCH, bool BLEND = false, bool DEV = false>
+template <typename R>
 __global__ void __launch_bounds__(NT) k_stage(StageArgs sa) {
   __shared__ Tile<R> T;
   __shared__ unsigned stop;  // workgroup-uniform copy of the flag word
@@ -688,21 +492,17 @@ __global__ void __launch_bounds__(NT) k_stage(StageArgs sa) {
   const double ca = sa.ca, cb = sa.cb;
   const int first = sa.first, skip_flagged = sa.skip_flagged;
   bool nonfinite = false;
-  // DEV, last stage: CFL rate maxima of the cells this thread writes
-  double cfl_a = 0.0, cfl_v = 0.0;
   // a batch: only the tiles of its active instances are numbered, so that
   // every XCD band holds an equal share of the work whichever instances are
   // active (instances finish their steps after different numbers of
   // attempts).  Active instance j is instance bid[j] and owns tiles
   // [bt0[j], bt0[j] + its ntiles); the numbering comes from two inclusive
   // scans over the instances (one per thread), done in place in bt0 / bid.
-  __shared__ int bt0[BATCH ? kMaxBatch : 1], bid[BATCH ? kMaxBatch : 1];
+  __shared__ int bt0[kMaxBatch], bid[kMaxBatch];
   int ntiles = sa.ntiles, nact = 0;
-  if constexpr (BATCH) {
-    static_assert(kMaxBatch == NT, "one instance per thread in the scans");
-    if (*sa.n_active == 0) return;  // every instance has finished its step
-  }
-  if (BATCH && sa.ninst == 1) {
+  static_assert(kMaxBatch == NT, "one instance per thread in the scans");
+  if (*sa.n_active == 0) return;  // every instance has finished its step
+  if (sa.ninst == 1) {
     // one instance, active (n_active is not 0): its tiles are all the tiles
     if (tid == 0) {
       bid[0] = 0;
@@ -711,7 +511,7 @@ __global__ void __launch_bounds__(NT) k_stage(StageArgs sa) {
     nact = 1;
     ntiles = sa.inst[0].ntiles;
     __syncthreads();
-  } else if constexpr (BATCH) {
+  } else {
     const bool act = tid < sa.ninst && sa.inst[tid].active;
     const int own = act ? sa.inst[tid].ntiles : 0;
     bid[tid] = act ? 1 : 0;
@@ -735,47 +535,9 @@ __global__ void __launch_bounds__(NT) k_stage(StageArgs sa) {
     }
     __syncthreads();
   }
-  // the one instance's buffers, dt and flag word, read once (a per-tile read
-  // of dt costs ~3% of the stage)
-  double dt1 = 0.0;
-  const double* Uk1 = nullptr;
-  const double* Un1 = nullptr;
-  double* Uout1 = nullptr;
-  unsigned* flags1 = nullptr;
-  if constexpr (!BATCH) {
-    if constexpr (DEV) {
-      const afi::BatchInst& I = *sa.dinst;
-      if (!I.active) return;  // its step is done; the round has nothing to do
-      // the three RK3 stages from buf[cur], through the other two buffers
-      const int c = I.cur, a = (c + 1) % 3, b = (c + 2) % 3;
-      Un1 = I.buf[c];
-      Uk1 = sa.k == 0 ? I.buf[c] : (sa.k == 1 ? I.buf[a] : I.buf[b]);
-      Uout1 = sa.k == 1 ? I.buf[b] : I.buf[a];
-      dt1 = I.dt;
-      flags1 = &sa.dinst->flags;
-    } else {
-      dt1 = sa.dt_mul * (sa.dt_dev ? *sa.dt_dev : sa.dt_host);
-    }
-  }
-  // what tile t works on (built where used, from the kernel arguments or the
-  // batch descriptors, so that nothing of it stays live across tiles)
-  auto args = [&](int t) {
-    if constexpr (BATCH) {
-      return batch_tile(sa, bt0, bid, nact, t);
-    } else {
-      TileArgs A;
-      A.g = &sa.g;
-      A.phd = &sa.ph;
-      A.Uk = DEV ? Uk1 : sa.Uk;
-      A.Un = DEV ? Un1 : sa.Un;
-      A.Uout = DEV ? Uout1 : sa.Uout;
-      A.dt = dt1;
-      A.flags = DEV ? flags1 : sa.flags;
-      A.ntx = sa.ntx;
-      A.lt = t;
-      return A;
-    }
-  };
+  // what tile t works on (built where used, from the batch descriptors, so
+  // that nothing of it stays live across tiles)
+  auto args = [&](int t) { return batch_tile(sa, bt0, bid, nact, t); };
   TileIter it(ntiles, blockIdx.x, gridDim.x);
   int tile = it.get();
   double pre[kRawPerThread][4];
@@ -807,24 +569,18 @@ __global__ void __launch_bounds__(NT) k_stage(StageArgs sa) {
   if (tid == 0) stop = skip_flagged ? peek_flags(flags) : 0u;
   __syncthreads();  // the previous tile is done with the LDS; stop is visible
   if (stop) {
-    if constexpr (BATCH) {
-      // with one active instance every later tile is that instance's too
-      if (nact == 1) break;
-      // every wave has read `stop` before thread 0 writes it for the next
-      // tile, which is loaded only once it is known not to be skipped too
-      __syncthreads();
-      tile = it.advance();
-      have_pre = false;
-      continue;
-    } else {
-      break;
-    }
+    // with one active instance every later tile is that instance's too
+    if (nact == 1) break;
+    // every wave has read `stop` before thread 0 writes it for the next
+    // tile, which is loaded only once it is known not to be skipped too
+    __syncthreads();
+    tile = it.advance();
+    have_pre = false;
+    continue;
   }
-  if constexpr (BATCH) {
-    if (!have_pre) {
-      load_raw(g, Uk, X0, Y0, tid, pre, flip);
-      have_pre = true;
-    }
+  if (!have_pre) {
+    load_raw(g, Uk, X0, Y0, tid, pre, flip);
+    have_pre = true;
   }
 
   // ---- phase 0a: raw values of the lattice region (prefetched) ----
@@ -927,28 +683,34 @@ __global__ void __launch_bounds__(NT) k_stage(StageArgs sa) {
     const int s = tid < NT / 2 ? tid : NT / 2 + (NT - 1 - tid);
     const int i = i0 - 1 + s % WC, j = j0 - 1 + s / WC;
     if (s < NC && i <= g.n1 && j <= g.n2) {
-    R C0[4], Cxm[4], Cxp[4], Cym[4], Cyp[4], o[23];
+    CellAvg<R> C0, Cxm, Cxp, Cym, Cyp;
+    R o[23];
     if constexpr (kFP64<R>) {
       // the cell's index among the centres of the region
       const int c = (s / WC + 1) * (TX + 4) + s % WC + 1;
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        C0[k] = T.AVG[k][c];
-        Cxm[k] = T.AVG[k][c - 1];
-        Cxp[k] = T.AVG[k][c + 1];
-        Cym[k] = T.AVG[k][c - (TX + 4)];
-        Cyp[k] = T.AVG[k][c + (TX + 4)];
+        C0.U[k] = T.AVG[k][c];
+        Cxm.U[k] = T.AVG[k][c - 1];
+        Cxp.U[k] = T.AVG[k][c + 1];
+        Cym.U[k] = T.AVG[k][c - (TX + 4)];
+        Cyp.U[k] = T.AVG[k][c + (TX + 4)];
       }
     } else {
       const int a = (2 * j + 1 - Y0 + 4) * WA + (2 * i + 1 - X0 + 4);
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        C0[k] = T.U[k][a];
-        Cxm[k] = T.U[k][a - 2];
-        Cxp[k] = T.U[k][a + 2];
-        Cym[k] = T.U[k][a - 2 * WA];
-        Cyp[k] = T.U[k][a + 2 * WA];
+        C0.U[k] = T.U[k][a];
+        Cxm.U[k] = T.U[k][a - 2];
+        Cxp.U[k] = T.U[k][a + 2];
+        Cym.U[k] = T.U[k][a - 2 * WA];
+        Cyp.U[k] = T.U[k][a + 2 * WA];
       }
+    }
+    // one reciprocal density per cell
+    for (CellAvg<R>* c : {&C0, &Cxm, &Cxp, &Cym, &Cyp}) {
+      c->r = rcp(c->U[0]);
+      c->p = pressure_r(ph, c->U, c->r);
     }
     cell_low(g, ph, C0, Cxm, Cxp, Cym, Cyp, o);
 #pragma unroll
@@ -1051,13 +813,7 @@ __global__ void __launch_bounds__(NT) k_stage(StageArgs sa) {
   __syncthreads();
 
   // ---- phase 3: limited face fluxes of the tile's cells ----
-  const float* blend = nullptr;
-  float* ts_out = nullptr;
-  if constexpr (BLEND && !BATCH) {
-    blend = sa.blend;
-    ts_out = sa.ts_out;
-  }
-  const int limc = (ph.lim & (LIM_SMOOTH | LIM_PP | LIM_LOWONLY)) | (blend ? 1 : 0);
+  const int limc = ph.lim & (LIM_SMOOTH | LIM_PP | LIM_LOWONLY);
   // FP64: the faces take waves 0-3 only; waves 4-7 compute the
   // x-direction site data of the low-order point scheme meanwhile (phase 5a
   // keeps the y-direction data, which overlay cell data the faces read)
@@ -1123,71 +879,18 @@ __global__ void __launch_bounds__(NT) k_stage(StageArgs sa) {
         Fcb[k] = T.C[4 * d + k][cbx];
         FL[k] = R(0.5) * (Fca[k] + Fcb[k]) - R(0.5) * lam * (T.C[14 + k][cbx] - T.C[14 + k][cax]);
       }
-      R ts = R(1.0);
-      double tpp = 1.0;
-      // the face's entries in per-face arrays: x-faces [n2][n1+1], then
-      // y-faces [n2+1][n1]; a periodic axis's last face is its first again
-      const bool use_blend = blend != nullptr;
-      if (ph.lim & LIM_LOWONLY) {
-        ts = R(0.0);
-        tpp = 0.0;
-      } else {
-        if (use_blend) {
-          // the given coefficient takes the place of theta^s
-          const long nfx = (long)g.n2 * (g.n1 + 1);
-          const int fi = (d == 0 && i == g.n1 && g.n1x == g.n1) ? 0 : i;
-          const int fj = (d == 1 && j == g.n2 && g.n2y == g.n2) ? 0 : j;
-          ts = R(blend[d == 0 ? (long)fj * (g.n1 + 1) + fi : nfx + (long)fj * g.n1 + fi]);
-        } else if (ph.lim & LIM_SMOOTH) {
-          ts = exp(-ph.Cs * mx(T.C[12][cax], T.C[12][cbx]) * mx(T.C[13][cax], T.C[13][cbx]));
-        }
-        if (ph.lim & LIM_PP) {
-          // the density and pressure blend in FP64 (Sec. 3.3)
-          const double m4 = 4.0 * dt / (d == 0 ? g.dx : g.dy);
-          double ULp[4], UHp[4], ULm[4], UHm[4];
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            const double fl = FL[k], fh = FH[k], fca = Fca[k], fcb = Fcb[k];
-            const double Fs = fl + double(ts) * (fh - fl);
-            ULp[k] = Ua[k] - m4 * (fl - fca);
-            UHp[k] = Ua[k] - m4 * (Fs - fca);
-            ULm[k] = Ub[k] - m4 * (fcb - fl);
-            UHm[k] = Ub[k] - m4 * (fcb - Fs);
-          }
-          tpp = 0.0;
-          bool bad = false;
-          if (!(ULp[0] > 0.0) || !(ULm[0] > 0.0)) {
-            bad = true;
-          } else {
-            const double pLp = pressure2(ULp[0], ULp[1], ULp[2], ULp[3], phd.gm1);
-            const double pLm = pressure2(ULm[0], ULm[1], ULm[2], ULm[3], phd.gm1);
-            if (!(pLp > 0.0) || !(pLm > 0.0)) bad = true;
-            const double tr = mn(theta_lin(ULp[0], UHp[0], mn(kPPEps, ULp[0])),
-                                 theta_lin(ULm[0], UHm[0], mn(kPPEps, ULm[0])));
-            double Tp[4], Tm[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-              Tp[k] = ULp[k] + tr * (UHp[k] - ULp[k]);
-              Tm[k] = ULm[k] + tr * (UHm[k] - ULm[k]);
-            }
-            const bool ex = ph.lim & LIM_PEXACT;
-            const double tp = mn(theta_p2(ULp, pLp, Tp, mn(kPPEps, pLp), phd.gm1, ex),
-                                 theta_p2(ULm, pLm, Tm, mn(kPPEps, pLm), phd.gm1, ex));
-            tpp = tr * tp;
-          }
-          if (bad) raise_flag(flags, FLAG_CELL_LOW);
-        }
-      }
-      const double th = double(ts) * tpp;
-      if (ts_out) {
-        const long nfx = (long)g.n2 * (g.n1 + 1);
-        ts_out[d == 0 ? (long)j * (g.n1 + 1) + i : nfx + (long)j * g.n1 + i] = float(ts);
-      }
+      FaceCells<R> fc;
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const double fl = FL[k], fh = FH[k];
-        F[k] = R(fl + th * (fh - fl));
+        fc.Ua[k] = Ua[k];
+        fc.Ub[k] = Ub[k];
+        fc.Fa[k] = Fca[k];
+        fc.Fb[k] = Fcb[k];
+        fc.FL[k] = FL[k];
       }
+      fc.phi1 = mx(T.C[12][cax], T.C[12][cbx]);
+      fc.phi2 = mx(T.C[13][cax], T.C[13][cbx]);
+      limit_face(g, ph, phd, d, i, j, dt, fc, FH, nullptr, nullptr, true, flags, F);
     }
     if (d == 0) {
 #pragma unroll
@@ -1215,7 +918,6 @@ __global__ void __launch_bounds__(NT) k_stage(StageArgs sa) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) un[k] = Un[k * nc + gi];
       }
-      double o4[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const double dfx = double(T.FX[k][jj * (TX + 1) + ii + 1]) - double(T.FX[k][jj * (TX + 1) + ii]);
@@ -1229,18 +931,6 @@ __global__ void __launch_bounds__(NT) k_stage(StageArgs sa) {
         const double o = first ? fe : ca * un[k] + cb * fe;
         if (!isfinite(o)) nonfinite = true;
         Uout[k * nc + gi] = o;
-        o4[k] = o;
-      }
-      if constexpr (DEV) {
-        // the last stage of a device-resident step: the CFL rates (eq. cfl)
-        // of the new average, as the CFL kernel takes them, for the next step
-        if (sa.k == 2) {
-          const double p = pressure2(o4[0], o4[1], o4[2], o4[3], phd.gm1);
-          const double cs = sqrt(phd.gam * p / o4[0]);
-          cfl_a = mx(cfl_a, (fabs(o4[1] / o4[0]) + cs) * sa.dinst->icx);
-          cfl_a = mx(cfl_a, (fabs(o4[2] / o4[0]) + cs) * sa.dinst->icy);
-          cfl_v = mx(cfl_v, sa.dinst->vcoef / o4[0]);
-        }
       }
     }
   }
@@ -1380,42 +1070,10 @@ __global__ void __launch_bounds__(NT) k_stage(StageArgs sa) {
       }
     }
   }
-  if constexpr (BATCH) {
-    if (nonfinite) raise_flag(flags, FLAG_NONFINITE);
-    nonfinite = false;
-  }
+  if (nonfinite) raise_flag(flags, FLAG_NONFINITE);
+  nonfinite = false;
   tile = next;
   }  // tiles
-  if constexpr (!BATCH) {
-    if (nonfinite) raise_flag(DEV ? flags1 : sa.flags, FLAG_NONFINITE);
-  }
-  if constexpr (DEV) {
-    // the workgroup's CFL maxima of the new state, one pair per workgroup
-    // (rates of cells this workgroup did not write are 0, neutral for max)
-    if (sa.k == 2) {
-      __shared__ double cfl_w[2][NT / 64];
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        cfl_a = mx(cfl_a, __shfl_xor(cfl_a, o, 64));
-        cfl_v = mx(cfl_v, __shfl_xor(cfl_v, o, 64));
-      }
-      __syncthreads();
-      if ((tid & 63) == 0) {
-        cfl_w[0][tid >> 6] = cfl_a;
-        cfl_w[1][tid >> 6] = cfl_v;
-      }
-      __syncthreads();
-      if (tid == 0) {
-        double a = 0.0, v = 0.0;
-        for (int w = 0; w < NT / 64; ++w) {
-          a = mx(a, cfl_w[0][w]);
-          v = mx(v, cfl_w[1][w]);
-        }
-        sa.cfl_partial[blockIdx.x] = a;
-        sa.cfl_partial[afi::kSingleCflBlocks + blockIdx.x] = v;
-      }
-    }
-  }
 }
 
 // persistent workgroups of a stage kernel instance: as many as fit on the
@@ -1430,78 +1088,12 @@ int resident_workgroups() {
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         cus <= 0)
       cus = 256;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_stage<R, false>, NT, 0) != hipSuccess ||
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_stage<R>, NT, 0) != hipSuccess ||
         per <= 0)
       per = 1;
     cache[dev] = cus * per;
   }
   return cache[dev];
-}
-
-template <typename R>
-hipError_t launch(const G2& g, const Phys& ph, const afi::Work& w, const double* Un,
-                  const double* Uk, double* Uout, const double* dt_dev, double dt_host,
-                  afi::StageCoef sc, hipStream_t s, afi::Timer* tm) {
-  // tiles cover cells [0, n1) and the point columns up to index n1
-  const int ntx = g.n1 / TX + 1, nty = g.n2 / TY + 1;
-  const int ntiles = ntx * nty;
-  int nwg = resident_workgroups<R>();
-  if (nwg > ntiles) nwg = ntiles;
-  if (nwg >= 8) nwg -= nwg % 8;
-  StageArgs sa{};
-  sa.g = g;
-  sa.ph = ph;
-  sa.Uk = Uk;
-  sa.Un = Un;
-  sa.Uout = Uout;
-  sa.dt_dev = dt_dev;
-  sa.dt_host = dt_host;
-  sa.dt_mul = sc.dt_mul;
-  sa.flags = w.flags;
-  sa.ntx = ntx;
-  sa.ca = sc.a;
-  sa.cb = sc.b;
-  sa.first = sc.first;
-  sa.skip_flagged = sc.skip_flagged;
-  sa.blend = sc.blend;
-  sa.ts_out = sc.ts_out;
-  sa.ntiles = ntiles;
-  if (sa.blend || sa.ts_out) {
-    AFI_TIMED(tm, 7, s,
-              hipLaunchKernelGGL((k_stage<R, false, true>), dim3((unsigned)nwg), dim3(NT), 0, s,
-                                 sa));
-  } else {
-    AFI_TIMED(tm, 7, s,
-              hipLaunchKernelGGL((k_stage<R, false>), dim3((unsigned)nwg), dim3(NT), 0, s, sa));
-  }
-  return hipGetLastError();
-}
-
-// stage k of the current attempt of the one instance whose descriptor is
-// dinst (the device-resident step loop of af_run_graph): the single-instance
-// kernel, with its buffers, dt and flags read from the descriptor
-template <typename R>
-hipError_t launch_dev(const G2& g, const Phys& ph, afi::BatchInst* dinst, double* cfl_partial,
-                      int k, hipStream_t s) {
-  const int ntx = g.n1 / TX + 1, nty = g.n2 / TY + 1;
-  const int ntiles = ntx * nty;
-  int nwg = resident_workgroups<R>();
-  if (nwg > ntiles) nwg = ntiles;
-  if (nwg >= 8) nwg -= nwg % 8;
-  StageArgs sa{};
-  sa.g = g;
-  sa.ph = ph;
-  sa.dinst = dinst;
-  sa.cfl_partial = cfl_partial;
-  sa.k = k;
-  sa.ntx = ntx;
-  sa.ca = k == 0 ? 0.0 : (k == 1 ? 0.75 : 1.0 / 3.0);
-  sa.cb = k == 0 ? 1.0 : (k == 1 ? 0.25 : 2.0 / 3.0);
-  sa.first = k == 0;
-  sa.skip_flagged = 1;
-  sa.ntiles = ntiles;
-  hipLaunchKernelGGL((k_stage<R, false, false, true>), dim3((unsigned)nwg), dim3(NT), 0, s, sa);
-  return hipGetLastError();
 }
 
 template <typename R>
@@ -1522,7 +1114,7 @@ hipError_t launch_batch(afi::BatchInst* inst, int ninst, int total_tiles, const 
   if (nwg > total_tiles) nwg = total_tiles;
   if (nwg >= 8) nwg -= nwg % 8;
   AFI_TIMED(tm, 7, s,
-            hipLaunchKernelGGL((k_stage<R, true>), dim3((unsigned)nwg), dim3(NT), 0, s, sa));
+            hipLaunchKernelGGL((k_stage<R>), dim3((unsigned)nwg), dim3(NT), 0, s, sa));
   return hipGetLastError();
 }
 
@@ -1530,29 +1122,8 @@ hipError_t launch_batch(afi::BatchInst* inst, int ninst, int total_tiles, const 
 
 namespace afi {
 
-hipError_t AF_STAGE_ENTRY(const Geo& geo, const Phys& ph, const Work& w, const double* Un,
-                          const double* Uk, double* Uout, const double* dt_dev, double dt_host,
-                          StageCoef sc, hipStream_t s, Timer* tm) {
-  return launch<AF_STAGE_REAL>(afi::stage_geo(geo), ph, w, Un, Uk, Uout, dt_dev, dt_host, sc, s, tm);
-}
-
 // tiles of one 2D grid for this instance's tile shape
 int AF_STAGE_TILES(const Geo& geo) { return (geo.n1 / TX + 1) * (geo.n2 / TY + 1); }
-
-// stage k of the current attempt of the single instance described at dinst
-hipError_t AF_CAT(AF_STAGE_ENTRY, _dev)(const Geo& geo, const Phys& ph, BatchInst* dinst,
-                                        double* cfl_partial, int k, hipStream_t s) {
-  return launch_dev<AF_STAGE_REAL>(afi::stage_geo(geo), ph, dinst, cfl_partial, k, s);
-}
-
-// workgroups of a single-instance stage launch of grid geo
-int AF_CAT(AF_STAGE_ENTRY, _nwg)(const Geo& geo) {
-  const int ntiles = AF_STAGE_TILES(geo);
-  int nwg = resident_workgroups<AF_STAGE_REAL>();
-  if (nwg > ntiles) nwg = ntiles;
-  if (nwg >= 8) nwg -= nwg % 8;
-  return nwg;
-}
 
 // stage k of a step attempt of every active instance of a batch, one launch
 hipError_t AF_STAGE_BATCH(BatchInst* inst, int ninst, int total_tiles, const int* n_active, int k,

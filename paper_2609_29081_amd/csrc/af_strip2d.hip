@@ -1,0 +1,1253 @@
+// af_strip2d.hip -- one SSP-RK3 stage of the 2D compact AF method on gfx950
+// as a pipeline of wavefronts that marches up a strip of the grid.
+//
+// The tile kernel (af_stage2d.hip) spends more than half of its vector
+// instructions on index arithmetic and halo sites, and its waves wait for
+// each other at seven barriers per tile.  Here a workgroup of eight wave64s
+// takes a strip of 60 cell columns (one per lane, two more on either side) and
+// a range of rows, and each wave does one part of the scheme for one row of
+// cells per step of the march:
+//   wave 0  loads row r (raw values a row ahead), primitives of its points and
+//           averages, the Simpson centres of row r-1
+//   wave 1  gradients around row r-1, low-order data of the cells of row r-1
+//   wave 2  limited x-face fluxes of row r-3
+//   wave 3  limited y-face fluxes below row r-2, averages of row r-3
+//   wave 4  x-direction terms of the points ye, co of row r-2
+//   wave 5  x-direction terms of the points xe of row r-3, and their update
+//   wave 6  y-direction terms of the points co, xe of row r-3, update of co
+//   wave 7  y-direction terms of the points ye of row r-3, and their update
+// Everything is computed once per site and row (the columns at the sides of a
+// strip and a few rows at its ends apart), lanes address LDS at unit stride,
+// and directions are compile-time constants.  The waves meet at two barriers
+// per row: between wave 0's writes and wave 1's reads of row r, and at the end.
+// Rows pass through LDS rings of two to four slots (159 KB in FP64); what a
+// wave needs again in the next row stays in its registers.
+//
+// The arithmetic is the tile kernel's, expression by expression, so the two
+// give the same bits.  Single instances run here; batches, whose instances
+// may be smaller than a strip is long, run on the tile kernel.
+#include <algorithm>
+
+#include "af_scheme2d.hpp"
+
+using namespace afd;
+
+namespace {
+
+constexpr int W = 64;                 // lanes: cell columns of a strip with its margins
+constexpr int SX = 60;                // cell columns a strip owns: lanes 2 .. 61
+constexpr int NT = 512;
+constexpr int CO = 0, YE = 1, XE = 2; // point types
+
+template <typename R>
+constexpr bool kFP64 = std::is_same<R, double>::value;
+
+// LDS of a strip.  Column c of a row holds cell column i0 - 2 + c: its points
+// co, xe at the column's lower side, ye and the average or centre at its
+// middle.  A row's slot is its distance from the first loaded row, modulo the
+// number of slots.
+template <typename R>
+struct Rings {
+  R P[3][9][4][W];      // points: U (4), u, v, p, T, c; rows r .. r-3
+  R Z[9][3][W];         // centres, rows r-1 .. r-3
+  R GE0[6][2][W];       // gradients at co and ...
+  R GO0[6][2][W];       // ... ye: rows r-1, r-2
+  R GE1[6][3][W];       // at xe: rows r-1 .. r-3
+  R GO1[4][2][W];       // at centres (u_x, v_x, u_y, v_y): rows r-2, r-3
+  R AV[10][4][W];       // averages: U (4), u, v, p, T, c, 1/rho; rows r .. r-3
+  R C[14][3][W];        // cell low-order data, rows r-1 .. r-3
+  R FX[4][W];           // limited x-face fluxes, row r-3
+  R XC[8][2][W];        // x-direction residual and low-order terms: of co ...
+  R XY[8][2][W];        // ... and ye, rows r-2, r-3
+  R X1[8][W];           // y-direction terms of xe, row r-3
+  // FP32 stencils: FP64 averages, and the low parts V - float(V) of the points
+  double AVD[4][4][kFP64<R> ? 1 : W];
+  float PL[3][4][4][kFP64<R> ? 1 : W];
+  unsigned stop;
+};
+
+// one lattice site: U (4), u, v, p, T, c
+template <typename R>
+struct Site {
+  R U[4], a[5];
+};
+
+template <typename R, int S>
+__device__ __forceinline__ Site<R> site9(const R (&A)[9][S][W], int slot, int c) {
+  Site<R> s;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) s.U[k] = A[k][slot][c];
+#pragma unroll
+  for (int k = 0; k < 5; ++k) s.a[k] = A[4 + k][slot][c];
+  return s;
+}
+template <typename R>
+__device__ __forceinline__ Site<R> avg_site(const R (&A)[10][4][W], int slot, int c) {
+  Site<R> s;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) s.U[k] = A[k][slot][c];
+#pragma unroll
+  for (int k = 0; k < 5; ++k) s.a[k] = A[4 + k][slot][c];
+  return s;
+}
+
+// (u, v, T) of a site
+template <typename R>
+struct Z3 {
+  R u, v, T;
+};
+template <typename R, int Q, int S>
+__device__ __forceinline__ Z3<R> z3(const R (&A)[Q][S][W], int slot, int c) {
+  return Z3<R>{A[4][slot][c], A[5][slot][c], A[7][slot][c]};
+}
+template <typename R>
+__device__ __forceinline__ Z3<R> z3(const Site<R>& s) {
+  return Z3<R>{s.a[0], s.a[1], s.a[3]};
+}
+
+// value of x in the lane to the left (lane - 1) or right (lane + 1); the
+// first or last lane keeps its own
+template <int CTRL>
+__device__ __forceinline__ int lane_shift(int x) {
+  return __builtin_amdgcn_update_dpp(x, x, CTRL, 0xF, 0xF, false);
+}
+template <int CTRL>
+__device__ __forceinline__ float lane_shift(float x) {
+  return __int_as_float(lane_shift<CTRL>(__float_as_int(x)));
+}
+template <int CTRL>
+__device__ __forceinline__ double lane_shift(double x) {
+  const long long v = __double_as_longlong(x);
+  const int lo = lane_shift<CTRL>((int)v), hi = lane_shift<CTRL>((int)(v >> 32));
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+template <typename R>
+__device__ __forceinline__ R from_left(R x) { return lane_shift<0x138>(x); }   // wave_shr:1
+template <typename R>
+__device__ __forceinline__ R from_right(R x) { return lane_shift<0x130>(x); }  // wave_shl:1
+
+// direction-D terms of the residual of a point, from the five sites s of its
+// line and the derivatives across D of the velocities at them: ga of the one
+// along D, gb of the other (index 2 unused).  See point_resid_dir of the tile
+// kernel for the terms.
+template <int D, typename R>
+__device__ __forceinline__ void line_resid(const PhysT<R>& ph, double h, const Site<R>* const* s,
+                                           const R* ga, const R* gb, R* Rd) {
+  const R i6h = R(1.0 / (6.0 * h));
+  R alpha = R(0.0);
+#pragma unroll
+  for (int o = 0; o < 5; ++o) alpha = mx(alpha, fabs(s[o]->a[D]) + s[o]->a[4]);
+  R Rr[4];
+  const R ai = alpha * i6h;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    R f[5], w[5];
+#pragma unroll
+    for (int o = 0; o < 5; ++o) {
+      const R ud = s[o]->a[D], pb = s[o]->a[2];
+      w[o] = k == 0 ? s[o]->U[0] : (k == 1 ? s[o]->U[1 + D] : (k == 2 ? s[o]->U[2 - D] : s[o]->U[3]));
+      f[o] = k == 0 ? s[o]->U[1 + D]
+                    : (k == 1 ? w[o] * ud + pb : (k == 2 ? w[o] * ud : (w[o] + pb) * ud));
+    }
+    Rr[k] = -(dc5(f[0], f[1], f[3], f[4], i6h) + ai * d4(w[0], w[1], w[2], w[3], w[4]));
+  }
+  R va[5], vb[5], Tt[5];
+#pragma unroll
+  for (int o = 0; o < 5; ++o) {
+    va[o] = s[o]->a[D];
+    vb[o] = s[o]->a[1 - D];
+    Tt[o] = s[o]->a[3];
+  }
+  const R s4 = R(4.0 / (h * h));
+  const R mu = ph.mu, m43 = R(4.0 / 3.0) * ph.mu;
+  Rr[1] += s4 * m43 * bcol(va);
+  Rr[2] += s4 * mu * bcol(vb);
+  Rr[3] += s4 * (m43 * bquad(va) + mu * bquad(vb) + ph.kap * bcol(Tt));
+  R m1[5], m2[5], m3[5];
+#pragma unroll
+  for (int o = 0; o < 5; ++o) {
+    if (o == 2) {
+      m1[o] = m2[o] = m3[o] = R(0.0);
+      continue;
+    }
+    m1[o] = -R(2.0 / 3.0) * mu * gb[o];
+    m2[o] = mu * ga[o];
+    m3[o] = mu * (vb[o] * ga[o] - R(2.0 / 3.0) * va[o] * gb[o]);
+  }
+  Rr[1] += dc5(m1[0], m1[1], m1[3], m1[4], i6h);
+  Rr[2] += dc5(m2[0], m2[1], m2[3], m2[4], i6h);
+  Rr[3] += dc5(m3[0], m3[1], m3[3], m3[4], i6h);
+  Rd[0] = Rr[0];
+  Rd[1] = D ? Rr[2] : Rr[1];
+  Rd[2] = D ? Rr[1] : Rr[2];
+  Rd[3] = Rr[3];
+}
+
+// direction-D data of a site of the low-order point scheme (Sec. 3.4): total
+// flux and b, from its central differences over the four neighbours
+template <typename R>
+struct LoFlux {
+  R F[4], b;
+};
+template <int D, typename R>
+__device__ __forceinline__ LoFlux<R> lo_flux(const PhysT<R>& ph, const Site<R>& s, const Z3<R>& xm,
+                                             const Z3<R>& xp, const Z3<R>& ym, const Z3<R>& yp,
+                                             R ihx, R ihy) {
+  R gr[6];
+  gr[0] = (xp.u - xm.u) * ihx;
+  gr[1] = (xp.v - xm.v) * ihx;
+  gr[2] = (xp.T - xm.T) * ihx;
+  gr[3] = (yp.u - ym.u) * ihy;
+  gr[4] = (yp.v - ym.v) * ihy;
+  gr[5] = (yp.T - ym.T) * ihy;
+  LoFlux<R> f;
+  tot_flux(D, s.U, s.a[0], s.a[1], s.a[2], gr, ph, f.F);
+  // the density component is the momentum itself
+  f.F[0] = s.U[1 + D];
+  f.b = bvisc2_dir(D, s.a[2], s.a[3], gr[0], gr[1], gr[2], gr[3], gr[4], gr[5], ph);
+  return f;
+}
+// LLF flux between sites a (minus) and b (plus) of a line of direction D
+template <int D, typename R>
+__device__ __forceinline__ void lo_face(const Site<R>& a, const LoFlux<R>& fa, const Site<R>& b,
+                                        const LoFlux<R>& fb, R* F) {
+  const R ra = fabs(a.a[D]) + a.a[4], rb = fabs(b.a[D]) + b.a[4];
+  const R lam = mx(ra, rb) + mx(fa.b, fb.b);
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    F[k] = R(0.5) * (fa.F[k] + fb.F[k]) - R(0.5) * lam * (b.U[k] - a.U[k]);
+}
+
+// what every wave of the workgroup knows
+template <typename R>
+struct Ctx {
+  const G2& g;
+  const Phys& phd;
+  PhysT<R> ph;
+  const double* __restrict__ Uk;
+  const double* __restrict__ Un;
+  double* __restrict__ Uout;
+  double dt, ca, cb;
+  int first;
+  unsigned* flags;
+  int lane, i0;        // cell column of lane c: i0 - 2 + c
+  int j0, j1;          // rows of the strip
+  int rows;            // rows of the march: r = j0 - 2 .. j0 - 3 + rows
+};
+
+// ring slots of the rows around row r (k = r - (j0 - 2) >= 0)
+__device__ __forceinline__ int slot4(int k) { return k & 3; }
+__device__ __forceinline__ int slot2(int k) { return k & 1; }
+__device__ __forceinline__ int slot3(int k) { return (k + 3) % 3; }
+
+// the stage's update of a point from its residual Rs and low-order terms Ls
+// (Sec. 2.2, 3.4), the RK combination, and the store
+template <typename R>
+__device__ __forceinline__ void point_finish(const Ctx<R>& X, int t, int i, int j, const double* U0,
+                                             const R* Rs, const double* Ls, const double* un,
+                                             bool own, bool& nonfinite) {
+  const G2& g = X.g;
+  double UH[4], out[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) UH[k] = U0[k] + X.dt * double(Rs[k]);
+  if (X.ph.lim & LIM_POINT) {
+    double UL[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) UL[k] = U0[k] - Ls[k];
+    bool lbad = false;
+    double th = theta_pair2(UL, UH, X.phd.gm1, lbad, X.ph.lim & LIM_PEXACT);
+    if (X.ph.lim & LIM_LOWONLY) th = 0.0;
+    if (lbad && own) raise_flag(X.flags, FLAG_POINT_LOW);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) out[k] = (th == 1.0) ? UH[k] : UL[k] + th * (UH[k] - UL[k]);
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) out[k] = UH[k];
+  }
+  if (t != YE) {
+    if (i == 0) project(wall_of(g.bc0), 0, out);
+    if (i == g.n1) project(wall_of(g.bc1), 0, out);
+  }
+  if (t != XE) {
+    if (j == 0) project(wall_of(g.bc2), 1, out);
+    if (j == g.n2) project(wall_of(g.bc3), 1, out);
+  }
+  if (!own) return;
+  const int ni = t == YE ? g.n1 : g.n1x, nj = t == XE ? g.n2 : g.n2y;
+  const long np = (long)ni * nj;
+  double* o = X.Uout + (t == XE ? g.off_xe : (t == YE ? g.off_ye : g.off_co)) + (long)j * ni;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const double v = X.first ? out[k] : X.ca * un[k] + X.cb * out[k];
+    if (!isfinite(v)) nonfinite = true;
+    o[k * np + i] = v;
+  }
+}
+
+// U^n of point (i, j) of type t, or of cell average (i, j) (t = -1)
+template <typename R>
+__device__ __forceinline__ void load_un(const Ctx<R>& X, int t, int i, int j, bool own, double* un) {
+  const G2& g = X.g;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) un[k] = 0.0;
+  if (X.first || !own) return;
+  const int ni = (t == YE || t < 0) ? g.n1 : g.n1x, nj = (t == XE || t < 0) ? g.n2 : g.n2y;
+  const long np = (long)ni * nj;
+  const double* p =
+      X.Un + (t < 0 ? 0L : (t == XE ? g.off_xe : (t == YE ? g.off_ye : g.off_co))) + (long)j * ni;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) un[k] = p[k * np + i];
+}
+
+// FP64 value of a point, from its LDS copy (and, with FP32 stencils, the low part)
+template <typename R>
+__device__ __forceinline__ void fp64_point(const Rings<R>& S, int t, int slot, int c, const R* U,
+                                           double* U0) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    if constexpr (kFP64<R>)
+      U0[k] = U[k];
+    else
+      U0[k] = double(U[k]) + double(S.PL[t][k][slot][c]);
+  }
+}
+
+#define STRIP_BARRIER() __syncthreads()
+
+// the barrier in the middle of a row; true if the attempt was rejected meanwhile
+template <typename R>
+__device__ __forceinline__ bool mid_row(const Rings<R>& S) {
+  STRIP_BARRIER();
+  return __builtin_amdgcn_readfirstlane(S.stop) != 0u;
+}
+
+// ---- wave 0 ----------------------------------------------------------------
+template <typename R>
+struct RawRow {
+  double v[4][4];  // co, ye, xe, average
+  int flipE, flipO;  // momentum flips of the row's even and odd lattice line
+};
+
+template <typename R>
+__device__ __forceinline__ void wave_load(Rings<R>& S, const Ctx<R>& X) {
+  const G2& g = X.g;
+  const int lane = X.lane;
+  const int Xlim = 2 * g.n1, Ylim = 2 * g.n2;
+  // the lane's two lattice columns: image columns, and momentum flips.  Lanes
+  // beyond the grid's ghosts (strips at the upper side) read column 0.
+  const int XE_ = 2 * (X.i0 - 2 + lane);
+  const bool inE = XE_ <= Xlim + kMargin, inO = XE_ + 1 <= Xlim + kMargin;
+  int kxE = -1, kxO = -1;
+  int iE = inE ? axis_image(XE_, Xlim, g.bc0, g.bc1, kxE) : 0;
+  const int iO = inO ? axis_image(XE_ + 1, Xlim, g.bc0, g.bc1, kxO) : 1;
+  if (iE == Xlim && g.n1x == g.n1) iE = 0;
+  const unsigned cE = (unsigned)(iE >> 1), cO = (unsigned)(iO >> 1);
+  const int fxE = image_flips(kxE, -1), fxO = image_flips(kxO, -1);
+  // a centre beyond a wall or outflow side takes the value of its image
+  // column, which another lane of the strip holds
+  const bool ghost_col = inO && (XE_ + 1 < 0 || XE_ + 1 > Xlim) && g.bc0 != BC_PERIODIC;
+  const int image_lane = ((iO - 1) >> 1) - X.i0 + 2;
+  const bool has_ghost_col = g.bc0 != BC_PERIODIC && (X.i0 < 2 || 2 * (X.i0 + 62) > Xlim);
+
+  const int n1 = g.n1, n1x = g.n1x, n2 = g.n2, n2y = g.n2y;
+  const int pl[4] = {n1x * n2y, n1 * n2y, n1x * n2, n1 * n2};  // plane strides
+  auto issue = [&](int r, RawRow<R>& q) {
+    // the row's two lattice lines (rows past the last ghost are never used)
+    int ky, Y = 2 * r;
+    if (Y > Ylim + kMargin) Y = Ylim;
+    int rE = axis_image(Y, Ylim, g.bc2, g.bc3, ky);
+    if (rE == Ylim && n2y == n2) rE = 0;
+    rE >>= 1;
+    q.flipE = image_flips(-1, ky);
+    Y = 2 * r + 1;
+    if (Y > Ylim + kMargin) Y = Ylim - 1;
+    const int rO = axis_image(Y, Ylim, g.bc2, g.bc3, ky) >> 1;
+    q.flipO = image_flips(-1, ky);
+    const double* b[4] = {X.Uk + g.off_co + (long)rE * n1x, X.Uk + g.off_ye + (long)rE * n1,
+                          X.Uk + g.off_xe + (long)rO * n1x, X.Uk + (long)rO * n1};
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) q.v[t][k] = b[t][(long)k * pl[t] + ((t & 1) ? cO : cE)];
+  };
+  // centre of the lane's cell of row r straight from the state (for the row
+  // beyond a lower wall or outflow side, whose image the march has not reached)
+  auto centre_of = [&](int r, R* V, R* w) {
+    int kd, XR = XE_ + 2;
+    const bool inR = XR <= Xlim + kMargin;
+    int iR = inR ? axis_image(XR, Xlim, g.bc0, g.bc1, kd) : 0;
+    if (iR == Xlim && n1x == n1) iR = 0;
+    const unsigned cR = (unsigned)(iR >> 1);
+    R Ub[4], e[4], c[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const double* co = X.Uk + g.off_co + (long)k * pl[0] + (long)r * n1x;
+      const double* ye = X.Uk + g.off_ye + (long)k * pl[1] + (long)r * n1;
+      const double* xe = X.Uk + g.off_xe + (long)k * pl[2] + (long)r * n1x;
+      const double* av = X.Uk + (long)k * pl[3] + (long)r * n1;
+      Ub[k] = R(av[cO]);
+      e[k] = R(xe[cE]) + R(xe[cR]) + R(ye[cO]) + R(ye[n1 + cO]);
+      c[k] = R(co[cE]) + R(co[cR]) + R(co[n1x + cE]) + R(co[n1x + cR]);
+    }
+    centre_value(X.ph, X.phd, Ub, e, c, V, w);
+  };
+  auto flipped = [](R v, bool neg) { return neg ? -v : v; };
+
+  RawRow<R> nx;
+  issue(X.j0 - 2, nx);
+  // the previous row's values in this lane, and its co and xe to the right
+  R pco[4], pye[4], pxe[4], pav[4], pcoR[4], pxeR[4];
+  R zv[4], zw[5];  // the latest centre
+#pragma unroll
+  for (int k = 0; k < 4; ++k) pco[k] = pye[k] = pxe[k] = pav[k] = pcoR[k] = pxeR[k] = zv[k] = R(0.0);
+#pragma unroll
+  for (int k = 0; k < 5; ++k) zw[k] = R(0.0);
+  R lowv[4], loww[5];
+  const bool low_ghost = X.j0 == 0 && g.bc2 != BC_PERIODIC;
+  if (low_ghost) centre_of(0, lowv, loww);
+
+  for (int k = 0; k < X.rows; ++k) {
+    const int r = X.j0 - 2 + k;
+    const int s = slot4(k);
+    RawRow<R> q = nx;
+    if (k + 1 < X.rows) issue(r + 1, nx);
+    // row r: points, then the averages
+    R cur[4][4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int f = ((t & 1) ? fxO : fxE) ^ ((t & 2) ? q.flipO : q.flipE);
+      double V[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const bool neg = (c == 1 && (f & 1)) || (c == 2 && (f & 2));
+        V[c] = neg ? -q.v[t][c] : q.v[t][c];
+        cur[t][c] = R(V[c]);
+      }
+      if (t < 3) {
+        R w[5];
+        aux_of_fp64(X.phd, V, w);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) S.P[t][c][s][lane] = cur[t][c];
+#pragma unroll
+        for (int c = 0; c < 5; ++c) S.P[t][4 + c][s][lane] = w[c];
+        if constexpr (!kFP64<R>) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c) S.PL[t][c][s][lane] = float(V[c] - double(float(V[c])));
+        }
+      } else {
+        const R* C0 = cur[3];
+        const R r0 = rcp(C0[0]);
+        const R p0 = pressure_r(X.ph, C0, r0);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) S.AV[c][s][lane] = C0[c];
+        S.AV[4][s][lane] = C0[1] * r0;
+        S.AV[5][s][lane] = C0[2] * r0;
+        S.AV[6][s][lane] = p0;
+        S.AV[7][s][lane] = p0 * r0;
+        S.AV[8][s][lane] = sqrt(X.ph.gam * p0 * r0);
+        S.AV[9][s][lane] = r0;
+        if constexpr (!kFP64<R>) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c) S.AVD[c][s][lane] = V[c];
+        }
+      }
+    }
+    // co and xe of the column to the right, from the lane that holds it
+    R coR[4], xeR[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      coR[c] = from_right(cur[CO][c]);
+      xeR[c] = from_right(cur[XE][c]);
+    }
+    // centre of row r-1
+    const int rc = r - 1;
+    if (k >= 2) {
+      int f = 0;
+      if (rc < 0 && low_ghost) {
+        int ky;
+        (void)axis_image(2 * rc + 1, Ylim, g.bc2, g.bc3, ky);
+        f = image_flips(-1, ky);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) zv[c] = lowv[c];
+#pragma unroll
+        for (int c = 0; c < 5; ++c) zw[c] = loww[c];
+      } else if (rc >= n2 && g.bc2 != BC_PERIODIC) {
+        // the row beyond the upper side: its image is the row below, whose
+        // centre this lane computed last
+        int ky;
+        (void)axis_image(2 * rc + 1 <= Ylim + kMargin ? 2 * rc + 1 : Ylim, Ylim, g.bc2, g.bc3, ky);
+        f = image_flips(-1, ky);
+      } else {
+        R e[4], cc[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          e[c] = pxe[c] + pxeR[c] + pye[c] + cur[YE][c];
+          cc[c] = pco[c] + pcoR[c] + cur[CO][c] + coR[c];
+        }
+        centre_value(X.ph, X.phd, pav, e, cc, zv, zw);
+      }
+      const int sz = slot3(k - 1);
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        S.Z[c][sz][lane] = flipped(zv[c], (c == 1 && (f & 1)) || (c == 2 && (f & 2)));
+#pragma unroll
+      for (int c = 0; c < 5; ++c)
+        S.Z[4 + c][sz][lane] = flipped(zw[c], (c == 0 && (f & 1)) || (c == 1 && (f & 2)));
+      if (has_ghost_col) {
+        __builtin_amdgcn_wave_barrier();
+        if (ghost_col) {
+          R z[9];
+#pragma unroll
+          for (int c = 0; c < 9; ++c) z[c] = S.Z[c][sz][image_lane];
+#pragma unroll
+          for (int c = 0; c < 9; ++c)
+            S.Z[c][sz][lane] = flipped(z[c], ((c == 1 || c == 4) && (fxO & 1)) ||
+                                                 ((c == 2 || c == 5) && (fxO & 2)));
+        }
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      pco[c] = cur[CO][c];
+      pye[c] = cur[YE][c];
+      pxe[c] = cur[XE][c];
+      pav[c] = cur[3][c];
+      pcoR[c] = coR[c];
+      pxeR[c] = xeR[c];
+    }
+    if (mid_row(S)) return;
+    STRIP_BARRIER();
+  }
+}
+
+// ---- wave 1 ----------------------------------------------------------------
+template <typename R>
+__device__ __forceinline__ void wave_grad(Rings<R>& S, const Ctx<R>& X, int skip_flagged) {
+  const G2& g = X.g;
+  const int c = X.lane, cl = c > 0 ? c - 1 : 0, cr = c < W - 1 ? c + 1 : W - 1;
+  const R ihx = R(1.0 / (6.0 * g.dx)), ihy = R(1.0 / (6.0 * g.dy));
+  // inside a step attempt: stop once any workgroup has flagged it (it is
+  // rejected and its output is never read).  The flag word of the row before
+  // is the one that counts, so that nobody waits for its load.
+  unsigned fl = 0u;
+  for (int k = 0; k < X.rows; ++k) {
+    if (c == 0) S.stop = fl;
+    if (mid_row(S)) return;
+    if (skip_flagged) fl = peek_flags(X.flags);
+    if (k >= 2) {
+      // rows r, r-1, r-2 of the points and averages; r-1 .. r-3 of the centres
+      const int p0 = slot4(k), p1 = slot4(k - 1), p2 = slot4(k - 2);
+      const int z1 = slot3(k - 1), z2 = slot3(k - 2), z3s = slot3(k - 3);
+      const int src[3] = {4, 5, 7};  // u, v, T
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        const int s = src[q];
+        const R (&co)[4][W] = S.P[CO][s];
+        const R (&ye)[4][W] = S.P[YE][s];
+        const R (&xe)[4][W] = S.P[XE][s];
+        const R (&zz)[3][W] = S.Z[s];
+        const int ge = slot2(k - 1);
+        // co and ye of row r-1
+        S.GE0[q][ge][c] = dc5(co[p1][cl], ye[p1][cl], ye[p1][c], co[p1][cr], ihx);
+        S.GE0[3 + q][ge][c] = dc5(co[p2][c], xe[p2][c], xe[p1][c], co[p0][c], ihy);
+        S.GO0[q][ge][c] = dc5(ye[p1][cl], co[p1][c], co[p1][cr], ye[p1][cr], ihx);
+        S.GO0[3 + q][ge][c] = dc5(ye[p2][c], zz[z2][c], zz[z1][c], ye[p0][c], ihy);
+        // xe of row r-1
+        const int g1 = slot3(k - 1);
+        S.GE1[q][g1][c] = dc5(xe[p1][cl], zz[z1][cl], zz[z1][c], xe[p1][cr], ihx);
+        S.GE1[3 + q][g1][c] = dc5(xe[p2][c], co[p1][c], co[p0][c], xe[p0][c], ihy);
+        // centres of row r-2
+        if (q < 2) {
+          const int g2 = slot2(k - 2);
+          S.GO1[q][g2][c] = dc5(zz[z2][cl], xe[p2][c], xe[p2][cr], zz[z2][cr], ihx);
+          S.GO1[2 + q][g2][c] = dc5(zz[z3s][c], ye[p2][c], ye[p1][c], zz[z1][c], ihy);
+        }
+      }
+      // low-order data of the cells of row r-1
+      auto cell = [&](int slot, int col) {
+        CellAvg<R> a;
+#pragma unroll
+        for (int n = 0; n < 4; ++n) a.U[n] = S.AV[n][slot][col];
+        a.p = S.AV[6][slot][col];
+        a.r = S.AV[9][slot][col];
+        return a;
+      };
+      R o[23];
+      cell_low(g, X.ph, cell(p1, c), cell(p1, cl), cell(p1, cr), cell(p2, c), cell(p0, c), o);
+      const int sc = slot3(k - 1);
+#pragma unroll
+      for (int n = 0; n < 14; ++n) S.C[n][sc][c] = o[n];
+    }
+    STRIP_BARRIER();
+  }
+}
+
+// what a face needs of one of its cells
+template <typename R>
+struct FaceCell {
+  double U64[4];
+  R U[4], F[4], rs, b, phi1, phi2;
+};
+template <typename R>
+__device__ __forceinline__ FaceCell<R> face_cell(const Rings<R>& S, int d, int sc, int sa, int c) {
+  FaceCell<R> f;
+#pragma unroll
+  for (int n = 0; n < 4; ++n) {
+    f.U[n] = S.AV[n][sa][c];
+    if constexpr (kFP64<R>)
+      f.U64[n] = f.U[n];
+    else
+      f.U64[n] = S.AVD[n][sa][c];
+    f.F[n] = S.C[4 * d + n][sc][c];
+  }
+  f.rs = S.C[8 + d][sc][c];
+  f.b = S.C[10 + d][sc][c];
+  f.phi1 = S.C[12][sc][c];
+  f.phi2 = S.C[13][sc][c];
+  return f;
+}
+
+template <typename R>
+__device__ __forceinline__ void face_between(const Ctx<R>& X, int d, int i, int j,
+                                             const FaceCell<R>& a, const FaceCell<R>& b, const R* FH,
+                                             const float* blend, float* ts_out, bool own, R* F) {
+  const int limc = (X.ph.lim & (LIM_SMOOTH | LIM_PP | LIM_LOWONLY)) | (blend ? 1 : 0);
+  if (!limc) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) F[k] = FH[k];
+    return;
+  }
+  FaceCells<R> fc;
+  const R lam = mx(a.rs, b.rs) + mx(a.b, b.b);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    fc.Ua[k] = a.U64[k];
+    fc.Ub[k] = b.U64[k];
+    fc.Fa[k] = a.F[k];
+    fc.Fb[k] = b.F[k];
+    fc.FL[k] = R(0.5) * (a.F[k] + b.F[k]) - R(0.5) * lam * (b.U[k] - a.U[k]);
+  }
+  fc.phi1 = mx(a.phi1, b.phi1);
+  fc.phi2 = mx(a.phi2, b.phi2);
+  limit_face(X.g, X.ph, X.phd, d, i, j, X.dt, fc, FH, blend, ts_out, own, X.flags, F);
+}
+
+// total flux of direction D at a point of type t, gradients gr
+template <int D, typename R, int S1, int S2>
+__device__ __forceinline__ void point_flux(const PhysT<R>& ph, const R (&P)[9][S1][W], int sp,
+                                           const R (&G)[6][S2][W], int sg, int c, R* F) {
+  R U[4], gr[6];
+  U[0] = R(0.0);  // not read
+#pragma unroll
+  for (int k = 1; k < 4; ++k) U[k] = P[k][sp][c];
+#pragma unroll
+  for (int k = 0; k < 6; ++k) gr[k] = G[k][sg][c];
+  tot_flux(D, U, P[4][sp][c], P[5][sp][c], P[6][sp][c], gr, ph, F);
+}
+
+// ---- wave 2: x-face fluxes of row r-3 ---------------------------------------
+template <typename R>
+__device__ __forceinline__ void wave_xface(Rings<R>& S, const Ctx<R>& X, const float* blend,
+                                           float* ts_out) {
+  const G2& g = X.g;
+  const int c = X.lane, cl = c > 0 ? c - 1 : 0, i = X.i0 - 2 + c;
+  const bool own_col = c >= 2 && c <= SX + 2 && i <= g.n1;
+  R Fco[4], Fxe[4];  // fluxes at co and xe of the row before
+#pragma unroll
+  for (int n = 0; n < 4; ++n) Fco[n] = Fxe[n] = R(0.0);
+  for (int k = 0; k < X.rows; ++k) {
+    const int r = X.j0 - 2 + k;
+    if (k >= 4) {
+      R F0[4], F1[4];
+      point_flux<0>(X.ph, S.P[CO], slot4(k - 2), S.GE0, slot2(k - 2), c, F0);
+      point_flux<0>(X.ph, S.P[XE], slot4(k - 2), S.GE1, slot3(k - 2), c, F1);
+      const int j = r - 3;
+      if (j >= X.j0 && j < X.j1 && j < g.n2) {
+        R FH[4], F[4];
+#pragma unroll
+        for (int n = 0; n < 4; ++n) FH[n] = (Fco[n] + R(4.0) * Fxe[n] + F0[n]) * R(1.0 / 6.0);
+        const FaceCell<R> a = face_cell(S, 0, slot3(k - 3), slot4(k - 3), cl);
+        const FaceCell<R> b = face_cell(S, 0, slot3(k - 3), slot4(k - 3), c);
+        face_between(X, 0, i, j, a, b, FH, blend, ts_out, own_col, F);
+#pragma unroll
+        for (int n = 0; n < 4; ++n) S.FX[n][c] = F[n];
+      }
+#pragma unroll
+      for (int n = 0; n < 4; ++n) {
+        Fco[n] = F0[n];
+        Fxe[n] = F1[n];
+      }
+    }
+    if (mid_row(S)) return;
+    STRIP_BARRIER();
+  }
+}
+
+// ---- wave 3: y-face fluxes below row r-2, averages of row r-3 ----------------
+template <typename R, bool DEV>
+__device__ __forceinline__ void wave_yface(Rings<R>& S, const Ctx<R>& X, const float* blend,
+                                           float* ts_out, bool& nonfinite, const afi::BatchInst* dinst,
+                                           int rates, double& cfl_a, double& cfl_v) {
+  const G2& g = X.g;
+  const int c = X.lane, i = X.i0 - 2 + c;
+  const bool own_col = c >= 2 && c < SX + 2 && i < g.n1;
+  const int cr = c < W - 1 ? c + 1 : W - 1;
+  FaceCell<R> low;  // the cell below the face
+  R Flow[4];        // flux through the lower side of row r-3
+#pragma unroll
+  for (int n = 0; n < 4; ++n) {
+    Flow[n] = R(0.0);
+    low.U64[n] = 0.0;
+    low.U[n] = low.F[n] = R(0.0);
+  }
+  low.rs = low.b = low.phi1 = low.phi2 = R(0.0);
+  const double mxd = X.dt / g.dx, myd = X.dt / g.dy;
+  const long nc = (long)g.n1 * g.n2;
+  for (int k = 0; k < X.rows; ++k) {
+    const int r = X.j0 - 2 + k;
+    const int ju = r - 3;  // the row whose averages are updated
+    const bool upd = ju >= X.j0 && ju < X.j1 && ju < g.n2;
+    R F[4];
+    double un[4], av[4];
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+      F[n] = R(0.0);
+      av[n] = low.U64[n];  // the average of row r-3
+    }
+    load_un(X, -1, i, ju, own_col && upd, un);
+    if (k >= 3) {
+      const int j = r - 2;
+      const FaceCell<R> up = face_cell(S, 1, slot3(k - 2), slot4(k - 2), c);
+      if (j >= X.j0 && j <= X.j1 && j <= g.n2) {
+        R Fa[4], Fm[4], FH[4];
+        point_flux<1>(X.ph, S.P[CO], slot4(k - 2), S.GE0, slot2(k - 2), c, Fa);
+        point_flux<1>(X.ph, S.P[YE], slot4(k - 2), S.GO0, slot2(k - 2), c, Fm);
+#pragma unroll
+        for (int n = 0; n < 4; ++n)
+          FH[n] = (Fa[n] + R(4.0) * Fm[n] + from_right(Fa[n])) * R(1.0 / 6.0);
+        face_between(X, 1, i, j, low, up, FH, blend, ts_out, own_col, F);
+      }
+      low = up;
+    }
+    if (mid_row(S)) return;
+    if (upd) {
+      double o4[4];
+      const long gi = (long)ju * g.n1 + i;
+#pragma unroll
+      for (int n = 0; n < 4; ++n) {
+        const double dfx = double(S.FX[n][cr]) - double(S.FX[n][c]);
+        const double dfy = double(F[n]) - double(Flow[n]);
+        const double fe = av[n] - mxd * dfx - myd * dfy;
+        const double o = X.first ? fe : X.ca * un[n] + X.cb * fe;
+        o4[n] = o;
+        if (own_col) {
+          if (!isfinite(o)) nonfinite = true;
+          X.Uout[n * nc + gi] = o;
+        }
+      }
+      if constexpr (DEV) {
+        // the last stage of a device-resident step: the CFL rates (eq. cfl)
+        // of the new average, as the CFL kernel takes them, for the next step
+        if (rates && own_col) {
+          const double p = pressure2(o4[0], o4[1], o4[2], o4[3], X.phd.gm1);
+          const double cs = sqrt(X.phd.gam * p / o4[0]);
+          cfl_a = mx(cfl_a, (fabs(o4[1] / o4[0]) + cs) * dinst->icx);
+          cfl_a = mx(cfl_a, (fabs(o4[2] / o4[0]) + cs) * dinst->icy);
+          cfl_v = mx(cfl_v, dinst->vcoef / o4[0]);
+        }
+      }
+    }
+#pragma unroll
+    for (int n = 0; n < 4; ++n) Flow[n] = F[n];
+    STRIP_BARRIER();
+  }
+}
+
+// ---- wave 4: x-direction terms of co and ye, row r-2 -------------------------
+template <typename R>
+__device__ __forceinline__ void wave_x0(Rings<R>& S, const Ctx<R>& X) {
+  const G2& g = X.g;
+  const int c = X.lane, cl = c > 0 ? c - 1 : 0, cr = c < W - 1 ? c + 1 : W - 1;
+  const R ihx = R(1.0 / g.dx), ihy = R(1.0 / g.dy);
+  const R cL = R(2.0 * X.dt / g.dx);
+  for (int k = 0; k < X.rows; ++k) {
+    const int r = X.j0 - 2 + k, j = r - 2;
+    const bool on = j >= X.j0 && j < X.j1;
+    const int s2 = slot4(k - 2), s3 = slot4(k - 3), gs = slot2(k - 2);
+    Site<R> El, Ol, E, O, Er, Or;
+    if (on) {
+      El = site9(S.P[CO], s2, cl);
+      Ol = site9(S.P[YE], s2, cl);
+      E = site9(S.P[CO], s2, c);
+      O = site9(S.P[YE], s2, c);
+      Er = site9(S.P[CO], s2, cr);
+      Or = site9(S.P[YE], s2, cr);
+      // derivatives along y of u and v: across the line
+      R ue[3], ve[3], uo[3], vo[3];
+      const int cols[3] = {cl, c, cr};
+#pragma unroll
+      for (int n = 0; n < 3; ++n) {
+        ue[n] = S.GE0[3][gs][cols[n]];
+        ve[n] = S.GE0[4][gs][cols[n]];
+        uo[n] = S.GO0[3][gs][cols[n]];
+        vo[n] = S.GO0[4][gs][cols[n]];
+      }
+      R Rd[4];
+      {
+        const Site<R>* s[5] = {&El, &Ol, &E, &O, &Er};
+        const R ga[5] = {ue[0], uo[0], R(0.0), uo[1], ue[2]};
+        const R gb[5] = {ve[0], vo[0], R(0.0), vo[1], ve[2]};
+        line_resid<0>(X.ph, g.dx, s, ga, gb, Rd);
+#pragma unroll
+        for (int n = 0; n < 4; ++n) S.XC[n][gs][c] = Rd[n];
+      }
+      {
+        const Site<R>* s[5] = {&Ol, &E, &O, &Er, &Or};
+        const R ga[5] = {uo[0], ue[1], R(0.0), ue[2], uo[2]};
+        const R gb[5] = {vo[0], ve[1], R(0.0), ve[2], vo[2]};
+        line_resid<0>(X.ph, g.dx, s, ga, gb, Rd);
+#pragma unroll
+        for (int n = 0; n < 4; ++n) S.XY[n][gs][c] = Rd[n];
+      }
+    }
+    if (mid_row(S)) return;
+    if (on && (X.ph.lim & LIM_POINT)) {
+      const LoFlux<R> fE = lo_flux<0>(X.ph, E, z3(Ol), z3(O), z3(S.P[XE], s3, c),
+                                      z3(S.P[XE], s2, c), ihx, ihy);
+      const LoFlux<R> fO =
+          lo_flux<0>(X.ph, O, z3(E), z3(Er), z3(S.AV, s3, c), z3(S.AV, s2, c), ihx, ihy);
+      LoFlux<R> fEr;
+#pragma unroll
+      for (int n = 0; n < 4; ++n) fEr.F[n] = from_right(fE.F[n]);
+      fEr.b = from_right(fE.b);
+      R Feo[4], Foe[4];
+      lo_face<0>(E, fE, O, fO, Feo);
+      lo_face<0>(O, fO, Er, fEr, Foe);
+#pragma unroll
+      for (int n = 0; n < 4; ++n) {
+        S.XC[4 + n][gs][c] = cL * (Feo[n] - from_left(Foe[n]));
+        S.XY[4 + n][gs][c] = cL * (Foe[n] - Feo[n]);
+      }
+    }
+    STRIP_BARRIER();
+  }
+}
+
+// ---- wave 5: x-direction terms and update of xe, row r-3 ---------------------
+template <typename R>
+__device__ __forceinline__ void wave_x1(Rings<R>& S, const Ctx<R>& X, bool& nonfinite) {
+  const G2& g = X.g;
+  const int c = X.lane, cl = c > 0 ? c - 1 : 0, cr = c < W - 1 ? c + 1 : W - 1;
+  const int i = X.i0 - 2 + c;
+  const bool own_col = c >= 2 && c < SX + 2 && i < g.n1x;
+  const R ihx = R(1.0 / g.dx), ihy = R(1.0 / g.dy);
+  const R cL = R(2.0 * X.dt / g.dx);
+  for (int k = 0; k < X.rows; ++k) {
+    const int r = X.j0 - 2 + k, j = r - 3;
+    const bool on = j >= X.j0 && j < X.j1 && j < g.n2;
+    const int s2 = slot4(k - 2), s3 = slot4(k - 3), z = slot3(k - 3);
+    R Rx[4], Lx[4];
+    double un[4], U0[4];
+    if (on) {
+      load_un(X, XE, i, j, own_col, un);
+      const Site<R> E = site9(S.P[XE], s3, c);
+      fp64_point(S, XE, s3, c, E.U, U0);
+      {
+        const Site<R> El = site9(S.P[XE], s3, cl), Er = site9(S.P[XE], s3, cr);
+        const Site<R> Zl = site9(S.Z, z, cl), Zr = site9(S.Z, z, c);
+        const int e1 = slot3(k - 3), o1 = slot2(k - 3);
+        const Site<R>* s[5] = {&El, &Zl, &E, &Zr, &Er};
+        const R ga[5] = {S.GE1[3][e1][cl], S.GO1[2][o1][cl], R(0.0), S.GO1[2][o1][c],
+                         S.GE1[3][e1][cr]};
+        const R gb[5] = {S.GE1[4][e1][cl], S.GO1[3][o1][cl], R(0.0), S.GO1[3][o1][c],
+                         S.GE1[4][e1][cr]};
+        line_resid<0>(X.ph, g.dx, s, ga, gb, Rx);
+      }
+      if (X.ph.lim & LIM_POINT) {
+        // the line xe, average, xe
+        const Site<R> A = avg_site(S.AV, s3, c);
+        const Z3<R> Al = z3(S.AV, s3, cl), Er = z3(S.P[XE], s3, cr);
+        const LoFlux<R> fE = lo_flux<0>(X.ph, E, Al, z3(A), z3(S.P[CO], s3, c), z3(S.P[CO], s2, c),
+                                        ihx, ihy);
+        const LoFlux<R> fA = lo_flux<0>(X.ph, A, z3(E), Er, z3(S.P[YE], s3, c), z3(S.P[YE], s2, c),
+                                        ihx, ihy);
+        Site<R> Asl;
+        LoFlux<R> fAl;
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+          Asl.U[n] = from_left(A.U[n]);
+          fAl.F[n] = from_left(fA.F[n]);
+        }
+        Asl.a[0] = Al.u;
+        Asl.a[4] = from_left(A.a[4]);
+        fAl.b = from_left(fA.b);
+        R Fm[4], Fp[4];
+        lo_face<0>(Asl, fAl, E, fE, Fm);
+        lo_face<0>(E, fE, A, fA, Fp);
+#pragma unroll
+        for (int n = 0; n < 4; ++n) Lx[n] = cL * (Fp[n] - Fm[n]);
+      } else {
+#pragma unroll
+        for (int n = 0; n < 4; ++n) Lx[n] = R(0.0);
+      }
+    }
+    if (mid_row(S)) return;
+    if (on) {
+      R Rs[4];
+      double Ls[4];
+#pragma unroll
+      for (int n = 0; n < 4; ++n) {
+        Rs[n] = Rx[n] + S.X1[n][c];
+        Ls[n] = double(Lx[n]) + double(S.X1[4 + n][c]);
+      }
+      point_finish(X, XE, i, j, U0, Rs, Ls, un, own_col, nonfinite);
+    }
+    STRIP_BARRIER();
+  }
+}
+
+// ---- wave 6: y-direction terms of co and xe, row r-3; update of co ------------
+template <typename R>
+__device__ __forceinline__ void wave_y0(Rings<R>& S, const Ctx<R>& X, bool& nonfinite) {
+  const G2& g = X.g;
+  const int c = X.lane, cl = c > 0 ? c - 1 : 0, i = X.i0 - 2 + c;
+  const bool own_col = c >= 2 && c < SX + 2 && i < g.n1x;
+  const R ihx = R(1.0 / g.dx), ihy = R(1.0 / g.dy);
+  const R cL = R(2.0 * X.dt / g.dy);
+  // the line of the column: sites of rows r-4, r-3 (co, xe each), and their
+  // derivatives along x
+  Site<R> c4{}, x4{}, c3{}, x3{};
+  R gc4[2] = {}, gx4[2] = {}, gc3[2] = {}, gx3[2] = {};
+  LoFlux<R> fc3{};  // low-order data of co of row r-3
+  R Fprev[4] = {};  // LLF flux between xe of row r-4 and co of row r-3
+  for (int k = 0; k < X.rows; ++k) {
+    const int r = X.j0 - 2 + k, j = r - 3;
+    const bool on = j >= X.j0 && j < X.j1;  // co; xe too unless j = n2
+    const int s2 = slot4(k - 2), s3 = slot4(k - 3);
+    Site<R> c2{}, x2{};
+    R gc2[2] = {}, gx2[2] = {}, Fcx[4] = {}, Fxc[4] = {}, Rd[4];
+    LoFlux<R> fc2{};
+    double un[4];
+    load_un(X, CO, i, j, own_col && on, un);
+    if (k >= 3) {
+      c2 = site9(S.P[CO], s2, c);
+      x2 = site9(S.P[XE], s2, c);
+#pragma unroll
+      for (int n = 0; n < 2; ++n) {
+        gc2[n] = S.GE0[n][slot2(k - 2)][c];
+        gx2[n] = S.GE1[n][slot3(k - 2)][c];
+      }
+    }
+    if (k >= 4 && (X.ph.lim & LIM_POINT)) {
+      const LoFlux<R> fx3 = lo_flux<1>(X.ph, x3, z3(S.AV, s3, cl), z3(S.AV, s3, c), z3(c3), z3(c2),
+                                       ihx, ihy);
+      fc2 = lo_flux<1>(X.ph, c2, z3(S.P[YE], s2, cl), z3(S.P[YE], s2, c), z3(x3), z3(x2), ihx, ihy);
+      lo_face<1>(c3, fc3, x3, fx3, Fcx);
+      lo_face<1>(x3, fx3, c2, fc2, Fxc);
+    }
+    if (on) {
+      const Site<R>* s[5] = {&x4, &c3, &x3, &c2, &x2};
+      const R ga[5] = {gx4[1], gc3[1], R(0.0), gc2[1], gx2[1]};
+      const R gb[5] = {gx4[0], gc3[0], R(0.0), gc2[0], gx2[0]};
+      line_resid<1>(X.ph, g.dy, s, ga, gb, Rd);
+#pragma unroll
+      for (int n = 0; n < 4; ++n) {
+        S.X1[n][c] = Rd[n];
+        S.X1[4 + n][c] = cL * (Fxc[n] - Fcx[n]);
+      }
+    }
+    if (mid_row(S)) return;
+    if (on) {
+      const Site<R>* s[5] = {&c4, &x4, &c3, &x3, &c2};
+      const R ga[5] = {gc4[1], gx4[1], R(0.0), gx3[1], gc2[1]};
+      const R gb[5] = {gc4[0], gx4[0], R(0.0), gx3[0], gc2[0]};
+      line_resid<1>(X.ph, g.dy, s, ga, gb, Rd);
+      const int gs = slot2(k - 3);
+      R Rs[4];
+      double Ls[4], U0[4];
+#pragma unroll
+      for (int n = 0; n < 4; ++n) {
+        Rs[n] = S.XC[n][gs][c] + Rd[n];
+        const R Ly = cL * (Fcx[n] - Fprev[n]);  // rounded before the sum
+        Ls[n] = double(S.XC[4 + n][gs][c]) + double(Ly);
+      }
+      fp64_point(S, CO, s3, c, c3.U, U0);
+      point_finish(X, CO, i, j, U0, Rs, Ls, un, own_col, nonfinite);
+    }
+    c4 = c3;
+    x4 = x3;
+    c3 = c2;
+    x3 = x2;
+    fc3 = fc2;
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      gc4[n] = gc3[n];
+      gx4[n] = gx3[n];
+      gc3[n] = gc2[n];
+      gx3[n] = gx2[n];
+    }
+#pragma unroll
+    for (int n = 0; n < 4; ++n) Fprev[n] = Fxc[n];
+    STRIP_BARRIER();
+  }
+}
+
+// ---- wave 7: y-direction terms and update of ye, row r-3 ----------------------
+template <typename R>
+__device__ __forceinline__ void wave_y1(Rings<R>& S, const Ctx<R>& X, bool& nonfinite) {
+  const G2& g = X.g;
+  const int c = X.lane, cr = c < W - 1 ? c + 1 : W - 1, i = X.i0 - 2 + c;
+  const bool own_col = c >= 2 && c < SX + 2 && i < g.n1;
+  const R ihx = R(1.0 / g.dx), ihy = R(1.0 / g.dy);
+  const R cL = R(2.0 * X.dt / g.dy);
+  // the line of the column: ye and centre of row r-4, ye of row r-3
+  Site<R> y4{}, z4{}, y3{};
+  R gy4[2] = {}, gz4[2] = {}, gy3[2] = {};
+  LoFlux<R> fy3{};
+  R Fprev[4] = {};  // LLF flux between the average of row r-4 and ye of row r-3
+  for (int k = 0; k < X.rows; ++k) {
+    const int r = X.j0 - 2 + k, j = r - 3;
+    const bool on = j >= X.j0 && j < X.j1;
+    const int s2 = slot4(k - 2), s3 = slot4(k - 3);
+    Site<R> y2{}, z3_{};
+    R gy2[2] = {}, gz3[2] = {}, Fya[4] = {}, Fay[4] = {}, Rd[4];
+    LoFlux<R> fy2{};
+    double un[4];
+    load_un(X, YE, i, j, own_col && on, un);
+    if (k >= 3) {
+      y2 = site9(S.P[YE], s2, c);
+      z3_ = site9(S.Z, slot3(k - 3), c);
+#pragma unroll
+      for (int n = 0; n < 2; ++n) {
+        gy2[n] = S.GO0[n][slot2(k - 2)][c];
+        gz3[n] = S.GO1[n][slot2(k - 3)][c];
+      }
+    }
+    if (on) {
+      const Site<R>* s[5] = {&y4, &z4, &y3, &z3_, &y2};
+      const R ga[5] = {gy4[1], gz4[1], R(0.0), gz3[1], gy2[1]};
+      const R gb[5] = {gy4[0], gz4[0], R(0.0), gz3[0], gy2[0]};
+      line_resid<1>(X.ph, g.dy, s, ga, gb, Rd);
+    }
+    if (mid_row(S)) return;
+    if (k >= 4 && (X.ph.lim & LIM_POINT)) {
+      const Site<R> A = avg_site(S.AV, s3, c);
+      const LoFlux<R> fA = lo_flux<1>(X.ph, A, z3(S.P[XE], s3, c), z3(S.P[XE], s3, cr), z3(y3),
+                                      z3(y2), ihx, ihy);
+      fy2 = lo_flux<1>(X.ph, y2, z3(S.P[CO], s2, c), z3(S.P[CO], s2, cr), z3(A), z3(S.AV, s2, c),
+                       ihx, ihy);
+      lo_face<1>(y3, fy3, A, fA, Fya);
+      lo_face<1>(A, fA, y2, fy2, Fay);
+    }
+    if (on) {
+      const int gs = slot2(k - 3);
+      R Rs[4];
+      double Ls[4], U0[4];
+#pragma unroll
+      for (int n = 0; n < 4; ++n) {
+        Rs[n] = S.XY[n][gs][c] + Rd[n];
+        const R Ly = cL * (Fya[n] - Fprev[n]);  // rounded before the sum
+        Ls[n] = double(S.XY[4 + n][gs][c]) + double(Ly);
+      }
+      fp64_point(S, YE, s3, c, y3.U, U0);
+      point_finish(X, YE, i, j, U0, Rs, Ls, un, own_col, nonfinite);
+    }
+    y4 = y3;
+    z4 = z3_;
+    y3 = y2;
+    fy3 = fy2;
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      gy4[n] = gy3[n];
+      gz4[n] = gz3[n];
+      gy3[n] = gy2[n];
+    }
+#pragma unroll
+    for (int n = 0; n < 4; ++n) Fprev[n] = Fay[n];
+    STRIP_BARRIER();
+  }
+}
+
+// how a launch cuts its grid: nx columns of strips, ny ranges of H rows
+struct Strips {
+  int nx, ny, H;
+};
+
+// BLEND: per-face blend input/output arrays; DEV: buffers, dt and flag word
+// from the descriptor sa.dinst of a device-resident step loop.
+template <typename R, bool BLEND, bool DEV>
+__global__ void __launch_bounds__(NT) k_strip(StageArgs sa, Strips st) {
+  __shared__ Rings<R> S;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const double* Uk = sa.Uk;
+  const double* Un = sa.Un;
+  double* Uout = sa.Uout;
+  double dt;
+  unsigned* flags = sa.flags;
+  if constexpr (DEV) {
+    const afi::BatchInst& I = *sa.dinst;
+    if (!I.active) return;  // its step is done; the round has nothing to do
+    // the three RK3 stages from buf[cur], through the other two buffers
+    const int c = I.cur, a = (c + 1) % 3, b = (c + 2) % 3;
+    Un = I.buf[c];
+    Uk = sa.k == 0 ? I.buf[c] : (sa.k == 1 ? I.buf[a] : I.buf[b]);
+    Uout = sa.k == 1 ? I.buf[b] : I.buf[a];
+    dt = I.dt;
+    flags = &sa.dinst->flags;
+  } else {
+    dt = sa.dt_mul * (sa.dt_dev ? *sa.dt_dev : sa.dt_host);
+  }
+  const float* blend = BLEND ? sa.blend : nullptr;
+  float* ts_out = BLEND ? sa.ts_out : nullptr;
+  bool nonfinite = false;
+  double cfl_a = 0.0, cfl_v = 0.0;
+  const int j0 = blockIdx.y * st.H, j1 = min(j0 + st.H, sa.g.n2y);
+  // a row of the strip is finished when the march is three rows past it
+  const Ctx<R> X{sa.g,  sa.ph, phys_as<R>(sa.ph), Uk,    Un,
+                 Uout,  dt,    sa.ca,             sa.cb, sa.first,
+                 flags, (int)(threadIdx.x & 63),  (int)blockIdx.x * SX,
+                 j0,    j1,    j1 - j0 + 5};
+  switch (wave) {
+    case 0: wave_load(S, X); break;
+    case 1: wave_grad(S, X, sa.skip_flagged); break;
+    case 2: wave_xface(S, X, blend, ts_out); break;
+    case 3:
+      wave_yface<R, DEV>(S, X, blend, ts_out, nonfinite, sa.dinst, sa.k == 2, cfl_a,
+                         cfl_v);
+      break;
+    case 4: wave_x0(S, X); break;
+    case 5: wave_x1(S, X, nonfinite); break;
+    case 6: wave_y0(S, X, nonfinite); break;
+    default: wave_y1(S, X, nonfinite); break;
+  }
+  if (nonfinite) raise_flag(flags, FLAG_NONFINITE);
+  if constexpr (DEV) {
+    // the workgroup's CFL maxima of the new state (lanes that wrote no cell
+    // hold 0, neutral for max)
+    if (sa.k == 2 && wave == 3 && sa.cfl_partial) {
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        cfl_a = mx(cfl_a, __shfl_xor(cfl_a, o, 64));
+        cfl_v = mx(cfl_v, __shfl_xor(cfl_v, o, 64));
+      }
+      if ((threadIdx.x & 63) == 0) {
+        const int wg = blockIdx.y * gridDim.x + blockIdx.x;
+        sa.cfl_partial[wg] = cfl_a;
+        sa.cfl_partial[afi::kSingleCflBlocks + wg] = cfl_v;
+      }
+    }
+  }
+}
+
+int device_cus() {
+  static int cache[64] = {0};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+  if (cache[dev] == 0) {
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        cus <= 0)
+      cus = 256;
+    cache[dev] = cus;
+  }
+  return cache[dev];
+}
+
+// the strips of a grid.  One workgroup fills a CU (its LDS), so a launch runs
+// in ceil(nx ny / CUs) rounds of H + 5 row steps each (a row is finished three
+// rows behind the march, which starts two rows early): the H with the fewest
+// steps in all.
+Strips strips_of(const afi::Geo& g) {
+  const int cus = device_cus();
+  Strips b{(g.n1x + SX - 1) / SX, 0, 0};
+  long best = 0;
+  for (int ny = 1; ny <= g.n2y; ++ny) {
+    if (ny > 1 && (long)b.nx * ny > std::min(8L * cus, (long)afi::kSingleCflBlocks)) break;
+    const int H = (g.n2y + ny - 1) / ny;
+    const int used = (g.n2y + H - 1) / H;
+    const long steps = ((long)b.nx * used + cus - 1) / cus * (H + 5);
+    if (b.H == 0 || steps < best) {
+      b.ny = used;
+      b.H = H;
+      best = steps;
+    }
+  }
+  return b;
+}
+
+StageArgs stage_args(const afi::Geo& geo, const Phys& ph) {
+  StageArgs sa{};
+  sa.g = afi::stage_geo(geo);
+  sa.ph = ph;
+  return sa;
+}
+
+template <typename R>
+hipError_t launch(const afi::Geo& geo, const Phys& ph, const afi::Work& w, const double* Un,
+                  const double* Uk, double* Uout, const double* dt_dev, double dt_host,
+                  afi::StageCoef sc, hipStream_t s, afi::Timer* tm) {
+  const Strips b = strips_of(geo);
+  StageArgs sa = stage_args(geo, ph);
+  sa.Uk = Uk;
+  sa.Un = Un;
+  sa.Uout = Uout;
+  sa.dt_dev = dt_dev;
+  sa.dt_host = dt_host;
+  sa.dt_mul = sc.dt_mul;
+  sa.flags = w.flags;
+  sa.ca = sc.a;
+  sa.cb = sc.b;
+  sa.first = sc.first;
+  sa.skip_flagged = sc.skip_flagged;
+  sa.blend = sc.blend;
+  sa.ts_out = sc.ts_out;
+  const dim3 grid((unsigned)b.nx, (unsigned)b.ny);
+  if (sa.blend || sa.ts_out)
+    AFI_TIMED(tm, 7, s,
+              hipLaunchKernelGGL((k_strip<R, true, false>), grid, dim3(NT), 0, s, sa, b));
+  else
+    AFI_TIMED(tm, 7, s,
+              hipLaunchKernelGGL((k_strip<R, false, false>), grid, dim3(NT), 0, s, sa, b));
+  return hipGetLastError();
+}
+
+template <typename R>
+hipError_t launch_dev(const afi::Geo& geo, const Phys& ph, afi::BatchInst* dinst,
+                      double* cfl_partial, int k, hipStream_t s) {
+  const Strips b = strips_of(geo);
+  StageArgs sa = stage_args(geo, ph);
+  sa.dinst = dinst;
+  sa.cfl_partial = b.nx <= afi::kSingleCflBlocks ? cfl_partial : nullptr;
+  sa.k = k;
+  sa.ca = k == 0 ? 0.0 : (k == 1 ? 0.75 : 1.0 / 3.0);
+  sa.cb = k == 0 ? 1.0 : (k == 1 ? 0.25 : 2.0 / 3.0);
+  sa.first = k == 0;
+  sa.skip_flagged = 1;
+  hipLaunchKernelGGL((k_strip<R, false, true>), dim3((unsigned)b.nx, (unsigned)b.ny), dim3(NT), 0,
+                     s, sa, b);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+namespace afi {
+
+int stage2d_dev_nwg(const Geo& g) {
+  const Strips b = strips_of(g);
+  return b.nx <= kSingleCflBlocks ? b.nx * b.ny : 0;
+}
+
+hipError_t stage2d(const Geo& geo, const Phys& ph, const Work& w, const double* Un,
+                   const double* Uk, double* Uout, const double* dt_dev, double dt_host,
+                   StageCoef sc, hipStream_t s, Timer* tm) {
+  return geo.mixed ? launch<float>(geo, ph, w, Un, Uk, Uout, dt_dev, dt_host, sc, s, tm)
+                   : launch<double>(geo, ph, w, Un, Uk, Uout, dt_dev, dt_host, sc, s, tm);
+}
+
+hipError_t stage2d_dev(const Geo& geo, const Phys& ph, BatchInst* dinst, double* cfl_partial, int k,
+                       hipStream_t s) {
+  return geo.mixed ? launch_dev<float>(geo, ph, dinst, cfl_partial, k, s)
+                   : launch_dev<double>(geo, ph, dinst, cfl_partial, k, s);
+}
+
+}  // namespace afi

@@ -157,7 +157,7 @@ def _pass(counters: list, outdir: str, mixed: bool = False, wl: str = "tube", n1
             if cname not in vals:
                 continue
             v = float(r["Counter_Value"])
-            if "k_stage" in name:
+            if "k_strip" in name:
                 vals[cname]["stage"].append(v)
             elif "copyBuffer" in name:
                 vals[cname]["copy"].append(v)
