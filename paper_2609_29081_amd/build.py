@@ -22,7 +22,8 @@ SOURCES = [("af_capi.cpp", "af_capi.o", []),
            ("af_common.hip", "af_common.o", []),
            ("af_kern1d.hip", "af_kern1d.o", []),
            ("af_learn.hip", "af_learn.o", []),
-           ("af_strip2d.hip", "af_strip2d.o", [])] + [
+           # no hoisting out of the row loops: it spills (as for the tile kernel)
+           ("af_strip2d.hip", "af_strip2d.o", ["-mllvm", "--disable-machine-licm"])] + [
     ("af_stage2d.hip", f"{name}.o",
      [f"-DAF_STAGE_REAL={real}", f"-DAF_STAGE_TY={ty}", f"-DAF_STAGE_ENTRY={name}",
       # no hoisting of loop-invariant values out of the persistent tile

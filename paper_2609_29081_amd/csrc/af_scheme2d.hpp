@@ -97,22 +97,42 @@ __device__ __forceinline__ R pressure_r(const PhysT<R>& ph, const R* V, R ir) {
   return ph.gm1 * (V[3] - R(0.5) * (V[1] * V[1] + V[2] * V[2]) * ir);
 }
 
-// per-cell low-order data (Sec. 3.1-3.2):
+// per-cell low-order data (Sec. 3.1):
 //   o[0..3] F_x, o[4..7] F_y (total fluxes with S = central differences of
-//   Z(average)), o[8] |u|+c, o[9] |v|+c, o[10] b_x, o[11] b_y, o[12] phi1,
-//   o[13] phi2, o[14..17] the cell average, o[18..22] its (u, v, p, T, c);
-//   from the averages of the cell and of its four neighbours (ghost cells as
-//   boundary images)
+//   Z(average)), o[8] |u|+c, o[9] |v|+c, o[10] b_x, o[11] b_y, from the
+//   averages of the cell, with its sound speed c0, and of its four neighbours
+//   (ghost cells as boundary images)
+//
 // A cell average with its reciprocal density and pressure: neighbours enter
 // by their momenta, 1/rho and p.
 template <typename R>
 struct CellAvg {
   R U[4], r, p;
 };
+
+// smoothness sensors phi1, phi2 of a cell (Sec. 3.2)
+template <typename R>
+__device__ __forceinline__ void cell_sensors(const G2& g, const CellAvg<R>& a0,
+                                             const CellAvg<R>& xm, const CellAvg<R>& xp,
+                                             const CellAvg<R>& ym, const CellAvg<R>& yp, R* phi) {
+  const R *Cxm = xm.U, *Cxp = xp.U, *Cym = ym.U, *Cyp = yp.U;
+  const R rxm = xm.r, rxp = xp.r, rym = ym.r, ryp = yp.r;
+  const R p0 = a0.p, pxm = xm.p, pxp = xp.p, pym = ym.p, pyp = yp.p;
+  const R i2x = R(1.0 / (2.0 * g.dx)), i2y = R(1.0 / (2.0 * g.dy));
+  const R ux = (Cxp[1] * rxp - Cxm[1] * rxm) * i2x;
+  const R vx = (Cxp[2] * rxp - Cxm[2] * rxm) * i2x;
+  const R uy = (Cyp[1] * ryp - Cym[1] * rym) * i2y;
+  const R vy = (Cyp[2] * ryp - Cym[2] * rym) * i2y;
+  const R jx = fabs(pxp - R(2.0) * p0 + pxm) / fabs(pxp + R(2.0) * p0 + pxm);
+  const R jy = fabs(pyp - R(2.0) * p0 + pym) / fabs(pyp + R(2.0) * p0 + pym);
+  phi[0] = mx(jx, jy);
+  const R div = ux + vy, curl = vx - uy;
+  phi[1] = mx(-div / sqrt(div * div + curl * curl + R(kDucros)), R(0.0));
+}
 template <typename R>
 __device__ __forceinline__ void cell_low(const G2& g, const PhysT<R>& ph, const CellAvg<R>& a0,
                                          const CellAvg<R>& xm, const CellAvg<R>& xp,
-                                         const CellAvg<R>& ym, const CellAvg<R>& yp, R* o) {
+                                         const CellAvg<R>& ym, const CellAvg<R>& yp, R c0, R* o) {
   const R *C0 = a0.U, *Cxm = xm.U, *Cxp = xp.U, *Cym = ym.U, *Cyp = yp.U;
   const R r0 = a0.r, rxm = xm.r, rxp = xp.r, rym = ym.r, ryp = yp.r;
   const R p0 = a0.p, pxm = xm.p, pxp = xp.p, pym = ym.p, pyp = yp.p;
@@ -124,7 +144,6 @@ __device__ __forceinline__ void cell_low(const G2& g, const PhysT<R>& ph, const 
   const R uy = (Cyp[1] * ryp - Cym[1] * rym) * i2y;
   const R vy = (Cyp[2] * ryp - Cym[2] * rym) * i2y;
   const R Ty = (pyp * ryp - pym * rym) * i2y;
-  const R c0 = sqrt(ph.gam * p0 * r0);
   R Fv[4];
   visc_flux2(0, u0, v0, ux, vx, Tx, uy, vy, Ty, ph, Fv);
   o[0] = C0[1] - Fv[0];
@@ -138,19 +157,7 @@ __device__ __forceinline__ void cell_low(const G2& g, const PhysT<R>& ph, const 
   o[7] = (C0[3] + p0) * v0 - Fv[3];
   o[8] = fabs(u0) + c0;
   o[9] = fabs(v0) + c0;
-  o[18] = u0;
-  o[19] = v0;
-  o[20] = p0;
-  o[21] = p0 * r0;
-  o[22] = c0;
   bvisc2_xy(p0, p0 * r0, ux, vx, Tx, uy, vy, Ty, ph, o[10], o[11]);
-  const R jx = fabs(pxp - R(2.0) * p0 + pxm) / fabs(pxp + R(2.0) * p0 + pxm);
-  const R jy = fabs(pyp - R(2.0) * p0 + pym) / fabs(pyp + R(2.0) * p0 + pym);
-  o[12] = mx(jx, jy);
-  const R div = ux + vy, curl = vx - uy;
-  o[13] = mx(-div / sqrt(div * div + curl * curl + R(kDucros)), R(0.0));
-#pragma unroll
-  for (int k = 0; k < 4; ++k) o[14 + k] = C0[k];
 }
 
 // total flux F_d = F^c_d - F^v_d of state (m1, m2, E) with velocity (u, v),

@@ -712,7 +712,19 @@ __global__ void __launch_bounds__(NT) k_stage(StageArgs sa) {
       c->r = rcp(c->U[0]);
       c->p = pressure_r(ph, c->U, c->r);
     }
-    cell_low(g, ph, C0, Cxm, Cxp, Cym, Cyp, o);
+    const R u0 = C0.U[1] * C0.r, v0 = C0.U[2] * C0.r;
+    const R c0 = sqrt(ph.gam * C0.p * C0.r);
+    // 0-11 see cell_low, 12 phi1, 13 phi2, 14-17 the average, 18-22 its
+    // (u, v, p, T, c)
+    cell_low(g, ph, C0, Cxm, Cxp, Cym, Cyp, c0, o);
+    cell_sensors(g, C0, Cxm, Cxp, Cym, Cyp, o + 12);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) o[14 + k] = C0.U[k];
+    o[18] = u0;
+    o[19] = v0;
+    o[20] = C0.p;
+    o[21] = C0.p * C0.r;
+    o[22] = c0;
 #pragma unroll
     for (int k = 0; k < 23; ++k) T.C[k][s] = o[k];
     }

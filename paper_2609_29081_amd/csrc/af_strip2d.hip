@@ -3,25 +3,45 @@
 //
 // The tile kernel (af_stage2d.hip) spends more than half of its vector
 // instructions on index arithmetic and halo sites, and its waves wait for
-// each other at seven barriers per tile.  Here a workgroup of eight wave64s
+// each other at seven barriers per tile.  Here a workgroup of twelve wave64s
 // takes a strip of 60 cell columns (one per lane, two more on either side) and
-// a range of rows, and each wave does one part of the scheme for one row of
-// cells per step of the march:
-//   wave 0  loads row r (raw values a row ahead), primitives of its points and
-//           averages, the Simpson centres of row r-1
-//   wave 1  gradients around row r-1, low-order data of the cells of row r-1
-//   wave 2  limited x-face fluxes of row r-3
-//   wave 3  limited y-face fluxes below row r-2, averages of row r-3
-//   wave 4  x-direction terms of the points ye, co of row r-2
-//   wave 5  x-direction terms of the points xe of row r-3, and their update
-//   wave 6  y-direction terms of the points co, xe of row r-3, update of co
-//   wave 7  y-direction terms of the points ye of row r-3, and their update
-// Everything is computed once per site and row (the columns at the sides of a
-// strip and a few rows at its ends apart), lanes address LDS at unit stride,
-// and directions are compile-time constants.  The waves meet at two barriers
-// per row: between wave 0's writes and wave 1's reads of row r, and at the end.
-// Rows pass through LDS rings of two to four slots (159 KB in FP64); what a
-// wave needs again in the next row stays in its registers.
+// a range of rows, and each wave does one part of the scheme per step of the
+// march, which takes it one row of cells further.  When row r is loaded,
+//                 first half of the step         second half
+//   wave_centre   points co of row r, centres    gradients around row r-1
+//                 of row r-1
+//   wave_edges    points ye, xe of row r         low-order y terms of ye, r-2
+//   wave_cells    averages of row r              low-order data of cells, r-1
+//   wave_xface    limited x-face fluxes, r-3     smoothness sensors, r-1
+//   wave_yface    limited y-face fluxes, r-2     averages updated, r-3
+//   wave_xres0    x residual of co, r-2          x residual of ye, r-2
+//   wave_xlow0                                   low-order x terms of co, ye, r-2
+//   wave_xlow1                                   low-order x terms of xe, r-2
+//   wave_xe       x residual of xe, r-3          xe updated, r-3
+//   wave_yres0    y residual of co, r-3          low-order y terms of co, xe, r-2
+//   wave_yres1    y residual of xe, r-3          co updated, r-3
+//   wave_ye       y residual of ye, r-3          ye updated, r-3
+// (a strip's rows are finished three steps behind the march, which starts two
+// rows early).  Everything is computed once per site and row (the columns at
+// the sides of a strip and a few rows at its ends apart), lanes address LDS at
+// unit stride, and directions are compile-time constants.  Rows pass through
+// LDS rings of two to four slots (156 KB in FP64, so one workgroup fills a
+// CU); what a wave needs again in the next row and the rings no longer hold
+// stays in its registers.
+//
+// What bounds it: vector instructions.  A step of an FP64 strip takes 5,550
+// cycles (2,970 and 2,400 in the two halves, the rest at the barriers) for
+// about 3,950 vector instructions, of which two thirds are FP64 arithmetic, on
+// four SIMDs; LDS is busy a third of the time and HBM a fifth.  So the parts
+// are spread over the SIMDs to equal work in either half, and over three waves
+// per SIMD, which FP64 at 168 registers a wave just allows.  With eight waves
+// (two per SIMD, 245 registers) a step took 7,850 cycles: loads and centres
+// held up the first half, gradients and cell data the second.
+//
+// Measured, stage of the shock tube (tile kernel, eight waves, this):
+//   1000 x 500   FP64 212, 125, 107 us   FP32 stencils 155, 115, 89 us
+//   2048 x 1024  FP64 867, 490, 378 us   FP32 stencils 652, 450, 326 us
+//   64 x 32      FP64 28, 17, 14 us      FP32 stencils 42, 17, 14 us
 //
 // The arithmetic is the tile kernel's, expression by expression, so the two
 // give the same bits.  Single instances run here; batches, whose instances
@@ -36,7 +56,7 @@ namespace {
 
 constexpr int W = 64;                 // lanes: cell columns of a strip with its margins
 constexpr int SX = 60;                // cell columns a strip owns: lanes 2 .. 61
-constexpr int NT = 512;
+constexpr int NT = 768;               // twelve waves, three per SIMD
 constexpr int CO = 0, YE = 1, XE = 2; // point types
 
 template <typename R>
@@ -57,9 +77,13 @@ struct Rings {
   R AV[10][4][W];       // averages: U (4), u, v, p, T, c, 1/rho; rows r .. r-3
   R C[14][3][W];        // cell low-order data, rows r-1 .. r-3
   R FX[4][W];           // limited x-face fluxes, row r-3
-  R XC[8][2][W];        // x-direction residual and low-order terms: of co ...
-  R XY[8][2][W];        // ... and ye, rows r-2, r-3
-  R X1[8][W];           // y-direction terms of xe, row r-3
+  // residual and low-order terms on their way to the wave that updates the
+  // point; written in one half of a row, read in the next half
+  R XC[8][W], XY[8][W]; // x-direction, residual (4) and low-order: co, ye
+  R LX[4][W];           // x-direction low-order terms of xe
+  R LC[4][W], LE[4][W]; // y-direction low-order terms of co, xe ...
+  R LO[4][W];           // ... and ye
+  R RX[4][W], RC[4][W]; // y-direction residuals of xe, co
   // FP32 stencils: FP64 averages, and the low parts V - float(V) of the points
   double AVD[4][4][kFP64<R> ? 1 : W];
   float PL[3][4][4][kFP64<R> ? 1 : W];
@@ -221,8 +245,8 @@ __device__ __forceinline__ void lo_face(const Site<R>& a, const LoFlux<R>& fa, c
 // what every wave of the workgroup knows
 template <typename R>
 struct Ctx {
-  const G2& g;
-  const Phys& phd;
+  G2 g;
+  Phys phd;
   PhysT<R> ph;
   const double* __restrict__ Uk;
   const double* __restrict__ Un;
@@ -230,6 +254,8 @@ struct Ctx {
   double dt, ca, cb;
   int first;
   unsigned* flags;
+  const float* blend;  // see limit_face
+  float* ts_out;
   int lane, i0;        // cell column of lane c: i0 - 2 + c
   int j0, j1;          // rows of the strip
   int rows;            // rows of the march: r = j0 - 2 .. j0 - 3 + rows
@@ -321,85 +347,135 @@ __device__ __forceinline__ bool mid_row(const Rings<R>& S) {
   return __builtin_amdgcn_readfirstlane(S.stop) != 0u;
 }
 
-// ---- wave 0 ----------------------------------------------------------------
-template <typename R>
-struct RawRow {
-  double v[4][4];  // co, ye, xe, average
-  int flipE, flipO;  // momentum flips of the row's even and odd lattice line
+// ---- loads -------------------------------------------------------------------
+// The lane's two lattice columns of the strip (E: co, xe; O: ye, averages):
+// image columns and momentum flips.  Lanes beyond the grid's ghosts (strips at
+// the upper side) read column 0.
+struct Columns {
+  unsigned cE, cO;  // columns of the DOF arrays
+  int fE, fO;       // flips
 };
-
 template <typename R>
-__device__ __forceinline__ void wave_load(Rings<R>& S, const Ctx<R>& X) {
+__device__ __forceinline__ Columns columns_of(const Ctx<R>& X) {
   const G2& g = X.g;
-  const int lane = X.lane;
-  const int Xlim = 2 * g.n1, Ylim = 2 * g.n2;
-  // the lane's two lattice columns: image columns, and momentum flips.  Lanes
-  // beyond the grid's ghosts (strips at the upper side) read column 0.
-  const int XE_ = 2 * (X.i0 - 2 + lane);
-  const bool inE = XE_ <= Xlim + kMargin, inO = XE_ + 1 <= Xlim + kMargin;
-  int kxE = -1, kxO = -1;
-  int iE = inE ? axis_image(XE_, Xlim, g.bc0, g.bc1, kxE) : 0;
-  const int iO = inO ? axis_image(XE_ + 1, Xlim, g.bc0, g.bc1, kxO) : 1;
+  const int Xlim = 2 * g.n1, x = 2 * (X.i0 - 2 + X.lane);
+  int kE = -1, kO = -1;
+  int iE = x <= Xlim + kMargin ? axis_image(x, Xlim, g.bc0, g.bc1, kE) : 0;
+  const int iO = x + 1 <= Xlim + kMargin ? axis_image(x + 1, Xlim, g.bc0, g.bc1, kO) : 1;
   if (iE == Xlim && g.n1x == g.n1) iE = 0;
-  const unsigned cE = (unsigned)(iE >> 1), cO = (unsigned)(iO >> 1);
-  const int fxE = image_flips(kxE, -1), fxO = image_flips(kxO, -1);
+  return Columns{(unsigned)(iE >> 1), (unsigned)(iO >> 1), image_flips(kE, -1),
+                 image_flips(kO, -1)};
+}
+// image row and flips of the even (odd) lattice line of row r; rows past the
+// last ghost are never used
+template <typename R>
+__device__ __forceinline__ int even_line(const Ctx<R>& X, int r, int& flip) {
+  const G2& g = X.g;
+  const int Ylim = 2 * g.n2;
+  int ky;
+  int y = axis_image(2 * r <= Ylim + kMargin ? 2 * r : Ylim, Ylim, g.bc2, g.bc3, ky);
+  if (y == Ylim && g.n2y == g.n2) y = 0;
+  flip = image_flips(-1, ky);
+  return y >> 1;
+}
+template <typename R>
+__device__ __forceinline__ int odd_line(const Ctx<R>& X, int r, int& flip) {
+  const G2& g = X.g;
+  const int Ylim = 2 * g.n2;
+  int ky;
+  const int y =
+      axis_image(2 * r + 1 <= Ylim + kMargin ? 2 * r + 1 : Ylim - 1, Ylim, g.bc2, g.bc3, ky);
+  flip = image_flips(-1, ky);
+  return y >> 1;
+}
+
+// raw values of a site type in flight: CO, YE, XE, or AV (3) the averages
+struct Raw {
+  double v[4];
+  int flip;
+};
+template <int T, typename R>
+__device__ __forceinline__ void issue(const Ctx<R>& X, const Columns& col, int r, Raw& q) {
+  const G2& g = X.g;
+  int fy;
+  const int row = (T & 2) ? odd_line(X, r, fy) : even_line(X, r, fy);
+  q.flip = fy ^ ((T & 1) ? col.fO : col.fE);
+  const int ni = (T & 1) ? g.n1 : g.n1x, nj = (T & 2) ? g.n2 : g.n2y;
+  const double* b =
+      X.Uk + (T == CO ? g.off_co : (T == YE ? g.off_ye : (T == XE ? g.off_xe : 0L))) + (long)row * ni;
+  const long pl = (long)ni * nj;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) q.v[k] = b[k * pl + ((T & 1) ? col.cO : col.cE)];
+}
+// their values with the image's signs
+__device__ __forceinline__ void signed_values(const Raw& q, double* V) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const bool neg = (k == 1 && (q.flip & 1)) || (k == 2 && (q.flip & 2));
+    V[k] = neg ? -q.v[k] : q.v[k];
+  }
+}
+// a point of type t into its ring
+template <typename R>
+__device__ __forceinline__ void store_point(Rings<R>& S, const Ctx<R>& X, int t, int s,
+                                            const double* V) {
+  const int lane = X.lane;
+  R w[5];
+  aux_of_fp64(X.phd, V, w);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) S.P[t][k][s][lane] = R(V[k]);
+#pragma unroll
+  for (int k = 0; k < 5; ++k) S.P[t][4 + k][s][lane] = w[k];
+  if constexpr (!kFP64<R>) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) S.PL[t][k][s][lane] = float(V[k] - double(float(V[k])));
+  }
+}
+
+// ---- wave_centre -------------------------------------------------------------------
+template <typename R>
+__device__ __forceinline__ void wave_centre(Rings<R>& S, const Ctx<R>& X) {
+  const G2& g = X.g;
+  const int c = X.lane, cl = c > 0 ? c - 1 : 0, cr = c < W - 1 ? c + 1 : W - 1;
+  const int Xlim = 2 * g.n1, Ylim = 2 * g.n2, n1 = g.n1, n1x = g.n1x, n2 = g.n2;
+  const Columns col = columns_of(X);
   // a centre beyond a wall or outflow side takes the value of its image
   // column, which another lane of the strip holds
-  const bool ghost_col = inO && (XE_ + 1 < 0 || XE_ + 1 > Xlim) && g.bc0 != BC_PERIODIC;
-  const int image_lane = ((iO - 1) >> 1) - X.i0 + 2;
+  const int xo = 2 * (X.i0 - 2 + c) + 1;
+  const bool ghost_col =
+      xo <= Xlim + kMargin && (xo < 0 || xo > Xlim) && g.bc0 != BC_PERIODIC;
+  const int image_lane = (int)col.cO - X.i0 + 2;
   const bool has_ghost_col = g.bc0 != BC_PERIODIC && (X.i0 < 2 || 2 * (X.i0 + 62) > Xlim);
-
-  const int n1 = g.n1, n1x = g.n1x, n2 = g.n2, n2y = g.n2y;
-  const int pl[4] = {n1x * n2y, n1 * n2y, n1x * n2, n1 * n2};  // plane strides
-  auto issue = [&](int r, RawRow<R>& q) {
-    // the row's two lattice lines (rows past the last ghost are never used)
-    int ky, Y = 2 * r;
-    if (Y > Ylim + kMargin) Y = Ylim;
-    int rE = axis_image(Y, Ylim, g.bc2, g.bc3, ky);
-    if (rE == Ylim && n2y == n2) rE = 0;
-    rE >>= 1;
-    q.flipE = image_flips(-1, ky);
-    Y = 2 * r + 1;
-    if (Y > Ylim + kMargin) Y = Ylim - 1;
-    const int rO = axis_image(Y, Ylim, g.bc2, g.bc3, ky) >> 1;
-    q.flipO = image_flips(-1, ky);
-    const double* b[4] = {X.Uk + g.off_co + (long)rE * n1x, X.Uk + g.off_ye + (long)rE * n1,
-                          X.Uk + g.off_xe + (long)rO * n1x, X.Uk + (long)rO * n1};
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) q.v[t][k] = b[t][(long)k * pl[t] + ((t & 1) ? cO : cE)];
-  };
   // centre of the lane's cell of row r straight from the state (for the row
   // beyond a lower wall or outflow side, whose image the march has not reached)
   auto centre_of = [&](int r, R* V, R* w) {
-    int kd, XR = XE_ + 2;
-    const bool inR = XR <= Xlim + kMargin;
-    int iR = inR ? axis_image(XR, Xlim, g.bc0, g.bc1, kd) : 0;
+    int kd;
+    int iR = xo + 1 <= Xlim + kMargin ? axis_image(xo + 1, Xlim, g.bc0, g.bc1, kd) : 0;
     if (iR == Xlim && n1x == n1) iR = 0;
-    const unsigned cR = (unsigned)(iR >> 1);
-    R Ub[4], e[4], c[4];
+    const unsigned cR = (unsigned)(iR >> 1), cE = col.cE, cO = col.cO;
+    R Ub[4], e[4], cc[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const double* co = X.Uk + g.off_co + (long)k * pl[0] + (long)r * n1x;
-      const double* ye = X.Uk + g.off_ye + (long)k * pl[1] + (long)r * n1;
-      const double* xe = X.Uk + g.off_xe + (long)k * pl[2] + (long)r * n1x;
-      const double* av = X.Uk + (long)k * pl[3] + (long)r * n1;
+      const double* co = X.Uk + g.off_co + (long)k * n1x * g.n2y + (long)r * n1x;
+      const double* ye = X.Uk + g.off_ye + (long)k * n1 * g.n2y + (long)r * n1;
+      const double* xe = X.Uk + g.off_xe + (long)k * n1x * n2 + (long)r * n1x;
+      const double* av = X.Uk + (long)k * n1 * n2 + (long)r * n1;
       Ub[k] = R(av[cO]);
       e[k] = R(xe[cE]) + R(xe[cR]) + R(ye[cO]) + R(ye[n1 + cO]);
-      c[k] = R(co[cE]) + R(co[cR]) + R(co[n1x + cE]) + R(co[n1x + cR]);
+      cc[k] = R(co[cE]) + R(co[cR]) + R(co[n1x + cE]) + R(co[n1x + cR]);
     }
-    centre_value(X.ph, X.phd, Ub, e, c, V, w);
+    centre_value(X.ph, X.phd, Ub, e, cc, V, w);
   };
   auto flipped = [](R v, bool neg) { return neg ? -v : v; };
+  const R ihx = R(1.0 / (6.0 * g.dx)), ihy = R(1.0 / (6.0 * g.dy));
 
-  RawRow<R> nx;
-  issue(X.j0 - 2, nx);
-  // the previous row's values in this lane, and its co and xe to the right
-  R pco[4], pye[4], pxe[4], pav[4], pcoR[4], pxeR[4];
+  // (ye of row r is loaded here too: its ring entry comes in the same half row)
+  Raw nco, nye;
+  issue<CO>(X, col, X.j0 - 2, nco);
+  issue<YE>(X, col, X.j0 - 2, nye);
   R zv[4], zw[5];  // the latest centre
 #pragma unroll
-  for (int k = 0; k < 4; ++k) pco[k] = pye[k] = pxe[k] = pav[k] = pcoR[k] = pxeR[k] = zv[k] = R(0.0);
+  for (int k = 0; k < 4; ++k) zv[k] = R(0.0);
 #pragma unroll
   for (int k = 0; k < 5; ++k) zw[k] = R(0.0);
   R lowv[4], loww[5];
@@ -408,175 +484,199 @@ __device__ __forceinline__ void wave_load(Rings<R>& S, const Ctx<R>& X) {
 
   for (int k = 0; k < X.rows; ++k) {
     const int r = X.j0 - 2 + k;
-    const int s = slot4(k);
-    RawRow<R> q = nx;
-    if (k + 1 < X.rows) issue(r + 1, nx);
-    // row r: points, then the averages
-    R cur[4][4];
+    double V[4];
+    R co[4], ye[4];
+    signed_values(nye, V);
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int f = ((t & 1) ? fxO : fxE) ^ ((t & 2) ? q.flipO : q.flipE);
-      double V[4];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const bool neg = (c == 1 && (f & 1)) || (c == 2 && (f & 2));
-        V[c] = neg ? -q.v[t][c] : q.v[t][c];
-        cur[t][c] = R(V[c]);
-      }
-      if (t < 3) {
-        R w[5];
-        aux_of_fp64(X.phd, V, w);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) S.P[t][c][s][lane] = cur[t][c];
-#pragma unroll
-        for (int c = 0; c < 5; ++c) S.P[t][4 + c][s][lane] = w[c];
-        if constexpr (!kFP64<R>) {
-#pragma unroll
-          for (int c = 0; c < 4; ++c) S.PL[t][c][s][lane] = float(V[c] - double(float(V[c])));
-        }
-      } else {
-        const R* C0 = cur[3];
-        const R r0 = rcp(C0[0]);
-        const R p0 = pressure_r(X.ph, C0, r0);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) S.AV[c][s][lane] = C0[c];
-        S.AV[4][s][lane] = C0[1] * r0;
-        S.AV[5][s][lane] = C0[2] * r0;
-        S.AV[6][s][lane] = p0;
-        S.AV[7][s][lane] = p0 * r0;
-        S.AV[8][s][lane] = sqrt(X.ph.gam * p0 * r0);
-        S.AV[9][s][lane] = r0;
-        if constexpr (!kFP64<R>) {
-#pragma unroll
-          for (int c = 0; c < 4; ++c) S.AVD[c][s][lane] = V[c];
-        }
-      }
+    for (int n = 0; n < 4; ++n) ye[n] = R(V[n]);
+    signed_values(nco, V);
+    if (k + 1 < X.rows) {
+      issue<CO>(X, col, r + 1, nco);
+      issue<YE>(X, col, r + 1, nye);
     }
-    // co and xe of the column to the right, from the lane that holds it
-    R coR[4], xeR[4];
+    store_point(S, X, CO, slot4(k), V);
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      coR[c] = from_right(cur[CO][c]);
-      xeR[c] = from_right(cur[XE][c]);
-    }
+    for (int n = 0; n < 4; ++n) co[n] = R(V[n]);
     // centre of row r-1
     const int rc = r - 1;
     if (k >= 2) {
-      int f = 0;
+      int f = 0, ky;
       if (rc < 0 && low_ghost) {
-        int ky;
         (void)axis_image(2 * rc + 1, Ylim, g.bc2, g.bc3, ky);
         f = image_flips(-1, ky);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) zv[c] = lowv[c];
+        for (int n = 0; n < 4; ++n) zv[n] = lowv[n];
 #pragma unroll
-        for (int c = 0; c < 5; ++c) zw[c] = loww[c];
+        for (int n = 0; n < 5; ++n) zw[n] = loww[n];
       } else if (rc >= n2 && g.bc2 != BC_PERIODIC) {
         // the row beyond the upper side: its image is the row below, whose
         // centre this lane computed last
-        int ky;
         (void)axis_image(2 * rc + 1 <= Ylim + kMargin ? 2 * rc + 1 : Ylim, Ylim, g.bc2, g.bc3, ky);
         f = image_flips(-1, ky);
       } else {
-        R e[4], cc[4];
+        R Ub[4], e[4], cc[4];
+        const int s1 = slot4(k - 1);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          e[c] = pxe[c] + pxeR[c] + pye[c] + cur[YE][c];
-          cc[c] = pco[c] + pcoR[c] + cur[CO][c] + coR[c];
+        for (int n = 0; n < 4; ++n) {
+          Ub[n] = S.AV[n][s1][c];
+          e[n] = S.P[XE][n][s1][c] + S.P[XE][n][s1][cr] + S.P[YE][n][s1][c] + ye[n];
+          cc[n] = S.P[CO][n][s1][c] + S.P[CO][n][s1][cr] + co[n] + from_right(co[n]);
         }
-        centre_value(X.ph, X.phd, pav, e, cc, zv, zw);
+        centre_value(X.ph, X.phd, Ub, e, cc, zv, zw);
       }
       const int sz = slot3(k - 1);
 #pragma unroll
-      for (int c = 0; c < 4; ++c)
-        S.Z[c][sz][lane] = flipped(zv[c], (c == 1 && (f & 1)) || (c == 2 && (f & 2)));
+      for (int n = 0; n < 4; ++n)
+        S.Z[n][sz][c] = flipped(zv[n], (n == 1 && (f & 1)) || (n == 2 && (f & 2)));
 #pragma unroll
-      for (int c = 0; c < 5; ++c)
-        S.Z[4 + c][sz][lane] = flipped(zw[c], (c == 0 && (f & 1)) || (c == 1 && (f & 2)));
+      for (int n = 0; n < 5; ++n)
+        S.Z[4 + n][sz][c] = flipped(zw[n], (n == 0 && (f & 1)) || (n == 1 && (f & 2)));
       if (has_ghost_col) {
         __builtin_amdgcn_wave_barrier();
         if (ghost_col) {
           R z[9];
 #pragma unroll
-          for (int c = 0; c < 9; ++c) z[c] = S.Z[c][sz][image_lane];
+          for (int n = 0; n < 9; ++n) z[n] = S.Z[n][sz][image_lane];
 #pragma unroll
-          for (int c = 0; c < 9; ++c)
-            S.Z[c][sz][lane] = flipped(z[c], ((c == 1 || c == 4) && (fxO & 1)) ||
-                                                 ((c == 2 || c == 5) && (fxO & 2)));
+          for (int n = 0; n < 9; ++n)
+            S.Z[n][sz][c] = flipped(z[n], ((n == 1 || n == 4) && (col.fO & 1)) ||
+                                              ((n == 2 || n == 5) && (col.fO & 2)));
         }
       }
     }
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      pco[c] = cur[CO][c];
-      pye[c] = cur[YE][c];
-      pxe[c] = cur[XE][c];
-      pav[c] = cur[3][c];
-      pcoR[c] = coR[c];
-      pxeR[c] = xeR[c];
-    }
     if (mid_row(S)) return;
+    if (k >= 2) {
+      const int p0 = slot4(k), p1 = slot4(k - 1), p2 = slot4(k - 2);
+      const int z1 = slot3(k - 1), z2 = slot3(k - 2), z3s = slot3(k - 3);
+      const int ge = slot2(k - 1), g1 = slot3(k - 1), g2 = slot2(k - 2);
+      const int src[3] = {4, 5, 7};  // u, v, T
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        const R (&co_)[4][W] = S.P[CO][src[q]];
+        const R (&ye_)[4][W] = S.P[YE][src[q]];
+        const R (&xe_)[4][W] = S.P[XE][src[q]];
+        const R (&zz)[3][W] = S.Z[src[q]];
+        S.GE0[q][ge][c] = dc5(co_[p1][cl], ye_[p1][cl], ye_[p1][c], co_[p1][cr], ihx);
+        S.GE0[3 + q][ge][c] = dc5(co_[p2][c], xe_[p2][c], xe_[p1][c], co_[p0][c], ihy);
+        S.GO0[q][ge][c] = dc5(ye_[p1][cl], co_[p1][c], co_[p1][cr], ye_[p1][cr], ihx);
+        S.GO0[3 + q][ge][c] = dc5(ye_[p2][c], zz[z2][c], zz[z1][c], ye_[p0][c], ihy);
+        S.GE1[q][g1][c] = dc5(xe_[p1][cl], zz[z1][cl], zz[z1][c], xe_[p1][cr], ihx);
+        S.GE1[3 + q][g1][c] = dc5(xe_[p2][c], co_[p1][c], co_[p0][c], xe_[p0][c], ihy);
+        if (q < 2) {
+          S.GO1[q][g2][c] = dc5(zz[z2][cl], xe_[p2][c], xe_[p2][cr], zz[z2][cr], ihx);
+          S.GO1[2 + q][g2][c] = dc5(zz[z3s][c], ye_[p2][c], ye_[p1][c], zz[z1][c], ihy);
+        }
+      }
+    }
     STRIP_BARRIER();
   }
 }
 
-// ---- wave 1 ----------------------------------------------------------------
+// ---- wave_edges --------------------------------------------------------------------
 template <typename R>
-__device__ __forceinline__ void wave_grad(Rings<R>& S, const Ctx<R>& X, int skip_flagged) {
+__device__ __forceinline__ void wave_edges(Rings<R>& S, const Ctx<R>& X) {
+  const G2& g = X.g;
+  const int c = X.lane, cr = c < W - 1 ? c + 1 : W - 1;
+  const R ihx = R(1.0 / g.dx), ihy = R(1.0 / g.dy);
+  const R cL = R(2.0 * X.dt / g.dy);
+  Site<R> y2{};     // ye of row r-2, its low-order data, and the LLF flux below it
+  LoFlux<R> fy2{};
+  R Fprev[4] = {};
+  const Columns col = columns_of(X);
+  Raw nye, nxe;
+  issue<YE>(X, col, X.j0 - 2, nye);
+  issue<XE>(X, col, X.j0 - 2, nxe);
+  for (int k = 0; k < X.rows; ++k) {
+    const int r = X.j0 - 2 + k;
+    double V[4], Vx[4];
+    signed_values(nye, V);
+    signed_values(nxe, Vx);
+    if (k + 1 < X.rows) {
+      issue<YE>(X, col, r + 1, nye);
+      issue<XE>(X, col, r + 1, nxe);
+    }
+    store_point(S, X, YE, slot4(k), V);
+    store_point(S, X, XE, slot4(k), Vx);
+    if (mid_row(S)) return;
+    if (k >= 2 && (X.ph.lim & LIM_POINT)) {
+      // the line ye, average, ye of the column
+      const int s1 = slot4(k - 1), s2 = slot4(k - 2);
+      const Site<R> A = avg_site(S.AV, s2, c), y1 = site9(S.P[YE], s1, c);
+      const LoFlux<R> fA = lo_flux<1>(X.ph, A, z3(S.P[XE], s2, c), z3(S.P[XE], s2, cr), z3(y2),
+                                      z3(y1), ihx, ihy);
+      const LoFlux<R> fy1 = lo_flux<1>(X.ph, y1, z3(S.P[CO], s1, c), z3(S.P[CO], s1, cr), z3(A),
+                                       z3(S.AV, s1, c), ihx, ihy);
+      R Fya[4], Fay[4];
+      lo_face<1>(y2, fy2, A, fA, Fya);
+      lo_face<1>(A, fA, y1, fy1, Fay);
+#pragma unroll
+      for (int n = 0; n < 4; ++n) {
+        S.LO[n][c] = cL * (Fya[n] - Fprev[n]);
+        Fprev[n] = Fay[n];
+      }
+      y2 = y1;
+      fy2 = fy1;
+    }
+    STRIP_BARRIER();
+  }
+}
+
+// a cell average of the ring
+template <typename R>
+__device__ __forceinline__ CellAvg<R> ring_cell(const Rings<R>& S, int slot, int c) {
+  CellAvg<R> a;
+#pragma unroll
+  for (int n = 0; n < 4; ++n) a.U[n] = S.AV[n][slot][c];
+  a.p = S.AV[6][slot][c];
+  a.r = S.AV[9][slot][c];
+  return a;
+}
+
+// ---- wave_cells --------------------------------------------------------------------
+template <typename R>
+__device__ __forceinline__ void wave_cells(Rings<R>& S, const Ctx<R>& X, int skip_flagged) {
   const G2& g = X.g;
   const int c = X.lane, cl = c > 0 ? c - 1 : 0, cr = c < W - 1 ? c + 1 : W - 1;
-  const R ihx = R(1.0 / (6.0 * g.dx)), ihy = R(1.0 / (6.0 * g.dy));
+  const Columns col = columns_of(X);
+  Raw nav;
+  issue<3>(X, col, X.j0 - 2, nav);
   // inside a step attempt: stop once any workgroup has flagged it (it is
   // rejected and its output is never read).  The flag word of the row before
   // is the one that counts, so that nobody waits for its load.
   unsigned fl = 0u;
   for (int k = 0; k < X.rows; ++k) {
+    const int r = X.j0 - 2 + k, s = slot4(k);
     if (c == 0) S.stop = fl;
+    double V[4];
+    signed_values(nav, V);
+    if (k + 1 < X.rows) issue<3>(X, col, r + 1, nav);
+    R C0[4];
+#pragma unroll
+    for (int n = 0; n < 4; ++n) C0[n] = R(V[n]);
+    const R r0 = rcp(C0[0]);
+    const R pr = pressure_r(X.ph, C0, r0);
+#pragma unroll
+    for (int n = 0; n < 4; ++n) S.AV[n][s][c] = C0[n];
+    S.AV[4][s][c] = C0[1] * r0;
+    S.AV[5][s][c] = C0[2] * r0;
+    S.AV[6][s][c] = pr;
+    S.AV[7][s][c] = pr * r0;
+    S.AV[8][s][c] = sqrt(X.ph.gam * pr * r0);
+    S.AV[9][s][c] = r0;
+    if constexpr (!kFP64<R>) {
+#pragma unroll
+      for (int n = 0; n < 4; ++n) S.AVD[n][s][c] = V[n];
+    }
     if (mid_row(S)) return;
     if (skip_flagged) fl = peek_flags(X.flags);
     if (k >= 2) {
-      // rows r, r-1, r-2 of the points and averages; r-1 .. r-3 of the centres
       const int p0 = slot4(k), p1 = slot4(k - 1), p2 = slot4(k - 2);
-      const int z1 = slot3(k - 1), z2 = slot3(k - 2), z3s = slot3(k - 3);
-      const int src[3] = {4, 5, 7};  // u, v, T
-#pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        const int s = src[q];
-        const R (&co)[4][W] = S.P[CO][s];
-        const R (&ye)[4][W] = S.P[YE][s];
-        const R (&xe)[4][W] = S.P[XE][s];
-        const R (&zz)[3][W] = S.Z[s];
-        const int ge = slot2(k - 1);
-        // co and ye of row r-1
-        S.GE0[q][ge][c] = dc5(co[p1][cl], ye[p1][cl], ye[p1][c], co[p1][cr], ihx);
-        S.GE0[3 + q][ge][c] = dc5(co[p2][c], xe[p2][c], xe[p1][c], co[p0][c], ihy);
-        S.GO0[q][ge][c] = dc5(ye[p1][cl], co[p1][c], co[p1][cr], ye[p1][cr], ihx);
-        S.GO0[3 + q][ge][c] = dc5(ye[p2][c], zz[z2][c], zz[z1][c], ye[p0][c], ihy);
-        // xe of row r-1
-        const int g1 = slot3(k - 1);
-        S.GE1[q][g1][c] = dc5(xe[p1][cl], zz[z1][cl], zz[z1][c], xe[p1][cr], ihx);
-        S.GE1[3 + q][g1][c] = dc5(xe[p2][c], co[p1][c], co[p0][c], xe[p0][c], ihy);
-        // centres of row r-2
-        if (q < 2) {
-          const int g2 = slot2(k - 2);
-          S.GO1[q][g2][c] = dc5(zz[z2][cl], xe[p2][c], xe[p2][cr], zz[z2][cr], ihx);
-          S.GO1[2 + q][g2][c] = dc5(zz[z3s][c], ye[p2][c], ye[p1][c], zz[z1][c], ihy);
-        }
-      }
-      // low-order data of the cells of row r-1
-      auto cell = [&](int slot, int col) {
-        CellAvg<R> a;
-#pragma unroll
-        for (int n = 0; n < 4; ++n) a.U[n] = S.AV[n][slot][col];
-        a.p = S.AV[6][slot][col];
-        a.r = S.AV[9][slot][col];
-        return a;
-      };
-      R o[23];
-      cell_low(g, X.ph, cell(p1, c), cell(p1, cl), cell(p1, cr), cell(p2, c), cell(p0, c), o);
+      R o[12];
+      cell_low(g, X.ph, ring_cell(S, p1, c), ring_cell(S, p1, cl), ring_cell(S, p1, cr),
+               ring_cell(S, p2, c), ring_cell(S, p0, c), S.AV[8][p1][c], o);
       const int sc = slot3(k - 1);
 #pragma unroll
-      for (int n = 0; n < 14; ++n) S.C[n][sc][c] = o[n];
+      for (int n = 0; n < 12; ++n) S.C[n][sc][c] = o[n];
     }
     STRIP_BARRIER();
   }
@@ -610,7 +710,9 @@ __device__ __forceinline__ FaceCell<R> face_cell(const Rings<R>& S, int d, int s
 template <typename R>
 __device__ __forceinline__ void face_between(const Ctx<R>& X, int d, int i, int j,
                                              const FaceCell<R>& a, const FaceCell<R>& b, const R* FH,
-                                             const float* blend, float* ts_out, bool own, R* F) {
+                                             bool own, R* F) {
+  const float* blend = X.blend;
+  float* ts_out = X.ts_out;
   const int limc = (X.ph.lim & (LIM_SMOOTH | LIM_PP | LIM_LOWONLY)) | (blend ? 1 : 0);
   if (!limc) {
 #pragma unroll
@@ -645,12 +747,12 @@ __device__ __forceinline__ void point_flux(const PhysT<R>& ph, const R (&P)[9][S
   tot_flux(D, U, P[4][sp][c], P[5][sp][c], P[6][sp][c], gr, ph, F);
 }
 
-// ---- wave 2: x-face fluxes of row r-3 ---------------------------------------
+// ---- wave_xface --------------------------------------------------------------------
 template <typename R>
-__device__ __forceinline__ void wave_xface(Rings<R>& S, const Ctx<R>& X, const float* blend,
-                                           float* ts_out) {
+__device__ __forceinline__ void wave_xface(Rings<R>& S, const Ctx<R>& X) {
   const G2& g = X.g;
-  const int c = X.lane, cl = c > 0 ? c - 1 : 0, i = X.i0 - 2 + c;
+  const int c = X.lane, cl = c > 0 ? c - 1 : 0, cr = c < W - 1 ? c + 1 : W - 1;
+  const int i = X.i0 - 2 + c;
   const bool own_col = c >= 2 && c <= SX + 2 && i <= g.n1;
   R Fco[4], Fxe[4];  // fluxes at co and xe of the row before
 #pragma unroll
@@ -668,7 +770,7 @@ __device__ __forceinline__ void wave_xface(Rings<R>& S, const Ctx<R>& X, const f
         for (int n = 0; n < 4; ++n) FH[n] = (Fco[n] + R(4.0) * Fxe[n] + F0[n]) * R(1.0 / 6.0);
         const FaceCell<R> a = face_cell(S, 0, slot3(k - 3), slot4(k - 3), cl);
         const FaceCell<R> b = face_cell(S, 0, slot3(k - 3), slot4(k - 3), c);
-        face_between(X, 0, i, j, a, b, FH, blend, ts_out, own_col, F);
+        face_between(X, 0, i, j, a, b, FH, own_col, F);
 #pragma unroll
         for (int n = 0; n < 4; ++n) S.FX[n][c] = F[n];
       }
@@ -679,14 +781,21 @@ __device__ __forceinline__ void wave_xface(Rings<R>& S, const Ctx<R>& X, const f
       }
     }
     if (mid_row(S)) return;
+    if (k >= 2) {
+      const int p1 = slot4(k - 1);
+      R phi[2];
+      cell_sensors(g, ring_cell(S, p1, c), ring_cell(S, p1, cl), ring_cell(S, p1, cr),
+                   ring_cell(S, slot4(k - 2), c), ring_cell(S, slot4(k), c), phi);
+      S.C[12][slot3(k - 1)][c] = phi[0];
+      S.C[13][slot3(k - 1)][c] = phi[1];
+    }
     STRIP_BARRIER();
   }
 }
 
-// ---- wave 3: y-face fluxes below row r-2, averages of row r-3 ----------------
+// ---- wave_yface --------------------------------------------------------------------
 template <typename R, bool DEV>
-__device__ __forceinline__ void wave_yface(Rings<R>& S, const Ctx<R>& X, const float* blend,
-                                           float* ts_out, bool& nonfinite, const afi::BatchInst* dinst,
+__device__ __forceinline__ void wave_yface(Rings<R>& S, const Ctx<R>& X, bool& nonfinite, const afi::BatchInst* dinst,
                                            int rates, double& cfl_a, double& cfl_v) {
   const G2& g = X.g;
   const int c = X.lane, i = X.i0 - 2 + c;
@@ -725,7 +834,7 @@ __device__ __forceinline__ void wave_yface(Rings<R>& S, const Ctx<R>& X, const f
 #pragma unroll
         for (int n = 0; n < 4; ++n)
           FH[n] = (Fa[n] + R(4.0) * Fm[n] + from_right(Fa[n])) * R(1.0 / 6.0);
-        face_between(X, 1, i, j, low, up, FH, blend, ts_out, own_col, F);
+        face_between(X, 1, i, j, low, up, FH, own_col, F);
       }
       low = up;
     }
@@ -763,259 +872,314 @@ __device__ __forceinline__ void wave_yface(Rings<R>& S, const Ctx<R>& X, const f
   }
 }
 
-// ---- wave 4: x-direction terms of co and ye, row r-2 -------------------------
+// ---- wave_xres0 --------------------------------------------------------------------
 template <typename R>
-__device__ __forceinline__ void wave_x0(Rings<R>& S, const Ctx<R>& X) {
+__device__ __forceinline__ void wave_xres0(Rings<R>& S, const Ctx<R>& X) {
   const G2& g = X.g;
   const int c = X.lane, cl = c > 0 ? c - 1 : 0, cr = c < W - 1 ? c + 1 : W - 1;
-  const R ihx = R(1.0 / g.dx), ihy = R(1.0 / g.dy);
-  const R cL = R(2.0 * X.dt / g.dx);
   for (int k = 0; k < X.rows; ++k) {
-    const int r = X.j0 - 2 + k, j = r - 2;
+    const int j = X.j0 - 4 + k;
     const bool on = j >= X.j0 && j < X.j1;
-    const int s2 = slot4(k - 2), s3 = slot4(k - 3), gs = slot2(k - 2);
-    Site<R> El, Ol, E, O, Er, Or;
+    const int s2 = slot4(k - 2), gs = slot2(k - 2);
+    Site<R> Ol, E, O, Er;
+    R Rc[4], uo[2], vo[2], ue, ve;
     if (on) {
-      El = site9(S.P[CO], s2, cl);
+      const Site<R> El = site9(S.P[CO], s2, cl);
       Ol = site9(S.P[YE], s2, cl);
       E = site9(S.P[CO], s2, c);
       O = site9(S.P[YE], s2, c);
       Er = site9(S.P[CO], s2, cr);
-      Or = site9(S.P[YE], s2, cr);
       // derivatives along y of u and v: across the line
-      R ue[3], ve[3], uo[3], vo[3];
-      const int cols[3] = {cl, c, cr};
-#pragma unroll
-      for (int n = 0; n < 3; ++n) {
-        ue[n] = S.GE0[3][gs][cols[n]];
-        ve[n] = S.GE0[4][gs][cols[n]];
-        uo[n] = S.GO0[3][gs][cols[n]];
-        vo[n] = S.GO0[4][gs][cols[n]];
-      }
-      R Rd[4];
-      {
-        const Site<R>* s[5] = {&El, &Ol, &E, &O, &Er};
-        const R ga[5] = {ue[0], uo[0], R(0.0), uo[1], ue[2]};
-        const R gb[5] = {ve[0], vo[0], R(0.0), vo[1], ve[2]};
-        line_resid<0>(X.ph, g.dx, s, ga, gb, Rd);
-#pragma unroll
-        for (int n = 0; n < 4; ++n) S.XC[n][gs][c] = Rd[n];
-      }
-      {
-        const Site<R>* s[5] = {&Ol, &E, &O, &Er, &Or};
-        const R ga[5] = {uo[0], ue[1], R(0.0), ue[2], uo[2]};
-        const R gb[5] = {vo[0], ve[1], R(0.0), ve[2], vo[2]};
-        line_resid<0>(X.ph, g.dx, s, ga, gb, Rd);
-#pragma unroll
-        for (int n = 0; n < 4; ++n) S.XY[n][gs][c] = Rd[n];
-      }
+      uo[0] = S.GO0[3][gs][cl];
+      vo[0] = S.GO0[4][gs][cl];
+      uo[1] = S.GO0[3][gs][c];
+      vo[1] = S.GO0[4][gs][c];
+      ue = S.GE0[3][gs][cr];
+      ve = S.GE0[4][gs][cr];
+      const Site<R>* s[5] = {&El, &Ol, &E, &O, &Er};
+      const R ga[5] = {S.GE0[3][gs][cl], uo[0], R(0.0), uo[1], ue};
+      const R gb[5] = {S.GE0[4][gs][cl], vo[0], R(0.0), vo[1], ve};
+      line_resid<0>(X.ph, g.dx, s, ga, gb, Rc);
     }
     if (mid_row(S)) return;
-    if (on && (X.ph.lim & LIM_POINT)) {
-      const LoFlux<R> fE = lo_flux<0>(X.ph, E, z3(Ol), z3(O), z3(S.P[XE], s3, c),
-                                      z3(S.P[XE], s2, c), ihx, ihy);
-      const LoFlux<R> fO =
-          lo_flux<0>(X.ph, O, z3(E), z3(Er), z3(S.AV, s3, c), z3(S.AV, s2, c), ihx, ihy);
-      LoFlux<R> fEr;
-#pragma unroll
-      for (int n = 0; n < 4; ++n) fEr.F[n] = from_right(fE.F[n]);
-      fEr.b = from_right(fE.b);
-      R Feo[4], Foe[4];
-      lo_face<0>(E, fE, O, fO, Feo);
-      lo_face<0>(O, fO, Er, fEr, Foe);
+    if (on) {
+      const Site<R> Or = site9(S.P[YE], s2, cr);
+      const Site<R>* s[5] = {&Ol, &E, &O, &Er, &Or};
+      const R ga[5] = {uo[0], S.GE0[3][gs][c], R(0.0), ue, S.GO0[3][gs][cr]};
+      const R gb[5] = {vo[0], S.GE0[4][gs][c], R(0.0), ve, S.GO0[4][gs][cr]};
+      R Ry[4];
+      line_resid<0>(X.ph, g.dx, s, ga, gb, Ry);
 #pragma unroll
       for (int n = 0; n < 4; ++n) {
-        S.XC[4 + n][gs][c] = cL * (Feo[n] - from_left(Foe[n]));
-        S.XY[4 + n][gs][c] = cL * (Foe[n] - Feo[n]);
+        S.XC[n][c] = Rc[n];
+        S.XY[n][c] = Ry[n];
       }
     }
     STRIP_BARRIER();
   }
 }
 
-// ---- wave 5: x-direction terms and update of xe, row r-3 ---------------------
+// ---- wave_xlow0 --------------------------------------------------------------------
 template <typename R>
-__device__ __forceinline__ void wave_x1(Rings<R>& S, const Ctx<R>& X, bool& nonfinite) {
+__device__ __forceinline__ void wave_xlow0(Rings<R>& S, const Ctx<R>& X) {
+  const G2& g = X.g;
+  const int c = X.lane, cl = c > 0 ? c - 1 : 0, cr = c < W - 1 ? c + 1 : W - 1;
+  const R ihx = R(1.0 / g.dx), ihy = R(1.0 / g.dy);
+  const R cL = R(2.0 * X.dt / g.dx);
+  for (int k = 0; k < X.rows; ++k) {
+    const int j = X.j0 - 4 + k;
+    const bool on = j >= X.j0 && j < X.j1 && (X.ph.lim & LIM_POINT);
+    const int s2 = slot4(k - 2), s3 = slot4(k - 3);
+    if (mid_row(S)) return;
+    if (on) {
+      Site<R> E, O;
+      LoFlux<R> fE, fO;
+      E = site9(S.P[CO], s2, c);
+      O = site9(S.P[YE], s2, c);
+      fE = lo_flux<0>(X.ph, E, z3(S.P[YE], s2, cl), z3(O), z3(S.P[XE], s3, c), z3(S.P[XE], s2, c),
+                      ihx, ihy);
+      fO = lo_flux<0>(X.ph, O, z3(E), z3(S.P[CO], s2, cr), z3(S.AV, s3, c), z3(S.AV, s2, c), ihx,
+                      ihy);
+      LoFlux<R> fEr;
+      Site<R> Er;
+#pragma unroll
+      for (int n = 0; n < 4; ++n) {
+        fEr.F[n] = from_right(fE.F[n]);
+        Er.U[n] = from_right(E.U[n]);
+      }
+      fEr.b = from_right(fE.b);
+      Er.a[0] = from_right(E.a[0]);
+      Er.a[4] = from_right(E.a[4]);
+      R Feo[4], Foe[4];
+      lo_face<0>(E, fE, O, fO, Feo);
+      lo_face<0>(O, fO, Er, fEr, Foe);
+#pragma unroll
+      for (int n = 0; n < 4; ++n) {
+        S.XC[4 + n][c] = cL * (Feo[n] - from_left(Foe[n]));
+        S.XY[4 + n][c] = cL * (Foe[n] - Feo[n]);
+      }
+    }
+    STRIP_BARRIER();
+  }
+}
+
+// ---- wave_xe -----------------------------------------------------------------------
+template <typename R>
+__device__ __forceinline__ void wave_xe(Rings<R>& S, const Ctx<R>& X, bool& nonfinite) {
   const G2& g = X.g;
   const int c = X.lane, cl = c > 0 ? c - 1 : 0, cr = c < W - 1 ? c + 1 : W - 1;
   const int i = X.i0 - 2 + c;
   const bool own_col = c >= 2 && c < SX + 2 && i < g.n1x;
-  const R ihx = R(1.0 / g.dx), ihy = R(1.0 / g.dy);
-  const R cL = R(2.0 * X.dt / g.dx);
   for (int k = 0; k < X.rows; ++k) {
-    const int r = X.j0 - 2 + k, j = r - 3;
+    const int j = X.j0 - 5 + k;
     const bool on = j >= X.j0 && j < X.j1 && j < g.n2;
-    const int s2 = slot4(k - 2), s3 = slot4(k - 3), z = slot3(k - 3);
-    R Rx[4], Lx[4];
-    double un[4], U0[4];
+    const int s3 = slot4(k - 3), z = slot3(k - 3);
+    R Rx[4];
+    double un[4], U0[4], Ls[4];
     if (on) {
       load_un(X, XE, i, j, own_col, un);
       const Site<R> E = site9(S.P[XE], s3, c);
       fp64_point(S, XE, s3, c, E.U, U0);
-      {
-        const Site<R> El = site9(S.P[XE], s3, cl), Er = site9(S.P[XE], s3, cr);
-        const Site<R> Zl = site9(S.Z, z, cl), Zr = site9(S.Z, z, c);
-        const int e1 = slot3(k - 3), o1 = slot2(k - 3);
-        const Site<R>* s[5] = {&El, &Zl, &E, &Zr, &Er};
-        const R ga[5] = {S.GE1[3][e1][cl], S.GO1[2][o1][cl], R(0.0), S.GO1[2][o1][c],
-                         S.GE1[3][e1][cr]};
-        const R gb[5] = {S.GE1[4][e1][cl], S.GO1[3][o1][cl], R(0.0), S.GO1[3][o1][c],
-                         S.GE1[4][e1][cr]};
-        line_resid<0>(X.ph, g.dx, s, ga, gb, Rx);
-      }
-      if (X.ph.lim & LIM_POINT) {
-        // the line xe, average, xe
-        const Site<R> A = avg_site(S.AV, s3, c);
-        const Z3<R> Al = z3(S.AV, s3, cl), Er = z3(S.P[XE], s3, cr);
-        const LoFlux<R> fE = lo_flux<0>(X.ph, E, Al, z3(A), z3(S.P[CO], s3, c), z3(S.P[CO], s2, c),
-                                        ihx, ihy);
-        const LoFlux<R> fA = lo_flux<0>(X.ph, A, z3(E), Er, z3(S.P[YE], s3, c), z3(S.P[YE], s2, c),
-                                        ihx, ihy);
-        Site<R> Asl;
-        LoFlux<R> fAl;
+      const Site<R> El = site9(S.P[XE], s3, cl), Er = site9(S.P[XE], s3, cr);
+      const Site<R> Zl = site9(S.Z, z, cl), Zr = site9(S.Z, z, c);
+      const int e1 = slot3(k - 3), o1 = slot2(k - 3);
+      const Site<R>* s[5] = {&El, &Zl, &E, &Zr, &Er};
+      const R ga[5] = {S.GE1[3][e1][cl], S.GO1[2][o1][cl], R(0.0), S.GO1[2][o1][c],
+                       S.GE1[3][e1][cr]};
+      const R gb[5] = {S.GE1[4][e1][cl], S.GO1[3][o1][cl], R(0.0), S.GO1[3][o1][c],
+                       S.GE1[4][e1][cr]};
+      line_resid<0>(X.ph, g.dx, s, ga, gb, Rx);
 #pragma unroll
-        for (int n = 0; n < 4; ++n) {
-          Asl.U[n] = from_left(A.U[n]);
-          fAl.F[n] = from_left(fA.F[n]);
-        }
-        Asl.a[0] = Al.u;
-        Asl.a[4] = from_left(A.a[4]);
-        fAl.b = from_left(fA.b);
-        R Fm[4], Fp[4];
-        lo_face<0>(Asl, fAl, E, fE, Fm);
-        lo_face<0>(E, fE, A, fA, Fp);
-#pragma unroll
-        for (int n = 0; n < 4; ++n) Lx[n] = cL * (Fp[n] - Fm[n]);
-      } else {
-#pragma unroll
-        for (int n = 0; n < 4; ++n) Lx[n] = R(0.0);
-      }
+      for (int n = 0; n < 4; ++n) Ls[n] = double(S.LX[n][c]) + double(S.LE[n][c]);
     }
     if (mid_row(S)) return;
     if (on) {
       R Rs[4];
-      double Ls[4];
 #pragma unroll
-      for (int n = 0; n < 4; ++n) {
-        Rs[n] = Rx[n] + S.X1[n][c];
-        Ls[n] = double(Lx[n]) + double(S.X1[4 + n][c]);
-      }
+      for (int n = 0; n < 4; ++n) Rs[n] = Rx[n] + S.RX[n][c];
       point_finish(X, XE, i, j, U0, Rs, Ls, un, own_col, nonfinite);
     }
     STRIP_BARRIER();
   }
 }
 
-// ---- wave 6: y-direction terms of co and xe, row r-3; update of co ------------
+// ---- wave_xlow1 --------------------------------------------------------------------
 template <typename R>
-__device__ __forceinline__ void wave_y0(Rings<R>& S, const Ctx<R>& X, bool& nonfinite) {
+__device__ __forceinline__ void wave_xlow1(Rings<R>& S, const Ctx<R>& X) {
   const G2& g = X.g;
-  const int c = X.lane, cl = c > 0 ? c - 1 : 0, i = X.i0 - 2 + c;
-  const bool own_col = c >= 2 && c < SX + 2 && i < g.n1x;
+  const int c = X.lane, cl = c > 0 ? c - 1 : 0, cr = c < W - 1 ? c + 1 : W - 1;
   const R ihx = R(1.0 / g.dx), ihy = R(1.0 / g.dy);
-  const R cL = R(2.0 * X.dt / g.dy);
-  // the line of the column: sites of rows r-4, r-3 (co, xe each), and their
-  // derivatives along x
-  Site<R> c4{}, x4{}, c3{}, x3{};
-  R gc4[2] = {}, gx4[2] = {}, gc3[2] = {}, gx3[2] = {};
-  LoFlux<R> fc3{};  // low-order data of co of row r-3
-  R Fprev[4] = {};  // LLF flux between xe of row r-4 and co of row r-3
+  const R cL = R(2.0 * X.dt / g.dx);
   for (int k = 0; k < X.rows; ++k) {
-    const int r = X.j0 - 2 + k, j = r - 3;
-    const bool on = j >= X.j0 && j < X.j1;  // co; xe too unless j = n2
-    const int s2 = slot4(k - 2), s3 = slot4(k - 3);
-    Site<R> c2{}, x2{};
-    R gc2[2] = {}, gx2[2] = {}, Fcx[4] = {}, Fxc[4] = {}, Rd[4];
-    LoFlux<R> fc2{};
-    double un[4];
-    load_un(X, CO, i, j, own_col && on, un);
-    if (k >= 3) {
-      c2 = site9(S.P[CO], s2, c);
-      x2 = site9(S.P[XE], s2, c);
-#pragma unroll
-      for (int n = 0; n < 2; ++n) {
-        gc2[n] = S.GE0[n][slot2(k - 2)][c];
-        gx2[n] = S.GE1[n][slot3(k - 2)][c];
-      }
-    }
-    if (k >= 4 && (X.ph.lim & LIM_POINT)) {
-      const LoFlux<R> fx3 = lo_flux<1>(X.ph, x3, z3(S.AV, s3, cl), z3(S.AV, s3, c), z3(c3), z3(c2),
-                                       ihx, ihy);
-      fc2 = lo_flux<1>(X.ph, c2, z3(S.P[YE], s2, cl), z3(S.P[YE], s2, c), z3(x3), z3(x2), ihx, ihy);
-      lo_face<1>(c3, fc3, x3, fx3, Fcx);
-      lo_face<1>(x3, fx3, c2, fc2, Fxc);
-    }
-    if (on) {
-      const Site<R>* s[5] = {&x4, &c3, &x3, &c2, &x2};
-      const R ga[5] = {gx4[1], gc3[1], R(0.0), gc2[1], gx2[1]};
-      const R gb[5] = {gx4[0], gc3[0], R(0.0), gc2[0], gx2[0]};
-      line_resid<1>(X.ph, g.dy, s, ga, gb, Rd);
-#pragma unroll
-      for (int n = 0; n < 4; ++n) {
-        S.X1[n][c] = Rd[n];
-        S.X1[4 + n][c] = cL * (Fxc[n] - Fcx[n]);
-      }
-    }
+    const int j = X.j0 - 4 + k;
+    const bool on = j >= X.j0 && j < X.j1 && j < g.n2 && (X.ph.lim & LIM_POINT);
+    const int s1 = slot4(k - 1), s2 = slot4(k - 2);
     if (mid_row(S)) return;
     if (on) {
-      const Site<R>* s[5] = {&c4, &x4, &c3, &x3, &c2};
-      const R ga[5] = {gc4[1], gx4[1], R(0.0), gx3[1], gc2[1]};
-      const R gb[5] = {gc4[0], gx4[0], R(0.0), gx3[0], gc2[0]};
-      line_resid<1>(X.ph, g.dy, s, ga, gb, Rd);
-      const int gs = slot2(k - 3);
-      R Rs[4];
-      double Ls[4], U0[4];
+      Site<R> E, A;
+      LoFlux<R> fE, fA;
+      // the line xe, average, xe
+      E = site9(S.P[XE], s2, c);
+      A = avg_site(S.AV, s2, c);
+      fE = lo_flux<0>(X.ph, E, z3(S.AV, s2, cl), z3(A), z3(S.P[CO], s2, c), z3(S.P[CO], s1, c), ihx,
+                      ihy);
+      fA = lo_flux<0>(X.ph, A, z3(E), z3(S.P[XE], s2, cr), z3(S.P[YE], s2, c), z3(S.P[YE], s1, c),
+                      ihx, ihy);
+      Site<R> Al;
+      LoFlux<R> fAl;
 #pragma unroll
       for (int n = 0; n < 4; ++n) {
-        Rs[n] = S.XC[n][gs][c] + Rd[n];
-        const R Ly = cL * (Fcx[n] - Fprev[n]);  // rounded before the sum
-        Ls[n] = double(S.XC[4 + n][gs][c]) + double(Ly);
+        Al.U[n] = from_left(A.U[n]);
+        fAl.F[n] = from_left(fA.F[n]);
       }
-      fp64_point(S, CO, s3, c, c3.U, U0);
-      point_finish(X, CO, i, j, U0, Rs, Ls, un, own_col, nonfinite);
-    }
-    c4 = c3;
-    x4 = x3;
-    c3 = c2;
-    x3 = x2;
-    fc3 = fc2;
+      Al.a[0] = from_left(A.a[0]);
+      Al.a[4] = from_left(A.a[4]);
+      fAl.b = from_left(fA.b);
+      R Fm[4], Fp[4];
+      lo_face<0>(Al, fAl, E, fE, Fm);
+      lo_face<0>(E, fE, A, fA, Fp);
 #pragma unroll
-    for (int n = 0; n < 2; ++n) {
-      gc4[n] = gc3[n];
-      gx4[n] = gx3[n];
-      gc3[n] = gc2[n];
-      gx3[n] = gx2[n];
+      for (int n = 0; n < 4; ++n) S.LX[n][c] = cL * (Fp[n] - Fm[n]);
     }
-#pragma unroll
-    for (int n = 0; n < 4; ++n) Fprev[n] = Fxc[n];
     STRIP_BARRIER();
   }
 }
 
-// ---- wave 7: y-direction terms and update of ye, row r-3 ----------------------
+// ---- wave_yres1 --------------------------------------------------------------------
 template <typename R>
-__device__ __forceinline__ void wave_y1(Rings<R>& S, const Ctx<R>& X, bool& nonfinite) {
+__device__ __forceinline__ void wave_yres1(Rings<R>& S, const Ctx<R>& X, bool& nonfinite) {
   const G2& g = X.g;
-  const int c = X.lane, cr = c < W - 1 ? c + 1 : W - 1, i = X.i0 - 2 + c;
-  const bool own_col = c >= 2 && c < SX + 2 && i < g.n1;
+  const int c = X.lane, i = X.i0 - 2 + c;
+  const bool own_col = c >= 2 && c < SX + 2 && i < g.n1x;
+  Site<R> x4{};  // xe of row r-4, and its derivatives along x
+  R gx4[2] = {};
+  for (int k = 0; k < X.rows; ++k) {
+    const int j = X.j0 - 5 + k;
+    const bool on = j >= X.j0 && j < X.j1;
+    const int s2 = slot4(k - 2), s3 = slot4(k - 3);
+    R Rx[4];
+    double un[4], Ls[4];
+    if (k >= 3) {
+      const Site<R> x3 = site9(S.P[XE], s3, c);
+      const int e0 = slot2(k - 2), e1 = slot3(k - 2), e3 = slot3(k - 3);
+      if (on) {
+        const Site<R> c3 = site9(S.P[CO], s3, c), c2 = site9(S.P[CO], s2, c),
+                      x2 = site9(S.P[XE], s2, c);
+        const Site<R>* s[5] = {&x4, &c3, &x3, &c2, &x2};
+        const R ga[5] = {gx4[1], S.GE0[1][slot2(k - 3)][c], R(0.0), S.GE0[1][e0][c], S.GE1[1][e1][c]};
+        const R gb[5] = {gx4[0], S.GE0[0][slot2(k - 3)][c], R(0.0), S.GE0[0][e0][c], S.GE1[0][e1][c]};
+        R Rd[4];
+        line_resid<1>(X.ph, g.dy, s, ga, gb, Rd);
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+          S.RX[n][c] = Rd[n];
+          Rx[n] = S.XC[n][c];
+          Ls[n] = double(S.XC[4 + n][c]) + double(S.LC[n][c]);
+        }
+      }
+      x4 = x3;
+      gx4[0] = S.GE1[0][e3][c];
+      gx4[1] = S.GE1[1][e3][c];
+    }
+    load_un(X, CO, i, j, own_col && on, un);
+    if (mid_row(S)) return;
+    if (on) {
+      R U[4], Rs[4];
+      double U0[4];
+#pragma unroll
+      for (int n = 0; n < 4; ++n) {
+        U[n] = S.P[CO][n][s3][c];
+        Rs[n] = Rx[n] + S.RC[n][c];
+      }
+      fp64_point(S, CO, s3, c, U, U0);
+      point_finish(X, CO, i, j, U0, Rs, Ls, un, own_col, nonfinite);
+    }
+    STRIP_BARRIER();
+  }
+}
+
+// ---- wave_yres0 --------------------------------------------------------------------
+template <typename R>
+__device__ __forceinline__ void wave_yres0(Rings<R>& S, const Ctx<R>& X) {
+  const G2& g = X.g;
+  const int c = X.lane, cl = c > 0 ? c - 1 : 0;
   const R ihx = R(1.0 / g.dx), ihy = R(1.0 / g.dy);
   const R cL = R(2.0 * X.dt / g.dy);
+  // the line of the column: co and xe of row r-4 and their derivatives along x;
+  // co of row r-2, its low-order data, and the LLF flux below it
+  Site<R> c4{}, x4{}, c2{};
+  R gc4[2] = {}, gx4[2] = {};
+  LoFlux<R> fc2{};
+  R Fprev[4] = {};
+  for (int k = 0; k < X.rows; ++k) {
+    const int j = X.j0 - 5 + k;
+    const bool on = j >= X.j0 && j < X.j1;
+    const int s1 = slot4(k - 1), s2 = slot4(k - 2), s3 = slot4(k - 3);
+    if (k >= 3) {
+      const Site<R> c3 = site9(S.P[CO], s3, c), x3 = site9(S.P[XE], s3, c);
+      const int e0 = slot2(k - 2), e3 = slot3(k - 3);
+      const R gx3[2] = {S.GE1[0][e3][c], S.GE1[1][e3][c]};
+      if (on) {
+        const Site<R>* s[5] = {&c4, &x4, &c3, &x3, &c2};
+        const R ga[5] = {gc4[1], gx4[1], R(0.0), gx3[1], S.GE0[1][e0][c]};
+        const R gb[5] = {gc4[0], gx4[0], R(0.0), gx3[0], S.GE0[0][e0][c]};
+        R Rd[4];
+        line_resid<1>(X.ph, g.dy, s, ga, gb, Rd);
+#pragma unroll
+        for (int n = 0; n < 4; ++n) S.RC[n][c] = Rd[n];
+      }
+      c4 = c3;
+      x4 = x3;
+#pragma unroll
+      for (int n = 0; n < 2; ++n) {
+        gc4[n] = S.GE0[n][slot2(k - 3)][c];
+        gx4[n] = gx3[n];
+      }
+    }
+    if (mid_row(S)) return;
+    if (k >= 2) {
+      const Site<R> c1 = site9(S.P[CO], s1, c);
+      if (X.ph.lim & LIM_POINT) {
+        const Site<R> x2 = site9(S.P[XE], s2, c);
+        const LoFlux<R> fx2 = lo_flux<1>(X.ph, x2, z3(S.AV, s2, cl), z3(S.AV, s2, c), z3(c2), z3(c1),
+                                         ihx, ihy);
+        const LoFlux<R> fc1 = lo_flux<1>(X.ph, c1, z3(S.P[YE], s1, cl), z3(S.P[YE], s1, c), z3(x2),
+                                         z3(S.P[XE], s1, c), ihx, ihy);
+        R Fcx[4], Fxc[4];
+        lo_face<1>(c2, fc2, x2, fx2, Fcx);
+        lo_face<1>(x2, fx2, c1, fc1, Fxc);
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+          S.LC[n][c] = cL * (Fcx[n] - Fprev[n]);
+          S.LE[n][c] = cL * (Fxc[n] - Fcx[n]);
+          Fprev[n] = Fxc[n];
+        }
+        fc2 = fc1;
+      }
+      c2 = c1;
+    }
+    STRIP_BARRIER();
+  }
+}
+
+// ---- wave_ye -----------------------------------------------------------------------
+template <typename R>
+__device__ __forceinline__ void wave_ye(Rings<R>& S, const Ctx<R>& X, bool& nonfinite) {
+  const G2& g = X.g;
+  const int c = X.lane, i = X.i0 - 2 + c;
+  const bool own_col = c >= 2 && c < SX + 2 && i < g.n1;
   // the line of the column: ye and centre of row r-4, ye of row r-3
   Site<R> y4{}, z4{}, y3{};
   R gy4[2] = {}, gz4[2] = {}, gy3[2] = {};
-  LoFlux<R> fy3{};
-  R Fprev[4] = {};  // LLF flux between the average of row r-4 and ye of row r-3
   for (int k = 0; k < X.rows; ++k) {
-    const int r = X.j0 - 2 + k, j = r - 3;
+    const int j = X.j0 - 5 + k;
     const bool on = j >= X.j0 && j < X.j1;
-    const int s2 = slot4(k - 2), s3 = slot4(k - 3);
     Site<R> y2{}, z3_{};
-    R gy2[2] = {}, gz3[2] = {}, Fya[4] = {}, Fay[4] = {}, Rd[4];
-    LoFlux<R> fy2{};
-    double un[4];
+    R gy2[2] = {}, gz3[2] = {}, Rs[4];
+    double un[4], Ls[4];
     load_un(X, YE, i, j, own_col && on, un);
     if (k >= 3) {
-      y2 = site9(S.P[YE], s2, c);
+      y2 = site9(S.P[YE], slot4(k - 2), c);
       z3_ = site9(S.Z, slot3(k - 3), c);
 #pragma unroll
       for (int n = 0; n < 2; ++n) {
@@ -1027,43 +1191,29 @@ __device__ __forceinline__ void wave_y1(Rings<R>& S, const Ctx<R>& X, bool& nonf
       const Site<R>* s[5] = {&y4, &z4, &y3, &z3_, &y2};
       const R ga[5] = {gy4[1], gz4[1], R(0.0), gz3[1], gy2[1]};
       const R gb[5] = {gy4[0], gz4[0], R(0.0), gz3[0], gy2[0]};
+      R Rd[4];
       line_resid<1>(X.ph, g.dy, s, ga, gb, Rd);
-    }
-    if (mid_row(S)) return;
-    if (k >= 4 && (X.ph.lim & LIM_POINT)) {
-      const Site<R> A = avg_site(S.AV, s3, c);
-      const LoFlux<R> fA = lo_flux<1>(X.ph, A, z3(S.P[XE], s3, c), z3(S.P[XE], s3, cr), z3(y3),
-                                      z3(y2), ihx, ihy);
-      fy2 = lo_flux<1>(X.ph, y2, z3(S.P[CO], s2, c), z3(S.P[CO], s2, cr), z3(A), z3(S.AV, s2, c),
-                       ihx, ihy);
-      lo_face<1>(y3, fy3, A, fA, Fya);
-      lo_face<1>(A, fA, y2, fy2, Fay);
-    }
-    if (on) {
-      const int gs = slot2(k - 3);
-      R Rs[4];
-      double Ls[4], U0[4];
 #pragma unroll
       for (int n = 0; n < 4; ++n) {
-        Rs[n] = S.XY[n][gs][c] + Rd[n];
-        const R Ly = cL * (Fya[n] - Fprev[n]);  // rounded before the sum
-        Ls[n] = double(S.XY[4 + n][gs][c]) + double(Ly);
+        Rs[n] = S.XY[n][c] + Rd[n];
+        Ls[n] = double(S.XY[4 + n][c]) + double(S.LO[n][c]);
       }
-      fp64_point(S, YE, s3, c, y3.U, U0);
+    }
+    if (mid_row(S)) return;
+    if (on) {
+      double U0[4];
+      fp64_point(S, YE, slot4(k - 3), c, y3.U, U0);
       point_finish(X, YE, i, j, U0, Rs, Ls, un, own_col, nonfinite);
     }
     y4 = y3;
     z4 = z3_;
     y3 = y2;
-    fy3 = fy2;
 #pragma unroll
     for (int n = 0; n < 2; ++n) {
       gy4[n] = gy3[n];
       gz4[n] = gz3[n];
       gy3[n] = gy2[n];
     }
-#pragma unroll
-    for (int n = 0; n < 4; ++n) Fprev[n] = Fay[n];
     STRIP_BARRIER();
   }
 }
@@ -1072,6 +1222,19 @@ __device__ __forceinline__ void wave_y1(Rings<R>& S, const Ctx<R>& X, bool& nonf
 struct Strips {
   int nx, ny, H;
 };
+
+// the kernel's arguments where the launch put them
+struct AllArgs {
+  StageArgs sa;
+  Strips st;
+};
+
+// p, known to point to global memory (loads through a pointer that came from
+// memory would be flat ones)
+template <typename T>
+__device__ __forceinline__ T* in_global(T* p) {
+  return (T*)(__attribute__((address_space(1))) T*)(uintptr_t)p;
+}
 
 // BLEND: per-face blend input/output arrays; DEV: buffers, dt and flag word
 // from the descriptor sa.dinst of a device-resident step loop.
@@ -1097,34 +1260,61 @@ __global__ void __launch_bounds__(NT) k_strip(StageArgs sa, Strips st) {
   } else {
     dt = sa.dt_mul * (sa.dt_dev ? *sa.dt_dev : sa.dt_host);
   }
-  const float* blend = BLEND ? sa.blend : nullptr;
-  float* ts_out = BLEND ? sa.ts_out : nullptr;
   bool nonfinite = false;
   double cfl_a = 0.0, cfl_v = 0.0;
-  const int j0 = blockIdx.y * st.H, j1 = min(j0 + st.H, sa.g.n2y);
-  // a row of the strip is finished when the march is three rows past it
-  const Ctx<R> X{sa.g,  sa.ph, phys_as<R>(sa.ph), Uk,    Un,
-                 Uout,  dt,    sa.ca,             sa.cb, sa.first,
-                 flags, (int)(threadIdx.x & 63),  (int)blockIdx.x * SX,
-                 j0,    j1,    j1 - j0 + 5};
+  // Each wave reads what it needs of the arguments for itself, through a pointer
+  // the compiler does not see through: read once for all twelve, they are kept
+  // in scalar registers across every wave's loop, and most of them spill
+  auto ctx = [&]() {
+    auto* q = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(q));
+    const AllArgs* p = (const AllArgs*)q;
+    const int H = p->st.H, n2y = p->sa.g.n2y, j0 = blockIdx.y * H, j1 = min(j0 + H, n2y);
+    const Phys phd = p->sa.ph;
+    // a row of the strip is finished when the march is three rows past it
+    return Ctx<R>{p->sa.g,
+                  phd,
+                  phys_as<R>(phd),
+                  in_global(Uk),
+                  in_global(Un),
+                  in_global(Uout),
+                  dt,
+                  p->sa.ca,
+                  p->sa.cb,
+                  p->sa.first,
+                  in_global(flags),
+                  BLEND ? in_global(p->sa.blend) : nullptr,
+                  BLEND ? in_global(p->sa.ts_out) : nullptr,
+                  (int)(threadIdx.x & 63),
+                  (int)blockIdx.x * SX,
+                  j0,
+                  j1,
+                  j1 - j0 + 5};
+  };
+  // waves go to the SIMDs round-robin: w, w + 4 and w + 8 share one, and the
+  // parts are grouped so that the four carry equal work in either half
   switch (wave) {
-    case 0: wave_load(S, X); break;
-    case 1: wave_grad(S, X, sa.skip_flagged); break;
-    case 2: wave_xface(S, X, blend, ts_out); break;
-    case 3:
-      wave_yface<R, DEV>(S, X, blend, ts_out, nonfinite, sa.dinst, sa.k == 2, cfl_a,
+    case 0: wave_xface(S, ctx()); break;
+    case 4: wave_xlow1(S, ctx()); break;
+    case 8: wave_xe(S, ctx(), nonfinite); break;
+    case 1:
+      wave_yface<R, DEV>(S, ctx(), nonfinite, sa.dinst, sa.k == 2, cfl_a,
                          cfl_v);
       break;
-    case 4: wave_x0(S, X); break;
-    case 5: wave_x1(S, X, nonfinite); break;
-    case 6: wave_y0(S, X, nonfinite); break;
-    default: wave_y1(S, X, nonfinite); break;
+    case 5: wave_xlow0(S, ctx()); break;
+    case 9: wave_xres0(S, ctx()); break;
+    case 2: wave_yres1(S, ctx(), nonfinite); break;
+    case 6: wave_ye(S, ctx(), nonfinite); break;
+    case 10: wave_edges(S, ctx()); break;
+    case 3: wave_centre(S, ctx()); break;
+    case 7: wave_yres0(S, ctx()); break;
+    default: wave_cells(S, ctx(), sa.skip_flagged); break;
   }
   if (nonfinite) raise_flag(flags, FLAG_NONFINITE);
   if constexpr (DEV) {
     // the workgroup's CFL maxima of the new state (lanes that wrote no cell
     // hold 0, neutral for max)
-    if (sa.k == 2 && wave == 3 && sa.cfl_partial) {
+    if (sa.k == 2 && wave == 1 && sa.cfl_partial) {
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) {
         cfl_a = mx(cfl_a, __shfl_xor(cfl_a, o, 64));
