@@ -309,25 +309,29 @@ af_status af_batch_run(af_batch* b, double* const* U, void* ws, void* stream, do
                        double t_final, long max_steps, int attempts_per_slot, int use_graph,
                        long* steps, double* t, int* status, long* attempts);
 
-/* Compiled variants of the 2D stage kernel.  Each is the same arithmetic
- * (results are identical to the last bit) over a different tile shape:
+/* A batch's stages march up strips of the grids, as those of single instances
+ * do, unless its grids are too narrow for strips or a tile variant is set.
+ *
+ * Compiled tile variants of the 2D stage kernel.  Each is the same arithmetic
+ * (results are identical to the last bit, and to those on strips) over a
+ * different tile shape:
  * tiles are 16 cells wide and tile_height cells high, and the taller the
  * tile the fewer halo sites are recomputed but the more LDS a workgroup
- * takes, so fewer workgroups are resident per CU.  The first variant of
- * each precision is the one af_rk_stage, af_step, af_run and new batches
- * use. */
+ * takes, so fewer workgroups are resident per CU. */
 int af_stage_variant_count(void);
 /* name (static storage), precision (AF_PREC_*) and tile height of variant
  * i in [0, af_stage_variant_count()); any output may be NULL. */
 af_status af_stage_variant_info(int i, const char** name, int* precision, int* tile_height);
-/* Index of the variant the batch's stage launches use. */
+/* Index of the batch's tile variant (a new batch: its precision's first). */
 int af_batch_variant(const af_batch* b);
-/* Use variant i for the batch; it must have the batch's precision. */
+/* Run the batch on the tiles of variant i; it must have the batch's
+ * precision. */
 af_status af_batch_set_variant(af_batch* b, int i);
 /* Autotuner: for every variant of the batch's precision, time one step slot
  * (CFL step opening, one RK3 attempt of every instance from the states U at
  * time t0, and the accept/halve decision) reps times after one untimed slot,
- * and keep the fastest variant for the batch's later runs.  Synchronous; U
+ * and keep the fastest variant for the batch's later runs, which use it
+ * unless strips, timed in the same way, are faster still.  Synchronous; U
  * is read, never written (ws must be the batch's workspace).  us_per_slot,
  * if not NULL, receives af_stage_variant_count() entries: the fastest time
  * of each variant in microseconds, -1 for variants of the other precision. */

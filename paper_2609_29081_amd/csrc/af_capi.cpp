@@ -76,7 +76,7 @@ struct af_ctx {
   // descriptor)
   hipGraphExec_t run_exec = nullptr;
   const void* run_ws = nullptr;
-  int run_slot = 0, run_dev = -1;
+  int run_slot = 0, run_dev = -1, run_nwg = 0;
   const float* net = nullptr;  // learned-blend network parameters (device), or NULL
   double bcstate[2][3] = {{1.0, 0.0, 1.0}, {1.0, 0.0, 1.0}};  // 1D Dirichlet states
 };
@@ -85,10 +85,16 @@ struct af_batch {
   std::vector<af_ctx*> ctx;
   std::vector<afi::Geo> geo;
   int mixed = 0;
-  const afi::StageVariant* var = nullptr;  // stage variant (tile shape) of the batch
-  // workspace: descriptors, CFL partials, active count, then two stage
-  // buffers per instance
-  size_t off_partial = 0, off_nact = 0, bytes = 0;
+  // the stage marches up strips (shapes per instance, nwg workgroups in all),
+  // or, where the grids are narrow or a variant is set, runs on the tiles of
+  // variant var
+  bool strips = true;
+  std::vector<afi::StripShape> shape;
+  int nwg = 0;
+  const afi::StageVariant* var = nullptr;
+  // workspace: descriptors, the strips' instance per workgroup (one upload),
+  // CFL partials, active count, then two stage buffers per instance
+  size_t off_wg = 0, off_partial = 0, off_nact = 0, bytes = 0;
   std::vector<size_t> off_bufs;
 };
 
@@ -457,6 +463,14 @@ afi::BatchInst instance_of(const af_ctx* c, const afi::Geo& g, const afi::StageV
   return I;
 }
 
+// the strips of one instance, whose workgroups begin at wg0
+void set_strips(afi::BatchInst& I, const afi::StripShape& b, int wg0) {
+  I.wg0 = wg0;
+  I.nwg = b.nx * b.ny;
+  I.snx = b.nx;
+  I.sH = b.H;
+}
+
 // host copies of the batch descriptors for states U, times t0..t_final and
 // the tile shape of stage variant v; *total_tiles receives the tiles of all
 // instances (a stage launch has at most that many)
@@ -465,32 +479,90 @@ af_status batch_descriptors(const af_batch* b, const afi::StageVariant* v, doubl
                             std::vector<afi::BatchInst>& h, int* total_tiles) {
   const int n = (int)b->ctx.size();
   h.assign(n, afi::BatchInst{});
-  int total = 0;
+  int total = 0, wg = 0;
   for (int i = 0; i < n; ++i) {
     if (!U[i]) return fail(AF_E_ARG, "batch: state %d is NULL", i);
     h[i] = instance_of(b->ctx[i], b->geo[i], v, U[i], (double*)(base + b->off_bufs[2 * i]),
                        (double*)(base + b->off_bufs[2 * i + 1]), t0, t_final, max_steps);
+    set_strips(h[i], b->shape[i], wg);
+    wg += h[i].nwg;
     total += h[i].ntiles;
   }
   *total_tiles = total;
   return AF_OK;
 }
 
-// one slot of a batch: `rounds` rounds, each of which opens a step (fresh
-// CFL dt) for every instance that is between steps and then runs one RK3
-// attempt of every instance inside a step (three stage launches of variant
-// v, then the accept/halve decision).  An instance that accepts a step opens
-// the next one in the following round, while others redo theirs with dt/2.
-hipError_t batch_slot(const afi::StageVariant* v, afi::BatchInst* dinst, int n, int total_tiles,
-                      double* partial, int* nact, int rounds, hipStream_t q) {
+// descriptors and instance per workgroup to the device, in one copy from buf,
+// which the caller keeps until it has waited for s
+af_status upload_batch(const af_batch* b, const std::vector<afi::BatchInst>& h,
+                       std::vector<char>& buf, char* base, hipStream_t s) {
+  buf.resize(b->off_wg + sizeof(int) * (size_t)b->nwg);
+  memcpy(buf.data(), h.data(), sizeof(afi::BatchInst) * h.size());
+  int* wg = (int*)(buf.data() + b->off_wg);
+  for (size_t i = 0; i < h.size(); ++i)
+    for (int k = 0; k < h[i].nwg; ++k) *wg++ = (int)i;
+  AF_HIP(hipMemcpyAsync(base, buf.data(), buf.size(), hipMemcpyHostToDevice, s));
+  return AF_OK;
+}
+
+// how a batch's slots run: on strips, or on the tiles of variant v
+struct BatchPath {
+  const afi::StageVariant* v;  // NULL: strips
+  int mixed, n, total_tiles, nwg;
+  afi::BatchInst* inst;
+  const int* wg_inst;
+  double* partial;
+  int* nact;
+};
+
+BatchPath batch_path(const af_batch* b, const afi::StageVariant* v, char* base, int total_tiles) {
+  return BatchPath{v,
+                   b->mixed,
+                   (int)b->ctx.size(),
+                   total_tiles,
+                   b->nwg,
+                   (afi::BatchInst*)base,
+                   (const int*)(base + b->off_wg),
+                   (double*)(base + b->off_partial),
+                   (int*)(base + b->off_nact)};
+}
+
+// CFL step openings of every instance that may open one, by kernels of their own
+hipError_t batch_openings(const BatchPath& p, hipStream_t q) {
+  const int nb = p.n == 1 ? afi::kSingleCflBlocks : afi::kBatchCflBlocks;
+  hipError_t e = afi::batch_cfl(p.inst, p.n, p.partial, nb, q);
+  if (e != hipSuccess) return e;
+  return afi::batch_open(p.inst, p.n, p.partial, nb, p.nact, q);
+}
+
+// what comes before the first slot: strips open the first step here (later
+// ones open from what the last stage left)
+hipError_t batch_start(const BatchPath& p, hipStream_t q) {
+  return p.v ? hipSuccess : batch_openings(p, q);
+}
+
+// one slot of a batch: `rounds` rounds, each of which runs one RK3 attempt of
+// every instance inside a step and decides on it; instances between steps
+// open one (fresh CFL dt): on tiles before the attempt, on strips with the
+// decision.  An instance that accepts a step opens the next one in the
+// following round, while others redo theirs with dt/2.
+hipError_t batch_slot(const BatchPath& p, int rounds, hipStream_t q) {
   hipError_t e;
-  const int nb = n == 1 ? afi::kSingleCflBlocks : afi::kBatchCflBlocks;
   for (int a = 0; a < rounds; ++a) {
-    if ((e = afi::batch_cfl(dinst, n, partial, nb, q)) != hipSuccess) return e;
-    if ((e = afi::batch_open(dinst, n, partial, nb, nact, q)) != hipSuccess) return e;
-    for (int k = 0; k < 3; ++k)
-      if ((e = v->batch(dinst, n, total_tiles, nact, k, q, nullptr)) != hipSuccess) return e;
-    if ((e = afi::batch_decide(dinst, n, nact, q)) != hipSuccess) return e;
+    if (p.v) {
+      if ((e = batch_openings(p, q)) != hipSuccess) return e;
+      for (int k = 0; k < 3; ++k)
+        if ((e = p.v->batch(p.inst, p.n, p.total_tiles, p.nact, k, q, nullptr)) != hipSuccess)
+          return e;
+      if ((e = afi::batch_decide(p.inst, p.n, p.nact, q)) != hipSuccess) return e;
+    } else {
+      for (int k = 0; k < 3; ++k)
+        if ((e = afi::stage2d_dev(p.mixed, p.inst, p.wg_inst, p.nwg, (double2*)p.partial, k, q)) !=
+            hipSuccess)
+          return e;
+      if ((e = afi::batch_advance(p.inst, p.n, (const double2*)p.partial, q)) != hipSuccess)
+        return e;
+    }
   }
   return hipSuccess;
 }
@@ -991,10 +1063,6 @@ af_status af_batch_create(af_ctx* const* ctxs, int n, af_batch** out) {
     off += (bytes + 255) & ~(size_t)255;
     return o;
   };
-  take(sizeof(afi::BatchInst) * n);
-  b->off_partial = take(sizeof(double) * 2 *
-                        (n == 1 ? afi::kSingleCflBlocks : afi::kBatchCflBlocks * n));
-  b->off_nact = take(sizeof(int));
   for (int i = 0; i < n; ++i) {
     af_ctx* c = ctxs[i];
     if (!c) return fail(AF_E_ARG, "af_batch_create: context %d is NULL", i);
@@ -1006,6 +1074,16 @@ af_status af_batch_create(af_ctx* const* ctxs, int n, af_batch** out) {
     if (!geometry(c, &g)) return AF_E_ARG;
     b->ctx.push_back(c);
     b->geo.push_back(g);
+  }
+  b->shape.resize(n);
+  b->strips = afi::strip_shapes(b->geo.data(), n, b->shape.data());
+  for (const afi::StripShape& t : b->shape) b->nwg += t.nx * t.ny;
+  take(sizeof(afi::BatchInst) * n);
+  b->off_wg = take(sizeof(int) * (size_t)b->nwg);
+  const int cfl_blocks = n == 1 ? afi::kSingleCflBlocks : afi::kBatchCflBlocks * n;
+  b->off_partial = take(sizeof(double) * 2 * (size_t)std::max(cfl_blocks, b->nwg));
+  b->off_nact = take(sizeof(int));
+  for (const afi::Geo& g : b->geo) {
     b->off_bufs.push_back(take(sizeof(double) * g.state_len));
     b->off_bufs.push_back(take(sizeof(double) * g.state_len));
   }
@@ -1028,20 +1106,18 @@ af_status af_batch_run(af_batch* b, double* const* U, void* ws, void* stream, do
   const int n = (int)b->ctx.size();
   const hipStream_t s = (hipStream_t)stream;
   char* base = (char*)ws;
-  afi::BatchInst* dinst = (afi::BatchInst*)base;
-  double* partial = (double*)(base + b->off_partial);
-  int* nact = (int*)(base + b->off_nact);
   std::vector<afi::BatchInst> h;
+  std::vector<char> buf;
   int total_tiles = 0;
-  const af_status sd =
-      batch_descriptors(b, b->var, U, base, t0, t_final, max_steps, h, &total_tiles);
+  af_status sd = batch_descriptors(b, b->var, U, base, t0, t_final, max_steps, h, &total_tiles);
   if (sd != AF_OK) return sd;
-  AF_HIP(hipMemcpyAsync(dinst, h.data(), sizeof(afi::BatchInst) * n, hipMemcpyHostToDevice, s));
-  auto slot = [&](hipStream_t q) {
-    return batch_slot(b->var, dinst, n, total_tiles, partial, nact, attempts_per_slot, q);
-  };
+  if ((sd = upload_batch(b, h, buf, base, s)) != AF_OK) return sd;
+  const BatchPath path = batch_path(b, b->strips ? nullptr : b->var, base, total_tiles);
+  AF_HIP(batch_start(path, s));
+  auto slot = [&](hipStream_t q) { return batch_slot(path, attempts_per_slot, q); };
   const af_status st =
-      run_slots(slot, attempts_per_slot, dinst, n, use_graph, s, max_steps, t_final, h, "af_batch_run");
+      run_slots(slot, attempts_per_slot, path.inst, n, use_graph, s, max_steps, t_final, h,
+                "af_batch_run");
   if (st != AF_OK) return st;
   // the current state of every instance back into its U
   for (int i = 0; i < n; ++i)
@@ -1068,41 +1144,46 @@ af_status af_run_graph(af_ctx* c, double* U, void* ws, void* stream, double t0, 
   if (!geometry(c, &g)) return AF_E_ARG;
   const afi::Work w = work_of(c, g, ws);
   const hipStream_t s = (hipStream_t)stream;
-  const afi::StageVariant* v = afi::default_variant(g.mixed);
   std::vector<afi::BatchInst> h(1);
-  h[0] = instance_of(c, g, v, U, w.S1, w.S2, t0, t_final, max_steps);
-  const int nwg = afi::stage2d_dev_nwg(g);
-  h[0].stage_nwg = nwg;
+  h[0] = instance_of(c, g, afi::default_variant(g.mixed), U, w.S1, w.S2, t0, t_final, max_steps);
+  set_strips(h[0], afi::strip_shape(g), 0);
+  const int nwg = h[0].nwg;
+  // where the last stage leaves the CFL maxima of the new state; a grid of
+  // more strips than that has room for takes its dt by the reduction kernels
+  double2* maxima = nwg <= afi::kSingleCflBlocks ? (double2*)w.bpartial : nullptr;
   AF_HIP(hipMemcpyAsync(w.binst, h.data(), sizeof(afi::BatchInst), hipMemcpyHostToDevice, s));
-  // the first step's CFL maxima; every later step opens from those its
-  // predecessor's last stage left (the dt reduction fused into that stage)
-  AF_HIP(afi::batch_cfl(w.binst, 1, w.bpartial, afi::kSingleCflBlocks, s));
+  auto open = [&](hipStream_t q) {
+    const hipError_t e = afi::batch_cfl(w.binst, 1, w.bpartial, afi::kSingleCflBlocks, q);
+    return e != hipSuccess
+               ? e
+               : afi::batch_open(w.binst, 1, w.bpartial, afi::kSingleCflBlocks, w.bnact, q);
+  };
+  // the first step; every later one opens from the maxima its predecessor's
+  // last stage left (the dt reduction fused into that stage)
+  if (maxima) AF_HIP(open(s));
   int dev = 0;
   AF_HIP(hipGetDevice(&dev));
-  if (c->run_exec && (c->run_ws != ws || c->run_slot != attempts_per_slot || c->run_dev != dev)) {
+  if (c->run_exec && (c->run_ws != ws || c->run_slot != attempts_per_slot || c->run_dev != dev ||
+                      c->run_nwg != nwg)) {
     (void)hipGraphExecDestroy(c->run_exec);
     c->run_exec = nullptr;
   }
   c->run_ws = ws;
   c->run_slot = attempts_per_slot;
   c->run_dev = dev;
-  const afd::Phys ph = physics(c->p);
-  // a round: open a step if the last one was accepted (CFL dt from the
-  // maxima its last stage left), one RK3 attempt with the single-instance
-  // stage kernel, accept or halve
+  c->run_nwg = nwg;
+  // a round: one RK3 attempt, then accept or halve, and open the next step
   auto slot = [&](hipStream_t q) {
-    hipError_t e;
-    for (int a = 0; a < attempts_per_slot; ++a) {
-      if (!nwg && (e = afi::batch_cfl(w.binst, 1, w.bpartial, afi::kSingleCflBlocks, q)) != hipSuccess)
-        return e;
-      if ((e = afi::batch_open(w.binst, 1, w.bpartial, afi::kSingleCflBlocks, w.bnact, q)) !=
-          hipSuccess)
-        return e;
-      for (int k = 0; k < 3; ++k)
-        if ((e = afi::stage2d_dev(g, ph, w.binst, w.bpartial, k, q)) != hipSuccess) return e;
-      if ((e = afi::batch_decide(w.binst, 1, w.bnact, q)) != hipSuccess) return e;
+    hipError_t e = hipSuccess;
+    for (int a = 0; a < attempts_per_slot && e == hipSuccess; ++a) {
+      if (!maxima) e = open(q);
+      for (int k = 0; k < 3 && e == hipSuccess; ++k)
+        e = afi::stage2d_dev(g.mixed, w.binst, nullptr, nwg, maxima, k, q);
+      if (e != hipSuccess) break;
+      e = maxima ? afi::batch_advance(w.binst, 1, maxima, q)
+                 : afi::batch_decide(w.binst, 1, w.bnact, q);
     }
-    return hipSuccess;
+    return e;
   };
   const af_status st = run_slots(slot, attempts_per_slot, w.binst, 1, 1, s, max_steps, t_final, h, "af_run_graph",
                                  &c->run_exec, 4);
@@ -1295,6 +1376,7 @@ af_status af_batch_set_variant(af_batch* b, int i) {
     return fail(AF_E_ARG, "af_batch_set_variant: variant %s has another precision",
                 afi::kStageVariants[i].name);
   b->var = &afi::kStageVariants[i];
+  b->strips = false;
   return AF_OK;
 }
 
@@ -1303,57 +1385,59 @@ af_status af_batch_tune(af_batch* b, double* const* U, void* ws, void* stream, d
   if (!b || !U || !ws) return fail(AF_E_ARG, "af_batch_tune: NULL argument");
   if (reps < 1) return fail(AF_E_ARG, "af_batch_tune: reps must be >= 1");
   if (!(t_final > t0)) return fail(AF_E_ARG, "af_batch_tune: t_final must exceed t0");
-  const int n = (int)b->ctx.size();
   const hipStream_t s = (hipStream_t)stream;
   char* base = (char*)ws;
-  afi::BatchInst* dinst = (afi::BatchInst*)base;
-  double* partial = (double*)(base + b->off_partial);
-  int* nact = (int*)(base + b->off_nact);
   hipEvent_t e0 = nullptr, e1 = nullptr;
   AF_HIP(hipEventCreate(&e0));
   if (hipEventCreate(&e1) != hipSuccess) {
     (void)hipEventDestroy(e0);
     return fail(AF_E_HIP, "af_batch_tune: event creation failed");
   }
-  af_status st = AF_OK;
-  const afi::StageVariant* best = b->var;
-  double best_us = -1.0;
   std::vector<afi::BatchInst> h;
-  for (int i = 0; i < afi::kNumStageVariants && st == AF_OK; ++i) {
-    const afi::StageVariant* v = &afi::kStageVariants[i];
-    if (us_per_slot) us_per_slot[i] = -1.0;
-    if (v->mixed != b->mixed) continue;
+  std::vector<char> buf;
+  // microseconds of one slot on variant v (NULL: strips): one untimed slot,
+  // then the fastest of reps; every slot starts from the same descriptors
+  // (current buffer U, so U is never written)
+  auto time_slot = [&](const afi::StageVariant* v, double* us) -> af_status {
     int total = 0;
-    st = batch_descriptors(b, v, U, base, t0, t_final, 1, h, &total);
-    if (st != AF_OK) break;
-    // one untimed slot, then the fastest of reps; every slot starts from the
-    // same descriptors (current buffer U, so U is never written)
-    double best_v = -1.0;
+    af_status sd = batch_descriptors(b, v ? v : b->var, U, base, t0, t_final, 1, h, &total);
+    if (sd != AF_OK) return sd;
+    const BatchPath path = batch_path(b, v, base, total);
     for (int r = 0; r <= reps; ++r) {
-      hipError_t e = hipMemcpyAsync(dinst, h.data(), sizeof(afi::BatchInst) * n,
-                                    hipMemcpyHostToDevice, s);
-      if (e == hipSuccess) e = hipEventRecord(e0, s);
-      if (e == hipSuccess) e = batch_slot(v, dinst, n, total, partial, nact, 1, s);
+      if ((sd = upload_batch(b, h, buf, base, s)) != AF_OK) return sd;
+      hipError_t e = hipEventRecord(e0, s);
+      if (e == hipSuccess) e = batch_start(path, s);
+      if (e == hipSuccess) e = batch_slot(path, 1, s);
       if (e == hipSuccess) e = hipEventRecord(e1, s);
       if (e == hipSuccess) e = hipEventSynchronize(e1);
       float ms = 0.f;
       if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
-      if (e != hipSuccess) {
-        st = hip_fail(e, "af_batch_tune");
-        break;
-      }
-      if (r > 0 && (best_v < 0.0 || ms * 1e3 < best_v)) best_v = ms * 1e3;
+      if (e != hipSuccess) return hip_fail(e, "af_batch_tune");
+      if (r > 0 && (*us < 0.0 || ms * 1e3 < *us)) *us = ms * 1e3;
     }
-    if (st != AF_OK) break;
-    if (us_per_slot) us_per_slot[i] = best_v;
-    if (best_us < 0.0 || best_v < best_us) {
-      best_us = best_v;
+    return AF_OK;
+  };
+  const afi::StageVariant* best = b->var;
+  double best_us = -1.0, strips_us = -1.0;
+  af_status st = time_slot(nullptr, &strips_us);
+  for (int i = 0; i < afi::kNumStageVariants && st == AF_OK; ++i) {
+    const afi::StageVariant* v = &afi::kStageVariants[i];
+    if (us_per_slot) us_per_slot[i] = -1.0;
+    if (v->mixed != b->mixed) continue;
+    double us = -1.0;
+    st = time_slot(v, &us);
+    if (us_per_slot) us_per_slot[i] = us;
+    if (best_us < 0.0 || us < best_us) {
+      best_us = us;
       best = v;
     }
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
-  if (st == AF_OK) b->var = best;
+  if (st == AF_OK) {
+    b->var = best;
+    b->strips = strips_us < best_us;
+  }
   return st;
 }
 

@@ -231,8 +231,7 @@ __global__ void __launch_bounds__(kBlock) k_batch_open(afi::BatchInst* inst, int
     afi::BatchInst& I = inst[0];
     if (may_open(I)) {
       double a = 0.0, v = 0.0;
-      const int nr = I.cfl_nb > 0 ? I.cfl_nb : nb;  // maxima from the last stage, or all
-      for (int k = threadIdx.x; k < nr; k += blockDim.x) {
+      for (int k = threadIdx.x; k < nb; k += blockDim.x) {
         a = mx(a, partial[k]);
         v = mx(v, partial[nb + k]);
       }
@@ -256,34 +255,56 @@ __global__ void __launch_bounds__(kBlock) k_batch_open(afi::BatchInst* inst, int
   count_active(inst, n, n_active);
 }
 
-// after an attempt: accept it (the output becomes the current state) or
-// redo it with dt/2, up to max_halvings times (then the instance stops with
-// its status set and its state left at the start of the step)
+// after an attempt of an active instance: accept it (the output becomes the
+// current state) or redo it with dt/2, up to max_halvings times (then the
+// instance stops with its status set and its state left at the start of the
+// step)
+__device__ __forceinline__ void decide_one(afi::BatchInst& I) {
+  I.attempts += 1;
+  const unsigned f = I.flags;
+  if (f == 0u) {
+    I.t += I.dt;
+    I.steps += 1;
+    I.cur = (I.cur + 1) % 3;
+    I.active = 0;
+  } else if (I.halvings < I.max_halvings) {
+    I.dt *= 0.5;
+    I.halvings += 1;
+    I.flags = 0u;
+  } else {
+    I.status = (f & FLAG_NONFINITE) ? 4 : 3;  // AF_E_NONFINITE : AF_E_PP
+    I.active = 0;
+  }
+}
+
 __global__ void __launch_bounds__(kBlock) k_batch_decide(afi::BatchInst* inst, int n,
                                                          int* n_active) {
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    afi::BatchInst& I = inst[i];
-    if (!I.active) continue;
-    I.attempts += 1;
-    const unsigned f = I.flags;
-    if (f == 0u) {
-      I.t += I.dt;
-      I.steps += 1;
-      I.cur = (I.cur + 1) % 3;
-      I.active = 0;
-      // the accepted last stage left the new state's CFL maxima
-      if (I.stage_nwg > 0) I.cfl_nb = I.stage_nwg;
-    } else if (I.halvings < I.max_halvings) {
-      I.dt *= 0.5;
-      I.halvings += 1;
-      I.flags = 0u;
-    } else {
-      I.status = (f & FLAG_NONFINITE) ? 4 : 3;  // AF_E_NONFINITE : AF_E_PP
-      I.active = 0;
-    }
-  }
+  for (int i = threadIdx.x; i < n; i += blockDim.x)
+    if (inst[i].active) decide_one(inst[i]);
   __syncthreads();
   count_active(inst, n, n_active);
+}
+
+// the decision after an attempt and the opening of the next step in one
+// launch, one wave per instance: its last stage left the CFL maxima of the new
+// state, one pair per workgroup.  (A decision and an opening as kernels of
+// their own took 9.4 us of the 93 us of a round at 400 x 200.)
+__global__ void __launch_bounds__(64) k_batch_advance(afi::BatchInst* inst,
+                                                      const double2* __restrict__ partial) {
+  afi::BatchInst& I = inst[blockIdx.x];
+  // loaded beside the descriptor, for the step that opens if this one is accepted
+  double a = 0.0, v = 0.0;
+  for (int k = threadIdx.x; k < I.nwg; k += 64) {
+    const double2 q = partial[I.wg0 + k];
+    a = mx(a, q.x);
+    v = mx(v, q.y);
+  }
+  a = wave_max(a);
+  v = wave_max(v);
+  if (threadIdx.x == 0 && I.active) {
+    decide_one(I);
+    if (may_open(I)) open_one(I, a, v);
+  }
 }
 
 }  // namespace
@@ -422,6 +443,11 @@ hipError_t batch_open(BatchInst* inst, int n, const double* partial, int nb, int
 
 hipError_t batch_decide(BatchInst* inst, int n, int* n_active, hipStream_t s) {
   hipLaunchKernelGGL(k_batch_decide, dim3(1), dim3(kBlock), 0, s, inst, n, n_active);
+  return hipGetLastError();
+}
+
+hipError_t batch_advance(BatchInst* inst, int n, const double2* partial, hipStream_t s) {
+  hipLaunchKernelGGL(k_batch_advance, dim3((unsigned)n), dim3(64), 0, s, inst, partial);
   return hipGetLastError();
 }
 

@@ -66,18 +66,15 @@ struct BatchInst {
   double t_final;
   long max_steps;
   int max_halvings;
-  // a single instance whose last stage leaves the CFL maxima of the new
-  // state (af_run_graph): the number of its stage workgroups, else 0
-  int stage_nwg;
+  // strips (af_strip2d.hip): first workgroup and workgroups of the instance in
+  // a launch, strips along x, rows of a strip
+  int wg0, nwg, snx, sH;
   // updated on the device
   double dt, t;
   long steps;
   int cur, active, halvings, status;
   unsigned flags;
   long attempts;  // RK3 attempts so far (accepted and rejected)
-  // partial CFL maxima the next step opens from: 0 for the CFL kernel's own
-  // count, else the number written by the last accepted stage
-  int cfl_nb;
 };
 
 
@@ -216,14 +213,22 @@ hipError_t batch_cfl(BatchInst* inst, int n, double* partial, int nb, hipStream_
 hipError_t batch_open(BatchInst* inst, int n, const double* partial, int nb, int* n_active,
                       hipStream_t s);
 hipError_t batch_decide(BatchInst* inst, int n, int* n_active, hipStream_t s);
-// stage k of the current attempt of one instance whose step machinery is on
-// the device (descriptor dinst).  Its last stage writes the CFL maxima of the
-// new state per workgroup into cfl_partial (stride kSingleCflBlocks);
-// stage2d_dev_nwg: the number of its workgroups, or 0 where they are more and
-// leave no maxima (grids over 61440 cells wide)
-hipError_t stage2d_dev(const Geo& g, const afd::Phys& ph, BatchInst* dinst, double* cfl_partial,
-                       int k, hipStream_t s);
-int stage2d_dev_nwg(const Geo& g);
+// Strips of a grid (af_strip2d.hip): nx along x, ny ranges of H rows; for one
+// instance, and for the instances of a batch, which are launched together
+// (false: the tiles of the default variant are expected to be faster)
+struct StripShape {
+  int nx, ny, H;
+};
+StripShape strip_shape(const Geo& g);
+bool strip_shapes(const Geo* g, int n, StripShape* out);
+// stage k of the current attempt of every active instance of a batch: nwg
+// workgroups, instance wg_inst[wg] each (NULL: the first).  Stage 2 leaves the
+// CFL maxima of the new states per workgroup in cfl_partial, if not NULL.
+hipError_t stage2d_dev(int mixed, BatchInst* inst, const int* wg_inst, int nwg,
+                       double2* cfl_partial, int k, hipStream_t s);
+// after an attempt on strips: the decision of batch_decide, and the opening of
+// the next step from the maxima stage 2 left
+hipError_t batch_advance(BatchInst* inst, int n, const double2* partial, hipStream_t s);
 // Compiled variants of the 2D stage of a batch (af_stage2d.hip, one object
 // each): the stage, and the tile count of a grid.
 struct StageVariant {

@@ -1,8 +1,7 @@
 // af_scheme2d.hpp -- the pieces of the 2D stage that its kernels share: site
-// and cell data, the limited face flux, the wall projection, and the launch
-// arguments.  Kernels that evaluate the same expression of the same values
-// round alike (multiply-adds are fused within one expression only), so all of
-// them give the same bits.
+// and cell data, the limited face flux and the wall projection.  Kernels that
+// evaluate the same expression of the same values round alike (multiply-adds
+// are fused within one expression only), so all of them give the same bits.
 #pragma once
 
 #include <type_traits>
@@ -276,38 +275,5 @@ __device__ __forceinline__ void limit_face(const G2& g, const PhysT<R>& ph, cons
     F[k] = R(fl + th * (fh - fl));
   }
 }
-
-// launch arguments of a stage: one instance, or a batch of 2D instances
-constexpr int kMaxBatch = 512;
-struct StageArgs {
-  // one instance
-  G2 g;
-  Phys ph;
-  const double* Uk;
-  const double* Un;
-  double* Uout;
-  const double* dt_dev;
-  double dt_host, dt_mul;  // the step is dt_mul * dt
-  unsigned* flags;
-  int ntx;
-  // learned blend (one instance): a blend coefficient per face replacing
-  // theta^s, or NULL; and where to write theta^s per face, or NULL
-  const float* blend;
-  float* ts_out;
-  // a batch: its instances (stage k reads and writes their rotating buffers)
-  afi::BatchInst* inst;
-  int ninst, k;
-  const int* n_active;
-  // one instance whose step machinery lives on the device (a single
-  // descriptor; stage k of its current attempt, nothing once it is
-  // inactive), or NULL: then Uk, Un, Uout, dt and flags above are used.
-  // Its last stage leaves the CFL maxima of the new state in cfl_partial
-  // (a at [wg], v at [kSingleCflBlocks + wg]), for the next step's dt
-  afi::BatchInst* dinst;
-  double* cfl_partial;
-  // both
-  double ca, cb;
-  int first, skip_flagged, ntiles;
-};
 
 }  // namespace afd

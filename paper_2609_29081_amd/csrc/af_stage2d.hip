@@ -1,5 +1,7 @@
-// af_stage2d.hip -- one SSP-RK3 stage of the 2D compact AF method on gfx950
-// as a single fused, LDS-tiled kernel.
+// af_stage2d.hip -- one SSP-RK3 stage of a batch of 2D instances on gfx950 as
+// a single fused, LDS-tiled kernel: the tile variants of af_batch_set_variant
+// and af_batch_tune, and the stage of batches of grids too narrow for the
+// strips of af_strip2d.hip, which give the same bits.
 //
 // A workgroup owns a tile of TX x TY cells, i.e. the half-lattice block
 // [X0, X0+2TX) x [Y0, Y0+2TY): the cell averages, x-edge, y-edge and corner
@@ -431,11 +433,21 @@ struct TileIter {
   }
 };
 
+// launch arguments: a batch of 2D instances (stage k reads and writes their
+// rotating buffers)
+constexpr int kMaxBatch = 512;
+struct StageArgs {
+  afi::BatchInst* inst;
+  int ninst, k;
+  const int* n_active;
+  double ca, cb;
+  int first, skip_flagged, ntiles;
+};
+
 // what one tile of a stage works on.  Geometry and physics are referenced,
 // not copied: a copy would hold some thirty uniform values live across the
 // whole tile (register pressure of a kernel that is at its VGPR limit), while
-// a reference to the kernel arguments or to the batch descriptor in global
-// memory is re-read where needed.
+// a reference to the batch descriptor in global memory is re-read where needed.
 struct TileArgs {
   const G2* g;
   const Phys* phd;

@@ -44,8 +44,8 @@
 //   64 x 32      FP64 28, 17, 14 us      FP32 stencils 42, 17, 14 us
 //
 // The arithmetic is the tile kernel's, expression by expression, so the two
-// give the same bits.  Single instances run here; batches, whose instances
-// may be smaller than a strip is long, run on the tile kernel.
+// give the same bits.  The tile kernel remains for batches: see strip_shapes,
+// and the variants that af_batch_set_variant and af_batch_tune choose among.
 #include <algorithm>
 
 #include "af_scheme2d.hpp"
@@ -1218,15 +1218,34 @@ __device__ __forceinline__ void wave_ye(Rings<R>& S, const Ctx<R>& X, bool& nonf
   }
 }
 
-// how a launch cuts its grid: nx columns of strips, ny ranges of H rows
+// how a grid is cut: nx columns of strips, ny ranges of H rows
 struct Strips {
   int nx, ny, H;
 };
 
-// the kernel's arguments where the launch put them
-struct AllArgs {
-  StageArgs sa;
-  Strips st;
+// launch arguments
+struct StripArgs {
+  // one instance, its step driven by the host
+  G2 g;
+  Phys ph;
+  const double* Uk;
+  const double* Un;
+  double* Uout;
+  const double* dt_dev;
+  double dt_host, dt_mul;  // the step is dt_mul * dt
+  unsigned* flags;
+  int nx, H, skip_flagged;
+  const float* blend;  // see limit_face
+  float* ts_out;
+  // instances whose step machinery is on the device: their descriptors, the
+  // instance of each workgroup (NULL: the first one), and where stage 2 leaves
+  // the CFL maxima of the new state per workgroup (a, v), or NULL
+  afi::BatchInst* inst;
+  const int* wg_inst;
+  double2* cfl_partial;
+  int k;  // the stage
+  double ca, cb;
+  int first;
 };
 
 // p, known to point to global memory (loads through a pointer that came from
@@ -1235,62 +1254,91 @@ template <typename T>
 __device__ __forceinline__ T* in_global(T* p) {
   return (T*)(__attribute__((address_space(1))) T*)(uintptr_t)p;
 }
+// p, known to point to memory that the kernel does not write, for scalar loads
+template <typename T>
+__device__ __forceinline__ const T* in_constant(const T* p) {
+  return (const T*)(const __attribute__((address_space(4))) T*)(uintptr_t)p;
+}
 
-// BLEND: per-face blend input/output arrays; DEV: buffers, dt and flag word
-// from the descriptor sa.dinst of a device-resident step loop.
+// BLEND: per-face blend input/output arrays; DEV: instances with descriptors
 template <typename R, bool BLEND, bool DEV>
-__global__ void __launch_bounds__(NT) k_strip(StageArgs sa, Strips st) {
+__global__ void __launch_bounds__(NT) k_strip(StripArgs) {
   __shared__ Rings<R> S;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const double* Uk = sa.Uk;
-  const double* Un = sa.Un;
-  double* Uout = sa.Uout;
-  double dt;
-  unsigned* flags = sa.flags;
-  if constexpr (DEV) {
-    const afi::BatchInst& I = *sa.dinst;
-    if (!I.active) return;  // its step is done; the round has nothing to do
-    // the three RK3 stages from buf[cur], through the other two buffers
-    const int c = I.cur, a = (c + 1) % 3, b = (c + 2) % 3;
-    Un = I.buf[c];
-    Uk = sa.k == 0 ? I.buf[c] : (sa.k == 1 ? I.buf[a] : I.buf[b]);
-    Uout = sa.k == 1 ? I.buf[b] : I.buf[a];
-    dt = I.dt;
-    flags = &sa.dinst->flags;
-  } else {
-    dt = sa.dt_mul * (sa.dt_dev ? *sa.dt_dev : sa.dt_host);
-  }
-  bool nonfinite = false;
-  double cfl_a = 0.0, cfl_v = 0.0;
   // Each wave reads what it needs of the arguments for itself, through a pointer
   // the compiler does not see through: read once for all twelve, they are kept
   // in scalar registers across every wave's loop, and most of them spill
-  auto ctx = [&]() {
+  auto args = [&]() {
     auto* q = __builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(q));
-    const AllArgs* p = (const AllArgs*)q;
-    const int H = p->st.H, n2y = p->sa.g.n2y, j0 = blockIdx.y * H, j1 = min(j0 + H, n2y);
-    const Phys phd = p->sa.ph;
-    // a row of the strip is finished when the march is three rows past it
-    return Ctx<R>{p->sa.g,
-                  phd,
-                  phys_as<R>(phd),
-                  in_global(Uk),
-                  in_global(Un),
-                  in_global(Uout),
-                  dt,
-                  p->sa.ca,
-                  p->sa.cb,
-                  p->sa.first,
-                  in_global(flags),
-                  BLEND ? in_global(p->sa.blend) : nullptr,
-                  BLEND ? in_global(p->sa.ts_out) : nullptr,
-                  (int)(threadIdx.x & 63),
-                  (int)blockIdx.x * SX,
-                  j0,
-                  j1,
-                  j1 - j0 + 5};
+    return (const StripArgs*)q;
   };
+  // the workgroup's instance
+  afi::BatchInst* inst = nullptr;
+  if constexpr (DEV) {
+    const StripArgs* p = args();
+    inst = p->inst + (p->wg_inst ? in_constant(p->wg_inst)[blockIdx.x] : 0);
+    if (!in_constant(inst)->active) return;  // its step is done: nothing to do in this round
+  }
+  auto ctx = [&]() {
+    const StripArgs* p = args();
+    if constexpr (DEV) {
+      auto q = (uintptr_t)inst;
+      asm volatile("" : "+s"(q));
+      const afi::BatchInst* I = in_constant((const afi::BatchInst*)q);
+      // the three RK3 stages from buf[cur], through the other two buffers
+      const int c = I->cur, a = (c + 1) % 3, b = (c + 2) % 3, k = p->k;
+      const int wg = blockIdx.x - I->wg0;
+      const int j0 = wg / I->snx * I->sH, n2y = I->g.n2y, j1 = min(j0 + I->sH, n2y);
+      const Phys phd = I->ph;
+      const double* Uk = k == 0 ? I->buf[c] : (k == 1 ? I->buf[a] : I->buf[b]);
+      const double* Un = I->buf[c];
+      return Ctx<R>{I->g,
+                    phd,
+                    phys_as<R>(phd),
+                    in_global(Uk),
+                    in_global(Un),
+                    in_global(k == 1 ? I->buf[b] : I->buf[a]),
+                    I->dt,
+                    p->ca,
+                    p->cb,
+                    p->first,
+                    in_global(&inst->flags),
+                    nullptr,
+                    nullptr,
+                    (int)(threadIdx.x & 63),
+                    wg % I->snx * SX,
+                    j0,
+                    j1,
+                    j1 - j0 + 5};  // a row is finished when the march is three rows past it
+    } else {
+      const int wg = blockIdx.x, nx = p->nx, H = p->H;
+      const int j0 = wg / nx * H, n2y = p->g.n2y, j1 = min(j0 + H, n2y);
+      const Phys phd = p->ph;
+      const double* dt_dev = p->dt_dev;
+      const double dt = p->dt_mul * (dt_dev ? *in_constant(dt_dev) : p->dt_host);
+      return Ctx<R>{p->g,
+                    phd,
+                    phys_as<R>(phd),
+                    in_global(p->Uk),
+                    in_global(p->Un),
+                    in_global(p->Uout),
+                    dt,
+                    p->ca,
+                    p->cb,
+                    p->first,
+                    in_global(p->flags),
+                    BLEND ? in_global(p->blend) : nullptr,
+                    BLEND ? in_global(p->ts_out) : nullptr,
+                    (int)(threadIdx.x & 63),
+                    wg % nx * SX,
+                    j0,
+                    j1,
+                    j1 - j0 + 5};
+    }
+  };
+  bool nonfinite = false;
+  double cfl_a = 0.0, cfl_v = 0.0;
   // waves go to the SIMDs round-robin: w, w + 4 and w + 8 share one, and the
   // parts are grouped so that the four carry equal work in either half
   switch (wave) {
@@ -1298,8 +1346,7 @@ __global__ void __launch_bounds__(NT) k_strip(StageArgs sa, Strips st) {
     case 4: wave_xlow1(S, ctx()); break;
     case 8: wave_xe(S, ctx(), nonfinite); break;
     case 1:
-      wave_yface<R, DEV>(S, ctx(), nonfinite, sa.dinst, sa.k == 2, cfl_a,
-                         cfl_v);
+      wave_yface<R, DEV>(S, ctx(), nonfinite, inst, DEV && args()->k == 2, cfl_a, cfl_v);
       break;
     case 5: wave_xlow0(S, ctx()); break;
     case 9: wave_xres0(S, ctx()); break;
@@ -1308,23 +1355,20 @@ __global__ void __launch_bounds__(NT) k_strip(StageArgs sa, Strips st) {
     case 10: wave_edges(S, ctx()); break;
     case 3: wave_centre(S, ctx()); break;
     case 7: wave_yres0(S, ctx()); break;
-    default: wave_cells(S, ctx(), sa.skip_flagged); break;
+    default: wave_cells(S, ctx(), DEV || args()->skip_flagged); break;
   }
-  if (nonfinite) raise_flag(flags, FLAG_NONFINITE);
+  if (nonfinite) raise_flag(DEV ? &inst->flags : args()->flags, FLAG_NONFINITE);
   if constexpr (DEV) {
     // the workgroup's CFL maxima of the new state (lanes that wrote no cell
     // hold 0, neutral for max)
-    if (sa.k == 2 && wave == 1 && sa.cfl_partial) {
+    double2* part = args()->cfl_partial;
+    if (wave == 1 && part && args()->k == 2) {
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) {
         cfl_a = mx(cfl_a, __shfl_xor(cfl_a, o, 64));
         cfl_v = mx(cfl_v, __shfl_xor(cfl_v, o, 64));
       }
-      if ((threadIdx.x & 63) == 0) {
-        const int wg = blockIdx.y * gridDim.x + blockIdx.x;
-        sa.cfl_partial[wg] = cfl_a;
-        sa.cfl_partial[afi::kSingleCflBlocks + wg] = cfl_v;
-      }
+      if ((threadIdx.x & 63) == 0) part[blockIdx.x] = make_double2(cfl_a, cfl_v);
     }
   }
 }
@@ -1343,33 +1387,29 @@ int device_cus() {
   return cache[dev];
 }
 
+Strips strips_with(const afi::Geo& g, int H) {
+  return Strips{(g.n1x + SX - 1) / SX, (g.n2y + H - 1) / H, H};
+}
+
 // the strips of a grid.  One workgroup fills a CU (its LDS), so a launch runs
 // in ceil(nx ny / CUs) rounds of H + 5 row steps each (a row is finished three
 // rows behind the march, which starts two rows early): the H with the fewest
 // steps in all.
 Strips strips_of(const afi::Geo& g) {
   const int cus = device_cus();
-  Strips b{(g.n1x + SX - 1) / SX, 0, 0};
+  Strips b{};
   long best = 0;
   for (int ny = 1; ny <= g.n2y; ++ny) {
-    if (ny > 1 && (long)b.nx * ny > std::min(8L * cus, (long)afi::kSingleCflBlocks)) break;
-    const int H = (g.n2y + ny - 1) / ny;
-    const int used = (g.n2y + H - 1) / H;
-    const long steps = ((long)b.nx * used + cus - 1) / cus * (H + 5);
-    if (b.H == 0 || steps < best) {
-      b.ny = used;
-      b.H = H;
+    const Strips t = strips_with(g, (g.n2y + ny - 1) / ny);
+    const long wgs = (long)t.nx * t.ny;
+    if (ny > 1 && wgs > std::min(8L * cus, (long)afi::kSingleCflBlocks)) break;
+    const long steps = (wgs + cus - 1) / cus * (t.H + 5);
+    if (ny == 1 || steps < best) {
+      b = t;
       best = steps;
     }
   }
   return b;
-}
-
-StageArgs stage_args(const afi::Geo& geo, const Phys& ph) {
-  StageArgs sa{};
-  sa.g = afi::stage_geo(geo);
-  sa.ph = ph;
-  return sa;
 }
 
 template <typename R>
@@ -1377,7 +1417,11 @@ hipError_t launch(const afi::Geo& geo, const Phys& ph, const afi::Work& w, const
                   const double* Uk, double* Uout, const double* dt_dev, double dt_host,
                   afi::StageCoef sc, hipStream_t s, afi::Timer* tm) {
   const Strips b = strips_of(geo);
-  StageArgs sa = stage_args(geo, ph);
+  StripArgs sa{};
+  sa.g = afi::stage_geo(geo);
+  sa.ph = ph;
+  sa.nx = b.nx;
+  sa.H = b.H;
   sa.Uk = Uk;
   sa.Un = Un;
   sa.Uout = Uout;
@@ -1391,30 +1435,11 @@ hipError_t launch(const afi::Geo& geo, const Phys& ph, const afi::Work& w, const
   sa.skip_flagged = sc.skip_flagged;
   sa.blend = sc.blend;
   sa.ts_out = sc.ts_out;
-  const dim3 grid((unsigned)b.nx, (unsigned)b.ny);
+  const dim3 grid((unsigned)(b.nx * b.ny));
   if (sa.blend || sa.ts_out)
-    AFI_TIMED(tm, 7, s,
-              hipLaunchKernelGGL((k_strip<R, true, false>), grid, dim3(NT), 0, s, sa, b));
+    AFI_TIMED(tm, 7, s, hipLaunchKernelGGL((k_strip<R, true, false>), grid, dim3(NT), 0, s, sa));
   else
-    AFI_TIMED(tm, 7, s,
-              hipLaunchKernelGGL((k_strip<R, false, false>), grid, dim3(NT), 0, s, sa, b));
-  return hipGetLastError();
-}
-
-template <typename R>
-hipError_t launch_dev(const afi::Geo& geo, const Phys& ph, afi::BatchInst* dinst,
-                      double* cfl_partial, int k, hipStream_t s) {
-  const Strips b = strips_of(geo);
-  StageArgs sa = stage_args(geo, ph);
-  sa.dinst = dinst;
-  sa.cfl_partial = b.nx <= afi::kSingleCflBlocks ? cfl_partial : nullptr;
-  sa.k = k;
-  sa.ca = k == 0 ? 0.0 : (k == 1 ? 0.75 : 1.0 / 3.0);
-  sa.cb = k == 0 ? 1.0 : (k == 1 ? 0.25 : 2.0 / 3.0);
-  sa.first = k == 0;
-  sa.skip_flagged = 1;
-  hipLaunchKernelGGL((k_strip<R, false, true>), dim3((unsigned)b.nx, (unsigned)b.ny), dim3(NT), 0,
-                     s, sa, b);
+    AFI_TIMED(tm, 7, s, hipLaunchKernelGGL((k_strip<R, false, false>), grid, dim3(NT), 0, s, sa));
   return hipGetLastError();
 }
 
@@ -1422,9 +1447,55 @@ hipError_t launch_dev(const afi::Geo& geo, const Phys& ph, afi::BatchInst* dinst
 
 namespace afi {
 
-int stage2d_dev_nwg(const Geo& g) {
+StripShape strip_shape(const Geo& g) {
   const Strips b = strips_of(g);
-  return b.nx <= kSingleCflBlocks ? b.nx * b.ny : 0;
+  return StripShape{b.nx, b.ny, b.H};
+}
+
+// One H for all instances of a batch: the strips of the instances run together,
+// in any order, so a launch takes about the steps of all of them over the CUs,
+// plus half a strip at its end, but no less than one strip.  (At 1024 rows the
+// five steps a strip costs beyond its rows are half a percent: no need to look
+// further.)
+//
+// Whether that beats the tiles is a question of how many of a strip's 60
+// columns the grids fill.  A tile (16 x 7 cells FP64, 16 x 14 mixed) takes as
+// long as 6.5 or 12 row steps, and the tile kernel's start some 3 or 1 more.
+// Measured, us per RK3 step on strips and on the tiles (FP64; mixed):
+//   8 grids up to 512 x 256     458, 601;   390, 479
+//   2 of 1000 x 500             821, 1636;  713, 1192
+//   512 of 64 x 32              1479, 2533; 1274, 2106
+//   512 of 16 x 8               462, 683;   424, 526
+//   256 of 8 x 8                242, 259;   225, 223
+//   32 of 8 x 200               274, 227;   224, 172
+bool strip_shapes(const Geo* g, int n, StripShape* out) {
+  const int cus = device_cus();
+  int tallest = 1;
+  for (int i = 0; i < n; ++i) tallest = std::max(tallest, g[i].n2y);
+  long best = 0;  // twice the steps
+  int best_H = 0;
+  for (int H = std::min(4, tallest); H <= std::min(1024, tallest); ++H) {
+    long work = 0;
+    for (int i = 0; i < n; ++i) {
+      const Strips t = strips_with(g[i], H);
+      const int last = g[i].n2y - (t.ny - 1) * H;  // rows of the last range
+      work += (long)t.nx * ((long)(t.ny - 1) * (H + 5) + last + 5);
+    }
+    const long steps =
+        std::max(2L * (H + 5), 2 * work / cus + (work > (long)cus * (H + 5) ? H + 5 : 0));
+    if (best_H == 0 || steps < best) {
+      best = steps;
+      best_H = H;
+    }
+  }
+  long tiles = 0;
+  for (int i = 0; i < n; ++i) {
+    const Strips t = strips_with(g[i], best_H);
+    out[i] = StripShape{t.nx, t.ny, t.H};
+    tiles += default_variant(g[i].mixed)->tiles(g[i]);
+  }
+  const long rounds = (tiles + cus - 1) / cus;
+  return best <= (g[0].mixed ? 24 * rounds + 2 : 13 * rounds + 6);
 }
 
 hipError_t stage2d(const Geo& geo, const Phys& ph, const Work& w, const double* Un,
@@ -1434,10 +1505,21 @@ hipError_t stage2d(const Geo& geo, const Phys& ph, const Work& w, const double* 
                    : launch<double>(geo, ph, w, Un, Uk, Uout, dt_dev, dt_host, sc, s, tm);
 }
 
-hipError_t stage2d_dev(const Geo& geo, const Phys& ph, BatchInst* dinst, double* cfl_partial, int k,
-                       hipStream_t s) {
-  return geo.mixed ? launch_dev<float>(geo, ph, dinst, cfl_partial, k, s)
-                   : launch_dev<double>(geo, ph, dinst, cfl_partial, k, s);
+hipError_t stage2d_dev(int mixed, BatchInst* inst, const int* wg_inst, int nwg,
+                       double2* cfl_partial, int k, hipStream_t s) {
+  StripArgs sa{};
+  sa.inst = inst;
+  sa.wg_inst = wg_inst;
+  sa.cfl_partial = cfl_partial;
+  sa.k = k;
+  sa.ca = k == 0 ? 0.0 : (k == 1 ? 0.75 : 1.0 / 3.0);
+  sa.cb = k == 0 ? 1.0 : (k == 1 ? 0.25 : 2.0 / 3.0);
+  sa.first = k == 0;
+  if (mixed)
+    hipLaunchKernelGGL((k_strip<float, false, true>), dim3((unsigned)nwg), dim3(NT), 0, s, sa);
+  else
+    hipLaunchKernelGGL((k_strip<double, false, true>), dim3((unsigned)nwg), dim3(NT), 0, s, sa);
+  return hipGetLastError();
 }
 
 }  // namespace afi
