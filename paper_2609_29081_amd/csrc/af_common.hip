@@ -48,12 +48,12 @@ __global__ void __launch_bounds__(kBlock) k_cfl(int dim, long ncell, double gm1,
     if (dim == 1) {
       const double m = U[ncell + c], E = U[2 * ncell + c];
       const double p = pressure1(r, m, E, gm1);
-      const double cs = sqrt(gam * p / r);
+      const double cs = root(gam * p / r);
       a = mx(a, (fabs(m / r) + cs) * icx);
     } else {
       const double m1 = U[ncell + c], m2 = U[2 * ncell + c], E = U[3 * ncell + c];
       const double p = pressure2(r, m1, m2, E, gm1);
-      const double cs = sqrt(gam * p / r);
+      const double cs = root(gam * p / r);
       a = mx(a, (fabs(m1 / r) + cs) * icx);
       a = mx(a, (fabs(m2 / r) + cs) * icy);
     }
@@ -181,7 +181,7 @@ __global__ void __launch_bounds__(kBlock) k_batch_cfl(afi::BatchInst* inst, doub
     const double r = U[c];
     const double m1 = U[nc + c], m2 = U[2 * nc + c], E = U[3 * nc + c];
     const double p = pressure2(r, m1, m2, E, gm1);
-    const double cs = sqrt(gam * p / r);
+    const double cs = root(gam * p / r);
     a = mx(a, (fabs(m1 / r) + cs) * I.icx);
     a = mx(a, (fabs(m2 / r) + cs) * I.icy);
     v = mx(v, I.vcoef / r);

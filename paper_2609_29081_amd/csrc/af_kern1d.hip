@@ -131,7 +131,7 @@ __device__ __forceinline__ void lattice_site(const G1& g, const Phys& ph,
   S.A[0][t] = u;
   S.A[1][t] = p;
   S.A[2][t] = p / V[0];
-  S.A[3][t] = sqrt(ph.gam * p / V[0]);
+  S.A[3][t] = root(ph.gam * p / V[0]);
 }
 
 // low-order data of cell i (ghosts as boundary images) into ring entry t
@@ -152,10 +152,10 @@ __device__ __forceinline__ void cell_site(const G1& g, const Phys& ph,
   S.C[0][t] = C0[1];
   S.C[1][t] = C0[1] * u0 + p0 - tau;
   S.C[2][t] = (C0[2] + p0) * u0 - (u0 * tau + ph.kap * Tx);
-  S.C[3][t] = fabs(u0) + sqrt(ph.gam * p0 / C0[0]);
+  S.C[3][t] = fabs(u0) + root(ph.gam * p0 / C0[0]);
   S.C[4][t] = bvisc1(C0[0], p0, ux, Tx, ph);
   S.C[5][t] = fabs(pp - 2.0 * p0 + pm) / fabs(pp + 2.0 * p0 + pm);
-  S.C[6][t] = mx(-ux / sqrt(ux * ux + kDucros), 0.0);
+  S.C[6][t] = mx(-ux / root(ux * ux + kDucros), 0.0);
 #pragma unroll
   for (int k = 0; k < 3; ++k) S.C[7 + k][t] = C0[k];
 }
@@ -321,7 +321,7 @@ __device__ __forceinline__ void point_update(const G1& g, const Phys& ph, const 
       lu[o] = V[o][1] * ir;
       lp[o] = pressure1(V[o][0], V[o][1], V[o][2], ph.gm1);
       lT[o] = lp[o] * ir;
-      lc[o] = sqrt(ph.gam * lT[o]);
+      lc[o] = root(ph.gam * lT[o]);
     }
     const double ih = 1.0 / g.dx;
     double F1[3], F2[3], F3[3], r1, r2, r3, b1, b2, b3;
@@ -394,7 +394,7 @@ __global__ void __launch_bounds__(kThreads) k_stage1(G1 g, Phys ph, Stage1 st,
     for (int c = tid; c < g.n; c += kThreads) {
       const double r = Uk[c], m = Uk[g.n + c], E = Uk[2 * g.n + c];
       const double p = pressure1(r, m, E, ph.gm1);
-      const double cs = sqrt(ph.gam * p / r);
+      const double cs = root(ph.gam * p / r);
       ra = mx(ra, (fabs(m / r) + cs) * st.icx);
       rv = mx(rv, st.vcoef / r);
     }

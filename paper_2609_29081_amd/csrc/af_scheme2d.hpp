@@ -20,7 +20,7 @@ __device__ __forceinline__ void aux_of(const PhysT<R>& ph, const R* V, R ir, R* 
   w[1] = V[2] * ir;
   w[2] = p;
   w[3] = p * ir;
-  w[4] = sqrt(ph.gam * w[3]);
+  w[4] = root(ph.gam * w[3]);
 }
 
 // Simpson centre value from the cell average, the sum of the four edge
@@ -67,7 +67,7 @@ __device__ __forceinline__ void centre_value(const PhysT<R>& ph, const Phys& phd
           w[1] = R(Wd[2] * ird);
           w[2] = R(pd);
           w[3] = R(pd * ird);
-          w[4] = R(sqrt(phd.gam * (pd * ird)));
+          w[4] = R(root(phd.gam * (pd * ird)));
           return;
         }
       }
@@ -87,7 +87,7 @@ __device__ __forceinline__ void aux_of_fp64(const PhysT<double>& pd, const doubl
   w[1] = R(V[2] * ir);
   w[2] = R(p);
   w[3] = R(Tt);
-  w[4] = R(sqrt(pd.gam * Tt));
+  w[4] = R(root(pd.gam * Tt));
 }
 
 // pressure of state V, given 1/rho
@@ -126,7 +126,7 @@ __device__ __forceinline__ void cell_sensors(const G2& g, const CellAvg<R>& a0,
   const R jy = fabs(pyp - R(2.0) * p0 + pym) / fabs(pyp + R(2.0) * p0 + pym);
   phi[0] = mx(jx, jy);
   const R div = ux + vy, curl = vx - uy;
-  phi[1] = mx(-div / sqrt(div * div + curl * curl + R(kDucros)), R(0.0));
+  phi[1] = mx(-div / root(div * div + curl * curl + R(kDucros)), R(0.0));
 }
 template <typename R>
 __device__ __forceinline__ void cell_low(const G2& g, const PhysT<R>& ph, const CellAvg<R>& a0,

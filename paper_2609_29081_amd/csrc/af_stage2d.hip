@@ -725,7 +725,7 @@ __global__ void __launch_bounds__(NT) k_stage(StageArgs sa) {
       c->p = pressure_r(ph, c->U, c->r);
     }
     const R u0 = C0.U[1] * C0.r, v0 = C0.U[2] * C0.r;
-    const R c0 = sqrt(ph.gam * C0.p * C0.r);
+    const R c0 = root(ph.gam * C0.p * C0.r);
     // 0-11 see cell_low, 12 phi1, 13 phi2, 14-17 the average, 18-22 its
     // (u, v, p, T, c)
     cell_low(g, ph, C0, Cxm, Cxp, Cym, Cyp, c0, o);

@@ -71,8 +71,8 @@ struct Rings {
   R P[3][9][4][W];      // points: U (4), u, v, p, T, c; rows r .. r-3
   R Z[9][3][W];         // centres, rows r-1 .. r-3
   R GE0[6][2][W];       // gradients at co and ...
-  R GO0[6][2][W];       // ... ye: rows r-1, r-2
-  R GE1[6][3][W];       // at xe: rows r-1 .. r-3
+  R GO0[6][2][W];       // ... ye (but T_x): rows r-1, r-2
+  R GE1[6][3][W];       // at xe (but T_y): rows r-1 .. r-3
   R GO1[4][2][W];       // at centres (u_x, v_x, u_y, v_y): rows r-2, r-3
   R AV[10][4][W];       // averages: U (4), u, v, p, T, c, 1/rho; rows r .. r-3
   R C[14][3][W];        // cell low-order data, rows r-1 .. r-3
@@ -158,9 +158,10 @@ template <int D, typename R>
 __device__ __forceinline__ void line_resid(const PhysT<R>& ph, double h, const Site<R>* const* s,
                                            const R* ga, const R* gb, R* Rd) {
   const R i6h = R(1.0 / (6.0 * h));
-  R alpha = R(0.0);
+  R sp[5];
 #pragma unroll
-  for (int o = 0; o < 5; ++o) alpha = mx(alpha, fabs(s[o]->a[D]) + s[o]->a[4]);
+  for (int o = 0; o < 5; ++o) sp[o] = fabs(s[o]->a[D]) + s[o]->a[4];
+  const R alpha = mx5(sp[0], sp[1], sp[2], sp[3], sp[4]);
   R Rr[4];
   const R ai = alpha * i6h;
 #pragma unroll
@@ -354,6 +355,7 @@ __device__ __forceinline__ bool mid_row(const Rings<R>& S) {
 struct Columns {
   unsigned cE, cO;  // columns of the DOF arrays
   int fE, fO;       // flips
+  bool flips;       // any lane of the strip has one
 };
 template <typename R>
 __device__ __forceinline__ Columns columns_of(const Ctx<R>& X) {
@@ -363,8 +365,8 @@ __device__ __forceinline__ Columns columns_of(const Ctx<R>& X) {
   int iE = x <= Xlim + kMargin ? axis_image(x, Xlim, g.bc0, g.bc1, kE) : 0;
   const int iO = x + 1 <= Xlim + kMargin ? axis_image(x + 1, Xlim, g.bc0, g.bc1, kO) : 1;
   if (iE == Xlim && g.n1x == g.n1) iE = 0;
-  return Columns{(unsigned)(iE >> 1), (unsigned)(iO >> 1), image_flips(kE, -1),
-                 image_flips(kO, -1)};
+  const int fE = image_flips(kE, -1), fO = image_flips(kO, -1);
+  return Columns{(unsigned)(iE >> 1), (unsigned)(iO >> 1), fE, fO, __ballot(fE | fO) != 0};
 }
 // image row and flips of the even (odd) lattice line of row r; rows past the
 // last ghost are never used
@@ -393,6 +395,7 @@ __device__ __forceinline__ int odd_line(const Ctx<R>& X, int r, int& flip) {
 struct Raw {
   double v[4];
   int flip;
+  bool flips;  // any lane's flip is not 0
 };
 template <int T, typename R>
 __device__ __forceinline__ void issue(const Ctx<R>& X, const Columns& col, int r, Raw& q) {
@@ -400,6 +403,7 @@ __device__ __forceinline__ void issue(const Ctx<R>& X, const Columns& col, int r
   int fy;
   const int row = (T & 2) ? odd_line(X, r, fy) : even_line(X, r, fy);
   q.flip = fy ^ ((T & 1) ? col.fO : col.fE);
+  q.flips = fy != 0 || col.flips;
   const int ni = (T & 1) ? g.n1 : g.n1x, nj = (T & 2) ? g.n2 : g.n2y;
   const double* b =
       X.Uk + (T == CO ? g.off_co : (T == YE ? g.off_ye : (T == XE ? g.off_xe : 0L))) + (long)row * ni;
@@ -410,9 +414,10 @@ __device__ __forceinline__ void issue(const Ctx<R>& X, const Columns& col, int r
 // their values with the image's signs
 __device__ __forceinline__ void signed_values(const Raw& q, double* V) {
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const bool neg = (k == 1 && (q.flip & 1)) || (k == 2 && (q.flip & 2));
-    V[k] = neg ? -q.v[k] : q.v[k];
+  for (int k = 0; k < 4; ++k) V[k] = q.v[k];
+  if (q.flips) {  // rows and strips at a wall only
+    V[1] = (q.flip & 1) ? -V[1] : V[1];
+    V[2] = (q.flip & 2) ? -V[2] : V[2];
   }
 }
 // a point of type t into its ring
@@ -526,11 +531,15 @@ __device__ __forceinline__ void wave_centre(Rings<R>& S, const Ctx<R>& X) {
       }
       const int sz = slot3(k - 1);
 #pragma unroll
-      for (int n = 0; n < 4; ++n)
-        S.Z[n][sz][c] = flipped(zv[n], (n == 1 && (f & 1)) || (n == 2 && (f & 2)));
+      for (int n = 0; n < 4; ++n) S.Z[n][sz][c] = zv[n];
 #pragma unroll
-      for (int n = 0; n < 5; ++n)
-        S.Z[4 + n][sz][c] = flipped(zw[n], (n == 0 && (f & 1)) || (n == 1 && (f & 2)));
+      for (int n = 0; n < 5; ++n) S.Z[4 + n][sz][c] = zw[n];
+      if (f) {
+        S.Z[1][sz][c] = flipped(zv[1], f & 1);
+        S.Z[4][sz][c] = flipped(zw[0], f & 1);
+        S.Z[2][sz][c] = flipped(zv[2], f & 2);
+        S.Z[5][sz][c] = flipped(zw[1], f & 2);
+      }
       if (has_ghost_col) {
         __builtin_amdgcn_wave_barrier();
         if (ghost_col) {
@@ -558,10 +567,11 @@ __device__ __forceinline__ void wave_centre(Rings<R>& S, const Ctx<R>& X) {
         const R (&zz)[3][W] = S.Z[src[q]];
         S.GE0[q][ge][c] = dc5(co_[p1][cl], ye_[p1][cl], ye_[p1][c], co_[p1][cr], ihx);
         S.GE0[3 + q][ge][c] = dc5(co_[p2][c], xe_[p2][c], xe_[p1][c], co_[p0][c], ihy);
-        S.GO0[q][ge][c] = dc5(ye_[p1][cl], co_[p1][c], co_[p1][cr], ye_[p1][cr], ihx);
+        if (q < 2) S.GO0[q][ge][c] = dc5(ye_[p1][cl], co_[p1][c], co_[p1][cr], ye_[p1][cr], ihx);
         S.GO0[3 + q][ge][c] = dc5(ye_[p2][c], zz[z2][c], zz[z1][c], ye_[p0][c], ihy);
         S.GE1[q][g1][c] = dc5(xe_[p1][cl], zz[z1][cl], zz[z1][c], xe_[p1][cr], ihx);
-        S.GE1[3 + q][g1][c] = dc5(xe_[p2][c], co_[p1][c], co_[p0][c], xe_[p0][c], ihy);
+        if (q < 2)
+          S.GE1[3 + q][g1][c] = dc5(xe_[p2][c], co_[p1][c], co_[p0][c], xe_[p0][c], ihy);
         if (q < 2) {
           S.GO1[q][g2][c] = dc5(zz[z2][cl], xe_[p2][c], xe_[p2][cr], zz[z2][cr], ihx);
           S.GO1[2 + q][g2][c] = dc5(zz[z3s][c], ye_[p2][c], ye_[p1][c], zz[z1][c], ihy);
@@ -661,7 +671,7 @@ __device__ __forceinline__ void wave_cells(Rings<R>& S, const Ctx<R>& X, int ski
     S.AV[5][s][c] = C0[2] * r0;
     S.AV[6][s][c] = pr;
     S.AV[7][s][c] = pr * r0;
-    S.AV[8][s][c] = sqrt(X.ph.gam * pr * r0);
+    S.AV[8][s][c] = root(X.ph.gam * pr * r0);
     S.AV[9][s][c] = r0;
     if constexpr (!kFP64<R>) {
 #pragma unroll
@@ -859,7 +869,7 @@ __device__ __forceinline__ void wave_yface(Rings<R>& S, const Ctx<R>& X, bool& n
         // of the new average, as the CFL kernel takes them, for the next step
         if (rates && own_col) {
           const double p = pressure2(o4[0], o4[1], o4[2], o4[3], X.phd.gm1);
-          const double cs = sqrt(X.phd.gam * p / o4[0]);
+          const double cs = root(X.phd.gam * p / o4[0]);
           cfl_a = mx(cfl_a, (fabs(o4[1] / o4[0]) + cs) * dinst->icx);
           cfl_a = mx(cfl_a, (fabs(o4[2] / o4[0]) + cs) * dinst->icy);
           cfl_v = mx(cfl_v, dinst->vcoef / o4[0]);
