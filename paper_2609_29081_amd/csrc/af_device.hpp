@@ -176,6 +176,12 @@ __device__ __forceinline__ double pressure1(double r, double m, double E, double
   return gm1 * (E - m * m / (2.0 * r));
 }
 
+// whether the rule's parameter from a state of density rL and pressure pL toward
+// one of density rH and pressure pH is 1 at a glance
+__device__ __forceinline__ bool keeps(double rL, double pL, double rH, double pH) {
+  return rL > 0.0 && pL > 0.0 && rH >= kPPEps && pH >= kPPEps;
+}
+
 // ---------------------------------------------------------------------------
 // theta^p solved exactly (the pressure quadratic; switch LIM_PEXACT): the
 // largest t in [0, 1] keeping p >= eps on the whole segment from
@@ -234,13 +240,18 @@ __device__ __forceinline__ double theta_p1(const double* UL, double pL, const do
 
 // Density-then-pressure blend from UL toward UH (2D, 4 components).  Returns
 // theta^rho theta^p; sets bad if UL is not admissible (rho<=0 gives 0).
+// Where UL is admissible and UH has density and pressure of at least eps the
+// rule's parameter is 1, which is looked at first: almost every state is such.
+// (The rule is continuous at that threshold, so only round-off separates this
+// test from the one of the blended state.)
 __device__ __forceinline__ double theta_pair2(const double* UL, const double* UH, double gm1,
                                               bool& bad, bool exact) {
+  const double pL = pressure2(UL[0], UL[1], UL[2], UL[3], gm1);
+  if (keeps(UL[0], pL, UH[0], pressure2(UH[0], UH[1], UH[2], UH[3], gm1))) return 1.0;
   if (!(UL[0] > 0.0)) {
     bad = true;
     return 0.0;
   }
-  const double pL = pressure2(UL[0], UL[1], UL[2], UL[3], gm1);
   if (!(pL > 0.0)) bad = true;
   const double tr = theta_lin(UL[0], UH[0], mn(kPPEps, UL[0]));
   const double t0 = UL[0] + tr * (UH[0] - UL[0]);
@@ -254,11 +265,12 @@ __device__ __forceinline__ double theta_pair2(const double* UL, const double* UH
 
 __device__ __forceinline__ double theta_pair1(const double* UL, const double* UH, double gm1,
                                               bool& bad, bool exact) {
+  const double pL = pressure1(UL[0], UL[1], UL[2], gm1);
+  if (keeps(UL[0], pL, UH[0], pressure1(UH[0], UH[1], UH[2], gm1))) return 1.0;
   if (!(UL[0] > 0.0)) {
     bad = true;
     return 0.0;
   }
-  const double pL = pressure1(UL[0], UL[1], UL[2], gm1);
   if (!(pL > 0.0)) bad = true;
   const double tr = theta_lin(UL[0], UH[0], mn(kPPEps, UL[0]));
   const double t0 = UL[0] + tr * (UH[0] - UL[0]);

@@ -211,13 +211,16 @@ __device__ __forceinline__ void face_flux(const G1& g, const Phys& ph, const Til
           ULm[k] = Ub[k] - m2 * (Fb[k] - FL[k]);
           UHm[k] = Ub[k] - m2 * (Fb[k] - Fs);
         }
-        tpp = 0.0;
         bool bad = false;
-        if (!(ULp[0] > 0.0) || !(ULm[0] > 0.0)) {
+        const double pLp = pressure1(ULp[0], ULp[1], ULp[2], ph.gm1);
+        const double pLm = pressure1(ULm[0], ULm[1], ULm[2], ph.gm1);
+        if (keeps(ULp[0], pLp, UHp[0], pressure1(UHp[0], UHp[1], UHp[2], ph.gm1)) &&
+            keeps(ULm[0], pLm, UHm[0], pressure1(UHm[0], UHm[1], UHm[2], ph.gm1))) {
+          tpp = 1.0;  // as almost everywhere: see theta_pair2
+        } else if (!(ULp[0] > 0.0) || !(ULm[0] > 0.0)) {
+          tpp = 0.0;
           bad = true;
         } else {
-          const double pLp = pressure1(ULp[0], ULp[1], ULp[2], ph.gm1);
-          const double pLm = pressure1(ULm[0], ULm[1], ULm[2], ph.gm1);
           if (!(pLp > 0.0) || !(pLm > 0.0)) bad = true;
           const double tr = mn(theta_lin(ULp[0], UHp[0], mn(kPPEps, ULp[0])),
                                  theta_lin(ULm[0], UHm[0], mn(kPPEps, ULm[0])));
@@ -298,7 +301,7 @@ __device__ __forceinline__ void point_update(const G1& g, const Phys& ph, const 
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     U0[k] = Us[2][k];
-    UH[k] = U0[k] + dt * R[k];
+    out[k] = UH[k] = U0[k] + dt * R[k];
   }
   if (ph.lim & LIM_POINT) {
     // low-order LLF scheme on the lattice of point values (X-2, X, X+2) and
@@ -342,11 +345,10 @@ __device__ __forceinline__ void point_update(const G1& g, const Phys& ph, const 
     double th = theta_pair1(UL, UH, ph.gm1, lbad, ph.lim & LIM_PEXACT);
     if (ph.lim & LIM_LOWONLY) th = 0.0;
     if (lbad) raise_flag(flags, FLAG_POINT_LOW);
+    if (th != 1.0) {
 #pragma unroll
-    for (int k = 0; k < 3; ++k) out[k] = (th == 1.0) ? UH[k] : UL[k] + th * (UH[k] - UL[k]);
-  } else {
-#pragma unroll
-    for (int k = 0; k < 3; ++k) out[k] = UH[k];
+      for (int k = 0; k < 3; ++k) out[k] = UL[k] + th * (UH[k] - UL[k]);
+    }
   }
   const int wl = (g.bc0 == BC_NOSLIP || g.bc0 == BC_SYMMETRY);
   const int wr = (g.bc1 == BC_NOSLIP || g.bc1 == BC_SYMMETRY);

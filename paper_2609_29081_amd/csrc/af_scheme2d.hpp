@@ -240,13 +240,16 @@ __device__ __forceinline__ void limit_face(const G2& g, const PhysT<R>& ph, cons
         ULm[k] = c.Ub[k] - m4 * (fcb - fl);
         UHm[k] = c.Ub[k] - m4 * (fcb - Fs);
       }
-      tpp = 0.0;
       bool bad = false;
-      if (!(ULp[0] > 0.0) || !(ULm[0] > 0.0)) {
+      const double pLp = pressure2(ULp[0], ULp[1], ULp[2], ULp[3], phd.gm1);
+      const double pLm = pressure2(ULm[0], ULm[1], ULm[2], ULm[3], phd.gm1);
+      if (keeps(ULp[0], pLp, UHp[0], pressure2(UHp[0], UHp[1], UHp[2], UHp[3], phd.gm1)) &&
+          keeps(ULm[0], pLm, UHm[0], pressure2(UHm[0], UHm[1], UHm[2], UHm[3], phd.gm1))) {
+        tpp = 1.0;  // as almost everywhere: see theta_pair2
+      } else if (!(ULp[0] > 0.0) || !(ULm[0] > 0.0)) {
+        tpp = 0.0;
         bad = true;
       } else {
-        const double pLp = pressure2(ULp[0], ULp[1], ULp[2], ULp[3], phd.gm1);
-        const double pLm = pressure2(ULm[0], ULm[1], ULm[2], ULm[3], phd.gm1);
         if (!(pLp > 0.0) || !(pLm > 0.0)) bad = true;
         const double tr = mn(theta_lin(ULp[0], UHp[0], mn(kPPEps, ULp[0])),
                              theta_lin(ULm[0], UHm[0], mn(kPPEps, ULm[0])));

@@ -267,6 +267,29 @@ __device__ __forceinline__ int slot4(int k) { return k & 3; }
 __device__ __forceinline__ int slot2(int k) { return k & 1; }
 __device__ __forceinline__ int slot3(int k) { return (k + 3) % 3; }
 
+// p, known to point to global memory (loads through a pointer that came from
+// memory would be flat ones)
+template <typename T>
+__device__ __forceinline__ T* in_global(T* p) {
+  return (T*)(__attribute__((address_space(1))) T*)(uintptr_t)p;
+}
+// byte offset of element i >= 0 of a row of doubles, for at()
+__device__ __forceinline__ unsigned element(unsigned i) {
+  unsigned o = i * 8u;
+  asm("" : "+v"(o));
+  return o;
+}
+// element of the row at p, which is the same for the whole wave: its address is
+// p in scalar registers and a 32-bit offset.  (Left to itself the compiler adds
+// the two up per lane, an instruction more for every access; hence the asm here
+// and above, which hides from it what they are.)
+template <typename T>
+__device__ __forceinline__ T& at(T* p, unsigned o) {
+  asm("" : "+s"(p));
+  using Byte = __attribute__((address_space(1))) char;
+  return *(T*)((Byte*)(uintptr_t)p + o);
+}
+
 // the stage's update of a point from its residual Rs and low-order terms Ls
 // (Sec. 2.2, 3.4), the RK combination, and the store
 template <typename R>
@@ -276,7 +299,7 @@ __device__ __forceinline__ void point_finish(const Ctx<R>& X, int t, int i, int 
   const G2& g = X.g;
   double UH[4], out[4];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) UH[k] = U0[k] + X.dt * double(Rs[k]);
+  for (int k = 0; k < 4; ++k) out[k] = UH[k] = U0[k] + X.dt * double(Rs[k]);
   if (X.ph.lim & LIM_POINT) {
     double UL[4];
 #pragma unroll
@@ -285,11 +308,10 @@ __device__ __forceinline__ void point_finish(const Ctx<R>& X, int t, int i, int 
     double th = theta_pair2(UL, UH, X.phd.gm1, lbad, X.ph.lim & LIM_PEXACT);
     if (X.ph.lim & LIM_LOWONLY) th = 0.0;
     if (lbad && own) raise_flag(X.flags, FLAG_POINT_LOW);
+    if (th != 1.0) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) out[k] = (th == 1.0) ? UH[k] : UL[k] + th * (UH[k] - UL[k]);
-  } else {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) out[k] = UH[k];
+      for (int k = 0; k < 4; ++k) out[k] = UL[k] + th * (UH[k] - UL[k]);
+    }
   }
   if (t != YE) {
     if (i == 0) project(wall_of(g.bc0), 0, out);
@@ -303,11 +325,12 @@ __device__ __forceinline__ void point_finish(const Ctx<R>& X, int t, int i, int 
   const int ni = t == YE ? g.n1 : g.n1x, nj = t == XE ? g.n2 : g.n2y;
   const long np = (long)ni * nj;
   double* o = X.Uout + (t == XE ? g.off_xe : (t == YE ? g.off_ye : g.off_co)) + (long)j * ni;
+  const unsigned e = element(i);
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     const double v = X.first ? out[k] : X.ca * un[k] + X.cb * out[k];
     if (!isfinite(v)) nonfinite = true;
-    o[k * np + i] = v;
+    at(o + k * np, e) = v;
   }
 }
 
@@ -322,8 +345,9 @@ __device__ __forceinline__ void load_un(const Ctx<R>& X, int t, int i, int j, bo
   const long np = (long)ni * nj;
   const double* p =
       X.Un + (t < 0 ? 0L : (t == XE ? g.off_xe : (t == YE ? g.off_ye : g.off_co))) + (long)j * ni;
+  const unsigned e = element(i);
 #pragma unroll
-  for (int k = 0; k < 4; ++k) un[k] = p[k * np + i];
+  for (int k = 0; k < 4; ++k) un[k] = at(p + k * np, e);
 }
 
 // FP64 value of a point, from its LDS copy (and, with FP32 stencils, the low part)
@@ -408,8 +432,9 @@ __device__ __forceinline__ void issue(const Ctx<R>& X, const Columns& col, int r
   const double* b =
       X.Uk + (T == CO ? g.off_co : (T == YE ? g.off_ye : (T == XE ? g.off_xe : 0L))) + (long)row * ni;
   const long pl = (long)ni * nj;
+  const unsigned e = element((T & 1) ? col.cO : col.cE);
 #pragma unroll
-  for (int k = 0; k < 4; ++k) q.v[k] = b[k * pl + ((T & 1) ? col.cO : col.cE)];
+  for (int k = 0; k < 4; ++k) q.v[k] = at(b + k * pl, e);
 }
 // their values with the image's signs
 __device__ __forceinline__ void signed_values(const Raw& q, double* V) {
@@ -851,7 +876,8 @@ __device__ __forceinline__ void wave_yface(Rings<R>& S, const Ctx<R>& X, bool& n
     if (mid_row(S)) return;
     if (upd) {
       double o4[4];
-      const long gi = (long)ju * g.n1 + i;
+      double* row = X.Uout + (long)ju * g.n1;
+      const unsigned e = element(i);
 #pragma unroll
       for (int n = 0; n < 4; ++n) {
         const double dfx = double(S.FX[n][cr]) - double(S.FX[n][c]);
@@ -861,7 +887,7 @@ __device__ __forceinline__ void wave_yface(Rings<R>& S, const Ctx<R>& X, bool& n
         o4[n] = o;
         if (own_col) {
           if (!isfinite(o)) nonfinite = true;
-          X.Uout[n * nc + gi] = o;
+          at(row + n * nc, e) = o;
         }
       }
       if constexpr (DEV) {
@@ -1258,12 +1284,6 @@ struct StripArgs {
   int first;
 };
 
-// p, known to point to global memory (loads through a pointer that came from
-// memory would be flat ones)
-template <typename T>
-__device__ __forceinline__ T* in_global(T* p) {
-  return (T*)(__attribute__((address_space(1))) T*)(uintptr_t)p;
-}
 // p, known to point to memory that the kernel does not write, for scalar loads
 template <typename T>
 __device__ __forceinline__ const T* in_constant(const T* p) {
