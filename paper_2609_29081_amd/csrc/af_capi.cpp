@@ -212,21 +212,11 @@ hipError_t launch_coef(const afi::Geo& g, const afd::Phys& ph, const afi::Work& 
                     : afi::stage2d(g, ph, w, Un, Uk, Uout, dt_dev, dt_host, sc, s, tm);
 }
 
-// what the stages of a 1D step do beside it: fix dt in the first one, keep
-// the run's time in the last one
-struct StepExtras {
-  afi::StageCoef::Cfl cfl = {};
-  double* adv = nullptr;
-};
-
 hipError_t launch_stage(const afi::Geo& g, const afd::Phys& ph, const afi::Work& w, int k,
                         const double* Un, const double* Uk, double* Uout, const double* dt_dev,
-                        double dt_host, hipStream_t s, afi::Timer* tm, bool in_step = true,
-                        const StepExtras& x = {}) {
+                        double dt_host, hipStream_t s, afi::Timer* tm, bool in_step = true) {
   afi::StageCoef sc = kCoef[k];
   sc.skip_flagged = in_step ? 1 : 0;
-  if (k == 0) sc.cfl = x.cfl;
-  if (k == 2) sc.adv = x.adv;
   return launch_coef(g, ph, w, sc, Un, Uk, Uout, dt_dev, dt_host, s, tm);
 }
 
@@ -249,11 +239,26 @@ constexpr double kB10 = 0.391752226571890, kB21 = 0.368410593050371;
 constexpr double kB32 = 0.251891774271694, kB43 = 0.544974750228521;
 constexpr double kB54 = 0.226007483236906;
 
+// the stages of a 1D step in one launch (no sources)
+const afi::StepCoef1 kStep3 = {
+    3, {0.0, 0.75, 1.0 / 3.0}, {1.0, 0.25, 2.0 / 3.0}, {1.0, 1.0, 1.0}, 0.0, 0.0, 0.0, 0.0};
+const afi::StepCoef1 kStep54 = {5,
+                                {0.0, kA20, kA30, 0.0, 1.0},
+                                {1.0, kA21, kA32, 1.0, kA54},
+                                {kB10, kB21 / kA21, kB32 / kA32, kB43 / kA43, kB54 / kA54},
+                                kA40,
+                                kA43,
+                                kA52,
+                                kA53};
+
 // one SSP-RK54 attempt from u0 (kept) through buffers A, B into X; src as
-// for rk3 (five stage inputs)
+// for rk3 (five stage inputs); x: 1D steps without sources
 hipError_t rk54(const afi::Geo& g, const afd::Phys& ph, const afi::Work& w, const double* u0,
                 double* A, double* B, double* X, const double* dt_dev, double dt, hipStream_t s,
-                afi::Timer* tm, const double* const* src = nullptr, const StepExtras& x = {}) {
+                afi::Timer* tm, const double* const* src = nullptr,
+                const afi::StepExtras1& x = {}) {
+  if (g.dim == 1 && !src)
+    return afi::step1d(g, ph, w, u0, X, dt_dev, dt, kStep54, x, s, tm);
   auto coef = [](double a, double b, double mul) {
     afi::StageCoef c{};
     c.a = a;
@@ -266,9 +271,8 @@ hipError_t rk54(const afi::Geo& g, const afd::Phys& ph, const afi::Work& w, cons
   const long n = g.state_len;
   hipError_t e;
   auto S = [&](int k) { return src ? src[k] : nullptr; };
-  afi::StageCoef c0 = coef(0.0, 1.0, kB10);
-  c0.cfl = x.cfl;
-  if ((e = launch_coef(g, ph, w, c0, u0, u0, A, dt_dev, dt, s, tm)) != hipSuccess)
+  if ((e = launch_coef(g, ph, w, coef(0.0, 1.0, kB10), u0, u0, A, dt_dev, dt, s, tm)) !=
+      hipSuccess)
     return e;  // A = u1
   if ((e = add_source(g, A, kB10 * dt, S(0), s)) != hipSuccess) return e;
   if ((e = launch_coef(g, ph, w, coef(kA20, kA21, kB21 / kA21), u0, A, B, dt_dev, dt, s, tm)) !=
@@ -279,25 +283,16 @@ hipError_t rk54(const afi::Geo& g, const afd::Phys& ph, const afi::Work& w, cons
       hipSuccess)
     return e;  // X = u3
   if ((e = add_source(g, X, kB32 * dt, S(2), s)) != hipSuccess) return e;
-  // E3 = FE(u3): A = u4 = a40 u0 + a43 E3 and B = a52 u2 + a53 E3, in the 1D
-  // stage itself where no source comes between
-  afi::StageCoef c3 = coef(0.0, 1.0, kB43 / kA43);
-  if (g.dim == 1 && !src) {
-    c3.acc = B;
-    c3.wa = kA40;
-    c3.wb = kA43;
-    c3.ga = kA52;
-    c3.gb = kA53;
-    if ((e = launch_coef(g, ph, w, c3, u0, X, A, dt_dev, dt, s, tm)) != hipSuccess) return e;
-  } else {
-    if ((e = launch_coef(g, ph, w, c3, u0, X, A, dt_dev, dt, s, tm)) != hipSuccess) return e;
-    if ((e = add_source(g, A, kB43 / kA43 * dt, S(3), s)) != hipSuccess) return e;
-    if ((e = afi::lincomb(B, kA52, B, kA53, A, n, s)) != hipSuccess) return e;
-    if ((e = afi::lincomb(A, kA40, u0, kA43, A, n, s)) != hipSuccess) return e;
-  }
-  afi::StageCoef c4 = coef(1.0, kA54, kB54 / kA54);
-  c4.adv = x.adv;
-  if ((e = launch_coef(g, ph, w, c4, B, A, X, dt_dev, dt, s, tm)) != hipSuccess) return e;
+  // E3 = FE(u3): A = u4 = a40 u0 + a43 E3 and B = a52 u2 + a53 E3
+  if ((e = launch_coef(g, ph, w, coef(0.0, 1.0, kB43 / kA43), u0, X, A, dt_dev, dt, s, tm)) !=
+      hipSuccess)
+    return e;
+  if ((e = add_source(g, A, kB43 / kA43 * dt, S(3), s)) != hipSuccess) return e;
+  if ((e = afi::lincomb(B, kA52, B, kA53, A, n, s)) != hipSuccess) return e;
+  if ((e = afi::lincomb(A, kA40, u0, kA43, A, n, s)) != hipSuccess) return e;
+  if ((e = launch_coef(g, ph, w, coef(1.0, kA54, kB54 / kA54), B, A, X, dt_dev, dt, s, tm)) !=
+      hipSuccess)
+    return e;
   return add_source(g, X, kB54 * dt, S(4), s);
 }
 
@@ -309,11 +304,11 @@ hipError_t launch_cfl(const af_ctx* c, const afi::Geo& g, const afi::Work& w, co
                      U, t_host, t_dev, t_final, dt_out, s, c->timer);
 }
 
-// the CFL step of a 1D stage that fixes dt itself, as launch_cfl takes it
-afi::StageCoef::Cfl stage_cfl(const af_ctx* c, const afi::Geo& g, double t_host,
+// the CFL step of a 1D step that fixes dt itself, as launch_cfl takes it
+afi::StepExtras1::Cfl step_cfl(const af_ctx* c, const afi::Geo& g, double t_host,
                               const double* t_dev, double t_final) {
   const af_params& p = c->p;
-  afi::StageCoef::Cfl f;
+  afi::StepExtras1::Cfl f;
   f.on = 1;
   f.icx = 1.0 / (p.cfl_c * g.dx);
   f.vcoef = fmax(4.0 * p.mu / 3.0, p.gamma * p.mu / p.Pr) / (p.cfl_v * g.dx * g.dx);
@@ -423,9 +418,10 @@ af_status scratch_on_current_device(void** out) {
 // forward Euler step then adds tau S_k after its limited update
 hipError_t rk3(const afi::Geo& g, const afd::Phys& ph, const afi::Work& w, const double* cur,
                double* out, const double* dt_dev, double dt, hipStream_t s, afi::Timer* tm,
-               const double* const* src = nullptr, const StepExtras& x = {}) {
+               const double* const* src = nullptr, const afi::StepExtras1& x = {}) {
+  if (g.dim == 1 && !src) return afi::step1d(g, ph, w, cur, out, dt_dev, dt, kStep3, x, s, tm);
   hipError_t e;
-  if ((e = launch_stage(g, ph, w, 0, cur, cur, w.S1, dt_dev, dt, s, tm, true, x)) != hipSuccess)
+  if ((e = launch_stage(g, ph, w, 0, cur, cur, w.S1, dt_dev, dt, s, tm)) != hipSuccess)
     return e;
   if (src && (e = add_source(g, w.S1, dt, src[0], s)) != hipSuccess) return e;
   if ((e = launch_stage(g, ph, w, 1, cur, w.S1, w.S2, dt_dev, dt, s, tm)) != hipSuccess) return e;
@@ -882,11 +878,11 @@ static af_status step_in(af_ctx* c, double* U, void* ws, void* stream, double dt
   // the CFL step stays on the device for the first attempt; the host reads it
   // with the flags
   const double* dt_dev = nullptr;
-  StepExtras x;
+  afi::StepExtras1 x{};
   if (dt <= 0.0) {
     dt_dev = w.scal;
-    if (afi::stage1d_takes_cfl(g))
-      x.cfl = stage_cfl(c, g, t, nullptr, t_final);
+    if (afi::step1d_takes_cfl(g))
+      x.cfl = step_cfl(c, g, t, nullptr, t_final);
     else
       AF_HIP(launch_cfl(c, g, w, U, t, nullptr, t_final, w.scal, s));
   } else if (t + dt > t_final) {
@@ -969,26 +965,27 @@ af_status af_run(af_ctx* c, double* U, void* ws, void* stream, double t0, double
   unsigned fl = 0;
   SlotHolder slot;
   auto read_back = [&]() { return read_scalars(w, s, slot.slot, sc, &fl); };
-  auto three_stages = [&](int from, const StepExtras& x = {}) -> hipError_t {
+  auto attempt = [&](int from, const afi::StepExtras1& x = {}) -> hipError_t {
     if (rk54s)
       return rk54(g, ph, w, bufs[from], bufs[(from + 1) % 4], bufs[(from + 2) % 4],
                   bufs[(from + 3) % 4], w.scal, 0.0, s, c->timer, nullptr, x);
     const int a = (from + 1) % 3, b = (from + 2) % 3;
+    if (g.dim == 1)
+      return afi::step1d(g, ph, w, bufs[from], bufs[a], w.scal, 0.0, kStep3, x, s, c->timer);
     hipError_t e;
     if ((e = launch_stage(g, ph, w, 0, bufs[from], bufs[from], bufs[a], w.scal, 0.0, s,
-                          c->timer, true, x)) != hipSuccess)
+                          c->timer)) != hipSuccess)
       return e;
     if ((e = launch_stage(g, ph, w, 1, bufs[from], bufs[a], bufs[b], w.scal, 0.0, s,
                           c->timer)) != hipSuccess)
       return e;
-    return launch_stage(g, ph, w, 2, bufs[from], bufs[b], bufs[a], w.scal, 0.0, s, c->timer, true,
-                        x);
+    return launch_stage(g, ph, w, 2, bufs[from], bufs[b], bufs[a], w.scal, 0.0, s, c->timer);
   };
-  // in 1D the stages of a block's step fix dt and keep the time themselves
-  StepExtras in_stages;
-  const bool cfl_in_stage = afi::stage1d_takes_cfl(g);
-  if (cfl_in_stage) in_stages.cfl = stage_cfl(c, g, 0.0, w.scal + 1, t_final);
-  if (g.dim == 1) in_stages.adv = w.scal;
+  // in 1D a block's steps fix dt and keep the time themselves
+  const bool cfl_in_step = afi::step1d_takes_cfl(g);
+  afi::StepExtras1 in_step{};
+  if (cfl_in_step) in_step.cfl = step_cfl(c, g, 0.0, nullptr, t_final);
+  in_step.steps = w.scal + 2;
   AF_HIP(afi::set_scalar(w.scal + 1, t, s));
   while (done < max_steps && t < t_final) {
     const long K = (max_steps - done) < check_every ? (max_steps - done) : check_every;
@@ -996,12 +993,22 @@ af_status af_run(af_ctx* c, double* U, void* ws, void* stream, double t0, double
       // optimistic block of K steps with one synchronisation at its end
       AF_HIP(afi::copy_state(w.SAVE, bufs[cur], g.state_len, s, w.flags));
       AF_HIP(afi::set_scalar(w.scal + 2, 0.0, s));
+      // steps that take dt and the time in one launch read the time from one
+      // place and leave it in another, the last one in scal[1]
+      double* at[2] = {w.scal + 1, w.scal + (cfl_in_step ? 3 : 1)};
+      if (cfl_in_step && (K & 1)) AF_HIP(afi::set_scalar(at[1], t, s));
       int c2 = cur;
       for (long k = 0; k < K; ++k) {
-        if (!cfl_in_stage)
+        if (!cfl_in_step)
           AF_HIP(launch_cfl(c, g, w, bufs[c2], 0.0, w.scal + 1, t_final, w.scal, s));
-        AF_HIP(three_stages(c2, in_stages));
-        if (!in_stages.adv) AF_HIP(afi::advance_time(w, s));
+        if (g.dim == 1) {
+          in_step.t_in = in_step.cfl.t_dev = at[(K - k) & 1];
+          in_step.t_out = at[(K - k + 1) & 1];
+          AF_HIP(attempt(c2, in_step));
+        } else {
+          AF_HIP(attempt(c2));
+          AF_HIP(afi::advance_time(w, s));
+        }
         c2 = next(c2);
       }
       if ((status = read_back()) != AF_OK) break;
@@ -1021,7 +1028,7 @@ af_status af_run(af_ctx* c, double* U, void* ws, void* stream, double t0, double
       int h;
       for (h = 0; h <= c->p.max_halvings; ++h) {
         AF_HIP(afi::clear_flags(w, s));
-        AF_HIP(three_stages(cur));
+        AF_HIP(attempt(cur));
         if ((status = read_back()) != AF_OK) break;
         if (fl == 0) break;
         AF_HIP(afi::scale_scalar(w.scal, 0.5, s));  // redo with dt/2

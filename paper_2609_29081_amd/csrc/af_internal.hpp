@@ -116,19 +116,6 @@ struct StageCoef {
   float* ts_out;
   // the forward-Euler step is dt_mul * dt (the stages of SSP-RK54)
   double dt_mul = 1.0;
-  // 1D only, the rest.  acc != NULL (SSP-RK54's shared evaluation o): the
-  // stage writes Uout = wa Un + wb o and acc = ga acc + gb o in place of o
-  double* acc = nullptr;
-  double wa = 0.0, wb = 0.0, ga = 0.0, gb = 0.0;
-  // the stage fixes the step's dt itself (eq. cfl, from its input's averages,
-  // as k_cfl takes it) and leaves it in scal[0]
-  struct Cfl {
-    int on;
-    double icx, vcoef, t_host, t_final;
-    const double* t_dev;
-  } cfl = {};
-  // the stage ends an accepted step: t += dt, one step more (scal[1], scal[2])
-  double* adv = nullptr;
 };
 
 size_t workspace_layout(const Geo& g, Work* w, char* base);
@@ -169,12 +156,36 @@ hipError_t mlp_adam(float* params, const float* grad, float* m, float* v, long s
 hipError_t stage2d(const Geo& g, const afd::Phys& ph, const Work& w, const double* Un,
                    const double* Uk, double* Uout, const double* dt_dev, double dt_host,
                    StageCoef sc, hipStream_t s, Timer* tm);
-// whether a 1D stage of this grid can fix dt itself (every workgroup reads
-// all averages, which pays while they are few)
-bool stage1d_takes_cfl(const Geo& g);
+// one 1D stage; a whole 1D step from U to Uout (other memory) in one launch
 hipError_t stage1d(const Geo& g, const afd::Phys& ph, const Work& w, const double* Un,
                    const double* Uk, double* Uout, const double* dt_dev, double dt_host,
                    StageCoef sc, hipStream_t s, Timer* tm);
+// stages a[k] base + b[k] FE(., mul[k] dt) of a step: three of SSP-RK3, or the
+// five of SSP-RK54, whose fourth gives wa u0 + wb o for the fifth's input and
+// ga u2 + gb o for its base
+struct StepCoef1 {
+  int stages;
+  double a[5], b[5], mul[5];
+  double wa, wb, ga, gb;
+};
+// what a 1D step does beside its stages: fix dt itself (eq. cfl, from its
+// averages, as k_cfl takes it), left in scal[0]; and keep a run's time, t_out =
+// t_in + dt, one step more
+struct StepExtras1 {
+  struct Cfl {
+    int on;
+    double icx, vcoef, t_host, t_final;
+    const double* t_dev;
+  } cfl;
+  const double* t_in;
+  double *t_out, *steps;
+};
+// whether a 1D step of this grid can fix dt itself (every workgroup reads all
+// averages, which pays while they are few)
+bool step1d_takes_cfl(const Geo& g);
+hipError_t step1d(const Geo& g, const afd::Phys& ph, const Work& w, const double* U, double* Uout,
+                  const double* dt_dev, double dt_host, const StepCoef1& sc, const StepExtras1& x,
+                  hipStream_t s, Timer* tm);
 hipError_t cfl_dt(const Geo& g, const afd::Phys& ph, double cfl_c, double cfl_v, double visc_a,
                   double visc_b, const Work& w, const double* U, double t_host,
                   const double* t_dev, double t_final, double* dt_out, hipStream_t s,

@@ -1,23 +1,31 @@
-// af_kern1d.hip -- one SSP-RK3 stage of the 1D compact AF method (Sec. 2.1)
-// on gfx950, FP64, as one launch.  Same pipeline as the 2D stage (lattice,
-// gradients, per-cell low-order data, limited face fluxes, cell update, point
-// update), with U = (rho, rho u, E), W = (rho, u, p), Z = (0, u, T) and
+// af_kern1d.hip -- the 1D compact AF method (Sec. 2.1) on gfx950, FP64: one
+// SSP-RK3 stage as one launch, and a whole step (SSP-RK3 or SSP-RK54) as one.
+// Same pipeline as the 2D stage (lattice, gradients, per-cell low-order data,
+// limited face fluxes, cell update, point update), with U = (rho, rho u, E),
+// W = (rho, u, p), Z = (0, u, T) and
 //   K(W) = [[0,0,0],[0,4mu/3,0],[0,4mu u/3,kappa]].
 //
 // The 1D problems are small (hundreds of cells), so a stage is bound by
-// latency: launches, and the chain of dependent FP64 operations.  A workgroup
-// of three wave64s takes 61 cells and the points at their lower sides, and
-// passes everything through LDS with one barrier:
-//   before it  waves 0-1 one lattice site each (values, centres, primitives),
-//              wave 2 one cell each of the tile +- 1 (low-order data); and, in
-//              the first stage of a step that fixes dt, all three the CFL
-//              maxima of the whole grid (each workgroup for itself: the
-//              averages of a small grid are a few loads per thread, where the
-//              reduction as kernels of its own cost two launches)
-//   after it   wave 0 one face each (limited flux), whose neighbours' fluxes
-//              come by a lane shift to the cell update; wave 1 one point each
+// latency: launches, loads, and the chain of dependent FP64 operations.  A
+// workgroup of three wave64s takes 61 cells and the points at their lower
+// sides, and passes everything through LDS:
+//   before a barrier  waves 0-1 one lattice site each (values, centres,
+//                     primitives), wave 2 one cell each of the tile +- 1
+//                     (low-order data)
+//   after it          wave 0 one face each (limited flux), whose neighbours'
+//                     fluxes come by a lane shift to the cell update; wave 1
+//                     one point each
 // 61 cells are the most for which sites (2 x 61 + 5), ring cells (63) and
 // faces (62) fit one per lane.
+//
+// A step keeps its tile in LDS from stage to stage.  A stage's values depend
+// on two cells at either side, so a tile's outer cells are computed along with
+// those of its neighbours, two fewer at either side in each stage: 61 - 8 cells
+// of a tile are its own in SSP-RK3, 61 - 16 in SSP-RK54.  That is 1.15 and 1.36
+// times the work, and one launch, one read and one write of the state instead
+// of three or five: a step of a run of 800 cells took 21.7 us with a launch per
+// stage and takes 16.6, one of SSP-RK54 at 160 cells (af_step) 62 and 40; of
+// 2,000,000 cells 1130 with the stage in several launches and 880.
 #include "af_device.hpp"
 #include "af_internal.hpp"
 
@@ -37,29 +45,58 @@ struct G1 {
   double dl[3], dr[3];  // states of Dirichlet sides (x-low, x-high)
 };
 
-// what a launch does beside the forward-Euler step (see StageCoef)
+// a stage's launch (see StageCoef)
 struct Stage1 {
   double ca, cb;
   int first, skip_flagged;
   unsigned* flags;
   const double* dt_dev;
   double dt_host, dt_mul;
-  double* acc;
-  double wa, wb, ga, gb;
-  double* adv;
-  int cfl;
-  double icx, vcoef, t_host, t_final;
-  const double* t_dev;
+};
+
+// a step's launch: its stages out = ca base + cb FE(in, mul dt), where base is
+// the step's first state but in the last stage of SSP-RK54 (see rk54)
+struct Step1 {
+  int stages;
+  double ca[5], cb[5], mul[5];
+  double wa, wb, ga, gb;  // SSP-RK54's shared evaluation
+  unsigned* flags;
+  const double* dt_dev;
+  double dt_host;
+  afi::StepExtras1 x;
   double* dt_out;
 };
 
-__device__ __forceinline__ double pt(const G1& g, const double* __restrict__ U, int X, int k) {
-  if (X == 2 * g.n && g.np == g.n) X = 0;
-  return U[g.off_pts + (long)k * g.np + (X >> 1)];
-}
+// the state a stage reads: in global memory, its ghosts the images of what
+// axis_image says ...
+struct Global1 {
+  const double* __restrict__ U;
+  __device__ __forceinline__ int image(const G1& g, int X, int& kind) const {
+    return axis_image(X, 2 * g.n, g.bc0, g.bc1, kind);
+  }
+  __device__ __forceinline__ double cell(const G1& g, int i, int k) const {
+    return U[(long)k * g.n + i];
+  }
+  __device__ __forceinline__ double point(const G1& g, int j, int k) const {
+    if (j == g.n && g.np == g.n) j = 0;
+    return U[g.off_pts + (long)k * g.np + j];
+  }
+};
+// ... or in LDS: cells b - 2 .. b + 62 and points b - 1 .. b + 62, continued
+// beyond periodic sides
+struct Held1 {
+  double C[3][kCells + 4], P[3][kCells + 3];
+  int b;
+  __device__ __forceinline__ int image(const G1& g, int X, int& kind) const {
+    kind = -1;
+    return g.bc0 == BC_PERIODIC ? X : axis_image(X, 2 * g.n, g.bc0, g.bc1, kind);
+  }
+  __device__ __forceinline__ double cell(const G1&, int i, int k) const { return C[k][i - b + 2]; }
+  __device__ __forceinline__ double point(const G1&, int j, int k) const { return P[k][j - b + 1]; }
+};
 
-__device__ __forceinline__ void cell_image1(const G1& g, const double* __restrict__ U, int i,
-                                            double* V) {
+template <typename Src>
+__device__ __forceinline__ void cell_image1(const G1& g, const Src& U, int i, double* V) {
   // beyond a Dirichlet side, its state
   if ((i < 0 && g.bc0 == BC_DIRICHLET) || (i >= g.n && g.bc1 == BC_DIRICHLET)) {
     const double* d = i < 0 ? g.dl : g.dr;
@@ -68,12 +105,12 @@ __device__ __forceinline__ void cell_image1(const G1& g, const double* __restric
     return;
   }
   int kind;
-  const int Xi = axis_image(2 * i + 1, 2 * g.n, g.bc0, g.bc1, kind);
+  const int Xi = U.image(g, 2 * i + 1, kind);
   const double s = (kind == BC_NOSLIP || kind == BC_SYMMETRY) ? -1.0 : 1.0;
   const int ii = Xi >> 1;
-  V[0] = U[ii];
-  V[1] = s * U[g.n + ii];
-  V[2] = U[2 * g.n + ii];
+  V[0] = U.cell(g, ii, 0);
+  V[1] = s * U.cell(g, ii, 1);
+  V[2] = U.cell(g, ii, 2);
 }
 
 // data of a tile in LDS
@@ -87,10 +124,11 @@ struct Tile1 {
 };
 
 // lattice site X into tile entry t
-__device__ __forceinline__ void lattice_site(const G1& g, const Phys& ph,
-                                             const double* __restrict__ U, int X, int t, Tile1& S) {
+template <typename Src>
+__device__ __forceinline__ void lattice_site(const G1& g, const Phys& ph, const Src& U, int X,
+                                             int t, Tile1& S) {
   int kind;
-  const int Xi = axis_image(X, 2 * g.n, g.bc0, g.bc1, kind);
+  const int Xi = U.image(g, X, kind);
   const double s = (kind == BC_NOSLIP || kind == BC_SYMMETRY) ? -1.0 : 1.0;
   double V[3];
   if (Xi & 1) {
@@ -98,8 +136,8 @@ __device__ __forceinline__ void lattice_site(const G1& g, const Phys& ph,
     double Ub[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      Ub[k] = U[k * g.n + i];
-      V[k] = (6.0 * Ub[k] - (pt(g, U, Xi - 1, k) + pt(g, U, Xi + 1, k))) / 4.0;
+      Ub[k] = U.cell(g, i, k);
+      V[k] = (6.0 * Ub[k] - (U.point(g, i, k) + U.point(g, i + 1, k))) / 4.0;
     }
     if (ph.lim & LIM_CENTRE) {
       if (!(Ub[0] > 0.0)) {
@@ -116,7 +154,7 @@ __device__ __forceinline__ void lattice_site(const G1& g, const Phys& ph,
     }
   } else {
 #pragma unroll
-    for (int k = 0; k < 3; ++k) V[k] = pt(g, U, Xi, k);
+    for (int k = 0; k < 3; ++k) V[k] = U.point(g, Xi >> 1, k);
   }
   V[1] *= s;
   if ((X < 0 && g.bc0 == BC_DIRICHLET) || (X > 2 * g.n && g.bc1 == BC_DIRICHLET)) {
@@ -135,8 +173,9 @@ __device__ __forceinline__ void lattice_site(const G1& g, const Phys& ph,
 }
 
 // low-order data of cell i (ghosts as boundary images) into ring entry t
-__device__ __forceinline__ void cell_site(const G1& g, const Phys& ph,
-                                          const double* __restrict__ U, int i, int t, Tile1& S) {
+template <typename Src>
+__device__ __forceinline__ void cell_site(const G1& g, const Phys& ph, const Src& U, int i, int t,
+                                          Tile1& S) {
   double C0[3], Cm[3], Cp[3];
   cell_image1(g, U, i, C0);
   cell_image1(g, U, i - 1, Cm);
@@ -364,21 +403,6 @@ __device__ __forceinline__ void point_update(const G1& g, const Phys& ph, const 
   }
 }
 
-// RK combination of the forward-Euler value fe of DOF array element a, and
-// the further combinations a stage may carry (see StageCoef); false if the
-// value is not finite
-__device__ __forceinline__ bool combine(const Stage1& st, const double* __restrict__ Un,
-                                        double* __restrict__ Uout, long a, double fe) {
-  const double o = st.first ? fe : st.ca * Un[a] + st.cb * fe;
-  if (st.acc) {
-    Uout[a] = st.wa * Un[a] + st.wb * o;
-    st.acc[a] = st.ga * st.acc[a] + st.gb * o;
-  } else {
-    Uout[a] = o;
-  }
-  return isfinite(o);
-}
-
 __global__ void __launch_bounds__(kThreads) k_stage1(G1 g, Phys ph, Stage1 st,
                                                      const double* __restrict__ Un,
                                                      const double* __restrict__ Uk,
@@ -391,14 +415,83 @@ __global__ void __launch_bounds__(kThreads) k_stage1(G1 g, Phys ph, Stage1 st,
   // inside a step attempt: stop once the attempt's flag word is set (it is
   // rejected and the stage output is never read)
   if (tid == 0) S.stop = st.skip_flagged ? peek_flags(st.flags) : 0u;
-  double ra = 0.0, rv = 0.0;
-  if (st.cfl) {
+  // entry t of the tile's lattice is site 2 i0 - 2 + t; ring entry t is cell
+  // i0 - 1 + t
+  const Global1 U{Uk};
+  if (wave < 2) {
+    if (tid < 2 * nc + 5) lattice_site(g, ph, U, 2 * i0 - 2 + tid, tid, S);
+  } else if (lane < nc + 2) {
+    cell_site(g, ph, U, i0 - 1 + lane, lane, S);
+  }
+  __syncthreads();
+  if (S.stop) return;
+  double dt = st.dt_dev ? *st.dt_dev : st.dt_host;
+  if (st.dt_mul != 1.0) dt = st.dt_mul * dt;
+  bool ok = true;
+  // RK combination of the forward-Euler value fe of DOF array element a
+  auto combine = [&](long a, double fe) {
+    const double o = st.first ? fe : st.ca * Un[a] + st.cb * fe;
+    Uout[a] = o;
+    ok &= (bool)isfinite(o);
+  };
+  if (wave == 0) {
+    double F[3] = {0.0, 0.0, 0.0};
+    if (nc > 0 && lane <= nc) face_flux(g, ph, S, lane, 2 * lane + 2, dt, st.flags, F);
+    const double m = dt / g.dx;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const double Fp = __shfl_down(F[k], 1, 64);
+      if (lane < nc) combine((long)k * g.n + i0 + lane, S.C[7 + k][lane + 1] - m * (Fp - F[k]));
+    }
+  } else if (wave == 1 && lane < npt) {
+    double out[3];
+    point_update(g, ph, S, i0 + lane, 2 * lane + 2, lane, dt, st.flags, out);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) combine(g.off_pts + (long)k * g.np + i0 + lane, out[k]);
+  }
+  if (!ok) raise_flag(st.flags, FLAG_NONFINITE);
+}
+
+// a whole step from U to Uout (other memory: neighbouring tiles read U)
+__global__ void __launch_bounds__(kThreads) k_step1(G1 g, Phys ph, Step1 st,
+                                                    const double* __restrict__ U,
+                                                    double* __restrict__ Uout) {
+  __shared__ Tile1 S;
+  __shared__ Held1 H;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int halo = 2 * (st.stages - 1), own = kCells - 2 * halo;
+  const int b = (int)blockIdx.x * own - halo;  // first cell of the tile, and lane 0's
+  const bool periodic = g.bc0 == BC_PERIODIC;
+  if (tid == 0) {
+    S.stop = peek_flags(st.flags);
+    H.b = b;
+  }
+  // the tile of the state.  Beyond periodic sides it goes on; beyond others
+  // nothing is read from here (ghosts are images)
+  auto within = [&](int i, int n) {
+    if (!periodic) return i < 0 ? 0 : min(i, n - 1);
+    const int r = i % n;
+    return r < 0 ? r + n : r;
+  };
+  for (int e = tid; e < 3 * (kCells + 4); e += kThreads) {
+    const int k = e / (kCells + 4), t = e % (kCells + 4);
+    H.C[k][t] = U[(long)k * g.n + within(b - 2 + t, g.n)];
+  }
+  for (int e = tid; e < 3 * (kCells + 3); e += kThreads) {
+    const int k = e / (kCells + 3), t = e % (kCells + 3);
+    H.P[k][t] = U[g.off_pts + (long)k * g.np + within(b - 1 + t, g.np)];
+  }
+  // the step's dt (eq. cfl, as k_cfl takes it) from the averages of the whole
+  // grid, each workgroup for itself: a few loads per thread on a small grid,
+  // where a reduction as kernels of its own costs two launches
+  if (st.x.cfl.on) {
+    double ra = 0.0, rv = 0.0;
     for (int c = tid; c < g.n; c += kThreads) {
-      const double r = Uk[c], m = Uk[g.n + c], E = Uk[2 * g.n + c];
+      const double r = U[c], m = U[g.n + c], E = U[2 * g.n + c];
       const double p = pressure1(r, m, E, ph.gm1);
       const double cs = root(ph.gam * p / r);
-      ra = mx(ra, (fabs(m / r) + cs) * st.icx);
-      rv = mx(rv, st.vcoef / r);
+      ra = mx(ra, (fabs(m / r) + cs) * st.x.cfl.icx);
+      rv = mx(rv, st.x.cfl.vcoef / r);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -410,65 +503,101 @@ __global__ void __launch_bounds__(kThreads) k_stage1(G1 g, Phys ph, Stage1 st,
       S.red[1][wave] = rv;
     }
   }
-  // entry t of the tile's lattice is site 2 i0 - 2 + t; ring entry t is cell
-  // i0 - 1 + t
-  if (wave < 2) {
-    if (tid < 2 * nc + 5) lattice_site(g, ph, Uk, 2 * i0 - 2 + tid, tid, S);
-  } else if (lane < nc + 2) {
-    cell_site(g, ph, Uk, i0 - 1 + lane, lane, S);
-  }
   __syncthreads();
+  // a step before this one, or a faster tile, was rejected already
   if (S.stop) return;
-  double dt;
-  if (st.cfl) {
+  double dt0;
+  if (st.x.cfl.on) {
     const double a = mx(mx(S.red[0][0], S.red[0][1]), S.red[0][2]);
     const double v = mx(mx(S.red[1][0], S.red[1][1]), S.red[1][2]);
-    const double t = st.t_dev ? *st.t_dev : st.t_host;
-    dt = 1.0 / (a + v);
-    if (t + dt > st.t_final) dt = st.t_final - t;
-    if (!(dt > 0.0)) dt = 0.0;
-    if (blockIdx.x == 0 && tid == 0) *st.dt_out = dt;
+    const double t = st.x.cfl.t_dev ? *st.x.cfl.t_dev : st.x.cfl.t_host;
+    dt0 = 1.0 / (a + v);
+    if (t + dt0 > st.x.cfl.t_final) dt0 = st.x.cfl.t_final - t;
+    if (!(dt0 > 0.0)) dt0 = 0.0;
+    if (blockIdx.x == 0 && tid == 0) *st.dt_out = dt0;
   } else {
-    dt = st.dt_dev ? *st.dt_dev : st.dt_host;
+    dt0 = st.dt_dev ? *st.dt_dev : st.dt_host;
   }
-  // a run's last stage keeps the time (no other workgroup reads it here)
-  if (st.adv && blockIdx.x == 0 && tid == 0 && dt > 0.0) {
-    st.adv[1] = st.adv[1] + dt;
-    st.adv[2] = st.adv[2] + 1.0;
+  // a run's step keeps the time (t_in is read by other workgroups too, so t_out
+  // is other memory where dt comes from it)
+  if (st.x.t_out && blockIdx.x == 0 && tid == 0) {
+    const double t = *st.x.t_in;
+    *st.x.t_out = dt0 > 0.0 ? t + dt0 : t;
+    if (dt0 > 0.0) *st.x.steps = *st.x.steps + 1.0;
   }
-  if (st.dt_mul != 1.0) dt = st.dt_mul * dt;
   bool ok = true;
-  if (wave == 0) {
-    double F[3] = {0.0, 0.0, 0.0};
-    if (nc > 0 && lane <= nc) face_flux(g, ph, S, lane, 2 * lane + 2, dt, st.flags, F);
-    const double m = dt / g.dx;
+  // the lane's cell (wave 0) or point (wave 1): the step's first state, and
+  // SSP-RK54's second stage, which its last one builds on
+  double un[3], u2[3] = {0.0, 0.0, 0.0}, now[3];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const double Fp = __shfl_down(F[k], 1, 64);
-      if (lane < nc) {
-        const double fe = S.C[7 + k][lane + 1] - m * (Fp - F[k]);
-        ok &= combine(st, Un, Uout, (long)k * g.n + i0 + lane, fe);
+  for (int k = 0; k < 3; ++k) now[k] = un[k] = wave == 0 ? H.C[k][lane < 61 ? lane + 2 : 0]
+                                                        : H.P[k][lane < 62 ? lane + 1 : 0];
+  const int j = b + lane;
+  const bool real_face = periodic || (j >= 0 && j <= g.n);
+  const bool real_cell = periodic || (j >= 0 && j < g.n);
+  const bool real_point = periodic || (j >= 0 && j < g.np);
+  for (int s = 0; s < st.stages; ++s) {
+    // entry t of the lattice is site 2 b - 2 + t, of the ring cell b - 1 + t;
+    // of the ghosts, those that faces and points of the grid reach
+    if (wave < 2) {
+      const int X = 2 * b - 2 + tid;
+      if (tid < kSites && (periodic || (X >= -2 && X <= 2 * g.n + 2)))
+        lattice_site(g, ph, H, X, tid, S);
+    } else if (lane < kRing && (periodic || (j - 1 >= -1 && j - 1 <= g.n))) {
+      cell_site(g, ph, H, j - 1, lane, S);
+    }
+    __syncthreads();
+    double dt = dt0;
+    if (st.mul[s] != 1.0) dt = st.mul[s] * dt;
+    const double ca = st.ca[s], cb = st.cb[s];
+    const bool first = ca == 0.0, five = st.stages == 5;
+    // the stage's combinations for the forward-Euler value fe of component k
+    auto combine = [&](int k, double fe) {
+      const double base = five && s == 4 ? u2[k] : un[k];
+      const double o = first ? fe : ca * base + cb * fe;
+      ok &= (bool)isfinite(o);
+      now[k] = o;
+      if (five && s == 1) u2[k] = o;
+      if (five && s == 3) {
+        now[k] = st.wa * un[k] + st.wb * o;
+        u2[k] = st.ga * u2[k] + st.gb * o;
+      }
+    };
+    if (wave == 0) {
+      double F[3] = {0.0, 0.0, 0.0};
+      if (real_face && lane >= 2 * s && lane <= kCells - 2 * s)
+        face_flux(g, ph, S, lane, 2 * lane + 2, dt, st.flags, F);
+      const double m = dt / g.dx;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const double Fp = __shfl_down(F[k], 1, 64);
+        if (real_cell && lane >= 2 * s && lane < kCells - 2 * s) {
+          combine(k, S.C[7 + k][lane + 1] - m * (Fp - F[k]));
+          H.C[k][lane + 2] = now[k];
+        }
+      }
+    } else if (wave == 1 && real_point && lane >= 2 * s && lane <= kCells - 2 * s) {
+      double out[3];
+      point_update(g, ph, S, j, 2 * lane + 2, lane, dt, st.flags, out);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        combine(k, out[k]);
+        H.P[k][lane + 1] = now[k];
       }
     }
-  } else if (wave == 1 && lane < npt) {
-    double out[3];
-    point_update(g, ph, S, i0 + lane, 2 * lane + 2, lane, dt, st.flags, out);
+    __syncthreads();
+  }
+  if (lane >= halo && lane < halo + own) {
 #pragma unroll
-    for (int k = 0; k < 3; ++k)
-      ok &= combine(st, Un, Uout, g.off_pts + (long)k * g.np + i0 + lane, out[k]);
+    for (int k = 0; k < 3; ++k) {
+      if (wave == 0 && j < g.n) Uout[(long)k * g.n + j] = now[k];
+      if (wave == 1 && j < g.np) Uout[g.off_pts + (long)k * g.np + j] = now[k];
+    }
   }
   if (!ok) raise_flag(st.flags, FLAG_NONFINITE);
 }
 
-}  // namespace
-
-namespace afi {
-
-bool stage1d_takes_cfl(const Geo& g) { return g.dim == 1 && g.n1 <= 4096; }
-
-hipError_t stage1d(const Geo& geo, const Phys& ph, const Work& w, const double* Un,
-                   const double* Uk, double* Uout, const double* dt_dev, double dt_host,
-                   StageCoef sc, hipStream_t s, Timer* tm) {
+G1 geo1(const afi::Geo& geo) {
   G1 g;
   g.n = geo.n1;
   g.np = geo.n1x;
@@ -480,6 +609,19 @@ hipError_t stage1d(const Geo& geo, const Phys& ph, const Work& w, const double* 
     g.dl[k] = geo.bcstate[0][k];
     g.dr[k] = geo.bcstate[1][k];
   }
+  return g;
+}
+
+}  // namespace
+
+namespace afi {
+
+bool step1d_takes_cfl(const Geo& g) { return g.dim == 1 && g.n1 <= 4096; }
+
+hipError_t stage1d(const Geo& geo, const Phys& ph, const Work& w, const double* Un,
+                   const double* Uk, double* Uout, const double* dt_dev, double dt_host,
+                   StageCoef sc, hipStream_t s, Timer* tm) {
+  const G1 g = geo1(geo);
   Stage1 st{};
   st.ca = sc.a;
   st.cb = sc.b;
@@ -489,22 +631,36 @@ hipError_t stage1d(const Geo& geo, const Phys& ph, const Work& w, const double* 
   st.dt_dev = dt_dev;
   st.dt_host = dt_host;
   st.dt_mul = sc.dt_mul;
-  st.acc = sc.acc;
+  AFI_TIMED(tm, 0, s,
+            hipLaunchKernelGGL(k_stage1, dim3((unsigned)((g.np + kCells - 1) / kCells)),
+                               dim3(kThreads), 0, s, g, ph, st, Un, Uk, Uout));
+  return hipGetLastError();
+}
+
+hipError_t step1d(const Geo& geo, const Phys& ph, const Work& w, const double* U, double* Uout,
+                  const double* dt_dev, double dt_host, const StepCoef1& sc, const StepExtras1& x,
+                  hipStream_t s, Timer* tm) {
+  const G1 g = geo1(geo);
+  Step1 st{};
+  st.stages = sc.stages;
+  for (int k = 0; k < sc.stages; ++k) {
+    st.ca[k] = sc.a[k];
+    st.cb[k] = sc.b[k];
+    st.mul[k] = sc.mul[k];
+  }
   st.wa = sc.wa;
   st.wb = sc.wb;
   st.ga = sc.ga;
   st.gb = sc.gb;
-  st.adv = sc.adv;
-  st.cfl = sc.cfl.on;
-  st.icx = sc.cfl.icx;
-  st.vcoef = sc.cfl.vcoef;
-  st.t_host = sc.cfl.t_host;
-  st.t_dev = sc.cfl.t_dev;
-  st.t_final = sc.cfl.t_final;
+  st.flags = w.flags;
+  st.dt_dev = dt_dev;
+  st.dt_host = dt_host;
+  st.x = x;
   st.dt_out = w.scal;
+  const int own = kCells - 4 * (sc.stages - 1);
   AFI_TIMED(tm, 0, s,
-            hipLaunchKernelGGL(k_stage1, dim3((unsigned)((g.np + kCells - 1) / kCells)),
-                               dim3(kThreads), 0, s, g, ph, st, Un, Uk, Uout));
+            hipLaunchKernelGGL(k_step1, dim3((unsigned)((g.np + own - 1) / own)), dim3(kThreads),
+                               0, s, g, ph, st, U, Uout));
   return hipGetLastError();
 }
 

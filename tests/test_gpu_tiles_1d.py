@@ -62,3 +62,27 @@ def test_run_equals_steps_with_given_dt(n, rk):
         tb += dt
     assert st == af.AF_OK and steps == 4 and t == tb == t_final
     assert torch.equal(A, B)
+
+
+@pytest.mark.parametrize("n", [4, 45, 46, 52, 53, 54, 90, 107, 300])
+@pytest.mark.parametrize("bc", [W.PERIODIC, W.OUTFLOW, W.NOSLIP, W.SYMMETRY, W.DIRICHLET])
+def test_step_equals_its_stages(n, bc):
+    """the step in one launch against its stages in a launch each, bit for bit,
+    at the edges of the step's tiles (53 cells of their own, 45 in SSP-RK54)"""
+    g, U, kw = field(n, bc)
+    S = af.Solver(g, gamma=GAMMA, **kw)
+    A = S.to_device(U)
+    dt = float(S.af_cfl_dt(A).item())
+    one, two, out = (torch.empty_like(A) for _ in range(3))
+    S.af_rk_stage(0, A, A, one, dt=dt)
+    S.af_rk_stage(1, A, one, two, dt=dt)
+    S.af_rk_stage(2, A, two, out, dt=dt)
+    B = A.clone()
+    assert S.af_step(B, dt=dt)[0] == 0
+    assert torch.equal(B, out)
+    # SSP-RK54: with sources of zero, its stages have a launch each as well
+    S = af.Solver(g, gamma=GAMMA, rk=54, **kw)
+    B, C = A.clone(), A.clone()
+    assert S.af_step(B, dt=dt)[0] == 0
+    S.af_step_source(C, dt, [torch.zeros_like(A)] * 5)
+    assert torch.equal(B, C)
