@@ -36,9 +36,12 @@ constexpr int OFF_W1 = 0, OFF_B1 = NH * NIN, OFF_W2 = OFF_B1 + NH, OFF_B2 = OFF_
               OFF_W3 = OFF_B2 + NH, OFF_B3 = OFF_W3 + NH;
 static_assert(OFF_B3 + 1 == afi::kMlpParams, "parameter layout");
 
-// round to nearest even (one hardware conversion on gfx950)
-__device__ __forceinline__ unsigned short to_bf16(float x) {
-  return __builtin_bit_cast(unsigned short, (__bf16)x);
+// two values rounded to nearest even, the first in the low half (one hardware
+// conversion on gfx950)
+__device__ __forceinline__ unsigned pack_bf16(float x, float y) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const bf16x2 v = {(__bf16)x, (__bf16)y};
+  return __builtin_bit_cast(unsigned, v);
 }
 // (rho, u, v, p) as FP32 from a cell average (FP64 arithmetic)
 __device__ __forceinline__ void prims_of(double gm1, const double* V, float* P) {
@@ -51,63 +54,59 @@ __device__ __forceinline__ void prims_of(double gm1, const double* V, float* P) 
 
 __device__ __forceinline__ float pos_or_tiny(float v) { return v > 1e-30f ? v : 1e-30f; }
 
-// features of face (d, i, j) from the primitives of its stencil cells:
-// cell(s, q, P) fills the (rho, u, v, p) of tangential offset s-1 and normal
-// offset q in (-2, -1, +1, +2).  Half h of the features (h = 0, 1; -1 for
-// all) is the triples of stencil cells 6h .. 6h+5 (cell 4s+q) and the
-// density ratios of q = 2h, 2h+1; put(n, value) receives feature n.
-template <typename CellFn, typename PutFn>
-__device__ __forceinline__ void features_of(int d, float gam, CellFn cell, PutFn put,
-                                            int h = -1) {
-  const int c0 = h < 0 ? 0 : 6 * h, c1 = h < 0 ? 12 : 6 * h + 6;
-  const int q0 = h < 0 ? 0 : 2 * h, q1 = h < 0 ? 4 : 2 * h + 2;
+// ln(x) from the hardware's log2, for x > 0 (values below the normal ones count
+// as the smallest of those)
+__device__ __forceinline__ float ln_fast(float x) {
+  // ln 2 in two parts, so that the product rounds once
+  constexpr float hi = 0.693147182464599609375f, lo = -1.90465429995776787854e-9f;
+  const float l = __builtin_amdgcn_logf(fmaxf(x, 0x1p-126f));
+  const float r = l * hi;
+  return r + fmaf(l, lo, fmaf(l, hi, -r));
+}
+
+// half H of the features of a face from the primitives of its stencil cells:
+// cell(s, q, P) fills (rho, u_n, u_t, p) in the face's frame of tangential
+// offset s-1 and normal offset q in (-2, -1, +1, +2).  The half is the triples
+// of stencil cells 6H .. 6H+5 (cell 4s+q), features 18H .. 18H+17, and the
+// density ratios of q = 2H, 2H+1, features 36+2H, 37+2H: twenty values f.
+template <int H, typename CellFn>
+__device__ __forceinline__ void features_of(float gam, CellFn cell, float* f) {
   // face values from the two cells that adjoin the face
   float A[4], B[4];
   cell(1, 1, A);
   cell(1, 2, B);
   const float rf = 0.5f * (A[0] + B[0]), pf = 0.5f * (A[3] + B[3]);
-  const float unf = 0.5f * (d == 0 ? A[1] + B[1] : A[2] + B[2]);
-  const float utf = 0.5f * (d == 0 ? A[2] + B[2] : A[1] + B[1]);
-  const float icf = 1.0f / sqrtf(gam * pos_or_tiny(pf) / pos_or_tiny(rf));
-  const float ipf = 1.0f / pos_or_tiny(pf), irf = 1.0f / pos_or_tiny(rf);
+  const float unf = 0.5f * (A[1] + B[1]), utf = 0.5f * (A[2] + B[2]);
+  const float pt = pos_or_tiny(pf), rt = pos_or_tiny(rf);
+  const float ipf = rcp(pt), irf = rcp(rt);
+  // gamma p / rho: the quotient by the reciprocal, rounded as the division
+  const float gp = gam * pt;
+  float c2 = gp * irf;
+  c2 = fmaf(fmaf(-rt, c2, gp), irf, c2);
+  const float icf = rcp(root(c2));
 #pragma unroll
-  for (int c = 0; c < 12; ++c) {
-    if (c < c0 || c >= c1) continue;
+  for (int c = 0; c < 6; ++c) {
     float P[4];
-    cell(c / 4, c % 4, P);
-    const float un = d == 0 ? P[1] : P[2], ut = d == 0 ? P[2] : P[1];
-    put(3 * c, __logf(pos_or_tiny(P[3]) * ipf));
-    put(3 * c + 1, (un - unf) * icf);
-    put(3 * c + 2, (ut - utf) * icf);
+    cell((6 * H + c) / 4, (6 * H + c) % 4, P);
+    f[3 * c] = ln_fast(pos_or_tiny(P[3]) * ipf);
+    f[3 * c + 1] = (P[1] - unf) * icf;
+    f[3 * c + 2] = (P[2] - utf) * icf;
   }
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    if (q < q0 || q >= q1) continue;
+  for (int q = 0; q < 2; ++q) {
     float P[4];
-    cell(1, q, P);
-    put(36 + q, __logf(pos_or_tiny(P[0]) * irf));
+    cell(1, 2 * H + q, P);
+    f[18 + q] = ln_fast(pos_or_tiny(P[0]) * irf);
   }
 }
 
-// tanh from the exponential: 1 - 2 / (1 + e^{2x}), with the hardware
-// exponential and reciprocal (the result feeds bfloat16 operands; its error
-// is far below their rounding)
-__device__ __forceinline__ float tanh_fast(float x) {
-  return 1.0f - 2.0f * __builtin_amdgcn_rcpf(1.0f + __expf(2.0f * x));
+// 1 / (1 + e^{2x}) with the hardware exponential and reciprocal: tanh x is
+// 1 - 2 of it (the result feeds bfloat16 operands; its error is far below their
+// rounding)
+__device__ __forceinline__ float sigma_fast(float x) {
+  return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(x * 2.885390043258666992f));
 }
-
-// stencil cell (ci, cj) of face (d, i, j) at tangential offset s-1, normal
-// offset index q
-__device__ __forceinline__ void stencil_cell(int d, int i, int j, int s, int q, int& ci, int& cj) {
-  const int m = q - 2;  // -2, -1, 0, +1 relative to cell b
-  if (d == 0) {
-    ci = i + m;
-    cj = j + s - 1;
-  } else {
-    ci = i + s - 1;
-    cj = j + m;
-  }
-}
+__device__ __forceinline__ float tanh_fast(float x) { return 1.0f - 2.0f * sigma_fast(x); }
 
 // ---------------------------------------------------------------------------
 // Blocks of faces: a workgroup of 256 threads takes up to 128 consecutive
@@ -185,19 +184,38 @@ __device__ __forceinline__ void stage_cells(const G2& g, double gm1, const doubl
   }
 }
 
-// half h of the features of face (i0 + fl, row) of block b
-template <typename PutFn>
+// half h of the features of face (i0 + fl, row) of block b; direction and half
+// are the same for a wave, and known to the code that reads the cells, so that
+// all reads of a face share one address
+template <int D, int H>
+__device__ __forceinline__ void face_features(const FaceBlock& b, const CellBlock& cell, float gam,
+                                              int fl, int row, float* f) {
+  // the cell of the face's own index, the one on its plus side
+  const float* at = &cell[0][row - b.r0][b.i0 + fl - b.c0];
+  constexpr int plane = (RB + 3) * CW;
+  features_of<H>(gam,
+                 [&](int s, int q, float* P) {
+                   const float* c = at + (D == 0 ? (s - 1) * CW + q - 2 : (q - 2) * CW + s - 1);
+                   P[0] = c[0];
+                   P[1] = c[(1 + D) * plane];
+                   P[2] = c[(2 - D) * plane];
+                   P[3] = c[3 * plane];
+                 },
+                 f);
+}
 __device__ __forceinline__ void block_features(const FaceBlock& b, const CellBlock& cell, float gam,
-                                               int fl, int row, int h, PutFn put) {
-  const int i = b.i0 + fl;
-  features_of(b.d, gam,
-              [&](int s, int q, float* P) {
-                int ci, cj;
-                stencil_cell(b.d, i, row, s, q, ci, cj);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) P[k] = cell[k][cj - b.r0][ci - b.c0];
-              },
-              put, h);
+                                               int fl, int row, int h, float* f) {
+  if (b.d == 0) {
+    if (h == 0)
+      face_features<0, 0>(b, cell, gam, fl, row, f);
+    else
+      face_features<0, 1>(b, cell, gam, fl, row, f);
+  } else {
+    if (h == 0)
+      face_features<1, 0>(b, cell, gam, fl, row, f);
+    else
+      face_features<1, 1>(b, cell, gam, fl, row, f);
+  }
 }
 
 // index of the first face of a block's row
@@ -221,15 +239,23 @@ __global__ void __launch_bounds__(256) k_features(G2 g, double gm1, float gam,
                                                   float* __restrict__ out, FaceBlocks fb) {
   __shared__ CellBlock cell;
   __shared__ float feat[IB * OROW];
-  const int tid = threadIdx.x, fl = tid & (IB - 1), half = tid / IB;
+  const int tid = threadIdx.x, fl = tid & (IB - 1);
+  const int half = __builtin_amdgcn_readfirstlane(tid / IB);
   for (long blk = blockIdx.x; blk < fb.nblocks; blk += gridDim.x) {
     const FaceBlock B = block_of(g, fb, blk);
     stage_cells(g, gm1, U, B, cell);
     for (int rr = 0; rr < B.nr; ++rr) {
       const int row = B.row0 + rr;
       __syncthreads();  // the cells are in; the previous row is written
-      if (fl < B.cnt)
-        block_features(B, cell, gam, fl, row, half, [&](int n, float v) { feat[fl * OROW + n] = v; });
+      if (fl < B.cnt) {
+        float f[20];
+        block_features(B, cell, gam, fl, row, half, f);
+        float* o = feat + fl * OROW;
+#pragma unroll
+        for (int n = 0; n < 18; ++n) o[18 * half + n] = f[n];
+        o[36 + 2 * half] = f[18];
+        o[37 + 2 * half] = f[19];
+      }
       __syncthreads();
       float* o = out + first_face(g, B, row) * NIN;
       for (int e = tid; e < B.cnt * NIN; e += 256) o[e] = feat[e / NIN * OROW + e % NIN];
@@ -251,6 +277,12 @@ __global__ void __launch_bounds__(256) k_features(G2 g, double gm1, float gam,
 // layer 2's weights are stored.  So hidden values never leave the
 // registers, and the output layer's sum over units ends with one exchange
 // between the two halves of the wave.
+//
+// The vector units bound it: 128 activations of an exponential and a
+// reciprocal per face, then the features.  Activations of six instructions
+// (output layer: four) and features that share an address, one reciprocal per
+// quotient and packed stores take 62 us at 1000 x 500 and 237 at 2048 x 1024
+// (eight and six, and features selected by direction and half: 74 and 277).
 // ---------------------------------------------------------------------------
 constexpr int KIN = 48;                 // inputs padded to three K steps of 16
 constexpr int FROW = KIN + 8;           // feature row (bf16; 16-byte aligned)
@@ -262,7 +294,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 struct InferShared {
   CellBlock cell;
   unsigned short feat[IB * FROW];
-  float b1[NH], b2[NH], w3[NH];         // biases, and the output weights (bf16 values)
+  float b1[NH], b2[NH], w3[NH];         // biases, and -2 times the output weights (bf16 values)
   // layer 2's A operands, per lane (in LDS rather than registers: with them
   // in registers the kernel holds 188 VGPRs, two waves per SIMD, and ran 18 %
   // slower at 2048 x 1024)
@@ -291,7 +323,6 @@ __global__ void __launch_bounds__(256, 3) k_infer(G2 g, double gm1, float gam,
   __shared__ InferShared S;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int h = lane >> 5, c32 = lane & 31;
-  const float b3 = p[OFF_B3];
   // A operands: lane (m = c32, h) holds row 32 nb + m, inputs 16 kb + 8 h + e
   // (layer 2's written to LDS by the first wave, read after the first
   // barrier), from the FP32 parameters: each workgroup rounds them for itself
@@ -325,11 +356,17 @@ __global__ void __launch_bounds__(256, 3) k_infer(G2 g, double gm1, float gam,
     }
   }
   static_assert(NIN % 8 == 0, "whole groups of eight inputs");
+  if (tid < IB)  // inputs 40..47 of every face are zero
+#pragma unroll
+    for (int n = 0; n < KIN - NIN; ++n) S.feat[tid * FROW + NIN + n] = 0;
   if (tid < NH) {
     S.b1[tid] = p[OFF_B1 + tid];
     S.b2[tid] = p[OFF_B2 + tid];
-    S.w3[tid] = (float)(__bf16)p[OFF_W3 + tid];
+    S.w3[tid] = -2.0f * (float)(__bf16)p[OFF_W3 + tid];
   }
+  float z0 = p[OFF_B3];  // plus the sum of the output weights: z where all sigma are 0
+#pragma unroll 8
+  for (int k = 0; k < NH; ++k) z0 += (float)(__bf16)p[OFF_W3 + k];
   for (long blk = blockIdx.x; blk < fb.nblocks; blk += gridDim.x) {
     // (held one block ahead, the loads of the averages took more registers
     // than three workgroups per CU leave; the other workgroups on the CU hide
@@ -341,18 +378,16 @@ __global__ void __launch_bounds__(256, 3) k_infer(G2 g, double gm1, float gam,
       const int row = B.row0 + rr;
       __syncthreads();  // the cells are in; the previous row is done with the features
       {
-        // two threads per face, one half of its features each; inputs 40..47
-        // are zero
-        const int fl = tid & (IB - 1), half = tid / IB;
-        unsigned short* fo = S.feat + fl * FROW;
-        if (fl < cnt) {
-          block_features(B, S.cell, gam, fl, row, half,
-                         [&](int n, float v) { fo[n] = to_bf16(v); });
-        } else {
-          for (int n = half; n < NIN; n += 2) fo[n] = 0;
-        }
+        // two threads per face, one half of its features each
+        const int fl = tid & (IB - 1), half = __builtin_amdgcn_readfirstlane(tid / IB);
+        float f[20];
 #pragma unroll
-        for (int n = 0; n < 4; ++n) fo[NIN + 4 * half + n] = 0;
+        for (int n = 0; n < 20; ++n) f[n] = 0.0f;
+        if (fl < cnt) block_features(B, S.cell, gam, fl, row, half, f);
+        unsigned* fo = reinterpret_cast<unsigned*>(S.feat + fl * FROW);
+#pragma unroll
+        for (int n = 0; n < 9; ++n) fo[9 * half + n] = pack_bf16(f[2 * n], f[2 * n + 1]);
+        fo[18 + half] = pack_bf16(f[18], f[19]);
       }
       __syncthreads();
       // the wave's 32 faces: lane (c32, h) works on face 32 wave + c32
@@ -381,35 +416,41 @@ __global__ void __launch_bounds__(256, 3) k_infer(G2 g, double gm1, float gam,
           for (int i = 0; i < 4; ++i)
             hb[2 * nb + (j >> 1)][4 * (j & 1) + i] = (__bf16)tanh_fast(acc[nb][4 * j + i] + bj[i]);
         }
+      // layer 2, summed up from its bias
 #pragma unroll
       for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[nb][r] = 0.0f;
+        for (int j = 0; j < 4; ++j) {
+          const float4 bias = *reinterpret_cast<const float4*>(&S.b2[32 * nb + 8 * j + 4 * h]);
+          acc[nb][4 * j] = bias.x;
+          acc[nb][4 * j + 1] = bias.y;
+          acc[nb][4 * j + 2] = bias.z;
+          acc[nb][4 * j + 3] = bias.w;
+        }
 #pragma unroll
       for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
         for (int nb = 0; nb < 2; ++nb)
           acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(S.a2[nb][kb][lane], hb[kb], acc[nb], 0, 0, 0);
-      // z = w3 . tanh(W2 h1 + b2) + b3: this lane's 32 units of its face, then
-      // the other half's 32 from the lane 32 away
+      // z = w3 . tanh(W2 h1 + b2) + b3, as (sum of w3 + b3) + (-2 w3) . sigma:
+      // this lane's 32 units of its face, then the other half's 32 from the
+      // lane 32 away
       float z = 0.0f;
 #pragma unroll
       for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const int u = 32 * nb + 8 * j + 4 * h;
-          const float4 bias = *reinterpret_cast<const float4*>(&S.b2[u]);
-          const float4 ow = *reinterpret_cast<const float4*>(&S.w3[u]);
-          z += ow.x * tanh_fast(acc[nb][4 * j] + bias.x);
-          z += ow.y * tanh_fast(acc[nb][4 * j + 1] + bias.y);
-          z += ow.z * tanh_fast(acc[nb][4 * j + 2] + bias.z);
-          z += ow.w * tanh_fast(acc[nb][4 * j + 3] + bias.w);
+          const float4 ow = *reinterpret_cast<const float4*>(&S.w3[32 * nb + 8 * j + 4 * h]);
+          z += ow.x * sigma_fast(acc[nb][4 * j]);
+          z += ow.y * sigma_fast(acc[nb][4 * j + 1]);
+          z += ow.z * sigma_fast(acc[nb][4 * j + 2]);
+          z += ow.w * sigma_fast(acc[nb][4 * j + 3]);
         }
       z += __shfl_xor(z, 32, 64);
       const int m = 32 * wave + c32;
       if (h == 0 && m < cnt) {
         const long f = first_face(g, B, row) + m;
-        theta[f] = fminf(fmaxf(z + b3, 0.0f), 1.0f);
+        theta[f] = fminf(fmaxf(z + z0, 0.0f), 1.0f);
       }
     }
   }
