@@ -208,8 +208,8 @@ hipError_t launch_coef(const afi::Geo& g, const afd::Phys& ph, const afi::Work& 
     if ((e = afi::blend_infer(g, ph, Uk, w.net, w.blend, s, tm)) != hipSuccess) return e;
     sc.blend = w.blend;
   }
-  return g.dim == 1 ? afi::stage1d(g, ph, w, Un, Uk, Uout, dt_dev, dt_host, sc, s, tm)
-                    : afi::stage2d(g, ph, w, Un, Uk, Uout, dt_dev, dt_host, sc, s, tm);
+  const auto stage = g.dim == 1 ? afi::stage1d : (g.mixed ? afi::strips_mixed : afi::strips_fp64);
+  return stage(g, ph, w, Un, Uk, Uout, dt_dev, dt_host, sc, s, tm);
 }
 
 hipError_t launch_stage(const afi::Geo& g, const afd::Phys& ph, const afi::Work& w, int k,
@@ -552,9 +552,9 @@ hipError_t batch_slot(const BatchPath& p, int rounds, hipStream_t q) {
           return e;
       if ((e = afi::batch_decide(p.inst, p.n, p.nact, q)) != hipSuccess) return e;
     } else {
+      const auto stage = p.mixed ? afi::strips_dev_mixed : afi::strips_dev_fp64;
       for (int k = 0; k < 3; ++k)
-        if ((e = afi::stage2d_dev(p.mixed, p.inst, p.wg_inst, p.nwg, (double2*)p.partial, k, q)) !=
-            hipSuccess)
+        if ((e = stage(p.inst, p.wg_inst, p.nwg, (double2*)p.partial, k, q)) != hipSuccess)
           return e;
       if ((e = afi::batch_advance(p.inst, p.n, (const double2*)p.partial, q)) != hipSuccess)
         return e;
@@ -1180,12 +1180,13 @@ af_status af_run_graph(af_ctx* c, double* U, void* ws, void* stream, double t0, 
   c->run_dev = dev;
   c->run_nwg = nwg;
   // a round: one RK3 attempt, then accept or halve, and open the next step
+  const auto stage = g.mixed ? afi::strips_dev_mixed : afi::strips_dev_fp64;
   auto slot = [&](hipStream_t q) {
     hipError_t e = hipSuccess;
     for (int a = 0; a < attempts_per_slot && e == hipSuccess; ++a) {
       if (!maxima) e = open(q);
       for (int k = 0; k < 3 && e == hipSuccess; ++k)
-        e = afi::stage2d_dev(g.mixed, w.binst, nullptr, nwg, maxima, k, q);
+        e = stage(w.binst, nullptr, nwg, maxima, k, q);
       if (e != hipSuccess) break;
       e = maxima ? afi::batch_advance(w.binst, 1, maxima, q)
                  : afi::batch_decide(w.binst, 1, w.bnact, q);
@@ -1268,7 +1269,8 @@ af_status af_rk_stage_blend(af_ctx* c, int k, const double* dt_dev, double dt_ho
     AF_HIP(afi::blend_infer(g, ph, Uk, c->net, w.blend, s, c->timer));
     sc.blend = w.blend;
   }
-  AF_HIP(afi::stage2d(g, ph, w, Un, Uk, Uout, dt_dev, dt_host, sc, s, c->timer));
+  const auto stage = g.mixed ? afi::strips_mixed : afi::strips_fp64;
+  AF_HIP(stage(g, ph, w, Un, Uk, Uout, dt_dev, dt_host, sc, s, c->timer));
   return AF_OK;
 }
 

@@ -152,10 +152,13 @@ hipError_t mlp_adam(float* params, const float* grad, float* m, float* v, long s
                     hipStream_t s);
 
 // launchers (enqueue on stream; return the first HIP error)
-// the 2D stage of one instance (af_strip2d.hip)
-hipError_t stage2d(const Geo& g, const afd::Phys& ph, const Work& w, const double* Un,
-                   const double* Uk, double* Uout, const double* dt_dev, double dt_host,
-                   StageCoef sc, hipStream_t s, Timer* tm);
+// the 2D stage of one instance (af_strip2d.hip, one object per arithmetic type)
+hipError_t strips_fp64(const Geo& g, const afd::Phys& ph, const Work& w, const double* Un,
+                       const double* Uk, double* Uout, const double* dt_dev, double dt_host,
+                       StageCoef sc, hipStream_t s, Timer* tm);
+hipError_t strips_mixed(const Geo& g, const afd::Phys& ph, const Work& w, const double* Un,
+                        const double* Uk, double* Uout, const double* dt_dev, double dt_host,
+                        StageCoef sc, hipStream_t s, Timer* tm);
 // one 1D stage; a whole 1D step from U to Uout (other memory) in one launch
 hipError_t stage1d(const Geo& g, const afd::Phys& ph, const Work& w, const double* Un,
                    const double* Uk, double* Uout, const double* dt_dev, double dt_host,
@@ -235,8 +238,10 @@ bool strip_shapes(const Geo* g, int n, StripShape* out);
 // stage k of the current attempt of every active instance of a batch: nwg
 // workgroups, instance wg_inst[wg] each (NULL: the first).  Stage 2 leaves the
 // CFL maxima of the new states per workgroup in cfl_partial, if not NULL.
-hipError_t stage2d_dev(int mixed, BatchInst* inst, const int* wg_inst, int nwg,
-                       double2* cfl_partial, int k, hipStream_t s);
+hipError_t strips_dev_fp64(BatchInst* inst, const int* wg_inst, int nwg, double2* cfl_partial,
+                           int k, hipStream_t s);
+hipError_t strips_dev_mixed(BatchInst* inst, const int* wg_inst, int nwg, double2* cfl_partial,
+                            int k, hipStream_t s);
 // after an attempt on strips: the decision of batch_decide, and the opening of
 // the next step from the maxima stage 2 left
 hipError_t batch_advance(BatchInst* inst, int n, const double2* partial, hipStream_t s);

@@ -1442,7 +1442,19 @@ Strips strips_of(const afi::Geo& g) {
   return b;
 }
 
-template <typename R>
+// One object file holds the kernels of one arithmetic type, each with its own
+// scheduling: with FP32 stencils there are registers to spare, and ordering the
+// instructions for independence of neighbours is worth 5 % (82 -> 78 us at 1000
+// x 500); the FP64 kernel spills over a hundred registers that way.
+#ifndef AF_STRIP_REAL
+#define AF_STRIP_REAL double
+#define AF_STRIP_ENTRY(name) name##_fp64
+#define AF_STRIP_SHAPES  // (once, in this object)
+#else
+#define AF_STRIP_ENTRY(name) name##_mixed
+#endif
+using Real = AF_STRIP_REAL;
+
 hipError_t launch(const afi::Geo& geo, const Phys& ph, const afi::Work& w, const double* Un,
                   const double* Uk, double* Uout, const double* dt_dev, double dt_host,
                   afi::StageCoef sc, hipStream_t s, afi::Timer* tm) {
@@ -1467,9 +1479,9 @@ hipError_t launch(const afi::Geo& geo, const Phys& ph, const afi::Work& w, const
   sa.ts_out = sc.ts_out;
   const dim3 grid((unsigned)(b.nx * b.ny));
   if (sa.blend || sa.ts_out)
-    AFI_TIMED(tm, 7, s, hipLaunchKernelGGL((k_strip<R, true, false>), grid, dim3(NT), 0, s, sa));
+    AFI_TIMED(tm, 7, s, hipLaunchKernelGGL((k_strip<Real, true, false>), grid, dim3(NT), 0, s, sa));
   else
-    AFI_TIMED(tm, 7, s, hipLaunchKernelGGL((k_strip<R, false, false>), grid, dim3(NT), 0, s, sa));
+    AFI_TIMED(tm, 7, s, hipLaunchKernelGGL((k_strip<Real, false, false>), grid, dim3(NT), 0, s, sa));
   return hipGetLastError();
 }
 
@@ -1477,6 +1489,7 @@ hipError_t launch(const afi::Geo& geo, const Phys& ph, const afi::Work& w, const
 
 namespace afi {
 
+#ifdef AF_STRIP_SHAPES
 StripShape strip_shape(const Geo& g) {
   const Strips b = strips_of(g);
   return StripShape{b.nx, b.ny, b.H};
@@ -1527,16 +1540,16 @@ bool strip_shapes(const Geo* g, int n, StripShape* out) {
   const long rounds = (tiles + cus - 1) / cus;
   return best <= (g[0].mixed ? 24 * rounds + 2 : 13 * rounds + 6);
 }
+#endif
 
-hipError_t stage2d(const Geo& geo, const Phys& ph, const Work& w, const double* Un,
-                   const double* Uk, double* Uout, const double* dt_dev, double dt_host,
-                   StageCoef sc, hipStream_t s, Timer* tm) {
-  return geo.mixed ? launch<float>(geo, ph, w, Un, Uk, Uout, dt_dev, dt_host, sc, s, tm)
-                   : launch<double>(geo, ph, w, Un, Uk, Uout, dt_dev, dt_host, sc, s, tm);
+hipError_t AF_STRIP_ENTRY(strips)(const Geo& geo, const Phys& ph, const Work& w, const double* Un,
+                                  const double* Uk, double* Uout, const double* dt_dev,
+                                  double dt_host, StageCoef sc, hipStream_t s, Timer* tm) {
+  return launch(geo, ph, w, Un, Uk, Uout, dt_dev, dt_host, sc, s, tm);
 }
 
-hipError_t stage2d_dev(int mixed, BatchInst* inst, const int* wg_inst, int nwg,
-                       double2* cfl_partial, int k, hipStream_t s) {
+hipError_t AF_STRIP_ENTRY(strips_dev)(BatchInst* inst, const int* wg_inst, int nwg,
+                                      double2* cfl_partial, int k, hipStream_t s) {
   StripArgs sa{};
   sa.inst = inst;
   sa.wg_inst = wg_inst;
@@ -1545,10 +1558,7 @@ hipError_t stage2d_dev(int mixed, BatchInst* inst, const int* wg_inst, int nwg,
   sa.ca = k == 0 ? 0.0 : (k == 1 ? 0.75 : 1.0 / 3.0);
   sa.cb = k == 0 ? 1.0 : (k == 1 ? 0.25 : 2.0 / 3.0);
   sa.first = k == 0;
-  if (mixed)
-    hipLaunchKernelGGL((k_strip<float, false, true>), dim3((unsigned)nwg), dim3(NT), 0, s, sa);
-  else
-    hipLaunchKernelGGL((k_strip<double, false, true>), dim3((unsigned)nwg), dim3(NT), 0, s, sa);
+  hipLaunchKernelGGL((k_strip<Real, false, true>), dim3((unsigned)nwg), dim3(NT), 0, s, sa);
   return hipGetLastError();
 }
 
