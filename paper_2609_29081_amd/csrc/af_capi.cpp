@@ -298,10 +298,10 @@ hipError_t rk54(const afi::Geo& g, const afd::Phys& ph, const afi::Work& w, cons
 
 hipError_t launch_cfl(const af_ctx* c, const afi::Geo& g, const afi::Work& w, const double* U,
                       double t_host, const double* t_dev, double t_final, double* dt_out,
-                      hipStream_t s) {
+                      hipStream_t s, double* save = nullptr) {
   const af_params& p = c->p;
   return afi::cfl_dt(g, physics(p), p.cfl_c, p.cfl_v, 4.0 * p.mu / 3.0, p.gamma * p.mu / p.Pr, w,
-                     U, t_host, t_dev, t_final, dt_out, s, c->timer);
+                     U, t_host, t_dev, t_final, dt_out, save, s, c->timer);
 }
 
 // the CFL step of a 1D step that fixes dt itself, as launch_cfl takes it
@@ -563,11 +563,12 @@ hipError_t batch_slot(const BatchPath& p, int rounds, hipStream_t q) {
   return hipSuccess;
 }
 
-// Enqueue step slots (slot(stream) enqueues one) for the n instances whose
-// descriptors (host copies h, already on the device at dinst) are set, on
-// stream s: captured once in a HIP graph (use_graph) or launched directly,
-// in chunks of up to `chunk` slots (`rounds` rounds each) with a read-back of the descriptors after each; stops
-// once no instance is active or may open a step.  h receives the final
+// Enqueue step slots (slot(stream, r) enqueues one of r rounds) for the n
+// instances whose descriptors (host copies h, already on the device at dinst)
+// are set, on stream s: captured once in a HIP graph (use_graph) or launched
+// directly, in chunks of up to `chunk` slots of `rounds` rounds (the last one of
+// what the steps left need) with a read-back of the descriptors after each;
+// stops once no instance is active or may open a step.  h receives the final
 // descriptors.
 // keep (cache != NULL): the instantiated graph is taken from *cache if set
 // there, else built and left in *cache for the caller to reuse and destroy.
@@ -585,7 +586,7 @@ af_status run_slots(Slot slot, int rounds, afi::BatchInst* dinst, int n, int use
     hipStream_t cs = nullptr;
     AF_HIP(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
     hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeRelaxed);
-    if (e == hipSuccess) e = slot(cs);
+    if (e == hipSuccess) e = slot(cs, rounds);
     hipGraph_t gcap = nullptr;
     const hipError_t e2 = hipStreamEndCapture(cs, &gcap);
     (void)hipStreamDestroy(cs);
@@ -612,7 +613,8 @@ af_status run_slots(Slot slot, int rounds, afi::BatchInst* dinst, int n, int use
     // steps of a batch: 750 of its 2460 us)
     const long slots = std::max(1L, std::min(chunk, (left + rounds - 1) / rounds));
     for (long c = 0; c < slots; ++c) {
-      const hipError_t e = exec ? hipGraphLaunch(exec, s) : slot(s);
+      const hipError_t e =
+          exec ? hipGraphLaunch(exec, s) : slot(s, (int)std::min((long)rounds, left - c * rounds));
       if (e != hipSuccess) {
         st = fail(AF_E_HIP, "%s: launch: %s", who, hipGetErrorString(e));
         break;
@@ -874,19 +876,22 @@ static af_status step_in(af_ctx* c, double* U, void* ws, void* stream, double dt
   const afi::Work w = work_of(c, g, ws);
   const hipStream_t s = (hipStream_t)stream;
   const afd::Phys ph = physics(c->p);
-  AF_HIP(afi::copy_state(w.SAVE, U, g.state_len, s, w.flags));
   // the CFL step stays on the device for the first attempt; the host reads it
   // with the flags
   const double* dt_dev = nullptr;
   afi::StepExtras1 x{};
-  if (dt <= 0.0) {
+  const bool cfl = dt <= 0.0;
+  if (cfl && !afi::step1d_takes_cfl(g)) {
     dt_dev = w.scal;
-    if (afi::step1d_takes_cfl(g))
+    AF_HIP(launch_cfl(c, g, w, U, t, nullptr, t_final, w.scal, s, w.SAVE));
+  } else {
+    AF_HIP(afi::copy_state(w.SAVE, U, g.state_len, s, w.flags));
+    if (cfl) {
+      dt_dev = w.scal;
       x.cfl = step_cfl(c, g, t, nullptr, t_final);
-    else
-      AF_HIP(launch_cfl(c, g, w, U, t, nullptr, t_final, w.scal, s));
-  } else if (t + dt > t_final) {
-    dt = t_final - t;
+    } else if (t + dt > t_final) {
+      dt = t_final - t;
+    }
   }
   unsigned fl = 0;
   int h;
@@ -1121,7 +1126,7 @@ af_status af_batch_run(af_batch* b, double* const* U, void* ws, void* stream, do
   if ((sd = upload_batch(b, h, buf, base, s)) != AF_OK) return sd;
   const BatchPath path = batch_path(b, b->strips ? nullptr : b->var, base, total_tiles);
   AF_HIP(batch_start(path, s));
-  auto slot = [&](hipStream_t q) { return batch_slot(path, attempts_per_slot, q); };
+  auto slot = [&](hipStream_t q, int rounds) { return batch_slot(path, rounds, q); };
   const af_status st =
       run_slots(slot, attempts_per_slot, path.inst, n, use_graph, s, max_steps, t_final, h,
                 "af_batch_run");
@@ -1181,9 +1186,9 @@ af_status af_run_graph(af_ctx* c, double* U, void* ws, void* stream, double t0, 
   c->run_nwg = nwg;
   // a round: one RK3 attempt, then accept or halve, and open the next step
   const auto stage = g.mixed ? afi::strips_dev_mixed : afi::strips_dev_fp64;
-  auto slot = [&](hipStream_t q) {
+  auto slot = [&](hipStream_t q, int rounds) {
     hipError_t e = hipSuccess;
-    for (int a = 0; a < attempts_per_slot && e == hipSuccess; ++a) {
+    for (int a = 0; a < rounds && e == hipSuccess; ++a) {
       if (!maxima) e = open(q);
       for (int k = 0; k < 3 && e == hipSuccess; ++k)
         e = stage(w.binst, nullptr, nwg, maxima, k, q);

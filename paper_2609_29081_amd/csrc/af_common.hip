@@ -1,5 +1,7 @@
 // af_common.hip -- CFL time-step reduction (eq. cfl), device-side time
 // bookkeeping, flag handling and the workspace layout.
+#include <algorithm>
+
 #include "af_device.hpp"
 #include "af_internal.hpp"
 
@@ -9,6 +11,11 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kMaxCflBlocks = 1024;
+constexpr int kOneBlock = 1024;
+// cells up to which one block takes a CFL step's maxima alone, in the launch
+// that saves the state: af_step of 64 x 32 takes 63.0 us so, 66.9 with the
+// reduction in two launches and the copy in a third; at 128 x 64 71.0 and 69.9
+constexpr long kOneBlockCells = 4096;
 
 __device__ __forceinline__ double wave_max(double v) {
 #pragma unroll
@@ -16,9 +23,10 @@ __device__ __forceinline__ double wave_max(double v) {
   return v;
 }
 
-// block max of two values; the result is valid in thread 0
+// max of two values over a block of N threads; the result is valid in thread 0
+template <int N>
 __device__ __forceinline__ void block_max2(double& a, double& b) {
-  __shared__ double sa[kBlock / 64], sb[kBlock / 64];
+  __shared__ double sa[N / 64], sb[N / 64];
   a = wave_max(a);
   b = wave_max(b);
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
@@ -28,61 +36,106 @@ __device__ __forceinline__ void block_max2(double& a, double& b) {
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int k = 1; k < kBlock / 64; ++k) {
+    for (int k = 1; k < N / 64; ++k) {
       a = mx(a, sa[k]);
       b = mx(b, sb[k]);
     }
   }
 }
 
+// a CFL step from the state U: its ncell averages, and where t comes from
+struct CflArgs {
+  int dim;
+  long ncell;
+  double gm1, gam, icx, icy, vcoef;
+  const double* U;
+  double t_host;
+  const double* t_dev;
+  double t_final;
+  double* dt_out;
+  // a step attempt's start, beside it: U's n values to save, flags cleared
+  double* save;
+  long n;
+  unsigned* flags;
+};
+
 // per-cell inviscid and viscous rates (eq. cfl): max_l (|u_l|+c)/(C^c dx_l)
-// and rho~/(C^v min_l dx_l^2), rho~ = max(4mu/3, gamma mu/Pr)/rho
-__global__ void __launch_bounds__(kBlock) k_cfl(int dim, long ncell, double gm1, double gam,
-                                                double icx, double icy, double vcoef,
-                                                const double* __restrict__ U,
-                                                double* __restrict__ partial) {
-  double a = 0.0, v = 0.0;
-  for (long c = (long)blockIdx.x * blockDim.x + threadIdx.x; c < ncell;
-       c += (long)gridDim.x * blockDim.x) {
+// and rho~/(C^v min_l dx_l^2), rho~ = max(4mu/3, gamma mu/Pr)/rho; the maxima
+// over cells first, first + step, ...
+__device__ __forceinline__ void cfl_rates(const CflArgs& A, long first, long step, double& a,
+                                          double& v) {
+  const double* __restrict__ U = A.U;
+  const long n = A.ncell;
+  for (long c = first; c < n; c += step) {
     const double r = U[c];
-    if (dim == 1) {
-      const double m = U[ncell + c], E = U[2 * ncell + c];
-      const double p = pressure1(r, m, E, gm1);
-      const double cs = root(gam * p / r);
-      a = mx(a, (fabs(m / r) + cs) * icx);
+    if (A.dim == 1) {
+      const double m = U[n + c], E = U[2 * n + c];
+      const double p = pressure1(r, m, E, A.gm1);
+      const double cs = root(A.gam * p / r);
+      a = mx(a, (fabs(m / r) + cs) * A.icx);
     } else {
-      const double m1 = U[ncell + c], m2 = U[2 * ncell + c], E = U[3 * ncell + c];
-      const double p = pressure2(r, m1, m2, E, gm1);
-      const double cs = root(gam * p / r);
-      a = mx(a, (fabs(m1 / r) + cs) * icx);
-      a = mx(a, (fabs(m2 / r) + cs) * icy);
+      const double m1 = U[n + c], m2 = U[2 * n + c], E = U[3 * n + c];
+      const double p = pressure2(r, m1, m2, E, A.gm1);
+      const double cs = root(A.gam * p / r);
+      a = mx(a, (fabs(m1 / r) + cs) * A.icx);
+      a = mx(a, (fabs(m2 / r) + cs) * A.icy);
     }
-    v = mx(v, vcoef / r);
+    v = mx(v, A.vcoef / r);
   }
-  block_max2(a, v);
+}
+// dt = 1/(a+v), clipped to t_final - t
+__device__ __forceinline__ void cfl_finish(const CflArgs& A, double a, double v) {
+  const double t = A.t_dev ? *A.t_dev : A.t_host;
+  double dt = 1.0 / (a + v);
+  if (t + dt > A.t_final) dt = A.t_final - t;
+  if (!(dt > 0.0)) dt = 0.0;
+  *A.dt_out = dt;
+}
+__device__ __forceinline__ void save_state(const CflArgs& A, long first, long step) {
+  if (!A.save) return;
+  const double* __restrict__ U = A.U;
+  double* __restrict__ d = A.save;
+#pragma unroll 4
+  for (long i = first; i < A.n; i += step) d[i] = U[i];
+  if (first == 0) *A.flags = 0u;
+}
+
+// partial maxima per block, and the saved state
+__global__ void __launch_bounds__(kBlock) k_cfl(CflArgs A, double* __restrict__ partial) {
+  const long first = (long)blockIdx.x * kBlock + threadIdx.x, step = (long)gridDim.x * kBlock;
+  double a = 0.0, v = 0.0;
+  cfl_rates(A, first, step, a, v);
+  save_state(A, first, step);
+  block_max2<kBlock>(a, v);
   if (threadIdx.x == 0) {
     partial[blockIdx.x] = a;
     partial[gridDim.x + blockIdx.x] = v;
   }
 }
-
-// final reduction: dt = 1/(a+v), clipped to t_final - t
-__global__ void __launch_bounds__(kBlock) k_cfl_finish(const double* __restrict__ partial, int nb,
-                                                       double t_host, const double* t_dev,
-                                                       double t_final, double* dt_out) {
+// the step from them
+__global__ void __launch_bounds__(kBlock) k_cfl_finish(CflArgs A, const double* __restrict__ partial,
+                                                       int nb) {
   double a = 0.0, v = 0.0;
-  for (int k = threadIdx.x; k < nb; k += blockDim.x) {
+  for (int k = threadIdx.x; k < nb; k += kBlock) {
     a = mx(a, partial[k]);
     v = mx(v, partial[nb + k]);
   }
-  block_max2(a, v);
-  if (threadIdx.x == 0) {
-    const double t = t_dev ? *t_dev : t_host;
-    double dt = 1.0 / (a + v);
-    if (t + dt > t_final) dt = t_final - t;
-    if (!(dt > 0.0)) dt = 0.0;
-    *dt_out = dt;
+  block_max2<kBlock>(a, v);
+  if (threadIdx.x == 0) cfl_finish(A, a, v);
+}
+
+// a small grid's step in one launch: the first block takes all cells, the
+// others save the state
+__global__ void __launch_bounds__(kOneBlock) k_cfl_one(CflArgs A) {
+  if (blockIdx.x > 0) {
+    save_state(A, (long)(blockIdx.x - 1) * kOneBlock + threadIdx.x,
+               (long)(gridDim.x - 1) * kOneBlock);
+    return;
   }
+  double a = 0.0, v = 0.0;
+  cfl_rates(A, threadIdx.x, kOneBlock, a, v);
+  block_max2<kOneBlock>(a, v);
+  if (threadIdx.x == 0) cfl_finish(A, a, v);
 }
 
 // t += dt and count the step if dt > 0 (scal[0] dt, scal[1] t, scal[2] steps)
@@ -186,7 +239,7 @@ __global__ void __launch_bounds__(kBlock) k_batch_cfl(afi::BatchInst* inst, doub
     a = mx(a, (fabs(m2 / r) + cs) * I.icy);
     v = mx(v, I.vcoef / r);
   }
-  block_max2(a, v);
+  block_max2<kBlock>(a, v);
   if (threadIdx.x == 0) {
     double* q = partial + 2L * gridDim.x * blockIdx.y;
     q[blockIdx.x] = a;
@@ -235,7 +288,7 @@ __global__ void __launch_bounds__(kBlock) k_batch_open(afi::BatchInst* inst, int
         a = mx(a, partial[k]);
         v = mx(v, partial[nb + k]);
       }
-      block_max2(a, v);
+      block_max2<kBlock>(a, v);
       if (threadIdx.x == 0) open_one(I, a, v);
     }
   } else {
@@ -352,22 +405,37 @@ size_t workspace_layout(const Geo& g, Work* w, char* base) {
 
 hipError_t cfl_dt(const Geo& g, const Phys& ph, double cfl_c, double cfl_v, double visc_a,
                   double visc_b, const Work& w, const double* U, double t_host,
-                  const double* t_dev, double t_final, double* dt_out, hipStream_t s,
+                  const double* t_dev, double t_final, double* dt_out, double* save, hipStream_t s,
                   Timer* tm) {
-  const long ncell = g.dim == 1 ? (long)g.n1 : (long)g.n1 * g.n2;
-  long nb = (ncell + kBlock - 1) / kBlock;
-  if (nb > w.nb_cfl) nb = w.nb_cfl;
-  if (nb < 1) nb = 1;
+  CflArgs A{};
+  A.dim = g.dim;
+  A.ncell = g.dim == 1 ? (long)g.n1 : (long)g.n1 * g.n2;
+  A.gm1 = ph.gm1;
+  A.gam = ph.gam;
   const double hmin = g.dim == 1 ? g.dx : fmin(g.dx, g.dy);
-  const double vcoef = fmax(visc_a, visc_b) / (cfl_v * hmin * hmin);
-  const double icx = 1.0 / (cfl_c * g.dx);
-  const double icy = g.dim == 1 ? 0.0 : 1.0 / (cfl_c * g.dy);
+  A.vcoef = fmax(visc_a, visc_b) / (cfl_v * hmin * hmin);
+  A.icx = 1.0 / (cfl_c * g.dx);
+  A.icy = g.dim == 1 ? 0.0 : 1.0 / (cfl_c * g.dy);
+  A.U = U;
+  A.t_host = t_host;
+  A.t_dev = t_dev;
+  A.t_final = t_final;
+  A.dt_out = dt_out;
+  A.save = save;
+  A.n = g.state_len;
+  A.flags = w.flags;
+  if (A.ncell <= kOneBlockCells) {
+    const long nb = save ? 1 + (A.n + 4L * kOneBlock - 1) / (4L * kOneBlock) : 1;
+    AFI_TIMED(tm, 6, s,
+              hipLaunchKernelGGL(k_cfl_one, dim3((unsigned)nb), dim3(kOneBlock), 0, s, A));
+    return hipGetLastError();
+  }
+  const long nb = std::min((A.ncell + kBlock - 1) / kBlock, (long)w.nb_cfl);
   AFI_TIMED(tm, 6, s,
-            hipLaunchKernelGGL(k_cfl, dim3((unsigned)nb), dim3(kBlock), 0, s, g.dim, ncell, ph.gm1,
-                               ph.gam, icx, icy, vcoef, U, w.partial));
+            hipLaunchKernelGGL(k_cfl, dim3((unsigned)nb), dim3(kBlock), 0, s, A, w.partial));
   AFI_TIMED(tm, 6, s,
-            hipLaunchKernelGGL(k_cfl_finish, dim3(1), dim3(kBlock), 0, s,
-                               (const double*)w.partial, (int)nb, t_host, t_dev, t_final, dt_out));
+            hipLaunchKernelGGL(k_cfl_finish, dim3(1), dim3(kBlock), 0, s, A,
+                               (const double*)w.partial, (int)nb));
   return hipGetLastError();
 }
 

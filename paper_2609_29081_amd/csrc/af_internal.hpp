@@ -189,9 +189,11 @@ bool step1d_takes_cfl(const Geo& g);
 hipError_t step1d(const Geo& g, const afd::Phys& ph, const Work& w, const double* U, double* Uout,
                   const double* dt_dev, double dt_host, const StepCoef1& sc, const StepExtras1& x,
                   hipStream_t s, Timer* tm);
+// the CFL step of U into dt_out; save (or NULL): receives a copy of U, and the
+// flag word is cleared (the start of a step attempt)
 hipError_t cfl_dt(const Geo& g, const afd::Phys& ph, double cfl_c, double cfl_v, double visc_a,
                   double visc_b, const Work& w, const double* U, double t_host,
-                  const double* t_dev, double t_final, double* dt_out, hipStream_t s,
+                  const double* t_dev, double t_final, double* dt_out, double* save, hipStream_t s,
                   Timer* tm);
 hipError_t advance_time(const Work& w, hipStream_t s);
 hipError_t clear_flags(const Work& w, hipStream_t s);
