@@ -288,8 +288,7 @@ hipError_t rk54(const afi::Geo& g, const afd::Phys& ph, const afi::Work& w, cons
       hipSuccess)
     return e;
   if ((e = add_source(g, A, kB43 / kA43 * dt, S(3), s)) != hipSuccess) return e;
-  if ((e = afi::lincomb(B, kA52, B, kA53, A, n, s)) != hipSuccess) return e;
-  if ((e = afi::lincomb(A, kA40, u0, kA43, A, n, s)) != hipSuccess) return e;
+  if ((e = afi::share_evaluation(A, B, u0, kA40, kA43, kA52, kA53, n, s)) != hipSuccess) return e;
   if ((e = launch_coef(g, ph, w, coef(1.0, kA54, kB54 / kA54), B, A, X, dt_dev, dt, s, tm)) !=
       hipSuccess)
     return e;

@@ -205,6 +205,9 @@ struct alignas(64) StepReport {
 };
 hipError_t report(const Work& w, StepReport* out, hipStream_t s);
 // a state; flags, if not NULL, is a flag word cleared with it
+// B = ga B + gb A, A = wa u + wb A (the old A in both)
+hipError_t share_evaluation(double* A, double* B, const double* u, double wa, double wb, double ga,
+                            double gb, long n, hipStream_t s);
 hipError_t copy_state(double* dst, const double* src, long n, hipStream_t s,
                       unsigned* flags = nullptr);
 // out = a x + b y over n values (out may be x or y)
