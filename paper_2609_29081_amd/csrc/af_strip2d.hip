@@ -499,7 +499,8 @@ __device__ __forceinline__ void wave_centre(Rings<R>& S, const Ctx<R>& X) {
   auto flipped = [](R v, bool neg) { return neg ? -v : v; };
   const R ihx = R(1.0 / (6.0 * g.dx)), ihy = R(1.0 / (6.0 * g.dy));
 
-  // (ye of row r is loaded here too: its ring entry comes in the same half row)
+  // (co and ye of row r are loaded here too: their ring entries come in the same
+  // half row)
   Raw nco, nye;
   issue<CO>(X, col, X.j0 - 2, nco);
   issue<YE>(X, col, X.j0 - 2, nye);
@@ -524,7 +525,6 @@ __device__ __forceinline__ void wave_centre(Rings<R>& S, const Ctx<R>& X) {
       issue<CO>(X, col, r + 1, nco);
       issue<YE>(X, col, r + 1, nye);
     }
-    store_point(S, X, CO, slot4(k), V);
 #pragma unroll
     for (int n = 0; n < 4; ++n) co[n] = R(V[n]);
     // centre of row r-1
@@ -962,10 +962,18 @@ __device__ __forceinline__ void wave_xlow0(Rings<R>& S, const Ctx<R>& X) {
   const int c = X.lane, cl = c > 0 ? c - 1 : 0, cr = c < W - 1 ? c + 1 : W - 1;
   const R ihx = R(1.0 / g.dx), ihy = R(1.0 / g.dy);
   const R cL = R(2.0 * X.dt / g.dx);
+  // the lane's corners come in here, in the half that this wave has to spare
+  const Columns col = columns_of(X);
+  Raw nco;
+  issue<CO>(X, col, X.j0 - 2, nco);
   for (int k = 0; k < X.rows; ++k) {
     const int j = X.j0 - 4 + k;
     const bool on = j >= X.j0 && j < X.j1 && (X.ph.lim & LIM_POINT);
     const int s2 = slot4(k - 2), s3 = slot4(k - 3);
+    double V[4];
+    signed_values(nco, V);
+    if (k + 1 < X.rows) issue<CO>(X, col, X.j0 - 1 + k, nco);
+    store_point(S, X, CO, slot4(k), V);
     if (mid_row(S)) return;
     if (on) {
       Site<R> E, O;
