@@ -581,8 +581,8 @@ __device__ __forceinline__ void wave_centre(Rings<R>& S, const Ctx<R>& X) {
     if (mid_row(S)) return;
     if (k >= 2) {
       const int p0 = slot4(k), p1 = slot4(k - 1), p2 = slot4(k - 2);
-      const int z1 = slot3(k - 1), z2 = slot3(k - 2), z3s = slot3(k - 3);
-      const int ge = slot2(k - 1), g1 = slot3(k - 1), g2 = slot2(k - 2);
+      const int z1 = slot3(k - 1), z2 = slot3(k - 2);
+      const int ge = slot2(k - 1), g1 = slot3(k - 1);
       const int src[3] = {4, 5, 7};  // u, v, T
 #pragma unroll
       for (int q = 0; q < 3; ++q) {
@@ -597,10 +597,6 @@ __device__ __forceinline__ void wave_centre(Rings<R>& S, const Ctx<R>& X) {
         S.GE1[q][g1][c] = dc5(xe_[p1][cl], zz[z1][cl], zz[z1][c], xe_[p1][cr], ihx);
         if (q < 2)
           S.GE1[3 + q][g1][c] = dc5(xe_[p2][c], co_[p1][c], co_[p0][c], xe_[p0][c], ihy);
-        if (q < 2) {
-          S.GO1[q][g2][c] = dc5(zz[z2][cl], xe_[p2][c], xe_[p2][cr], zz[z2][cr], ihx);
-          S.GO1[2 + q][g2][c] = dc5(zz[z3s][c], ye_[p2][c], ye_[p1][c], zz[z1][c], ihy);
-        }
       }
     }
     STRIP_BARRIER();
@@ -618,20 +614,14 @@ __device__ __forceinline__ void wave_edges(Rings<R>& S, const Ctx<R>& X) {
   LoFlux<R> fy2{};
   R Fprev[4] = {};
   const Columns col = columns_of(X);
-  Raw nye, nxe;
+  Raw nye;
   issue<YE>(X, col, X.j0 - 2, nye);
-  issue<XE>(X, col, X.j0 - 2, nxe);
   for (int k = 0; k < X.rows; ++k) {
     const int r = X.j0 - 2 + k;
-    double V[4], Vx[4];
+    double V[4];
     signed_values(nye, V);
-    signed_values(nxe, Vx);
-    if (k + 1 < X.rows) {
-      issue<YE>(X, col, r + 1, nye);
-      issue<XE>(X, col, r + 1, nxe);
-    }
+    if (k + 1 < X.rows) issue<YE>(X, col, r + 1, nye);
     store_point(S, X, YE, slot4(k), V);
-    store_point(S, X, XE, slot4(k), Vx);
     if (mid_row(S)) return;
     if (k >= 2 && (X.ph.lim & LIM_POINT)) {
       // the line ye, average, ye of the column
@@ -789,6 +779,7 @@ __device__ __forceinline__ void wave_xface(Rings<R>& S, const Ctx<R>& X) {
   const int c = X.lane, cl = c > 0 ? c - 1 : 0, cr = c < W - 1 ? c + 1 : W - 1;
   const int i = X.i0 - 2 + c;
   const bool own_col = c >= 2 && c <= SX + 2 && i <= g.n1;
+  const R ihx = R(1.0 / (6.0 * g.dx)), ihy = R(1.0 / (6.0 * g.dy));
   R Fco[4], Fxe[4];  // fluxes at co and xe of the row before
 #pragma unroll
   for (int n = 0; n < 4; ++n) Fco[n] = Fxe[n] = R(0.0);
@@ -823,6 +814,17 @@ __device__ __forceinline__ void wave_xface(Rings<R>& S, const Ctx<R>& X) {
                    ring_cell(S, slot4(k - 2), c), ring_cell(S, slot4(k), c), phi);
       S.C[12][slot3(k - 1)][c] = phi[0];
       S.C[13][slot3(k - 1)][c] = phi[1];
+      // gradients at the centres of row r-2
+      const int p2 = slot4(k - 2), g2 = slot2(k - 2);
+      const int z1 = slot3(k - 1), z2 = slot3(k - 2), z3s = slot3(k - 3);
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {  // u, v
+        const R (&ye_)[4][W] = S.P[YE][4 + q];
+        const R (&xe_)[4][W] = S.P[XE][4 + q];
+        const R (&zz)[3][W] = S.Z[4 + q];
+        S.GO1[q][g2][c] = dc5(zz[z2][cl], xe_[p2][c], xe_[p2][cr], zz[z2][cr], ihx);
+        S.GO1[2 + q][g2][c] = dc5(zz[z3s][c], ye_[p2][c], ye_[p1][c], zz[z1][c], ihy);
+      }
     }
     STRIP_BARRIER();
   }
@@ -1054,10 +1056,18 @@ __device__ __forceinline__ void wave_xlow1(Rings<R>& S, const Ctx<R>& X) {
   const int c = X.lane, cl = c > 0 ? c - 1 : 0, cr = c < W - 1 ? c + 1 : W - 1;
   const R ihx = R(1.0 / g.dx), ihy = R(1.0 / g.dy);
   const R cL = R(2.0 * X.dt / g.dx);
+  // and the lane's lower edges, as in wave_xlow0
+  const Columns col = columns_of(X);
+  Raw nxe;
+  issue<XE>(X, col, X.j0 - 2, nxe);
   for (int k = 0; k < X.rows; ++k) {
     const int j = X.j0 - 4 + k;
     const bool on = j >= X.j0 && j < X.j1 && j < g.n2 && (X.ph.lim & LIM_POINT);
     const int s1 = slot4(k - 1), s2 = slot4(k - 2);
+    double V[4];
+    signed_values(nxe, V);
+    if (k + 1 < X.rows) issue<XE>(X, col, X.j0 - 1 + k, nxe);
+    store_point(S, X, XE, slot4(k), V);
     if (mid_row(S)) return;
     if (on) {
       Site<R> E, A;
@@ -1381,12 +1391,12 @@ __global__ void __launch_bounds__(NT) k_strip(StripArgs) {
   // parts are grouped so that the four carry equal work in either half
   switch (wave) {
     case 0: wave_xface(S, ctx()); break;
-    case 4: wave_xlow1(S, ctx()); break;
+    case 4: wave_xlow0(S, ctx()); break;
     case 8: wave_xe(S, ctx(), nonfinite); break;
     case 1:
       wave_yface<R, DEV>(S, ctx(), nonfinite, inst, DEV && args()->k == 2, cfl_a, cfl_v);
       break;
-    case 5: wave_xlow0(S, ctx()); break;
+    case 5: wave_xlow1(S, ctx()); break;
     case 9: wave_xres0(S, ctx()); break;
     case 2: wave_yres1(S, ctx(), nonfinite); break;
     case 6: wave_ye(S, ctx(), nonfinite); break;
