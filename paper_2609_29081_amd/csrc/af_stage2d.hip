@@ -294,7 +294,6 @@ template <typename R>
 __device__ __forceinline__ void point_resid_dir(const Tile<R>& T, const PhysT<R>& ph, int a, int q,
                                                 int d, double h, R* Rd) {
   const int sa = d ? WA : 1, sq = d ? WG : 1;
-  const R i6h = R(1.0 / (6.0 * h));
   const R* Md = T.U[1 + d];
   const R* Mo = T.U[2 - d];
   const R* Va = T.A[d];
@@ -302,58 +301,28 @@ __device__ __forceinline__ void point_resid_dir(const Tile<R>& T, const PhysT<R>
   // derivatives across d of the velocity along d and of the other one
   const R* Ga = T.G[d ? 1 : 3];
   const R* Gb = T.G[d ? 0 : 4];
-  R alpha = R(0.0);
+  R sp[5], ga[5], gb[5], Rr[4];
 #pragma unroll
   for (int o = 0; o < 5; ++o) {
-    const int b = a + (o - 2) * sa;
-    alpha = mx(alpha, fabs(Va[b]) + T.A[4][b]);
+    const int b = a + (o - 2) * sa, qq = q + (o - 2) * sq;
+    sp[o] = fabs(Va[b]) + T.A[4][b];
+    ga[o] = o == 2 ? R(0.0) : Ga[qq];
+    gb[o] = o == 2 ? R(0.0) : Gb[qq];
   }
-  R Rr[4];
-  // inviscid, one component at a time (short live ranges)
-  const R ai = alpha * i6h;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    R f[5], w[5];
-#pragma unroll
-    for (int o = 0; o < 5; ++o) {
-      const int b = a + (o - 2) * sa;
-      const R ud = Va[b], pb = T.A[2][b];
-      w[o] = k == 0 ? T.U[0][b] : (k == 1 ? Md[b] : (k == 2 ? Mo[b] : T.U[3][b]));
-      f[o] = k == 0 ? Md[b] : (k == 1 ? w[o] * ud + pb : (k == 2 ? w[o] * ud : (w[o] + pb) * ud));
-    }
-    Rr[k] = -(dc5(f[0], f[1], f[3], f[4], i6h) + ai * d4(w[0], w[1], w[2], w[3], w[4]));
-  }
-  R va[5], vb[5], Tt[5];
-#pragma unroll
-  for (int o = 0; o < 5; ++o) {
-    const int b = a + (o - 2) * sa;
-    va[o] = Va[b];
-    vb[o] = Vb[b];
-    Tt[o] = T.A[3][b];
-  }
-  // compact D^{(d),2}(K_dd, Z)
-  const R s4 = R(4.0 / (h * h));
-  const R mu = ph.mu, m43 = R(4.0 / 3.0) * ph.mu;
-  Rr[1] += s4 * m43 * bcol(va);
-  Rr[2] += s4 * mu * bcol(vb);
-  Rr[3] += s4 * (m43 * bquad(va) + mu * bquad(vb) + ph.kap * bcol(Tt));
-  // mixed
-  R m1[5], m2[5], m3[5];
-#pragma unroll
-  for (int o = 0; o < 5; ++o) {
-    if (o == 2) {
-      m1[o] = m2[o] = m3[o] = R(0.0);
-      continue;
-    }
-    const int qq = q + (o - 2) * sq;
-    const R ga = Ga[qq], gb = Gb[qq];
-    m1[o] = -R(2.0 / 3.0) * mu * gb;
-    m2[o] = mu * ga;
-    m3[o] = mu * (vb[o] * ga - R(2.0 / 3.0) * va[o] * gb);
-  }
-  Rr[1] += dc5(m1[0], m1[1], m1[3], m1[4], i6h);
-  Rr[2] += dc5(m2[0], m2[1], m2[3], m2[4], i6h);
-  Rr[3] += dc5(m3[0], m3[1], m3[3], m3[4], i6h);
+  line_terms(
+      ph, h, mx5(sp[0], sp[1], sp[2], sp[3], sp[4]),
+      [&](LineValue v, int o) {
+        const int b = a + (o - 2) * sa;
+        return v == kRho  ? T.U[0][b]
+               : v == kMd ? Md[b]
+               : v == kMo ? Mo[b]
+               : v == kE  ? T.U[3][b]
+               : v == kVa ? Va[b]
+               : v == kVb ? Vb[b]
+               : v == kP  ? T.A[2][b]
+                          : T.A[3][b];
+      },
+      ga, gb, Rr);
   // back to (rho, m_x, m_y, E)
   Rd[0] = Rr[0];
   Rd[1] = d ? Rr[2] : Rr[1];

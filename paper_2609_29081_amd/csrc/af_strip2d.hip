@@ -151,57 +151,27 @@ template <typename R>
 __device__ __forceinline__ R from_right(R x) { return lane_shift<0x130>(x); }  // wave_shl:1
 
 // direction-D terms of the residual of a point, from the five sites s of its
-// line and the derivatives across D of the velocities at them: ga of the one
-// along D, gb of the other (index 2 unused).  See point_resid_dir of the tile
-// kernel for the terms.
+// line and the derivatives across D of the velocities at them (see line_terms)
 template <int D, typename R>
 __device__ __forceinline__ void line_resid(const PhysT<R>& ph, double h, const Site<R>* const* s,
                                            const R* ga, const R* gb, R* Rd) {
-  const R i6h = R(1.0 / (6.0 * h));
   R sp[5];
 #pragma unroll
   for (int o = 0; o < 5; ++o) sp[o] = fabs(s[o]->a[D]) + s[o]->a[4];
-  const R alpha = mx5(sp[0], sp[1], sp[2], sp[3], sp[4]);
   R Rr[4];
-  const R ai = alpha * i6h;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    R f[5], w[5];
-#pragma unroll
-    for (int o = 0; o < 5; ++o) {
-      const R ud = s[o]->a[D], pb = s[o]->a[2];
-      w[o] = k == 0 ? s[o]->U[0] : (k == 1 ? s[o]->U[1 + D] : (k == 2 ? s[o]->U[2 - D] : s[o]->U[3]));
-      f[o] = k == 0 ? s[o]->U[1 + D]
-                    : (k == 1 ? w[o] * ud + pb : (k == 2 ? w[o] * ud : (w[o] + pb) * ud));
-    }
-    Rr[k] = -(dc5(f[0], f[1], f[3], f[4], i6h) + ai * d4(w[0], w[1], w[2], w[3], w[4]));
-  }
-  R va[5], vb[5], Tt[5];
-#pragma unroll
-  for (int o = 0; o < 5; ++o) {
-    va[o] = s[o]->a[D];
-    vb[o] = s[o]->a[1 - D];
-    Tt[o] = s[o]->a[3];
-  }
-  const R s4 = R(4.0 / (h * h));
-  const R mu = ph.mu, m43 = R(4.0 / 3.0) * ph.mu;
-  Rr[1] += s4 * m43 * bcol(va);
-  Rr[2] += s4 * mu * bcol(vb);
-  Rr[3] += s4 * (m43 * bquad(va) + mu * bquad(vb) + ph.kap * bcol(Tt));
-  R m1[5], m2[5], m3[5];
-#pragma unroll
-  for (int o = 0; o < 5; ++o) {
-    if (o == 2) {
-      m1[o] = m2[o] = m3[o] = R(0.0);
-      continue;
-    }
-    m1[o] = -R(2.0 / 3.0) * mu * gb[o];
-    m2[o] = mu * ga[o];
-    m3[o] = mu * (vb[o] * ga[o] - R(2.0 / 3.0) * va[o] * gb[o]);
-  }
-  Rr[1] += dc5(m1[0], m1[1], m1[3], m1[4], i6h);
-  Rr[2] += dc5(m2[0], m2[1], m2[3], m2[4], i6h);
-  Rr[3] += dc5(m3[0], m3[1], m3[3], m3[4], i6h);
+  line_terms(
+      ph, h, mx5(sp[0], sp[1], sp[2], sp[3], sp[4]),
+      [&](LineValue v, int o) {
+        return v == kRho  ? s[o]->U[0]
+               : v == kMd ? s[o]->U[1 + D]
+               : v == kMo ? s[o]->U[2 - D]
+               : v == kE  ? s[o]->U[3]
+               : v == kVa ? s[o]->a[D]
+               : v == kVb ? s[o]->a[1 - D]
+               : v == kP  ? s[o]->a[2]
+                          : s[o]->a[3];
+      },
+      ga, gb, Rr);
   Rd[0] = Rr[0];
   Rd[1] = D ? Rr[2] : Rr[1];
   Rd[2] = D ? Rr[1] : Rr[2];
