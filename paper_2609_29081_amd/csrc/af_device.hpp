@@ -173,7 +173,7 @@ __device__ __forceinline__ double pressure2(double r, double mx, double my, doub
   return gm1 * (E - (mx * mx + my * my) * (0.5 * rcp(r)));
 }
 __device__ __forceinline__ double pressure1(double r, double m, double E, double gm1) {
-  return gm1 * (E - m * m / (2.0 * r));
+  return gm1 * (E - m * m * (0.5 * rcp(r)));
 }
 
 // whether the rule's parameter from a state of density rL and pressure pL toward
@@ -379,13 +379,11 @@ __device__ __forceinline__ R bvisc2_dir(int d, R p, R T, R ux, R vx, R Tx, R uy,
   return (root(q * q + e2 * t2) + fabs(q)) * (R(0.5) * ph.gm1 * rcp(p));
 }
 
-__device__ __forceinline__ double bvisc1(double rho, double p, double ux, double Tx,
-                                         const Phys& ph) {
+// in 1D
+__device__ __forceinline__ double bvisc1(double p, double T, double ux, double Tx, const Phys& ph) {
   const double tau = ph.mu * (4.0 / 3.0) * ux;
   const double q = ph.kap * Tx;
-  const double re = p / ph.gm1;
-  const double e = re / rho;
-  return (root(q * q + 2.0 * e * tau * tau) + fabs(q)) / (2.0 * re);
+  return (root(q * q + 2.0 * T * ph.igm1 * tau * tau) + fabs(q)) * (0.5 * ph.gm1 * rcp(p));
 }
 
 // sticky flag word

