@@ -399,7 +399,7 @@ def stage_variants() -> list:
 
 class Batch:
     """A batch of 2D solvers (one precision) advanced together by af_batch_run:
-    each stage of every instance is one persistent launch, each instance with
+    each stage of all instances is one launch, each instance with
     its own time step and halving.  The solvers must outlive the batch."""
 
     def __init__(self, solvers: list):

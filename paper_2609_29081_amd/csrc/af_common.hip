@@ -355,7 +355,7 @@ __global__ void __launch_bounds__(kBlock) k_batch_decide(afi::BatchInst* inst, i
 // the decision after an attempt and the opening of the next step in one
 // launch, one wave per instance: its last stage left the CFL maxima of the new
 // state, one pair per workgroup.  (A decision and an opening as kernels of
-// their own took 9.4 us of the 93 us of a round at 400 x 200.)
+// their own took 9.4 us of the 93 us of a round at 400 x 200; this 3.8.)
 __global__ void __launch_bounds__(64) k_batch_advance(afi::BatchInst* inst,
                                                       const double2* __restrict__ partial) {
   afi::BatchInst& I = inst[blockIdx.x];

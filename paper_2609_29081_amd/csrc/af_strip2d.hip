@@ -8,15 +8,15 @@
 // a range of rows, and each wave does one part of the scheme per step of the
 // march, which takes it one row of cells further.  When row r is loaded,
 //                 first half of the step         second half
-//   wave_centre   points co of row r, centres    gradients around row r-1
-//                 of row r-1
-//   wave_edges    points ye, xe of row r         low-order y terms of ye, r-2
+//   wave_centre   centres of row r-1             gradients around row r-1
+//   wave_edges    points ye of row r             low-order y terms of ye, r-2
 //   wave_cells    averages of row r              low-order data of cells, r-1
-//   wave_xface    limited x-face fluxes, r-3     smoothness sensors, r-1
+//   wave_xface    limited x-face fluxes, r-3     smoothness sensors, r-1; gradients
+//                                                at centres, r-2
 //   wave_yface    limited y-face fluxes, r-2     averages updated, r-3
 //   wave_xres0    x residual of co, r-2          x residual of ye, r-2
-//   wave_xlow0                                   low-order x terms of co, ye, r-2
-//   wave_xlow1                                   low-order x terms of xe, r-2
+//   wave_xlow0    points co of row r             low-order x terms of co, ye, r-2
+//   wave_xlow1    points xe of row r             low-order x terms of xe, r-2
 //   wave_xe       x residual of xe, r-3          xe updated, r-3
 //   wave_yres0    y residual of co, r-3          low-order y terms of co, xe, r-2
 //   wave_yres1    y residual of xe, r-3          co updated, r-3
@@ -29,19 +29,26 @@
 // CU); what a wave needs again in the next row and the rings no longer hold
 // stays in its registers.
 //
-// What bounds it: vector instructions.  A step of an FP64 strip takes 5,550
-// cycles (2,970 and 2,400 in the two halves, the rest at the barriers) for
-// about 3,950 vector instructions, of which two thirds are FP64 arithmetic, on
-// four SIMDs; LDS is busy a third of the time and HBM a fifth.  So the parts
-// are spread over the SIMDs to equal work in either half, and over three waves
-// per SIMD, which FP64 at 168 registers a wave just allows.  With eight waves
-// (two per SIMD, 245 registers) a step took 7,850 cycles: loads and centres
-// held up the first half, gradients and cell data the second.
+// What bounds it: vector instructions and, in FP64, the power they take.  A step
+// of a strip takes 5,060 cycles (FP32 stencils: 4,020) for 2,990 (2,890) vector
+// instructions on four SIMDs, which are busy 62 % (74 %) of the time; LDS is
+// busy 45 % and HBM a fifth.  An FP64 instruction takes 4.4 cycles of its SIMD
+// whatever it depends on, and under a stream of them the clock falls from 2.4
+// to about 2.05 GHz, so that large FP64 stages gain only from fewer
+// instructions.  Small grids (few rows per strip) are bound by the chains of
+// dependent work between two barriers.  So the parts are spread over the SIMDs
+// to equal work in either half (of 85 other assignments none is better), what a
+// half has to wait for is kept short, and three waves per SIMD, which FP64 at
+// 168 registers a wave just allows, hide each other's waits.
 //
-// Measured, stage of the shock tube (tile kernel, eight waves, this):
-//   1000 x 500   FP64 212, 125, 107 us   FP32 stencils 155, 115, 89 us
-//   2048 x 1024  FP64 867, 490, 378 us   FP32 stencils 652, 450, 326 us
-//   64 x 32      FP64 28, 17, 14 us      FP32 stencils 42, 17, 14 us
+// Measured, stage of the shock tube (tile kernel, this):
+//   1000 x 500   FP64 208, 101 us   FP32 stencils 157, 74 us
+//   2048 x 1024  FP64 860, 349 us   FP32 stencils 660, 265 us
+//   400 x 200    FP64 42, 25 us
+//   64 x 32      FP64 28, 12.1 us   FP32 stencils 42, 10.4 us
+// On the way, at 1000 x 500 in FP64: 125 with eight waves (two per SIMD), 107
+// with twelve, 103 with shorter maxima, square roots, limiters and addresses,
+// 101 with fewer operations in the residuals.
 //
 // The arithmetic is the tile kernel's, expression by expression, so the two
 // give the same bits.  The tile kernel remains for batches: see strip_shapes,
@@ -1493,12 +1500,12 @@ StripShape strip_shape(const Geo& g) {
 // columns the grids fill.  A tile (16 x 7 cells FP64, 16 x 14 mixed) takes as
 // long as 6.5 or 12 row steps, and the tile kernel's start some 3 or 1 more.
 // Measured, us per RK3 step on strips and on the tiles (FP64; mixed):
-//   8 grids up to 512 x 256     458, 601;   390, 479
-//   2 of 1000 x 500             821, 1636;  713, 1192
-//   512 of 64 x 32              1479, 2533; 1274, 2106
-//   512 of 16 x 8               462, 683;   424, 526
-//   256 of 8 x 8                242, 259;   225, 223
-//   32 of 8 x 200               274, 227;   224, 172
+//   8 grids up to 512 x 256     425, 586;   338, 465
+//   2 of 1000 x 500             773, 1563;  647, 1159
+//   512 of 64 x 32              1404, 2475; 1150, 2072
+//   512 of 16 x 8               407, 646;   397, 518
+//   256 of 8 x 8                214, 241;   219, 223
+//   32 of 8 x 200               254, 226;   204, 179
 bool strip_shapes(const Geo* g, int n, StripShape* out) {
   const int cus = device_cus();
   int tallest = 1;
