@@ -86,3 +86,19 @@ def test_step_equals_its_stages(n, bc):
     assert S.af_step(B, dt=dt)[0] == 0
     S.af_step_source(C, dt, [torch.zeros_like(A)] * 5)
     assert torch.equal(B, C)
+
+
+@pytest.mark.parametrize("n", [150, 4097])
+@pytest.mark.parametrize("rk", [3, 54])
+@pytest.mark.parametrize("check_every", [2, 3, 5])
+def test_run_in_blocks_equals_run_in_single_steps(n, rk, check_every):
+    """blocks of even and odd numbers of steps, whose time moves between two
+    scalars on the device, against steps whose dt the reduction gives: the same
+    states and times"""
+    g, U, kw = field(n, W.OUTFLOW)
+    S = af.Solver(g, gamma=GAMMA, rk=rk, **kw)
+    A, B = S.to_device(U), S.to_device(U)
+    one = S.af_run(A, 0.5, 1e30, 8, check_every=1)
+    assert one[:2] == (0, 8)
+    assert S.af_run(B, 0.5, 1e30, 8, check_every=check_every) == one
+    assert torch.equal(A, B)
