@@ -267,7 +267,7 @@ af_status af_reset_flags(af_ctx* ctx, void* ws, void* stream);
  * each kernel kind below, the number of launches and their summed duration
  * in milliseconds since the previous read (arrays of AF_K_COUNT entries). */
 enum {
-  AF_K_LATTICE = 0,  /* 1D: the stage kernel                            */
+  AF_K_LATTICE = 0,  /* 1D: the stage or step kernel                    */
   AF_K_GRAD = 1,     /* 1 to 5: no kernel of the library                */
   AF_K_CELLPRE = 2,
   AF_K_FACE = 3,
