@@ -201,13 +201,23 @@ __device__ __forceinline__ void compact2(const R* z, R& col, R& quad) {
 // at(v, o): value v of site o, in the line's frame: density, momentum along D
 // and across, energy, velocity along D and across, pressure, temperature.  Rr:
 // density, momentum along D and across, energy.
+//
+// In FP64 constants come after the differences and the form of B from
+// differences (120 of 3100 operations per row of a strip fewer, 357 -> 351 us
+// for the stage at 2048 x 1024), which moves a step by 4e-17 at most.  FP32
+// stencils keep every factor at its site: the shorter order moves a step of a
+// smooth flow by 2e-9 to 7e-9 (of the tube, whose steps are short, by 1e-10),
+// as much as a third of its distance from 64 bits, for callers who have such
+// runs to compare with, and gains little there (an RK3 step at 1000 x 500 221.3
+// us so, 222.0 with the factors; eight grids up to 512 x 256, three steps, 1458
+// and 1484).
 enum LineValue { kRho, kMd, kMo, kE, kVa, kVb, kP, kT };
 template <typename R, typename At>
 __device__ __forceinline__ void line_terms(const PhysT<R>& ph, double h, R alpha, At at,
                                            const R* ga, const R* gb, R* Rr) {
-  const R n6h = R(-1.0 / (6.0 * h)), s4 = R(4.0 / (h * h));
-  const R mu = ph.mu, mu23 = R(2.0 / 3.0) * ph.mu;
-  const R s4m = s4 * mu, s4m43 = s4 * (R(4.0 / 3.0) * ph.mu), s4k = s4 * ph.kap;
+  constexpr bool kShort = std::is_same<R, double>::value;
+  const R n6h = R(-1.0 / (6.0 * h)), i6h = R(1.0 / (6.0 * h)), s4 = R(4.0 / (h * h));
+  const R ai = alpha * i6h;
   R va[5], vb[5], Tt[5];
 #pragma unroll
   for (int o = 0; o < 5; ++o) {
@@ -226,24 +236,50 @@ __device__ __forceinline__ void line_terms(const PhysT<R>& ph, double h, R alpha
                     : (k == 1 ? w[o] * va[o] + at(kP, o)
                               : (k == 2 ? w[o] * va[o] : (w[o] + at(kP, o)) * va[o]));
     }
-    Rr[k] = diff5(f[0], f[1], f[3], f[4]) + alpha * d4(w[0], w[1], w[2], w[3], w[4]);
+    if constexpr (kShort)
+      Rr[k] = diff5(f[0], f[1], f[3], f[4]) + alpha * d4(w[0], w[1], w[2], w[3], w[4]);
+    else
+      Rr[k] = -(dc5(f[0], f[1], f[3], f[4], i6h) + ai * d4(w[0], w[1], w[2], w[3], w[4]));
   }
-  R n[5];
+  if constexpr (kShort) {
+    const R mu = ph.mu, mu23 = R(2.0 / 3.0) * ph.mu;
+    const R s4m = s4 * mu, s4m43 = s4 * (R(4.0 / 3.0) * ph.mu), s4k = s4 * ph.kap;
+    R n[5];
 #pragma unroll
-  for (int o = 0; o < 5; ++o)
-    n[o] = o == 2 ? R(0.0) : vb[o] * ga[o] - R(2.0 / 3.0) * (va[o] * gb[o]);
-  Rr[1] += mu23 * diff5(gb[0], gb[1], gb[3], gb[4]);
-  Rr[2] -= mu * diff5(ga[0], ga[1], ga[3], ga[4]);
-  Rr[3] -= mu * diff5(n[0], n[1], n[3], n[4]);
-  R ca, qa, cb, qb;
-  compact2(va, ca, qa);
-  compact2(vb, cb, qb);
-  Rr[0] = n6h * Rr[0];
-  Rr[1] = n6h * Rr[1] + s4m43 * ca;
-  Rr[2] = n6h * Rr[2] + s4m * cb;
-  Rr[3] = n6h * Rr[3] + s4m43 * qa;
-  Rr[3] += s4m * qb;
-  Rr[3] += s4k * bcol(Tt);
+    for (int o = 0; o < 5; ++o)
+      n[o] = o == 2 ? R(0.0) : vb[o] * ga[o] - R(2.0 / 3.0) * (va[o] * gb[o]);
+    Rr[1] += mu23 * diff5(gb[0], gb[1], gb[3], gb[4]);
+    Rr[2] -= mu * diff5(ga[0], ga[1], ga[3], ga[4]);
+    Rr[3] -= mu * diff5(n[0], n[1], n[3], n[4]);
+    R ca, qa, cb, qb;
+    compact2(va, ca, qa);
+    compact2(vb, cb, qb);
+    Rr[0] = n6h * Rr[0];
+    Rr[1] = n6h * Rr[1] + s4m43 * ca;
+    Rr[2] = n6h * Rr[2] + s4m * cb;
+    Rr[3] = n6h * Rr[3] + s4m43 * qa;
+    Rr[3] += s4m * qb;
+    Rr[3] += s4k * bcol(Tt);
+  } else {
+    const R mu = ph.mu, m43 = R(4.0 / 3.0) * ph.mu;
+    Rr[1] += s4 * m43 * bcol(va);
+    Rr[2] += s4 * mu * bcol(vb);
+    Rr[3] += s4 * (m43 * bquad(va) + mu * bquad(vb) + ph.kap * bcol(Tt));
+    R m1[5], m2[5], m3[5];
+#pragma unroll
+    for (int o = 0; o < 5; ++o) {
+      if (o == 2) {
+        m1[o] = m2[o] = m3[o] = R(0.0);
+        continue;
+      }
+      m1[o] = -R(2.0 / 3.0) * mu * gb[o];
+      m2[o] = mu * ga[o];
+      m3[o] = mu * (vb[o] * ga[o] - R(2.0 / 3.0) * va[o] * gb[o]);
+    }
+    Rr[1] += dc5(m1[0], m1[1], m1[3], m1[4], i6h);
+    Rr[2] += dc5(m2[0], m2[1], m2[3], m2[4], i6h);
+    Rr[3] += dc5(m3[0], m3[1], m3[3], m3[4], i6h);
+  }
 }
 
 // wall projection of a point value (no-slip: zero momentum; symmetry: zero
