@@ -469,7 +469,11 @@ __global__ void __launch_bounds__(kThreads) k_step1(G1 g, Phys ph, Step1 st,
   const int b = (int)blockIdx.x * own - halo;  // first cell of the tile, and lane 0's
   const bool periodic = g.bc0 == BC_PERIODIC;
   if (tid == 0) {
-    S.stop = peek_flags(st.flags);
+    // A step of a run's block stops once one before it was rejected (the block is
+    // redone).  Any other step is an attempt of its own, whose flag word was
+    // cleared before the launch: what is up by now came from a faster tile, and if
+    // the first tile stopped for it, nobody would write the step's dt.
+    S.stop = st.x.t_out ? peek_flags(st.flags) : 0u;
     H.b = b;
   }
   // the tile of the state.  Beyond periodic sides it goes on; beyond others
@@ -510,7 +514,6 @@ __global__ void __launch_bounds__(kThreads) k_step1(G1 g, Phys ph, Step1 st,
     }
   }
   __syncthreads();
-  // a step before this one, or a faster tile, was rejected already
   if (S.stop) return;
   double dt0;
   if (st.x.cfl.on) {
