@@ -217,6 +217,7 @@ hipError_t launch_stage(const afi::Geo& g, const afd::Phys& ph, const afi::Work&
                         double dt_host, hipStream_t s, afi::Timer* tm, bool in_step = true) {
   afi::StageCoef sc = kCoef[k];
   sc.skip_flagged = in_step ? 1 : 0;
+  sc.stage = k;
   return launch_coef(g, ph, w, sc, Un, Uk, Uout, dt_dev, dt_host, s, tm);
 }
 
@@ -259,8 +260,10 @@ hipError_t rk54(const afi::Geo& g, const afd::Phys& ph, const afi::Work& w, cons
                 const afi::StepExtras1& x = {}) {
   if (g.dim == 1 && !src)
     return afi::step1d(g, ph, w, u0, X, dt_dev, dt, kStep54, x, s, tm);
-  auto coef = [](double a, double b, double mul) {
+  int stage = 0;
+  auto coef = [&stage](double a, double b, double mul) {
     afi::StageCoef c{};
+    c.stage = stage++;
     c.a = a;
     c.b = b;
     c.first = a == 0.0 ? 1 : 0;
@@ -320,6 +323,7 @@ afi::StepExtras1::Cfl step_cfl(const af_ctx* c, const afi::Geo& g, double t_host
 af_status read_flags(const afi::Work& w, hipStream_t s, unsigned* out) {
   AF_HIP(hipMemcpyAsync(out, w.flags, sizeof(unsigned), hipMemcpyDeviceToHost, s));
   AF_HIP(hipStreamSynchronize(s));
+  *out = afd::first_flags(*out);
   return AF_OK;
 }
 
@@ -387,7 +391,7 @@ af_status read_scalars(const afi::Work& w, hipStream_t s, afi::StepReport* slot,
     memcpy(&r.flags, buf + at, sizeof(unsigned));
   }
   memcpy(sc, r.scal, sizeof(r.scal));
-  *flags = r.flags;
+  *flags = afd::first_flags(r.flags);
   return AF_OK;
 }
 
@@ -860,7 +864,7 @@ af_status af_reset_flags(af_ctx* c, void* ws, void* stream) {
   afi::Geo g;
   if (!geometry(c, &g)) return AF_E_ARG;
   const afi::Work w = work_of(c, g, ws);
-  AF_HIP(afi::clear_flags(w, (hipStream_t)stream));
+  AF_HIP(afi::set_flags(w, 0u, (hipStream_t)stream));
   return AF_OK;
 }
 
@@ -895,7 +899,7 @@ static af_status step_in(af_ctx* c, double* U, void* ws, void* stream, double dt
   unsigned fl = 0;
   int h;
   for (h = 0; h <= c->p.max_halvings; ++h) {
-    if (h > 0) AF_HIP(afi::clear_flags(w, s));
+    if (h > 0) AF_HIP(afi::set_flags(w, 0u, s));
     if (c->p.rk == 54)
       AF_HIP(rk54(g, ph, w, w.SAVE, w.S1, w.S2, U, dt_dev, dt, s, c->timer, nullptr, x));
     else
@@ -913,6 +917,7 @@ static af_status step_in(af_ctx* c, double* U, void* ws, void* stream, double dt
   if (halvings) *halvings = h;
   if (fl != 0) {
     AF_HIP(afi::copy_state(U, w.SAVE, g.state_len, s));
+    AF_HIP(afi::set_flags(w, fl, s));
     AF_HIP(hipStreamSynchronize(s));
     if (fl & AF_FLAG_NONFINITE) return fail(AF_E_NONFINITE, "non-finite values after %d halvings", h - 1);
     return fail(AF_E_PP, "low-order states inadmissible after %d halvings (flags %u)", h - 1, fl);
@@ -1031,7 +1036,7 @@ af_status af_run(af_ctx* c, double* U, void* ws, void* stream, double t0, double
       AF_HIP(launch_cfl(c, g, w, bufs[cur], 0.0, w.scal + 1, t_final, w.scal, s));
       int h;
       for (h = 0; h <= c->p.max_halvings; ++h) {
-        AF_HIP(afi::clear_flags(w, s));
+        AF_HIP(afi::set_flags(w, 0u, s));
         AF_HIP(attempt(cur));
         if ((status = read_back()) != AF_OK) break;
         if (fl == 0) break;
@@ -1043,6 +1048,7 @@ af_status af_run(af_ctx* c, double* U, void* ws, void* stream, double t0, double
                      ? fail(AF_E_NONFINITE, "non-finite values at t=%g after %d halvings", t, h - 1)
                      : fail(AF_E_PP, "low-order states inadmissible at t=%g after %d halvings", t,
                             h - 1);
+        AF_HIP(afi::set_flags(w, fl, s));
         break;
       }
       AF_HIP(afi::set_scalar(w.scal + 2, 0.0, s));
@@ -1358,6 +1364,7 @@ af_status af_step_source(af_ctx* c, double* U, void* ws, void* stream, double dt
   if (st != AF_OK) return st;
   if (fl != 0) {
     AF_HIP(afi::copy_state(U, w.SAVE, g.state_len, s));
+    AF_HIP(afi::set_flags(w, fl, s));
     AF_HIP(hipStreamSynchronize(s));
     if (fl & AF_FLAG_NONFINITE) return fail(AF_E_NONFINITE, "non-finite values (flags %u)", fl);
     return fail(AF_E_PP, "low-order states inadmissible (flags %u)", fl);

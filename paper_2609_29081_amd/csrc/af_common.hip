@@ -182,8 +182,8 @@ __global__ void k_zero_count(unsigned long long* count) {
   if (threadIdx.x == 0 && blockIdx.x == 0) count[0] = 0ull;
 }
 
-__global__ void k_clear_flags(unsigned* flags) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) flags[0] = 0u;
+__global__ void k_set_flags(unsigned* flags, unsigned v) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) flags[0] = v;
 }
 
 __global__ void k_report(const double* scal, const unsigned* flags, afi::StepReport* out) {
@@ -458,8 +458,8 @@ hipError_t advance_time(const Work& w, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t clear_flags(const Work& w, hipStream_t s) {
-  hipLaunchKernelGGL(k_clear_flags, dim3(1), dim3(64), 0, s, w.flags);
+hipError_t set_flags(const Work& w, unsigned v, hipStream_t s) {
+  hipLaunchKernelGGL(k_set_flags, dim3(1), dim3(64), 0, s, w.flags, v);
   return hipGetLastError();
 }
 

@@ -398,6 +398,32 @@ __device__ __forceinline__ double bvisc1(double p, double T, double ux, double T
   return (root(q * q + 2.0 * T * ph.igm1 * tau * tau) + fabs(q)) * (0.5 * ph.gm1 * rcp(p));
 }
 
+// Flags of a 1D step attempt.  Its stages were launches of their own once (face
+// fluxes, averages, points), what came after a flagged one was skipped, and the
+// status of a rejected attempt is that of the first launch that raised a flag.  In
+// one launch later stages go on from inadmissible data and raise more
+// (FLAG_NONFINITE at last), and workgroups raise theirs in any order, so the word
+// keeps where a flag came from: four bits a stage above those of FLAG_*, 23 in
+// all for SSP-RK54.
+constexpr int kAttemptBit = 3, kStageBits = 4;
+struct StageFlags {
+  unsigned cell_low, cells_nonfinite, point_low, points_nonfinite;
+};
+__device__ __forceinline__ StageFlags attempt_flags(int stage) {
+  const unsigned f = 1u << (kAttemptBit + kStageBits * stage);
+  return StageFlags{f, f << 1, f << 2, f << 3};
+}
+// the flags (FLAG_*) that a word stands for: in an attempt, those of the first
+// launch that would have raised any
+inline unsigned first_flags(unsigned word) {
+  if (word < (1u << kAttemptBit)) return word;
+  unsigned f = word >> kAttemptBit;
+  while (!(f & 15u)) f >>= kStageBits;
+  if (f & 1u) return FLAG_CELL_LOW;
+  if (f & 2u) return FLAG_NONFINITE;
+  return ((f & 4u) ? FLAG_POINT_LOW : 0u) | ((f & 8u) ? FLAG_NONFINITE : 0u);
+}
+
 // sticky flag word
 __device__ __forceinline__ void raise_flag(unsigned* flags, unsigned f) {
   atomicOr(flags, f);

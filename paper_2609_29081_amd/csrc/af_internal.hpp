@@ -116,6 +116,8 @@ struct StageCoef {
   float* ts_out;
   // the forward-Euler step is dt_mul * dt (the stages of SSP-RK54)
   double dt_mul = 1.0;
+  // 1D, skip_flagged: the stage's place in its step (for its flags)
+  int stage = 0;
 };
 
 size_t workspace_layout(const Geo& g, Work* w, char* base);
@@ -196,7 +198,7 @@ hipError_t cfl_dt(const Geo& g, const afd::Phys& ph, double cfl_c, double cfl_v,
                   const double* t_dev, double t_final, double* dt_out, double* save, hipStream_t s,
                   Timer* tm);
 hipError_t advance_time(const Work& w, hipStream_t s);
-hipError_t clear_flags(const Work& w, hipStream_t s);
+hipError_t set_flags(const Work& w, unsigned v, hipStream_t s);
 // the step scalars (dt, t, steps) and the flag word into host memory that the
 // device can write
 struct alignas(64) StepReport {

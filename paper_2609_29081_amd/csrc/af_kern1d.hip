@@ -47,7 +47,7 @@ struct G1 {
 // a stage's launch (see StageCoef)
 struct Stage1 {
   double ca, cb;
-  int first, skip_flagged;
+  int first, skip_flagged, stage;
   unsigned* flags;
   const double* dt_dev;
   double dt_host, dt_mul;
@@ -207,7 +207,8 @@ __device__ __forceinline__ void cell_site(const G1& g, const Phys& ph, const Src
 
 // limited flux of the face between ring cells a and a + 1, at lattice entry q
 __device__ __forceinline__ void face_flux(const G1& g, const Phys& ph, const Tile1& S, int a, int q,
-                                          double dt, unsigned* flags, double* F) {
+                                          double dt, unsigned* flags, const StageFlags& fl,
+                                          double* F) {
   const int b = a + 1;
   double FH[3];
   {
@@ -280,7 +281,7 @@ __device__ __forceinline__ void face_flux(const G1& g, const Phys& ph, const Til
                                theta_p1(ULm, pLm, Tm, mn(kPPEps, pLm), ph.gm1, ex));
           tpp = tr * tp;
         }
-        if (bad) raise_flag(flags, FLAG_CELL_LOW);
+        if (bad) raise_flag(flags, fl.cell_low);
       }
     }
     const double th = ts * tpp;
@@ -309,7 +310,7 @@ __device__ __forceinline__ void lo_site1(const Phys& ph, const double (&V)[5][3]
 // at its sides) into out
 __device__ __forceinline__ void point_update(const G1& g, const Phys& ph, const Tile1& S, int k0,
                                              int q, int r0, double dt, unsigned* flags,
-                                             double* out) {
+                                             const StageFlags& fl, double* out) {
   const int X = 2 * k0;
   const double i6h = 1.0 / (6.0 * g.dx);
   double Us[5][3], u[5], p[5], T[5];
@@ -389,7 +390,7 @@ __device__ __forceinline__ void point_update(const G1& g, const Phys& ph, const 
     bool lbad = false;
     double th = theta_pair1(UL, UH, ph.gm1, lbad, ph.lim & LIM_PEXACT);
     if (ph.lim & LIM_LOWONLY) th = 0.0;
-    if (lbad) raise_flag(flags, FLAG_POINT_LOW);
+    if (lbad) raise_flag(flags, fl.point_low);
     if (th != 1.0) {
 #pragma unroll
       for (int k = 0; k < 3; ++k) out[k] = UL[k] + th * (UH[k] - UL[k]);
@@ -418,9 +419,13 @@ __global__ void __launch_bounds__(kThreads) k_stage1(G1 g, Phys ph, Stage1 st,
   const int i0 = blockIdx.x * kCells;
   const int nc = min(kCells, g.n - i0);        // cells of the tile (0: a last point alone)
   const int npt = min(kCells, g.np - i0);      // its points
-  // inside a step attempt: stop once the attempt's flag word is set (it is
-  // rejected and the stage output is never read)
-  if (tid == 0) S.stop = st.skip_flagged ? peek_flags(st.flags) : 0u;
+  // inside a step attempt: stop if a stage before this one raised a flag (the
+  // attempt is rejected and the output never read); for one of this stage's own a
+  // late tile does not, since its flags may come before
+  const StageFlags fl =
+      st.skip_flagged ? attempt_flags(st.stage)
+                      : StageFlags{FLAG_CELL_LOW, FLAG_NONFINITE, FLAG_POINT_LOW, FLAG_NONFINITE};
+  if (tid == 0) S.stop = st.skip_flagged ? peek_flags(st.flags) & (fl.cell_low - 1u) : 0u;
   // entry t of the tile's lattice is site 2 i0 - 2 + t; ring entry t is cell
   // i0 - 1 + t
   const Global1 U{Uk};
@@ -442,7 +447,7 @@ __global__ void __launch_bounds__(kThreads) k_stage1(G1 g, Phys ph, Stage1 st,
   };
   if (wave == 0) {
     double F[3] = {0.0, 0.0, 0.0};
-    if (nc > 0 && lane <= nc) face_flux(g, ph, S, lane, 2 * lane + 2, dt, st.flags, F);
+    if (nc > 0 && lane <= nc) face_flux(g, ph, S, lane, 2 * lane + 2, dt, st.flags, fl, F);
     const double m = dt / g.dx;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
@@ -451,11 +456,11 @@ __global__ void __launch_bounds__(kThreads) k_stage1(G1 g, Phys ph, Stage1 st,
     }
   } else if (wave == 1 && lane < npt) {
     double out[3];
-    point_update(g, ph, S, i0 + lane, 2 * lane + 2, lane, dt, st.flags, out);
+    point_update(g, ph, S, i0 + lane, 2 * lane + 2, lane, dt, st.flags, fl, out);
 #pragma unroll
     for (int k = 0; k < 3; ++k) combine(g.off_pts + (long)k * g.np + i0 + lane, out[k]);
   }
-  if (!ok) raise_flag(st.flags, FLAG_NONFINITE);
+  if (!ok) raise_flag(st.flags, wave == 0 ? fl.cells_nonfinite : fl.points_nonfinite);
 }
 
 // a whole step from U to Uout (other memory: neighbouring tiles read U)
@@ -471,8 +476,9 @@ __global__ void __launch_bounds__(kThreads) k_step1(G1 g, Phys ph, Step1 st,
   if (tid == 0) {
     // A step of a run's block stops once one before it was rejected (the block is
     // redone).  Any other step is an attempt of its own, whose flag word was
-    // cleared before the launch: what is up by now came from a faster tile, and if
-    // the first tile stopped for it, nobody would write the step's dt.
+    // cleared before the launch: what is up by now came from a faster tile, and a
+    // tile that stopped for it would leave out flags of an earlier stage, or,
+    // being the first, the step's dt.
     S.stop = st.x.t_out ? peek_flags(st.flags) : 0u;
     H.b = b;
   }
@@ -534,7 +540,6 @@ __global__ void __launch_bounds__(kThreads) k_step1(G1 g, Phys ph, Step1 st,
     *st.x.t_out = dt0 > 0.0 ? t + dt0 : t;
     if (dt0 > 0.0) *st.x.steps = *st.x.steps + 1.0;
   }
-  bool ok = true;
   // the lane's cell (wave 0) or point (wave 1): the step's first state, and
   // SSP-RK54's second stage, which its last one builds on
   double un[3], u2[3] = {0.0, 0.0, 0.0}, now[3];
@@ -560,6 +565,8 @@ __global__ void __launch_bounds__(kThreads) k_step1(G1 g, Phys ph, Step1 st,
     if (st.mul[s] != 1.0) dt = st.mul[s] * dt;
     const double ca = st.ca[s], cb = st.cb[s];
     const bool first = ca == 0.0, five = st.stages == 5;
+    const StageFlags fl = attempt_flags(s);
+    bool ok = true;
     // the stage's combinations for the forward-Euler value fe of component k
     auto combine = [&](int k, double fe) {
       const double base = five && s == 4 ? u2[k] : un[k];
@@ -575,7 +582,7 @@ __global__ void __launch_bounds__(kThreads) k_step1(G1 g, Phys ph, Step1 st,
     if (wave == 0) {
       double F[3] = {0.0, 0.0, 0.0};
       if (real_face && lane >= 2 * s && lane <= kCells - 2 * s)
-        face_flux(g, ph, S, lane, 2 * lane + 2, dt, st.flags, F);
+        face_flux(g, ph, S, lane, 2 * lane + 2, dt, st.flags, fl, F);
       const double m = dt / g.dx;
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
@@ -587,13 +594,14 @@ __global__ void __launch_bounds__(kThreads) k_step1(G1 g, Phys ph, Step1 st,
       }
     } else if (wave == 1 && real_point && lane >= 2 * s && lane <= kCells - 2 * s) {
       double out[3];
-      point_update(g, ph, S, j, 2 * lane + 2, lane, dt, st.flags, out);
+      point_update(g, ph, S, j, 2 * lane + 2, lane, dt, st.flags, fl, out);
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
         combine(k, out[k]);
         H.P[k][lane + 1] = now[k];
       }
     }
+    if (!ok) raise_flag(st.flags, wave == 0 ? fl.cells_nonfinite : fl.points_nonfinite);
     __syncthreads();
   }
   if (lane >= halo && lane < halo + own) {
@@ -603,7 +611,6 @@ __global__ void __launch_bounds__(kThreads) k_step1(G1 g, Phys ph, Step1 st,
       if (wave == 1 && j < g.np) Uout[g.off_pts + (long)k * g.np + j] = now[k];
     }
   }
-  if (!ok) raise_flag(st.flags, FLAG_NONFINITE);
 }
 
 G1 geo1(const afi::Geo& geo) {
@@ -636,6 +643,7 @@ hipError_t stage1d(const Geo& geo, const Phys& ph, const Work& w, const double* 
   st.cb = sc.b;
   st.first = sc.first;
   st.skip_flagged = sc.skip_flagged;
+  st.stage = sc.stage;
   st.flags = w.flags;
   st.dt_dev = dt_dev;
   st.dt_host = dt_host;
