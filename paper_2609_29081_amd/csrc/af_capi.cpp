@@ -71,11 +71,13 @@ struct af_ctx {
   af_params p;
   int bc[4];
   EventTimer* timer = nullptr;
-  // af_run_graph's executable graph, reused while its workspace and slot
-  // length stay the same (the stages read everything else from the device
-  // descriptor)
+  // af_run_graph's executable graph, reused while the descriptor's place on the
+  // device, the workgroups and the slot length stay the same (the stages read
+  // everything else from the descriptor, and the maxima stand behind it).  The
+  // place is not a matter of the workspace alone: a periodic axis has a point
+  // less, so af_set_bc moves it
   hipGraphExec_t run_exec = nullptr;
-  const void* run_ws = nullptr;
+  const void* run_inst = nullptr;
   int run_slot = 0, run_dev = -1, run_nwg = 0;
   const float* net = nullptr;  // learned-blend network parameters (device), or NULL
   double bcstate[2][3] = {{1.0, 0.0, 1.0}, {1.0, 0.0, 1.0}};  // 1D Dirichlet states
@@ -1180,12 +1182,12 @@ af_status af_run_graph(af_ctx* c, double* U, void* ws, void* stream, double t0, 
   if (maxima) AF_HIP(open(s));
   int dev = 0;
   AF_HIP(hipGetDevice(&dev));
-  if (c->run_exec && (c->run_ws != ws || c->run_slot != attempts_per_slot || c->run_dev != dev ||
+  if (c->run_exec && (c->run_inst != w.binst || c->run_slot != attempts_per_slot || c->run_dev != dev ||
                       c->run_nwg != nwg)) {
     (void)hipGraphExecDestroy(c->run_exec);
     c->run_exec = nullptr;
   }
-  c->run_ws = ws;
+  c->run_inst = w.binst;
   c->run_slot = attempts_per_slot;
   c->run_dev = dev;
   c->run_nwg = nwg;
