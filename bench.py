@@ -36,6 +36,7 @@ CLOCK_HZ = 2.4e9
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 KERNEL_SOURCES = ["paper_2609_29081_amd/csrc/af_stage2d.hip", "paper_2609_29081_amd/csrc/af_device.hpp",
                   "paper_2609_29081_amd/csrc/af_strip2d.hip",
+                  "paper_2609_29081_amd/csrc/af_strips.hpp",
                   "paper_2609_29081_amd/csrc/af_scheme2d.hpp", "paper_2609_29081_amd/csrc/af_lattice.hpp",
                   "paper_2609_29081_amd/csrc/af_internal.hpp", "paper_2609_29081_amd/build.py"]
 

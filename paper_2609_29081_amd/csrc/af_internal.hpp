@@ -6,6 +6,7 @@
 #include <stddef.h>
 
 #include "af_device.hpp"
+#include "af_strips.hpp"
 
 namespace afi {
 
@@ -234,12 +235,8 @@ hipError_t batch_cfl(BatchInst* inst, int n, double* partial, int nb, hipStream_
 hipError_t batch_open(BatchInst* inst, int n, const double* partial, int nb, int* n_active,
                       hipStream_t s);
 hipError_t batch_decide(BatchInst* inst, int n, int* n_active, hipStream_t s);
-// Strips of a grid (af_strip2d.hip): nx along x, ny ranges of H rows; for one
-// instance, and for the instances of a batch, which are launched together
-// (false: the tiles of the default variant are expected to be faster)
-struct StripShape {
-  int nx, ny, H;
-};
+// the strips of a single grid on the current device, and those of the instances
+// of a batch (false: the tiles of the default variant are expected to be faster)
 StripShape strip_shape(const Geo& g);
 bool strip_shapes(const Geo* g, int n, StripShape* out);
 // stage k of the current attempt of every active instance of a batch: nwg

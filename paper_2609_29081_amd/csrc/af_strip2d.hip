@@ -62,7 +62,7 @@ using namespace afd;
 namespace {
 
 constexpr int W = 64;                 // lanes: cell columns of a strip with its margins
-constexpr int SX = 60;                // cell columns a strip owns: lanes 2 .. 61
+constexpr int SX = afi::kStripColumns;  // cell columns a strip owns: lanes 2 .. 61
 constexpr int NT = 768;               // twelve waves, three per SIMD
 constexpr int CO = 0, YE = 1, XE = 2; // point types
 
@@ -1249,11 +1249,6 @@ __device__ __forceinline__ void wave_ye(Rings<R>& S, const Ctx<R>& X, bool& nonf
   }
 }
 
-// how a grid is cut: nx columns of strips, ny ranges of H rows
-struct Strips {
-  int nx, ny, H;
-};
-
 // launch arguments
 struct StripArgs {
   // one instance, its step driven by the host
@@ -1412,29 +1407,8 @@ int device_cus() {
   return cache[dev];
 }
 
-Strips strips_with(const afi::Geo& g, int H) {
-  return Strips{(g.n1x + SX - 1) / SX, (g.n2y + H - 1) / H, H};
-}
-
-// the strips of a grid.  One workgroup fills a CU (its LDS), so a launch runs
-// in ceil(nx ny / CUs) rounds of H + 5 row steps each (a row is finished three
-// rows behind the march, which starts two rows early): the H with the fewest
-// steps in all.
-Strips strips_of(const afi::Geo& g) {
-  const int cus = device_cus();
-  Strips b{};
-  long best = 0;
-  for (int ny = 1; ny <= g.n2y; ++ny) {
-    const Strips t = strips_with(g, (g.n2y + ny - 1) / ny);
-    const long wgs = (long)t.nx * t.ny;
-    if (ny > 1 && wgs > std::min(8L * cus, (long)afi::kSingleCflBlocks)) break;
-    const long steps = (wgs + cus - 1) / cus * (t.H + 5);
-    if (ny == 1 || steps < best) {
-      b = t;
-      best = steps;
-    }
-  }
-  return b;
+afi::StripShape strips_of(const afi::Geo& g) {
+  return afi::strip_shape(g.n1x, g.n2y, device_cus(), afi::kSingleCflBlocks);
 }
 
 // One object file holds the kernels of one arithmetic type, each with its own
@@ -1453,7 +1427,7 @@ using Real = AF_STRIP_REAL;
 hipError_t launch(const afi::Geo& geo, const Phys& ph, const afi::Work& w, const double* Un,
                   const double* Uk, double* Uout, const double* dt_dev, double dt_host,
                   afi::StageCoef sc, hipStream_t s, afi::Timer* tm) {
-  const Strips b = strips_of(geo);
+  const afi::StripShape b = strips_of(geo);
   StripArgs sa{};
   sa.g = afi::stage_geo(geo);
   sa.ph = ph;
@@ -1485,10 +1459,7 @@ hipError_t launch(const afi::Geo& geo, const Phys& ph, const afi::Work& w, const
 namespace afi {
 
 #ifdef AF_STRIP_SHAPES
-StripShape strip_shape(const Geo& g) {
-  const Strips b = strips_of(g);
-  return StripShape{b.nx, b.ny, b.H};
-}
+StripShape strip_shape(const Geo& g) { return strips_of(g); }
 
 // One H for all instances of a batch: the strips of the instances run together,
 // in any order, so a launch takes about the steps of all of them over the CUs,
@@ -1515,7 +1486,7 @@ bool strip_shapes(const Geo* g, int n, StripShape* out) {
   for (int H = std::min(4, tallest); H <= std::min(1024, tallest); ++H) {
     long work = 0;
     for (int i = 0; i < n; ++i) {
-      const Strips t = strips_with(g[i], H);
+      const StripShape t = strips_with(g[i].n1x, g[i].n2y, H);
       const int last = g[i].n2y - (t.ny - 1) * H;  // rows of the last range
       work += (long)t.nx * ((long)(t.ny - 1) * (H + 5) + last + 5);
     }
@@ -1528,8 +1499,7 @@ bool strip_shapes(const Geo* g, int n, StripShape* out) {
   }
   long tiles = 0;
   for (int i = 0; i < n; ++i) {
-    const Strips t = strips_with(g[i], best_H);
-    out[i] = StripShape{t.nx, t.ny, t.H};
+    out[i] = strips_with(g[i].n1x, g[i].n2y, best_H);
     tiles += default_variant(g[i].mixed)->tiles(g[i]);
   }
   const long rounds = (tiles + cus - 1) / cus;
