@@ -10,9 +10,10 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libaf.so")
 # The 2D stage is compiled once per variant (arithmetic type, tile height):
 # the FP64 stage with 16x7 tiles (the largest its LDS admits) and 16x5, the
-# mixed-precision stage (FP32 stencils) with 16x14, 16x10 and 16x7.  The
-# first variant of each precision is the one single-instance stages use; the
-# batch autotuner chooses among all of a precision.  (entry name, type, TY)
+# mixed-precision stage (FP32 stencils) with 16x14, 16x10 and 16x7.  They serve
+# batches: the first of each precision is a new batch's, and the autotuner
+# chooses among all of a precision.  Those two also hold the stage of single
+# instances too narrow for strips.  (entry name, type, TY)
 STAGE_VARIANTS = [("stage2d_fp64_t7", "double", 7), ("stage2d_fp64_t5", "double", 5),
                   ("stage2d_mixed_t14", "float", 14), ("stage2d_mixed_t10", "float", 10),
                   ("stage2d_mixed_t7", "float", 7)]
@@ -35,7 +36,9 @@ SOURCES = [("af_capi.cpp", "af_capi.o", []),
       # no hoisting of loop-invariant values out of the persistent tile
       # loop: held across all phases they spilled; recomputed, the FP64
       # stage spills nothing and runs 2 % faster
-      "-mllvm", "--disable-machine-licm"])
+      "-mllvm", "--disable-machine-licm",
+      *([f"-DAF_STAGE_ONE=tiles_{'fp64' if real == 'double' else 'mixed'}"]
+        if name in ("stage2d_fp64_t7", "stage2d_mixed_t14") else [])])
     for name, real, ty in STAGE_VARIANTS]
 ARCH = "gfx950"
 

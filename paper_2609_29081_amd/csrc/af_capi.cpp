@@ -196,6 +196,13 @@ afd::Phys physics(const af_params& p) {
 
 const afi::StageCoef kCoef[3] = {{0.0, 1.0, 1, 0}, {0.75, 0.25, 0, 0}, {1.0 / 3.0, 2.0 / 3.0, 0, 0}};
 
+// the kernel of a grid's stages
+auto stage_of(const afi::Geo& g) {
+  if (g.dim == 1) return afi::stage1d;
+  if (afi::single_on_tiles(g)) return g.mixed ? afi::tiles_mixed : afi::tiles_fp64;
+  return g.mixed ? afi::strips_mixed : afi::strips_fp64;
+}
+
 // in_step: the stage is part of a step attempt (af_step, af_run), whose
 // output is discarded once a flag is raised, so it may stop early
 // one stage with coefficients sc: Uout = sc.a Un + sc.b FE(Uk, sc.dt_mul dt)
@@ -210,8 +217,7 @@ hipError_t launch_coef(const afi::Geo& g, const afd::Phys& ph, const afi::Work& 
     if ((e = afi::blend_infer(g, ph, Uk, w.net, w.blend, s, tm)) != hipSuccess) return e;
     sc.blend = w.blend;
   }
-  const auto stage = g.dim == 1 ? afi::stage1d : (g.mixed ? afi::strips_mixed : afi::strips_fp64);
-  return stage(g, ph, w, Un, Uk, Uout, dt_dev, dt_host, sc, s, tm);
+  return stage_of(g)(g, ph, w, Un, Uk, Uout, dt_dev, dt_host, sc, s, tm);
 }
 
 hipError_t launch_stage(const afi::Geo& g, const afd::Phys& ph, const afi::Work& w, int k,
@@ -1164,22 +1170,20 @@ af_status af_run_graph(af_ctx* c, double* U, void* ws, void* stream, double t0, 
   const afi::Work w = work_of(c, g, ws);
   const hipStream_t s = (hipStream_t)stream;
   std::vector<afi::BatchInst> h(1);
-  h[0] = instance_of(c, g, afi::default_variant(g.mixed), U, w.S1, w.S2, t0, t_final, max_steps);
+  const afi::StageVariant* v = afi::default_variant(g.mixed);
+  h[0] = instance_of(c, g, v, U, w.S1, w.S2, t0, t_final, max_steps);
   set_strips(h[0], afi::strip_shape(g), 0);
-  const int nwg = h[0].nwg;
+  // (a grid too narrow for strips: the slots of a batch of one on tiles)
+  const bool tiles = afi::single_on_tiles(g);
+  const BatchPath path{v, g.mixed, 1, h[0].ntiles, 0, w.binst, nullptr, w.bpartial, w.bnact};
+  const int nwg = tiles ? 0 : h[0].nwg;
   // where the last stage leaves the CFL maxima of the new state; a grid of
   // more strips than that has room for takes its dt by the reduction kernels
-  double2* maxima = nwg <= afi::kSingleCflBlocks ? (double2*)w.bpartial : nullptr;
+  double2* maxima = !tiles && nwg <= afi::kSingleCflBlocks ? (double2*)w.bpartial : nullptr;
   AF_HIP(hipMemcpyAsync(w.binst, h.data(), sizeof(afi::BatchInst), hipMemcpyHostToDevice, s));
-  auto open = [&](hipStream_t q) {
-    const hipError_t e = afi::batch_cfl(w.binst, 1, w.bpartial, afi::kSingleCflBlocks, q);
-    return e != hipSuccess
-               ? e
-               : afi::batch_open(w.binst, 1, w.bpartial, afi::kSingleCflBlocks, w.bnact, q);
-  };
   // the first step; every later one opens from the maxima its predecessor's
   // last stage left (the dt reduction fused into that stage)
-  if (maxima) AF_HIP(open(s));
+  if (maxima) AF_HIP(batch_openings(path, s));
   int dev = 0;
   AF_HIP(hipGetDevice(&dev));
   if (c->run_exec && (c->run_inst != w.binst || c->run_slot != attempts_per_slot || c->run_dev != dev ||
@@ -1194,9 +1198,10 @@ af_status af_run_graph(af_ctx* c, double* U, void* ws, void* stream, double t0, 
   // a round: one RK3 attempt, then accept or halve, and open the next step
   const auto stage = g.mixed ? afi::strips_dev_mixed : afi::strips_dev_fp64;
   auto slot = [&](hipStream_t q, int rounds) {
+    if (tiles) return batch_slot(path, rounds, q);
     hipError_t e = hipSuccess;
     for (int a = 0; a < rounds && e == hipSuccess; ++a) {
-      if (!maxima) e = open(q);
+      if (!maxima) e = batch_openings(path, q);
       for (int k = 0; k < 3 && e == hipSuccess; ++k)
         e = stage(w.binst, nullptr, nwg, maxima, k, q);
       if (e != hipSuccess) break;
@@ -1281,8 +1286,7 @@ af_status af_rk_stage_blend(af_ctx* c, int k, const double* dt_dev, double dt_ho
     AF_HIP(afi::blend_infer(g, ph, Uk, c->net, w.blend, s, c->timer));
     sc.blend = w.blend;
   }
-  const auto stage = g.mixed ? afi::strips_mixed : afi::strips_fp64;
-  AF_HIP(stage(g, ph, w, Un, Uk, Uout, dt_dev, dt_host, sc, s, c->timer));
+  AF_HIP(stage_of(g)(g, ph, w, Un, Uk, Uout, dt_dev, dt_host, sc, s, c->timer));
   return AF_OK;
 }
 

@@ -162,6 +162,14 @@ hipError_t strips_fp64(const Geo& g, const afd::Phys& ph, const Work& w, const d
 hipError_t strips_mixed(const Geo& g, const afd::Phys& ph, const Work& w, const double* Un,
                         const double* Uk, double* Uout, const double* dt_dev, double dt_host,
                         StageCoef sc, hipStream_t s, Timer* tm);
+// ... and on tiles (af_stage2d.hip), for the grids that single_on_tiles says
+hipError_t tiles_fp64(const Geo& g, const afd::Phys& ph, const Work& w, const double* Un,
+                      const double* Uk, double* Uout, const double* dt_dev, double dt_host,
+                      StageCoef sc, hipStream_t s, Timer* tm);
+hipError_t tiles_mixed(const Geo& g, const afd::Phys& ph, const Work& w, const double* Un,
+                       const double* Uk, double* Uout, const double* dt_dev, double dt_host,
+                       StageCoef sc, hipStream_t s, Timer* tm);
+bool single_on_tiles(const Geo& g);
 // one 1D stage; a whole 1D step from U to Uout (other memory) in one launch
 hipError_t stage1d(const Geo& g, const afd::Phys& ph, const Work& w, const double* Un,
                    const double* Uk, double* Uout, const double* dt_dev, double dt_host,

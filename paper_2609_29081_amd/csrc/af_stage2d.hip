@@ -402,13 +402,26 @@ struct TileIter {
   }
 };
 
-// launch arguments: a batch of 2D instances (stage k reads and writes their
-// rotating buffers)
+// launch arguments of a stage: one instance, or a batch of 2D instances
 constexpr int kMaxBatch = 512;
 struct StageArgs {
+  // one instance, its step driven by the host
+  G2 g;
+  Phys ph;
+  const double* Uk;
+  const double* Un;
+  double* Uout;
+  const double* dt_dev;
+  double dt_host, dt_mul;  // the step is dt_mul * dt
+  unsigned* flags;
+  int ntx;
+  const float* blend;  // see limit_face
+  float* ts_out;
+  // a batch: its instances (stage k reads and writes their rotating buffers)
   afi::BatchInst* inst;
   int ninst, k;
   const int* n_active;
+  // both
   double ca, cb;
   int first, skip_flagged, ntiles;
 };
@@ -416,7 +429,8 @@ struct StageArgs {
 // what one tile of a stage works on.  Geometry and physics are referenced,
 // not copied: a copy would hold some thirty uniform values live across the
 // whole tile (register pressure of a kernel that is at its VGPR limit), while
-// a reference to the batch descriptor in global memory is re-read where needed.
+// a reference to the kernel arguments or to the batch descriptor in global
+// memory is re-read where needed.
 struct TileArgs {
   const G2* g;
   const Phys* phd;
@@ -465,7 +479,9 @@ __device__ __forceinline__ TileArgs batch_tile(const StageArgs& sa, const int* t
   return A;
 }
 
-template <typename R>
+// BLEND: one instance with per-face blend input/output arrays (a kernel of its
+// own, so that the plain stage carries none of that code)
+template <typename R, bool BATCH, bool BLEND = false>
 __global__ void __launch_bounds__(NT) k_stage(StageArgs sa) {
   __shared__ Tile<R> T;
   __shared__ unsigned stop;  // workgroup-uniform copy of the flag word
@@ -479,20 +495,21 @@ __global__ void __launch_bounds__(NT) k_stage(StageArgs sa) {
   // attempts).  Active instance j is instance bid[j] and owns tiles
   // [bt0[j], bt0[j] + its ntiles); the numbering comes from two inclusive
   // scans over the instances (one per thread), done in place in bt0 / bid.
-  __shared__ int bt0[kMaxBatch], bid[kMaxBatch];
-  int ntiles = sa.ntiles, nact = 0;
-  static_assert(kMaxBatch == NT, "one instance per thread in the scans");
-  if (*sa.n_active == 0) return;  // every instance has finished its step
-  if (sa.ninst == 1) {
+  __shared__ int bt0[BATCH ? kMaxBatch : 1], bid[BATCH ? kMaxBatch : 1];
+  int ntiles = sa.ntiles, nact = 1;
+  if constexpr (BATCH) {
+    static_assert(kMaxBatch == NT, "one instance per thread in the scans");
+    if (*sa.n_active == 0) return;  // every instance has finished its step
+  }
+  if (BATCH && sa.ninst == 1) {
     // one instance, active (n_active is not 0): its tiles are all the tiles
     if (tid == 0) {
       bid[0] = 0;
       bt0[0] = 0;
     }
-    nact = 1;
     ntiles = sa.inst[0].ntiles;
     __syncthreads();
-  } else {
+  } else if constexpr (BATCH) {
     const bool act = tid < sa.ninst && sa.inst[tid].active;
     const int own = act ? sa.inst[tid].ntiles : 0;
     bid[tid] = act ? 1 : 0;
@@ -516,9 +533,17 @@ __global__ void __launch_bounds__(NT) k_stage(StageArgs sa) {
     }
     __syncthreads();
   }
-  // what tile t works on (built where used, from the batch descriptors, so
-  // that nothing of it stays live across tiles)
-  auto args = [&](int t) { return batch_tile(sa, bt0, bid, nact, t); };
+  // the one instance's dt, read once (a read per tile costs 3 % of the stage)
+  double dt1 = 0.0;
+  if constexpr (!BATCH) dt1 = sa.dt_mul * (sa.dt_dev ? *sa.dt_dev : sa.dt_host);
+  // what tile t works on (built where used, from the kernel arguments or the
+  // batch descriptors, so that nothing of it stays live across tiles)
+  auto args = [&](int t) {
+    if constexpr (BATCH)
+      return batch_tile(sa, bt0, bid, nact, t);
+    else
+      return TileArgs{&sa.g, &sa.ph, sa.Uk, sa.Un, sa.Uout, dt1, sa.flags, sa.ntx, t};
+  };
   TileIter it(ntiles, blockIdx.x, gridDim.x);
   int tile = it.get();
   double pre[kRawPerThread][4];
@@ -806,7 +831,9 @@ __global__ void __launch_bounds__(NT) k_stage(StageArgs sa) {
   __syncthreads();
 
   // ---- phase 3: limited face fluxes of the tile's cells ----
-  const int limc = ph.lim & (LIM_SMOOTH | LIM_PP | LIM_LOWONLY);
+  const float* blend = BLEND ? sa.blend : nullptr;
+  float* ts_out = BLEND ? sa.ts_out : nullptr;
+  const int limc = (ph.lim & (LIM_SMOOTH | LIM_PP | LIM_LOWONLY)) | (blend ? 1 : 0);
   // FP64: the faces take waves 0-3 only; waves 4-7 compute the
   // x-direction site data of the low-order point scheme meanwhile (phase 5a
   // keeps the y-direction data, which overlay cell data the faces read)
@@ -883,7 +910,7 @@ __global__ void __launch_bounds__(NT) k_stage(StageArgs sa) {
       }
       fc.phi1 = mx(T.C[12][cax], T.C[12][cbx]);
       fc.phi2 = mx(T.C[13][cax], T.C[13][cbx]);
-      limit_face(g, ph, phd, d, i, j, dt, fc, FH, nullptr, nullptr, true, flags, F);
+      limit_face(g, ph, phd, d, i, j, dt, fc, FH, blend, ts_out, true, flags, F);
     }
     if (d == 0) {
 #pragma unroll
@@ -1081,12 +1108,21 @@ int resident_workgroups() {
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         cus <= 0)
       cus = 256;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_stage<R>, NT, 0) != hipSuccess ||
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_stage<R, true>, NT, 0) != hipSuccess ||
         per <= 0)
       per = 1;
     cache[dev] = cus * per;
   }
   return cache[dev];
+}
+
+// workgroups of a launch over ntiles tiles (see TileIter)
+template <typename R>
+int workgroups(int ntiles) {
+  int nwg = resident_workgroups<R>();
+  if (nwg > ntiles) nwg = ntiles;
+  if (nwg >= 8) nwg -= nwg % 8;
+  return nwg;
 }
 
 template <typename R>
@@ -1103,11 +1139,9 @@ hipError_t launch_batch(afi::BatchInst* inst, int ninst, int total_tiles, const 
   sa.first = k == 0;
   sa.skip_flagged = 1;
   sa.ntiles = total_tiles;
-  int nwg = resident_workgroups<R>();
-  if (nwg > total_tiles) nwg = total_tiles;
-  if (nwg >= 8) nwg -= nwg % 8;
+  const int nwg = workgroups<R>(total_tiles);
   AFI_TIMED(tm, 7, s,
-            hipLaunchKernelGGL((k_stage<R>), dim3((unsigned)nwg), dim3(NT), 0, s, sa));
+            hipLaunchKernelGGL((k_stage<R, true>), dim3((unsigned)nwg), dim3(NT), 0, s, sa));
   return hipGetLastError();
 }
 
@@ -1117,6 +1151,39 @@ namespace afi {
 
 // tiles of one 2D grid for this instance's tile shape
 int AF_STAGE_TILES(const Geo& geo) { return (geo.n1 / TX + 1) * (geo.n2 / TY + 1); }
+
+#ifdef AF_STAGE_ONE
+// the stage of one instance (see single_on_tiles)
+hipError_t AF_STAGE_ONE(const Geo& geo, const Phys& ph, const Work& w, const double* Un,
+                        const double* Uk, double* Uout, const double* dt_dev, double dt_host,
+                        StageCoef sc, hipStream_t s, Timer* tm) {
+  using R = AF_STAGE_REAL;
+  StageArgs sa{};
+  sa.g = stage_geo(geo);
+  sa.ph = ph;
+  sa.Uk = Uk;
+  sa.Un = Un;
+  sa.Uout = Uout;
+  sa.dt_dev = dt_dev;
+  sa.dt_host = dt_host;
+  sa.dt_mul = sc.dt_mul;
+  sa.flags = w.flags;
+  sa.ntx = geo.n1 / TX + 1;
+  sa.ca = sc.a;
+  sa.cb = sc.b;
+  sa.first = sc.first;
+  sa.skip_flagged = sc.skip_flagged;
+  sa.blend = sc.blend;
+  sa.ts_out = sc.ts_out;
+  sa.ntiles = AF_STAGE_TILES(geo);
+  const dim3 grid((unsigned)workgroups<R>(sa.ntiles));
+  if (sa.blend || sa.ts_out)
+    AFI_TIMED(tm, 7, s, hipLaunchKernelGGL((k_stage<R, false, true>), grid, dim3(NT), 0, s, sa));
+  else
+    AFI_TIMED(tm, 7, s, hipLaunchKernelGGL((k_stage<R, false>), grid, dim3(NT), 0, s, sa));
+  return hipGetLastError();
+}
+#endif
 
 // stage k of a step attempt of every active instance of a batch, one launch
 hipError_t AF_STAGE_BATCH(BatchInst* inst, int ninst, int total_tiles, const int* n_active, int k,

@@ -51,8 +51,9 @@
 // 101 with fewer operations in the residuals.
 //
 // The arithmetic is the tile kernel's, expression by expression, so the two
-// give the same bits.  The tile kernel remains for batches: see strip_shapes,
-// and the variants that af_batch_set_variant and af_batch_tune choose among.
+// give the same bits.  The tile kernel remains for batches (see strip_shapes, and
+// the variants that af_batch_set_variant and af_batch_tune choose among) and for
+// single grids of few columns and many rows (single_on_tiles).
 #include <algorithm>
 
 #include "af_scheme2d.hpp"
@@ -1460,6 +1461,28 @@ namespace afi {
 
 #ifdef AF_STRIP_SHAPES
 StripShape strip_shape(const Geo& g) { return strips_of(g); }
+
+// A single grid of few columns fills few of a strip's 60, and one of many rows
+// too needs more row steps than tiles take.  Fitted to stages of 4 to 15 columns,
+// in row steps of 2.23 us (FP64; mixed 1.73): tiles take 5.6 (10.4) a round and 1.8
+// (1.7) to start, but no less than 13.3 (23).  Measured, us a stage on strips and
+// tiles at 12 columns (FP64; mixed), the line lying between the first two rows and
+// between the third and fourth:
+//   12 x 1800    29.0, 30.0;  23.2, 37.1
+//   12 x 2500    33.8, 29.3;  26.9, 39.7
+//   12 x 4000    47.6, 41.5;  37.1, 40.5
+//   12 x 5000    56.0, 42.1;  43.8, 39.7
+//   12 x 30000   274, 212;    213, 160
+// and at 16 columns, two of tiles: 273, 430; 213, 307 for 30000 rows.
+bool single_on_tiles(const Geo& g) {
+  if (g.n1 >= 16) return false;
+  const int cus = device_cus();
+  const StripShape b = strips_of(g);
+  const long steps = ((long)b.nx * b.ny + cus - 1) / cus * (b.H + 5);
+  const long rounds = (default_variant(g.mixed)->tiles(g) + cus - 1) / cus;
+  return g.mixed ? 10 * steps > std::max(230L, 104 * rounds + 17)
+                 : 10 * steps > std::max(133L, 56 * rounds + 18);
+}
 
 // One H for all instances of a batch: the strips of the instances run together,
 // in any order, so a launch takes about the steps of all of them over the CUs,
