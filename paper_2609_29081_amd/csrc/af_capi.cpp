@@ -20,6 +20,7 @@
 
 #include "af_device.hpp"
 #include "af_internal.hpp"
+#include "af_slots.hpp"
 
 // workspace of af_step_noalloc: one copy per GPU, resident for the life of
 // the process.  Host code never uses this name as an address (on the host it
@@ -619,10 +620,7 @@ af_status run_slots(Slot slot, int rounds, afi::BatchInst* dinst, int n, int use
   long progress = -1;  // sum of steps and attempts: it grows while any instance works
   long left = max_steps;  // most steps any instance may still take
   for (;;) {
-    // no more slots than those steps need when every attempt is accepted: a
-    // round with nothing left to do still costs its launches (32 rounds for 3
-    // steps of a batch: 750 of its 2460 us)
-    const long slots = std::max(1L, std::min(chunk, (left + rounds - 1) / rounds));
+    const long slots = afi::slots_for(left, rounds, chunk);
     for (long c = 0; c < slots; ++c) {
       const hipError_t e =
           exec ? hipGraphLaunch(exec, s) : slot(s, (int)std::min((long)rounds, left - c * rounds));
