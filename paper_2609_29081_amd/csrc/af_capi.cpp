@@ -1429,8 +1429,9 @@ af_status af_batch_tune(af_batch* b, double* const* U, void* ws, void* stream, d
     const BatchPath path = batch_path(b, v, base, total);
     for (int r = 0; r <= reps; ++r) {
       if ((sd = upload_batch(b, h, buf, base, s)) != AF_OK) return sd;
-      hipError_t e = hipEventRecord(e0, s);
-      if (e == hipSuccess) e = batch_start(path, s);
+      // (strips open the first step once a run, not in every slot)
+      hipError_t e = batch_start(path, s);
+      if (e == hipSuccess) e = hipEventRecord(e0, s);
       if (e == hipSuccess) e = batch_slot(path, 1, s);
       if (e == hipSuccess) e = hipEventRecord(e1, s);
       if (e == hipSuccess) e = hipEventSynchronize(e1);
