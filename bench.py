@@ -753,8 +753,8 @@ def batched_form(args, stream) -> dict:
     """The batched form: a seeded sweep of viscous shock tubes (random
     Reynolds number, density ratio and grid, see workloads.shock_tube_sweep),
     mixed precision, advanced together by af_batch_run with HIP-graph replay,
-    each instance with its own time step and halving; the stage variant (tile
-    shape) is chosen by af_batch_tune on the initial states.  Timed: K
+    each instance with its own time step and halving; strips or tiles (and
+    their shape) are chosen by af_batch_tune on the initial states.  Timed: K
     accepted steps of every instance from t = 0 (inputs resident in HBM).
     value = sum over instances of DOF sites x 3 stages x steps / second."""
     import torch
@@ -803,8 +803,8 @@ def batched_form(args, stream) -> dict:
             "instances": len(insts), "cells": cells, "dof_sites": dof,
             "rk3_attempts_per_step": round(sum(att) / (K * len(insts)), 3),
             "graph": True, "attempts_per_slot": 4,
-            "variant": chosen[0], "tile": f"16x{chosen[2]}",
-            "tune_us_per_slot": {nm[0]: round(u, 1) for nm, u in zip(names, us) if u > 0},
+            "stage": "strips" if B.on_strips else f"tiles of {chosen[0]} (16x{chosen[2]})",
+            "tune_us_per_slot_on_tiles": {nm[0]: round(u, 1) for nm, u in zip(names, us) if u > 0},
             "tune_s": round(tune_s, 2),
             "error": "bitwise equal to single-instance mixed runs; FP32-stencil error as in "
                      "the mixed form"}

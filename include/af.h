@@ -324,6 +324,9 @@ int af_stage_variant_count(void);
 af_status af_stage_variant_info(int i, const char** name, int* precision, int* tile_height);
 /* Index of the batch's tile variant (a new batch: its precision's first). */
 int af_batch_variant(const af_batch* b);
+/* 1 if the batch's runs march up strips, 0 if they run on the tiles of its
+ * variant (-1: NULL). */
+int af_batch_on_strips(const af_batch* b);
 /* Run the batch on the tiles of variant i; it must have the batch's
  * precision. */
 af_status af_batch_set_variant(af_batch* b, int i);

@@ -49,7 +49,7 @@ EXPORTS = ["af_default_params", "af_init_grid", "af_destroy", "af_set_bc", "af_s
            "af_read_flags", "af_reset_flags", "af_timing", "af_timing_read", "af_last_error",
            "af_batch_create", "af_batch_destroy", "af_batch_workspace_bytes", "af_batch_run",
            "af_stage_variant_count", "af_stage_variant_info", "af_batch_variant",
-           "af_batch_set_variant", "af_batch_tune", "af_face_count", "af_mlp_param_count",
+           "af_batch_on_strips", "af_batch_set_variant", "af_batch_tune", "af_face_count", "af_mlp_param_count",
            "af_blend_features", "af_set_blend_net", "af_blend_infer", "af_rk_stage_blend",
            "af_mlp_grad_workspace_bytes", "af_mlp_grad", "af_mlp_adam", "af_mlp_train",
            "af_stage_times", "af_step_source", "af_step_noalloc", "af_run_graph"]
@@ -110,6 +110,7 @@ def lib():
         L.af_stage_variant_info.argtypes = [ip, C.POINTER(C.c_char_p), C.POINTER(ip),
                                             C.POINTER(ip)]
         L.af_batch_variant.argtypes = [vp]
+        L.af_batch_on_strips.argtypes = [vp]
         L.af_batch_set_variant.argtypes = [vp, ip]
         L.af_batch_tune.argtypes = [vp, C.POINTER(vp), vp, vp, C.c_double, C.c_double, ip, dp]
         L.af_batch_run.argtypes = [vp, C.POINTER(vp), vp, vp, C.c_double, C.c_double, C.c_long, ip,
@@ -439,8 +440,13 @@ class Batch:
 
     @property
     def variant(self) -> int:
-        """index (into stage_variants()) of the stage variant the batch uses"""
+        """index (into stage_variants()) of the batch's tile variant"""
         return int(lib().af_batch_variant(self.h))
+
+    @property
+    def on_strips(self) -> bool:
+        """whether the batch's runs march up strips, not on the tiles of variant"""
+        return lib().af_batch_on_strips(self.h) == 1
 
     @variant.setter
     def variant(self, i: int):
@@ -449,8 +455,9 @@ class Batch:
     def af_batch_tune(self, states: list, t0: float, t_final: float, reps: int = 3,
                       stream=None) -> list:
         """time every stage variant of the batch's precision on one step slot
-        from the given states and keep the fastest; returns the time per slot
-        of each variant in microseconds (-1 for the other precision)"""
+        from the given states and keep the fastest, or strips if they are faster
+        still; returns the time per slot of each variant in microseconds (-1 for
+        the other precision)"""
         n = len(self.solvers)
         if len(states) != n:
             raise ValueError("one state per instance")

@@ -1392,6 +1392,8 @@ int af_batch_variant(const af_batch* b) {
   return b ? (int)(b->var - afi::kStageVariants) : -1;
 }
 
+int af_batch_on_strips(const af_batch* b) { return b ? (b->strips ? 1 : 0) : -1; }
+
 af_status af_batch_set_variant(af_batch* b, int i) {
   if (!b) return fail(AF_E_ARG, "af_batch_set_variant: NULL batch");
   if (i < 0 || i >= afi::kNumStageVariants)
