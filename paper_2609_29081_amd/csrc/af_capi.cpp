@@ -316,15 +316,12 @@ hipError_t launch_cfl(const af_ctx* c, const afi::Geo& g, const afi::Work& w, co
 }
 
 // the CFL step of a 1D step that fixes dt itself, as launch_cfl takes it
-afi::StepExtras1::Cfl step_cfl(const af_ctx* c, const afi::Geo& g, double t_host,
-                              const double* t_dev, double t_final) {
+afi::StepExtras1::Cfl step_cfl(const af_ctx* c, const afi::Geo& g, double t_final) {
   const af_params& p = c->p;
   afi::StepExtras1::Cfl f;
   f.on = 1;
   f.icx = 1.0 / (p.cfl_c * g.dx);
   f.vcoef = fmax(4.0 * p.mu / 3.0, p.gamma * p.mu / p.Pr) / (p.cfl_v * g.dx * g.dx);
-  f.t_host = t_host;
-  f.t_dev = t_dev;
   f.t_final = t_final;
   return f;
 }
@@ -430,8 +427,8 @@ af_status scratch_on_current_device(void** out) {
 // forward Euler step then adds tau S_k after its limited update
 hipError_t rk3(const afi::Geo& g, const afd::Phys& ph, const afi::Work& w, const double* cur,
                double* out, const double* dt_dev, double dt, hipStream_t s, afi::Timer* tm,
-               const double* const* src = nullptr, const afi::StepExtras1& x = {}) {
-  if (g.dim == 1 && !src) return afi::step1d(g, ph, w, cur, out, dt_dev, dt, kStep3, x, s, tm);
+               const double* const* src = nullptr) {
+  if (g.dim == 1 && !src) return afi::step1d(g, ph, w, cur, out, dt_dev, dt, kStep3, {}, s, tm);
   hipError_t e;
   if ((e = launch_stage(g, ph, w, 0, cur, cur, w.S1, dt_dev, dt, s, tm)) != hipSuccess)
     return e;
@@ -888,28 +885,21 @@ static af_status step_in(af_ctx* c, double* U, void* ws, void* stream, double dt
   // the CFL step stays on the device for the first attempt; the host reads it
   // with the flags
   const double* dt_dev = nullptr;
-  afi::StepExtras1 x{};
-  const bool cfl = dt <= 0.0;
-  if (cfl && !afi::step1d_takes_cfl(g)) {
+  if (dt <= 0.0) {
     dt_dev = w.scal;
     AF_HIP(launch_cfl(c, g, w, U, t, nullptr, t_final, w.scal, s, w.SAVE));
   } else {
     AF_HIP(afi::copy_state(w.SAVE, U, g.state_len, s, w.flags));
-    if (cfl) {
-      dt_dev = w.scal;
-      x.cfl = step_cfl(c, g, t, nullptr, t_final);
-    } else if (t + dt > t_final) {
-      dt = t_final - t;
-    }
+    if (t + dt > t_final) dt = t_final - t;
   }
   unsigned fl = 0;
   int h;
   for (h = 0; h <= c->p.max_halvings; ++h) {
     if (h > 0) AF_HIP(afi::set_flags(w, 0u, s));
     if (c->p.rk == 54)
-      AF_HIP(rk54(g, ph, w, w.SAVE, w.S1, w.S2, U, dt_dev, dt, s, c->timer, nullptr, x));
+      AF_HIP(rk54(g, ph, w, w.SAVE, w.S1, w.S2, U, dt_dev, dt, s, c->timer));
     else
-      AF_HIP(rk3(g, ph, w, w.SAVE, U, dt_dev, dt, s, c->timer, nullptr, x));
+      AF_HIP(rk3(g, ph, w, w.SAVE, U, dt_dev, dt, s, c->timer));
     double sc[3];
     af_status st = read_scalars(w, s, slot, sc, &fl);
     if (st != AF_OK) return st;
@@ -917,7 +907,6 @@ static af_status step_in(af_ctx* c, double* U, void* ws, void* stream, double dt
     if (fl == 0) break;
     dt *= 0.5;
     dt_dev = nullptr;
-    x = {};
   }
   if (dt_used) *dt_used = dt;
   if (halvings) *halvings = h;
@@ -996,10 +985,10 @@ af_status af_run(af_ctx* c, double* U, void* ws, void* stream, double t0, double
       return e;
     return launch_stage(g, ph, w, 2, bufs[from], bufs[b], bufs[a], w.scal, 0.0, s, c->timer);
   };
-  // in 1D a block's steps fix dt and keep the time themselves
+  // in 1D a block's steps keep the time themselves, and on small grids fix dt
   const bool cfl_in_step = afi::step1d_takes_cfl(g);
   afi::StepExtras1 in_step{};
-  if (cfl_in_step) in_step.cfl = step_cfl(c, g, 0.0, nullptr, t_final);
+  if (cfl_in_step) in_step.cfl = step_cfl(c, g, t_final);
   in_step.steps = w.scal + 2;
   AF_HIP(afi::set_scalar(w.scal + 1, t, s));
   while (done < max_steps && t < t_final) {
@@ -1017,7 +1006,7 @@ af_status af_run(af_ctx* c, double* U, void* ws, void* stream, double t0, double
         if (!cfl_in_step)
           AF_HIP(launch_cfl(c, g, w, bufs[c2], 0.0, w.scal + 1, t_final, w.scal, s));
         if (g.dim == 1) {
-          in_step.t_in = in_step.cfl.t_dev = at[(K - k) & 1];
+          in_step.t_in = at[(K - k) & 1];
           in_step.t_out = at[(K - k + 1) & 1];
           AF_HIP(attempt(c2, in_step));
         } else {

@@ -182,20 +182,18 @@ struct StepCoef1 {
   double a[5], b[5], mul[5];
   double wa, wb, ga, gb;
 };
-// what a 1D step does beside its stages: fix dt itself (eq. cfl, from its
-// averages, as k_cfl takes it), left in scal[0]; and keep a run's time, t_out =
-// t_in + dt, one step more
+// what a 1D step of a run's block does beside its stages: keep the time, t_out =
+// t_in + dt, one step more; and fix dt itself (eq. cfl, from its averages, as
+// k_cfl takes it)
 struct StepExtras1 {
   struct Cfl {
     int on;
-    double icx, vcoef, t_host, t_final;
-    const double* t_dev;
+    double icx, vcoef, t_final;
   } cfl;
   const double* t_in;
   double *t_out, *steps;
 };
-// whether a 1D step of this grid can fix dt itself (every workgroup reads all
-// averages, which pays while they are few)
+// whether a run's steps of this 1D grid fix dt themselves
 bool step1d_takes_cfl(const Geo& g);
 hipError_t step1d(const Geo& g, const afd::Phys& ph, const Work& w, const double* U, double* Uout,
                   const double* dt_dev, double dt_host, const StepCoef1& sc, const StepExtras1& x,

@@ -63,7 +63,6 @@ struct Step1 {
   const double* dt_dev;
   double dt_host;
   afi::StepExtras1 x;
-  double* dt_out;
 };
 
 // the state a stage reads: in global memory, its ghosts the images of what
@@ -205,9 +204,10 @@ __device__ __forceinline__ void cell_site(const G1& g, const Phys& ph, const Src
   for (int k = 0; k < 3; ++k) S.C[7 + k][t] = C0[k];
 }
 
-// limited flux of the face between ring cells a and a + 1, at lattice entry q
+// limited flux of the face between ring cells a and a + 1, at lattice entry q; low
+// is added to the flags raised where a low-order state is inadmissible
 __device__ __forceinline__ void face_flux(const G1& g, const Phys& ph, const Tile1& S, int a, int q,
-                                          double dt, unsigned* flags, const StageFlags& fl,
+                                          double dt, unsigned low, unsigned& raised,
                                           double* F) {
   const int b = a + 1;
   double FH[3];
@@ -281,7 +281,7 @@ __device__ __forceinline__ void face_flux(const G1& g, const Phys& ph, const Til
                                theta_p1(ULm, pLm, Tm, mn(kPPEps, pLm), ph.gm1, ex));
           tpp = tr * tp;
         }
-        if (bad) raise_flag(flags, fl.cell_low);
+        if (bad) raised |= low;
       }
     }
     const double th = ts * tpp;
@@ -309,8 +309,8 @@ __device__ __forceinline__ void lo_site1(const Phys& ph, const double (&V)[5][3]
 // forward-Euler value of point k0 (lattice entry q, ring cells r0 and r0 + 1
 // at its sides) into out
 __device__ __forceinline__ void point_update(const G1& g, const Phys& ph, const Tile1& S, int k0,
-                                             int q, int r0, double dt, unsigned* flags,
-                                             const StageFlags& fl, double* out) {
+                                             int q, int r0, double dt, unsigned low,
+                                             unsigned& raised, double* out) {
   const int X = 2 * k0;
   const double i6h = 1.0 / (6.0 * g.dx);
   double Us[5][3], u[5], p[5], T[5];
@@ -390,7 +390,7 @@ __device__ __forceinline__ void point_update(const G1& g, const Phys& ph, const 
     bool lbad = false;
     double th = theta_pair1(UL, UH, ph.gm1, lbad, ph.lim & LIM_PEXACT);
     if (ph.lim & LIM_LOWONLY) th = 0.0;
-    if (lbad) raise_flag(flags, fl.point_low);
+    if (lbad) raised |= low;
     if (th != 1.0) {
 #pragma unroll
       for (int k = 0; k < 3; ++k) out[k] = UL[k] + th * (UH[k] - UL[k]);
@@ -439,6 +439,7 @@ __global__ void __launch_bounds__(kThreads) k_stage1(G1 g, Phys ph, Stage1 st,
   double dt = st.dt_dev ? *st.dt_dev : st.dt_host;
   if (st.dt_mul != 1.0) dt = st.dt_mul * dt;
   bool ok = true;
+  unsigned raised = 0u;
   // RK combination of the forward-Euler value fe of DOF array element a
   auto combine = [&](long a, double fe) {
     const double o = st.first ? fe : st.ca * Un[a] + st.cb * fe;
@@ -447,7 +448,7 @@ __global__ void __launch_bounds__(kThreads) k_stage1(G1 g, Phys ph, Stage1 st,
   };
   if (wave == 0) {
     double F[3] = {0.0, 0.0, 0.0};
-    if (nc > 0 && lane <= nc) face_flux(g, ph, S, lane, 2 * lane + 2, dt, st.flags, fl, F);
+    if (nc > 0 && lane <= nc) face_flux(g, ph, S, lane, 2 * lane + 2, dt, fl.cell_low, raised, F);
     const double m = dt / g.dx;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
@@ -456,11 +457,12 @@ __global__ void __launch_bounds__(kThreads) k_stage1(G1 g, Phys ph, Stage1 st,
     }
   } else if (wave == 1 && lane < npt) {
     double out[3];
-    point_update(g, ph, S, i0 + lane, 2 * lane + 2, lane, dt, st.flags, fl, out);
+    point_update(g, ph, S, i0 + lane, 2 * lane + 2, lane, dt, fl.point_low, raised, out);
 #pragma unroll
     for (int k = 0; k < 3; ++k) combine(g.off_pts + (long)k * g.np + i0 + lane, out[k]);
   }
-  if (!ok) raise_flag(st.flags, wave == 0 ? fl.cells_nonfinite : fl.points_nonfinite);
+  if (!ok) raised |= wave == 0 ? fl.cells_nonfinite : fl.points_nonfinite;
+  if (raised) raise_flag(st.flags, raised);
 }
 
 // a whole step from U to Uout (other memory: neighbouring tiles read U)
@@ -477,8 +479,7 @@ __global__ void __launch_bounds__(kThreads) k_step1(G1 g, Phys ph, Step1 st,
     // A step of a run's block stops once one before it was rejected (the block is
     // redone).  Any other step is an attempt of its own, whose flag word was
     // cleared before the launch: what is up by now came from a faster tile, and a
-    // tile that stopped for it would leave out flags of an earlier stage, or,
-    // being the first, the step's dt.
+    // tile that stopped for it would leave out flags of an earlier stage.
     S.stop = st.x.t_out ? peek_flags(st.flags) : 0u;
     H.b = b;
   }
@@ -525,11 +526,10 @@ __global__ void __launch_bounds__(kThreads) k_step1(G1 g, Phys ph, Step1 st,
   if (st.x.cfl.on) {
     const double a = mx(mx(S.red[0][0], S.red[0][1]), S.red[0][2]);
     const double v = mx(mx(S.red[1][0], S.red[1][1]), S.red[1][2]);
-    const double t = st.x.cfl.t_dev ? *st.x.cfl.t_dev : st.x.cfl.t_host;
+    const double t = *st.x.t_in;
     dt0 = 1.0 / (a + v);
     if (t + dt0 > st.x.cfl.t_final) dt0 = st.x.cfl.t_final - t;
     if (!(dt0 > 0.0)) dt0 = 0.0;
-    if (blockIdx.x == 0 && tid == 0) *st.dt_out = dt0;
   } else {
     dt0 = st.dt_dev ? *st.dt_dev : st.dt_host;
   }
@@ -540,6 +540,7 @@ __global__ void __launch_bounds__(kThreads) k_step1(G1 g, Phys ph, Step1 st,
     *st.x.t_out = dt0 > 0.0 ? t + dt0 : t;
     if (dt0 > 0.0) *st.x.steps = *st.x.steps + 1.0;
   }
+  unsigned raised = 0u;
   // the lane's cell (wave 0) or point (wave 1): the step's first state, and
   // SSP-RK54's second stage, which its last one builds on
   double un[3], u2[3] = {0.0, 0.0, 0.0}, now[3];
@@ -582,7 +583,7 @@ __global__ void __launch_bounds__(kThreads) k_step1(G1 g, Phys ph, Step1 st,
     if (wave == 0) {
       double F[3] = {0.0, 0.0, 0.0};
       if (real_face && lane >= 2 * s && lane <= kCells - 2 * s)
-        face_flux(g, ph, S, lane, 2 * lane + 2, dt, st.flags, fl, F);
+        face_flux(g, ph, S, lane, 2 * lane + 2, dt, fl.cell_low, raised, F);
       const double m = dt / g.dx;
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
@@ -594,14 +595,14 @@ __global__ void __launch_bounds__(kThreads) k_step1(G1 g, Phys ph, Step1 st,
       }
     } else if (wave == 1 && real_point && lane >= 2 * s && lane <= kCells - 2 * s) {
       double out[3];
-      point_update(g, ph, S, j, 2 * lane + 2, lane, dt, st.flags, fl, out);
+      point_update(g, ph, S, j, 2 * lane + 2, lane, dt, fl.point_low, raised, out);
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
         combine(k, out[k]);
         H.P[k][lane + 1] = now[k];
       }
     }
-    if (!ok) raise_flag(st.flags, wave == 0 ? fl.cells_nonfinite : fl.points_nonfinite);
+    if (!ok) raised |= wave == 0 ? fl.cells_nonfinite : fl.points_nonfinite;
     __syncthreads();
   }
   if (lane >= halo && lane < halo + own) {
@@ -611,6 +612,7 @@ __global__ void __launch_bounds__(kThreads) k_step1(G1 g, Phys ph, Step1 st,
       if (wave == 1 && j < g.np) Uout[g.off_pts + (long)k * g.np + j] = now[k];
     }
   }
+  if (raised) raise_flag(st.flags, raised);
 }
 
 G1 geo1(const afi::Geo& geo) {
@@ -632,7 +634,17 @@ G1 geo1(const afi::Geo& geo) {
 
 namespace afi {
 
-bool step1d_takes_cfl(const Geo& g) { return g.dim == 1 && g.n1 <= 4096; }
+// Every workgroup takes the maxima of the whole grid for itself, which costs less
+// than a launch while the averages are few.  Measured, us a step of a run with dt
+// in the step and in a launch before it (SSP-RK3; SSP-RK54):
+//   400 cells    13.0, 14.3;  17.5, 18.7
+//   800          13.9, 14.4;  18.4, 19.0
+//   1200         14.8, 14.7;  19.2, 19.3
+//   1600         15.5, 15.1;  19.8, 19.6
+//   4096         20.1, 16.9;  24.3, 21.3
+// (A single step saves its state in the launch that fixes dt, so that dt in the
+// step itself gains it nothing: af_step of 400 cells takes 32.2 us so, 30.2 apart.)
+bool step1d_takes_cfl(const Geo& g) { return g.dim == 1 && g.n1 <= 1200; }
 
 hipError_t stage1d(const Geo& geo, const Phys& ph, const Work& w, const double* Un,
                    const double* Uk, double* Uout, const double* dt_dev, double dt_host,
@@ -673,7 +685,6 @@ hipError_t step1d(const Geo& geo, const Phys& ph, const Work& w, const double* U
   st.dt_dev = dt_dev;
   st.dt_host = dt_host;
   st.x = x;
-  st.dt_out = w.scal;
   const int own = kCells - 4 * (sc.stages - 1);
   AFI_TIMED(tm, 0, s,
             hipLaunchKernelGGL(k_step1, dim3((unsigned)((g.np + own - 1) / own)), dim3(kThreads),
