@@ -204,8 +204,6 @@ auto stage_of(const afi::Geo& g) {
   return g.mixed ? afi::strips_mixed : afi::strips_fp64;
 }
 
-// in_step: the stage is part of a step attempt (af_step, af_run), whose
-// output is discarded once a flag is raised, so it may stop early
 // one stage with coefficients sc: Uout = sc.a Un + sc.b FE(Uk, sc.dt_mul dt)
 hipError_t launch_coef(const afi::Geo& g, const afd::Phys& ph, const afi::Work& w,
                        afi::StageCoef sc, const double* Un, const double* Uk, double* Uout,
@@ -221,11 +219,13 @@ hipError_t launch_coef(const afi::Geo& g, const afd::Phys& ph, const afi::Work& 
   return stage_of(g)(g, ph, w, Un, Uk, Uout, dt_dev, dt_host, sc, s, tm);
 }
 
+// skip: the stage is part of a step attempt (see StageCoef), whose output is
+// discarded once a flag is raised
 hipError_t launch_stage(const afi::Geo& g, const afd::Phys& ph, const afi::Work& w, int k,
                         const double* Un, const double* Uk, double* Uout, const double* dt_dev,
-                        double dt_host, hipStream_t s, afi::Timer* tm, bool in_step = true) {
+                        double dt_host, hipStream_t s, afi::Timer* tm, int skip) {
   afi::StageCoef sc = kCoef[k];
-  sc.skip_flagged = in_step ? 1 : 0;
+  sc.skip_flagged = skip;
   sc.stage = k;
   return launch_coef(g, ph, w, sc, Un, Uk, Uout, dt_dev, dt_host, s, tm);
 }
@@ -262,21 +262,21 @@ const afi::StepCoef1 kStep54 = {5,
                                 kA53};
 
 // one SSP-RK54 attempt from u0 (kept) through buffers A, B into X; src as
-// for rk3 (five stage inputs); x: 1D steps without sources
+// for rk3 (five stage inputs); skip: see launch_stage; x: 1D steps without sources
 hipError_t rk54(const afi::Geo& g, const afd::Phys& ph, const afi::Work& w, const double* u0,
-                double* A, double* B, double* X, const double* dt_dev, double dt, hipStream_t s,
-                afi::Timer* tm, const double* const* src = nullptr,
+                double* A, double* B, double* X, const double* dt_dev, double dt, int skip,
+                hipStream_t s, afi::Timer* tm, const double* const* src = nullptr,
                 const afi::StepExtras1& x = {}) {
   if (g.dim == 1 && !src)
     return afi::step1d(g, ph, w, u0, X, dt_dev, dt, kStep54, x, s, tm);
   int stage = 0;
-  auto coef = [&stage](double a, double b, double mul) {
+  auto coef = [&stage, skip](double a, double b, double mul) {
     afi::StageCoef c{};
     c.stage = stage++;
     c.a = a;
     c.b = b;
     c.first = a == 0.0 ? 1 : 0;
-    c.skip_flagged = 1;
+    c.skip_flagged = skip;
     c.dt_mul = mul;
     return c;
   };
@@ -326,10 +326,10 @@ afi::StepExtras1::Cfl step_cfl(const af_ctx* c, const afi::Geo& g, double t_fina
   return f;
 }
 
-af_status read_flags(const afi::Work& w, hipStream_t s, unsigned* out) {
+af_status read_flags(const afi::Geo& g, const afi::Work& w, hipStream_t s, unsigned* out) {
   AF_HIP(hipMemcpyAsync(out, w.flags, sizeof(unsigned), hipMemcpyDeviceToHost, s));
   AF_HIP(hipStreamSynchronize(s));
-  *out = afd::first_flags(*out);
+  *out = afd::first_flags(*out, g.dim);
   return AF_OK;
 }
 
@@ -379,8 +379,8 @@ struct SlotHolder {
 // the call's host slot, or else in one copy (they are the first two entries
 // of the workspace).  A copy to pageable memory costs a synchronous call about
 // 15 us whatever its size.
-af_status read_scalars(const afi::Work& w, hipStream_t s, afi::StepReport* slot, double* sc,
-                       unsigned* flags) {
+af_status read_scalars(const afi::Geo& g, const afi::Work& w, hipStream_t s,
+                       afi::StepReport* slot, double* sc, unsigned* flags) {
   afi::StepReport r;
   if (slot) {
     AF_HIP(afi::report(w, slot, s));
@@ -397,7 +397,7 @@ af_status read_scalars(const afi::Work& w, hipStream_t s, afi::StepReport* slot,
     memcpy(&r.flags, buf + at, sizeof(unsigned));
   }
   memcpy(sc, r.scal, sizeof(r.scal));
-  *flags = afd::first_flags(r.flags);
+  *flags = afd::first_flags(r.flags, g.dim);
   return AF_OK;
 }
 
@@ -424,18 +424,21 @@ af_status scratch_on_current_device(void** out) {
 
 // three stages with a host-given dt; cur -> out through S1, S2.  src, if not
 // NULL, holds a source term at each stage input's time (host dt only): each
-// forward Euler step then adds tau S_k after its limited update
+// forward Euler step then adds tau S_k after its limited update.  skip: see
+// launch_stage
 hipError_t rk3(const afi::Geo& g, const afd::Phys& ph, const afi::Work& w, const double* cur,
-               double* out, const double* dt_dev, double dt, hipStream_t s, afi::Timer* tm,
-               const double* const* src = nullptr) {
+               double* out, const double* dt_dev, double dt, int skip, hipStream_t s,
+               afi::Timer* tm, const double* const* src = nullptr) {
   if (g.dim == 1 && !src) return afi::step1d(g, ph, w, cur, out, dt_dev, dt, kStep3, {}, s, tm);
   hipError_t e;
-  if ((e = launch_stage(g, ph, w, 0, cur, cur, w.S1, dt_dev, dt, s, tm)) != hipSuccess)
+  if ((e = launch_stage(g, ph, w, 0, cur, cur, w.S1, dt_dev, dt, s, tm, skip)) != hipSuccess)
     return e;
   if (src && (e = add_source(g, w.S1, dt, src[0], s)) != hipSuccess) return e;
-  if ((e = launch_stage(g, ph, w, 1, cur, w.S1, w.S2, dt_dev, dt, s, tm)) != hipSuccess) return e;
+  if ((e = launch_stage(g, ph, w, 1, cur, w.S1, w.S2, dt_dev, dt, s, tm, skip)) != hipSuccess)
+    return e;
   if (src && (e = add_source(g, w.S2, 0.25 * dt, src[1], s)) != hipSuccess) return e;
-  if ((e = launch_stage(g, ph, w, 2, cur, w.S2, out, dt_dev, dt, s, tm)) != hipSuccess) return e;
+  if ((e = launch_stage(g, ph, w, 2, cur, w.S2, out, dt_dev, dt, s, tm, skip)) != hipSuccess)
+    return e;
   if (src && (e = add_source(g, out, 2.0 / 3.0 * dt, src[2], s)) != hipSuccess) return e;
   return hipSuccess;
 }
@@ -835,7 +838,7 @@ af_status af_rk_stage(af_ctx* c, int k, const double* dt_dev, double dt_host, co
   if (!geometry(c, &g)) return AF_E_ARG;
   const afi::Work w = work_of(c, g, ws);
   hipError_t e = launch_stage(g, physics(c->p), w, k, Un, Uk, Uout, dt_dev, dt_host,
-                              (hipStream_t)stream, c->timer, false);
+                              (hipStream_t)stream, c->timer, 0);
   if (e != hipSuccess) return hip_fail(e, "af_rk_stage launch");
   return AF_OK;
 }
@@ -857,7 +860,7 @@ af_status af_read_flags(af_ctx* c, const void* ws, int* flags, void* stream) {
   if (!geometry(c, &g)) return AF_E_ARG;
   const afi::Work w = work_of(c, g, ws);
   unsigned f = 0;
-  af_status st = read_flags(w, (hipStream_t)stream, &f);
+  af_status st = read_flags(g, w, (hipStream_t)stream, &f);
   *flags = (int)f;
   return st;
 }
@@ -896,12 +899,13 @@ static af_status step_in(af_ctx* c, double* U, void* ws, void* stream, double dt
   int h;
   for (h = 0; h <= c->p.max_halvings; ++h) {
     if (h > 0) AF_HIP(afi::set_flags(w, 0u, s));
+    const int skip = h < c->p.max_halvings ? 1 : 2;
     if (c->p.rk == 54)
-      AF_HIP(rk54(g, ph, w, w.SAVE, w.S1, w.S2, U, dt_dev, dt, s, c->timer));
+      AF_HIP(rk54(g, ph, w, w.SAVE, w.S1, w.S2, U, dt_dev, dt, skip, s, c->timer));
     else
-      AF_HIP(rk3(g, ph, w, w.SAVE, U, dt_dev, dt, s, c->timer));
+      AF_HIP(rk3(g, ph, w, w.SAVE, U, dt_dev, dt, skip, s, c->timer));
     double sc[3];
-    af_status st = read_scalars(w, s, slot, sc, &fl);
+    af_status st = read_scalars(g, w, s, slot, sc, &fl);
     if (st != AF_OK) return st;
     if (dt_dev) dt = sc[0];
     if (fl == 0) break;
@@ -968,22 +972,22 @@ af_status af_run(af_ctx* c, double* U, void* ws, void* stream, double t0, double
   double sc[3];
   unsigned fl = 0;
   SlotHolder slot;
-  auto read_back = [&]() { return read_scalars(w, s, slot.slot, sc, &fl); };
-  auto attempt = [&](int from, const afi::StepExtras1& x = {}) -> hipError_t {
+  auto read_back = [&]() { return read_scalars(g, w, s, slot.slot, sc, &fl); };
+  auto attempt = [&](int from, int skip, const afi::StepExtras1& x = {}) -> hipError_t {
     if (rk54s)
       return rk54(g, ph, w, bufs[from], bufs[(from + 1) % 4], bufs[(from + 2) % 4],
-                  bufs[(from + 3) % 4], w.scal, 0.0, s, c->timer, nullptr, x);
+                  bufs[(from + 3) % 4], w.scal, 0.0, skip, s, c->timer, nullptr, x);
     const int a = (from + 1) % 3, b = (from + 2) % 3;
     if (g.dim == 1)
       return afi::step1d(g, ph, w, bufs[from], bufs[a], w.scal, 0.0, kStep3, x, s, c->timer);
     hipError_t e;
     if ((e = launch_stage(g, ph, w, 0, bufs[from], bufs[from], bufs[a], w.scal, 0.0, s,
-                          c->timer)) != hipSuccess)
+                          c->timer, skip)) != hipSuccess)
       return e;
     if ((e = launch_stage(g, ph, w, 1, bufs[from], bufs[a], bufs[b], w.scal, 0.0, s,
-                          c->timer)) != hipSuccess)
+                          c->timer, skip)) != hipSuccess)
       return e;
-    return launch_stage(g, ph, w, 2, bufs[from], bufs[b], bufs[a], w.scal, 0.0, s, c->timer);
+    return launch_stage(g, ph, w, 2, bufs[from], bufs[b], bufs[a], w.scal, 0.0, s, c->timer, skip);
   };
   // in 1D a block's steps keep the time themselves, and on small grids fix dt
   const bool cfl_in_step = afi::step1d_takes_cfl(g);
@@ -1008,9 +1012,9 @@ af_status af_run(af_ctx* c, double* U, void* ws, void* stream, double t0, double
         if (g.dim == 1) {
           in_step.t_in = at[(K - k) & 1];
           in_step.t_out = at[(K - k + 1) & 1];
-          AF_HIP(attempt(c2, in_step));
+          AF_HIP(attempt(c2, 1, in_step));
         } else {
-          AF_HIP(attempt(c2));
+          AF_HIP(attempt(c2, 1));
           AF_HIP(afi::advance_time(w, s));
         }
         c2 = next(c2);
@@ -1032,7 +1036,7 @@ af_status af_run(af_ctx* c, double* U, void* ws, void* stream, double t0, double
       int h;
       for (h = 0; h <= c->p.max_halvings; ++h) {
         AF_HIP(afi::set_flags(w, 0u, s));
-        AF_HIP(attempt(cur));
+        AF_HIP(attempt(cur, h < c->p.max_halvings ? 1 : 2));
         if ((status = read_back()) != AF_OK) break;
         if (fl == 0) break;
         AF_HIP(afi::scale_scalar(w.scal, 0.5, s));  // redo with dt/2
@@ -1349,11 +1353,11 @@ af_status af_step_source(af_ctx* c, double* U, void* ws, void* stream, double dt
   const afd::Phys ph = physics(c->p);
   AF_HIP(afi::copy_state(w.SAVE, U, g.state_len, s, w.flags));
   if (c->p.rk == 54)
-    AF_HIP(rk54(g, ph, w, w.SAVE, w.S1, w.S2, U, nullptr, dt, s, c->timer, src));
+    AF_HIP(rk54(g, ph, w, w.SAVE, w.S1, w.S2, U, nullptr, dt, 2, s, c->timer, src));
   else
-    AF_HIP(rk3(g, ph, w, w.SAVE, U, nullptr, dt, s, c->timer, src));
+    AF_HIP(rk3(g, ph, w, w.SAVE, U, nullptr, dt, 2, s, c->timer, src));
   unsigned fl = 0;
-  af_status st = read_flags(w, s, &fl);
+  af_status st = read_flags(g, w, s, &fl);
   if (st != AF_OK) return st;
   if (fl != 0) {
     AF_HIP(afi::copy_state(U, w.SAVE, g.state_len, s));

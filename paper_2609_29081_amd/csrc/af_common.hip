@@ -339,7 +339,7 @@ __device__ __forceinline__ void decide_one(afi::BatchInst& I) {
     I.halvings += 1;
     I.flags = 0u;
   } else {
-    I.status = (f & FLAG_NONFINITE) ? 4 : 3;  // AF_E_NONFINITE : AF_E_PP
+    I.status = (first_flags2(f) & FLAG_NONFINITE) ? 4 : 3;  // AF_E_NONFINITE : AF_E_PP
     I.active = 0;
   }
 }

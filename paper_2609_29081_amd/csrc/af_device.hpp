@@ -413,9 +413,21 @@ __device__ __forceinline__ StageFlags attempt_flags(int stage) {
   const unsigned f = 1u << (kAttemptBit + kStageBits * stage);
   return StageFlags{f, f << 1, f << 2, f << 3};
 }
+// In 2D a stage of an attempt is one launch, and strips stop in the middle of it
+// once the attempt is rejected, which leaves out what the rest of it would have
+// raised: a NaN would be known by the inadmissible face beside it, that is met
+// first.  So the last attempt that halving allows, whose flags decide the status,
+// stops for the stages before alone, which takes a stage's flags apart from theirs:
+// FLAG_* three bits further up from one stage to the next.
+constexpr int kStageShift = 3;
 // the flags (FLAG_*) that a word stands for: in an attempt, those of the first
-// launch that would have raised any
-inline unsigned first_flags(unsigned word) {
+// stage (1D: launch) that raised any
+__host__ __device__ inline unsigned first_flags2(unsigned word) {
+  while (word && !(word & 7u)) word >>= kStageShift;
+  return word & 7u;
+}
+inline unsigned first_flags(unsigned word, int dim) {
+  if (dim == 2) return first_flags2(word);
   if (word < (1u << kAttemptBit)) return word;
   unsigned f = word >> kAttemptBit;
   while (!(f & 15u)) f >>= kStageBits;

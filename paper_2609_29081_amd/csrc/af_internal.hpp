@@ -106,8 +106,10 @@ struct Work {
 struct StageCoef {
   double a, b;
   int first;  // 1: Uout = FE(Uk)
-  // 1: the stage belongs to a step attempt and stops as soon as the attempt's
-  // flag word is set (the attempt is rejected, so its output is never used)
+  // the stage belongs to a step attempt and stops, 1: as soon as the attempt's
+  // flag word is set (the attempt is rejected, so its output is never used); 2:
+  // if a stage before it set the word (the last attempt that halving allows: its
+  // flags decide the status)
   int skip_flagged;
   // 2D only: a blend coefficient per face that takes the place of theta^s
   // (the density/pressure limiter then clamps it as it clamps theta^s), or
@@ -117,7 +119,7 @@ struct StageCoef {
   float* ts_out;
   // the forward-Euler step is dt_mul * dt (the stages of SSP-RK54)
   double dt_mul = 1.0;
-  // 1D, skip_flagged: the stage's place in its step (for its flags)
+  // skip_flagged: the stage's place in its step (for its flags)
   int stage = 0;
 };
 

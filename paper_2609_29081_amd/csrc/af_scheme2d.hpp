@@ -312,12 +312,13 @@ struct FaceCells {
 // high-order flux FH.  blend: a coefficient per face that takes the place of
 // theta^s, or NULL; ts_out: receives the coefficient used in its place per
 // face, or NULL.  own: the face belongs to this workgroup (others are computed
-// along, raise no flag and write nothing).
+// along, raise no flag and write nothing).  low: the flag raised where a low-order
+// state is inadmissible.
 template <typename R>
 __device__ __forceinline__ void limit_face(const G2& g, const PhysT<R>& ph, const Phys& phd, int d,
                                            int i, int j, double dt, const FaceCells<R>& c,
                                            const R* FH, const float* blend, float* ts_out, bool own,
-                                           unsigned* flags, R* F) {
+                                           unsigned* flags, unsigned low, R* F) {
   R ts = R(1.0);
   double tpp = 1.0;
   // the face's entries in per-face arrays: x-faces [n2][n1+1], then
@@ -373,7 +374,7 @@ __device__ __forceinline__ void limit_face(const G2& g, const PhysT<R>& ph, cons
                              theta_p2(ULm, pLm, Tm, mn(kPPEps, pLm), phd.gm1, ex));
         tpp = tr * tp;
       }
-      if (bad && own) raise_flag(flags, FLAG_CELL_LOW);
+      if (bad && own) raise_flag(flags, low);
     }
   }
   const double th = double(ts) * tpp;

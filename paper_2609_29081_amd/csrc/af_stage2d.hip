@@ -910,7 +910,7 @@ __global__ void __launch_bounds__(NT) k_stage(StageArgs sa) {
       }
       fc.phi1 = mx(T.C[12][cax], T.C[12][cbx]);
       fc.phi2 = mx(T.C[13][cax], T.C[13][cbx]);
-      limit_face(g, ph, phd, d, i, j, dt, fc, FH, blend, ts_out, true, flags, F);
+      limit_face(g, ph, phd, d, i, j, dt, fc, FH, blend, ts_out, true, flags, FLAG_CELL_LOW, F);
     }
     if (d == 0) {
 #pragma unroll

@@ -233,6 +233,7 @@ struct Ctx {
   double dt, ca, cb;
   int first;
   unsigned* flags;
+  int shift;           // of the flags raised (see kStageShift)
   const float* blend;  // see limit_face
   float* ts_out;
   int lane, i0;        // cell column of lane c: i0 - 2 + c
@@ -285,7 +286,7 @@ __device__ __forceinline__ void point_finish(const Ctx<R>& X, int t, int i, int 
     bool lbad = false;
     double th = theta_pair2(UL, UH, X.phd.gm1, lbad, X.ph.lim & LIM_PEXACT);
     if (X.ph.lim & LIM_LOWONLY) th = 0.0;
-    if (lbad && own) raise_flag(X.flags, FLAG_POINT_LOW);
+    if (lbad && own) raise_flag(X.flags, FLAG_POINT_LOW << X.shift);
     if (th != 1.0) {
 #pragma unroll
       for (int k = 0; k < 4; ++k) out[k] = UL[k] + th * (UH[k] - UL[k]);
@@ -637,15 +638,15 @@ __device__ __forceinline__ CellAvg<R> ring_cell(const Rings<R>& S, int slot, int
 
 // ---- wave_cells --------------------------------------------------------------------
 template <typename R>
-__device__ __forceinline__ void wave_cells(Rings<R>& S, const Ctx<R>& X, int skip_flagged) {
+__device__ __forceinline__ void wave_cells(Rings<R>& S, const Ctx<R>& X, unsigned stop_for) {
   const G2& g = X.g;
   const int c = X.lane, cl = c > 0 ? c - 1 : 0, cr = c < W - 1 ? c + 1 : W - 1;
   const Columns col = columns_of(X);
   Raw nav;
   issue<3>(X, col, X.j0 - 2, nav);
-  // inside a step attempt: stop once any workgroup has flagged it (it is
-  // rejected and its output is never read).  The flag word of the row before
-  // is the one that counts, so that nobody waits for its load.
+  // inside a step attempt: stop once any workgroup has raised a flag of stop_for
+  // (it is rejected and its output is never read).  The flag word of the row
+  // before is the one that counts, so that nobody waits for its load.
   unsigned fl = 0u;
   for (int k = 0; k < X.rows; ++k) {
     const int r = X.j0 - 2 + k, s = slot4(k);
@@ -671,7 +672,7 @@ __device__ __forceinline__ void wave_cells(Rings<R>& S, const Ctx<R>& X, int ski
       for (int n = 0; n < 4; ++n) S.AVD[n][s][c] = V[n];
     }
     if (mid_row(S)) return;
-    if (skip_flagged) fl = peek_flags(X.flags);
+    if (stop_for) fl = peek_flags(X.flags) & stop_for;
     if (k >= 2) {
       const int p0 = slot4(k), p1 = slot4(k - 1), p2 = slot4(k - 2);
       R o[12];
@@ -734,7 +735,8 @@ __device__ __forceinline__ void face_between(const Ctx<R>& X, int d, int i, int 
   }
   fc.phi1 = mx(a.phi1, b.phi1);
   fc.phi2 = mx(a.phi2, b.phi2);
-  limit_face(X.g, X.ph, X.phd, d, i, j, X.dt, fc, FH, blend, ts_out, own, X.flags, F);
+  limit_face(X.g, X.ph, X.phd, d, i, j, X.dt, fc, FH, blend, ts_out, own, X.flags,
+             FLAG_CELL_LOW << X.shift, F);
 }
 
 // total flux of direction D at a point of type t, gradients gr
@@ -1261,7 +1263,9 @@ struct StripArgs {
   const double* dt_dev;
   double dt_host, dt_mul;  // the step is dt_mul * dt
   unsigned* flags;
-  int nx, H, skip_flagged;
+  int nx, H;
+  int shift;          // of the flags this stage raises
+  unsigned stop_for;  // flags for which it stops
   const float* blend;  // see limit_face
   float* ts_out;
   // instances whose step machinery is on the device: their descriptors, the
@@ -1325,6 +1329,7 @@ __global__ void __launch_bounds__(NT) k_strip(StripArgs) {
                     p->cb,
                     p->first,
                     in_global(&inst->flags),
+                    kStageShift * k,
                     nullptr,
                     nullptr,
                     (int)(threadIdx.x & 63),
@@ -1349,6 +1354,7 @@ __global__ void __launch_bounds__(NT) k_strip(StripArgs) {
                     p->cb,
                     p->first,
                     in_global(p->flags),
+                    p->shift,
                     BLEND ? in_global(p->blend) : nullptr,
                     BLEND ? in_global(p->ts_out) : nullptr,
                     (int)(threadIdx.x & 63),
@@ -1357,6 +1363,14 @@ __global__ void __launch_bounds__(NT) k_strip(StripArgs) {
                     j1,
                     j1 - j0 + 5};
     }
+  };
+  auto stop_for = [&]() -> unsigned {
+    if constexpr (DEV)
+      return in_constant(inst)->halvings < in_constant(inst)->max_halvings
+                 ? ~0u
+                 : (1u << kStageShift * args()->k) - 1u;
+    else
+      return args()->stop_for;
   };
   bool nonfinite = false;
   double cfl_a = 0.0, cfl_v = 0.0;
@@ -1376,9 +1390,11 @@ __global__ void __launch_bounds__(NT) k_strip(StripArgs) {
     case 10: wave_edges(S, ctx()); break;
     case 3: wave_centre(S, ctx()); break;
     case 7: wave_yres0(S, ctx()); break;
-    default: wave_cells(S, ctx(), DEV || args()->skip_flagged); break;
+    default: wave_cells(S, ctx(), stop_for()); break;
   }
-  if (nonfinite) raise_flag(DEV ? &inst->flags : args()->flags, FLAG_NONFINITE);
+  if (nonfinite)
+    raise_flag(DEV ? &inst->flags : args()->flags,
+               FLAG_NONFINITE << (DEV ? kStageShift * args()->k : args()->shift));
   if constexpr (DEV) {
     // the workgroup's CFL maxima of the new state (lanes that wrote no cell
     // hold 0, neutral for max)
@@ -1444,7 +1460,8 @@ hipError_t launch(const afi::Geo& geo, const Phys& ph, const afi::Work& w, const
   sa.ca = sc.a;
   sa.cb = sc.b;
   sa.first = sc.first;
-  sa.skip_flagged = sc.skip_flagged;
+  sa.shift = sc.skip_flagged ? kStageShift * sc.stage : 0;
+  sa.stop_for = sc.skip_flagged == 0 ? 0u : (sc.skip_flagged == 1 ? ~0u : (1u << sa.shift) - 1u);
   sa.blend = sc.blend;
   sa.ts_out = sc.ts_out;
   const dim3 grid((unsigned)(b.nx * b.ny));
