@@ -200,6 +200,10 @@ af_status af_cfl_dt(af_ctx* ctx, const double* U, double t, double t_final, doub
  * (either may be NULL) receive the step actually taken. */
 af_status af_step(af_ctx* ctx, double* U, void* ws, void* stream, double dt, double t,
                   double t_final, double* dt_used, int* halvings);
+/* (The first call of af_step or af_run in a process allocates one page of pinned
+ * host memory, 64 slots that calls in progress read their results from; it is
+ * kept for the life of the process.  A call that finds no slot free copies from
+ * the device instead.) */
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, serving loops, harnesses that forbid hipMalloc): af_step with its

@@ -81,7 +81,7 @@ struct BatchInst {
 
 // device workspace carve-up (all device pointers)
 struct Work {
-  double* scal;      // [0] dt  [1] t  [2] steps taken  [3] spare
+  double* scal;      // [0] dt  [1] t  [2] steps taken  [3] 1D blocks: t of every other step
   unsigned* flags;   // sticky flag word
   unsigned long long* count;  // result of the admissibility count
   double* partial;   // CFL partial maxima [2][nb_cfl]
@@ -215,10 +215,10 @@ struct alignas(64) StepReport {
   unsigned flags;
 };
 hipError_t report(const Work& w, StepReport* out, hipStream_t s);
-// a state; flags, if not NULL, is a flag word cleared with it
 // B = ga B + gb A, A = wa u + wb A (the old A in both)
 hipError_t share_evaluation(double* A, double* B, const double* u, double wa, double wb, double ga,
                             double gb, long n, hipStream_t s);
+// a copy of a state; flags, if not NULL, is a flag word cleared with it
 hipError_t copy_state(double* dst, const double* src, long n, hipStream_t s,
                       unsigned* flags = nullptr);
 // out = a x + b y over n values (out may be x or y)

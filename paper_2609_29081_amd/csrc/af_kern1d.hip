@@ -24,7 +24,9 @@
 // of a tile are its own in SSP-RK3, 61 - 16 in SSP-RK54.  That is 1.15 and 1.36
 // times the work, and one launch, one read and one write of the state instead
 // of three or five: a step of a run of 800 cells took 21.7 us with a launch per
-// stage and takes 14.8, one of SSP-RK54 at 160 cells (af_step) 62 and 38.5.
+// stage and takes 15.0, one of SSP-RK54 at 160 cells (af_step) 62 and 36.4.  The
+// step kernel takes 197 VGPRs and spills 47 scalar registers (into lanes of
+// vector ones, no memory): its arguments are held across the stages.
 #include "af_device.hpp"
 #include "af_internal.hpp"
 

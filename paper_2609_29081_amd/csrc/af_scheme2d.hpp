@@ -208,9 +208,9 @@ __device__ __forceinline__ void compact2(const R* z, R& col, R& quad) {
 // stencils keep every factor at its site: the shorter order moves a step of a
 // smooth flow by 2e-9 to 7e-9 (of the tube, whose steps are short, by 1e-10),
 // as much as a third of its distance from 64 bits, for callers who have such
-// runs to compare with, and gains little there (an RK3 step at 1000 x 500 221.3
-// us so, 222.0 with the factors; eight grids up to 512 x 256, three steps, 1458
-// and 1484).
+// runs to compare with, and gains little there (the stage 264 us so at 2048 x 1024
+// and 270 with the factors; eight grids up to 512 x 256, three steps, 1463 and
+// 1477).
 enum LineValue { kRho, kMd, kMo, kE, kVa, kVb, kP, kT };
 template <typename R, typename At>
 __device__ __forceinline__ void line_terms(const PhysT<R>& ph, double h, R alpha, At at,

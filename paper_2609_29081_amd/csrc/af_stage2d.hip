@@ -1,7 +1,8 @@
-// af_stage2d.hip -- one SSP-RK3 stage of a batch of 2D instances on gfx950 as
-// a single fused, LDS-tiled kernel: the tile variants of af_batch_set_variant
-// and af_batch_tune, and the stage of batches of grids too narrow for the
-// strips of af_strip2d.hip, which give the same bits.
+// af_stage2d.hip -- one stage of a 2D instance, or of a batch of them, on gfx950
+// as a single fused, LDS-tiled kernel: the tile variants of af_batch_set_variant
+// and af_batch_tune, and the stage of grids too narrow for the strips of
+// af_strip2d.hip (batches: strip_shapes, single instances: single_on_tiles),
+// which give the same bits.
 //
 // A workgroup owns a tile of TX x TY cells, i.e. the half-lattice block
 // [X0, X0+2TX) x [Y0, Y0+2TY): the cell averages, x-edge, y-edge and corner

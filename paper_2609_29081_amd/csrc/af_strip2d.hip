@@ -41,11 +41,12 @@
 // half has to wait for is kept short, and three waves per SIMD, which FP64 at
 // 168 registers a wave just allows, hide each other's waits.
 //
-// Measured, stage of the shock tube (tile kernel, this):
-//   1000 x 500   FP64 208, 101 us   FP32 stencils 157, 74 us
-//   2048 x 1024  FP64 860, 349 us   FP32 stencils 660, 265 us
-//   400 x 200    FP64 42, 25 us
-//   64 x 32      FP64 28, 12.1 us   FP32 stencils 42, 10.4 us
+// Measured, stage of the shock tube (tile kernel, this; the card's clock under
+// this load differs from hour to hour, 87 to 101 us for the first):
+//   1000 x 500   FP64 210, 87 us    FP32 stencils 157, 70 us
+//   2048 x 1024  FP64 879, 341 us   FP32 stencils 671, 270 us
+//   400 x 200    FP64 41, 25 us     FP32 stencils 40, 21 us
+//   64 x 32      FP64 28, 12.8 us   FP32 stencils 42, 11.0 us
 // On the way, at 1000 x 500 in FP64: 125 with eight waves (two per SIMD), 107
 // with twelve, 103 with shorter maxima, square roots, limiters and addresses,
 // 101 with fewer operations in the residuals.

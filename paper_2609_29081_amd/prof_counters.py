@@ -87,8 +87,8 @@ def target(reps: int = 10, mixed: bool = False, wl: str = "tube", n1: int = N1,
 
 def target_batch(steps: int = 3) -> None:
     """the batched form's launches: the 64-instance shock-tube sweep (mixed
-    precision), tuned, then `steps` accepted steps of every instance with
-    HIP-graph replay (for a kernel trace of the batch stage kernel)"""
+    precision), tuned, then `steps` accepted steps of every instance in slots of
+    four rounds (for a kernel trace of the batch stage kernel)"""
     sys.path.insert(0, ROOT)
     from paper_2609_29081_amd import af
     from paper_2609_29081_amd import workloads as W
@@ -101,8 +101,8 @@ def target_batch(steps: int = 3) -> None:
     B.af_batch_tune(states, 0.0, 1e30, reps=1)
     st, n, t, att = B.af_batch_run(states, 0.0, 1e30, steps, attempts_per_slot=4, use_graph=True)
     assert st == [af.AF_OK] * len(insts)
-    print("target done: variant", af.stage_variants()[B.variant][0], "attempts", sum(att),
-          flush=True)
+    print("target done:", "strips" if B.on_strips else af.stage_variants()[B.variant][0],
+          "attempts", sum(att), flush=True)
 
 
 def target_learned(steps: int = 3) -> None:
