@@ -173,27 +173,6 @@ __device__ __forceinline__ void tot_flux(int d, const R* U, R u, R v, R p, const
   F[3] = (U[3] + p) * ud - Fv[3];
 }
 
-// differences along a line of five sites: 6h D_c of z, and the undivided fourth
-// difference
-template <typename R>
-__device__ __forceinline__ R diff5(R zm2, R zm1, R zp1, R zp2) {
-  return (zm2 - zp2) + R(8.0) * (zp1 - zm1);
-}
-// the form sum_mn b_mn z_m z_n and the column sums sum_n (sum_m b_mn) z_n of the
-// compact second-derivative matrix B, from the differences to the middle site:
-// every row of B sums to zero, so the form of z is that of the differences plus
-// z_2 times the column sums
-template <typename R>
-__device__ __forceinline__ void compact2(const R* z, R& col, R& quad) {
-  const R d0 = z[0] - z[2], d1 = z[1] - z[2], d3 = z[3] - z[2], d4_ = z[4] - z[2];
-  col = R(-1.0 / 12.0) * (d0 + d4_) + R(4.0 / 3.0) * (d1 + d3);
-  const R t0 = R(-1.0 / 8.0) * d0 + R(1.0 / 3.0) * d1;
-  const R t1 = R(1.0 / 2.0) * d1 + R(1.0 / 3.0) * d3;
-  const R t3 = R(1.0 / 2.0) * d3 + R(1.0 / 3.0) * d4_;
-  const R t4 = R(-1.0 / 8.0) * d4_;
-  quad = d0 * t0 + d1 * t1 + d3 * t3 + d4_ * t4 + z[2] * col;
-}
-
 // direction-D terms of the residual of a point, from the five sites of its line:
 // the biased inviscid operators as central difference plus dissipation with
 // alpha, compact D^{(d),2}(K_dd, Z), and the mixed terms from the derivatives
@@ -202,21 +181,18 @@ __device__ __forceinline__ void compact2(const R* z, R& col, R& quad) {
 // and across, energy, velocity along D and across, pressure, temperature.  Rr:
 // density, momentum along D and across, energy.
 //
-// In FP64 constants come after the differences and the form of B from
-// differences (120 of 3100 operations per row of a strip fewer, 357 -> 351 us
-// for the stage at 2048 x 1024), which moves a step by 4e-17 at most.  FP32
-// stencils keep every factor at its site: the shorter order moves a step of a
-// smooth flow by 2e-9 to 7e-9 (of the tube, whose steps are short, by 1e-10),
-// as much as a third of its distance from 64 bits, for callers who have such
-// runs to compare with, and gains little there (the stage 264 us so at 2048 x 1024
-// and 270 with the factors; eight grids up to 512 x 256, three steps, 1463 and
-// 1477).
+// Every factor is applied at its site.  With the constants after the differences
+// and the form of B from differences the sum takes 120 of 3100 operations per row
+// of a strip less (the stage at 2048 x 1024 351 us instead of 357, FP32 stencils
+// 264 instead of 270), but rounds otherwise.  A step with FP32 stencils moves by up
+// to 7e-9 of a smooth flow's state, a third of its distance from 64 bits.  One in
+// FP64 moves by 4e-17, which was enough to keep SSP-RK54 in the opening transient of
+// the 1000 x 500 tube: from t = 3.5e-4 on every step was halved some 36 times.
 enum LineValue { kRho, kMd, kMo, kE, kVa, kVb, kP, kT };
 template <typename R, typename At>
 __device__ __forceinline__ void line_terms(const PhysT<R>& ph, double h, R alpha, At at,
                                            const R* ga, const R* gb, R* Rr) {
-  constexpr bool kShort = std::is_same<R, double>::value;
-  const R n6h = R(-1.0 / (6.0 * h)), i6h = R(1.0 / (6.0 * h)), s4 = R(4.0 / (h * h));
+  const R i6h = R(1.0 / (6.0 * h));
   const R ai = alpha * i6h;
   R va[5], vb[5], Tt[5];
 #pragma unroll
@@ -225,7 +201,7 @@ __device__ __forceinline__ void line_terms(const PhysT<R>& ph, double h, R alpha
     vb[o] = at(kVb, o);
     Tt[o] = at(kT, o);
   }
-  // one component at a time (short live ranges)
+  // inviscid, one component at a time (short live ranges)
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     R f[5], w[5];
@@ -236,50 +212,29 @@ __device__ __forceinline__ void line_terms(const PhysT<R>& ph, double h, R alpha
                     : (k == 1 ? w[o] * va[o] + at(kP, o)
                               : (k == 2 ? w[o] * va[o] : (w[o] + at(kP, o)) * va[o]));
     }
-    if constexpr (kShort)
-      Rr[k] = diff5(f[0], f[1], f[3], f[4]) + alpha * d4(w[0], w[1], w[2], w[3], w[4]);
-    else
-      Rr[k] = -(dc5(f[0], f[1], f[3], f[4], i6h) + ai * d4(w[0], w[1], w[2], w[3], w[4]));
+    Rr[k] = -(dc5(f[0], f[1], f[3], f[4], i6h) + ai * d4(w[0], w[1], w[2], w[3], w[4]));
   }
-  if constexpr (kShort) {
-    const R mu = ph.mu, mu23 = R(2.0 / 3.0) * ph.mu;
-    const R s4m = s4 * mu, s4m43 = s4 * (R(4.0 / 3.0) * ph.mu), s4k = s4 * ph.kap;
-    R n[5];
+  // compact D^{(d),2}(K_dd, Z)
+  const R s4 = R(4.0 / (h * h));
+  const R mu = ph.mu, m43 = R(4.0 / 3.0) * ph.mu;
+  Rr[1] += s4 * m43 * bcol(va);
+  Rr[2] += s4 * mu * bcol(vb);
+  Rr[3] += s4 * (m43 * bquad(va) + mu * bquad(vb) + ph.kap * bcol(Tt));
+  // mixed
+  R m1[5], m2[5], m3[5];
 #pragma unroll
-    for (int o = 0; o < 5; ++o)
-      n[o] = o == 2 ? R(0.0) : vb[o] * ga[o] - R(2.0 / 3.0) * (va[o] * gb[o]);
-    Rr[1] += mu23 * diff5(gb[0], gb[1], gb[3], gb[4]);
-    Rr[2] -= mu * diff5(ga[0], ga[1], ga[3], ga[4]);
-    Rr[3] -= mu * diff5(n[0], n[1], n[3], n[4]);
-    R ca, qa, cb, qb;
-    compact2(va, ca, qa);
-    compact2(vb, cb, qb);
-    Rr[0] = n6h * Rr[0];
-    Rr[1] = n6h * Rr[1] + s4m43 * ca;
-    Rr[2] = n6h * Rr[2] + s4m * cb;
-    Rr[3] = n6h * Rr[3] + s4m43 * qa;
-    Rr[3] += s4m * qb;
-    Rr[3] += s4k * bcol(Tt);
-  } else {
-    const R mu = ph.mu, m43 = R(4.0 / 3.0) * ph.mu;
-    Rr[1] += s4 * m43 * bcol(va);
-    Rr[2] += s4 * mu * bcol(vb);
-    Rr[3] += s4 * (m43 * bquad(va) + mu * bquad(vb) + ph.kap * bcol(Tt));
-    R m1[5], m2[5], m3[5];
-#pragma unroll
-    for (int o = 0; o < 5; ++o) {
-      if (o == 2) {
-        m1[o] = m2[o] = m3[o] = R(0.0);
-        continue;
-      }
-      m1[o] = -R(2.0 / 3.0) * mu * gb[o];
-      m2[o] = mu * ga[o];
-      m3[o] = mu * (vb[o] * ga[o] - R(2.0 / 3.0) * va[o] * gb[o]);
+  for (int o = 0; o < 5; ++o) {
+    if (o == 2) {
+      m1[o] = m2[o] = m3[o] = R(0.0);
+      continue;
     }
-    Rr[1] += dc5(m1[0], m1[1], m1[3], m1[4], i6h);
-    Rr[2] += dc5(m2[0], m2[1], m2[3], m2[4], i6h);
-    Rr[3] += dc5(m3[0], m3[1], m3[3], m3[4], i6h);
+    m1[o] = -R(2.0 / 3.0) * mu * gb[o];
+    m2[o] = mu * ga[o];
+    m3[o] = mu * (vb[o] * ga[o] - R(2.0 / 3.0) * va[o] * gb[o]);
   }
+  Rr[1] += dc5(m1[0], m1[1], m1[3], m1[4], i6h);
+  Rr[2] += dc5(m2[0], m2[1], m2[3], m2[4], i6h);
+  Rr[3] += dc5(m3[0], m3[1], m3[3], m3[4], i6h);
 }
 
 // wall projection of a point value (no-slip: zero momentum; symmetry: zero
