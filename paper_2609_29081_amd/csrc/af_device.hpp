@@ -406,13 +406,9 @@ __device__ __forceinline__ double bvisc1(double p, double T, double ux, double T
 // keeps where a flag came from: four bits a stage above those of FLAG_*, 23 in
 // all for SSP-RK54.
 constexpr int kAttemptBit = 3, kStageBits = 4;
-struct StageFlags {
-  unsigned cell_low, cells_nonfinite, point_low, points_nonfinite;
-};
-__device__ __forceinline__ StageFlags attempt_flags(int stage) {
-  const unsigned f = 1u << (kAttemptBit + kStageBits * stage);
-  return StageFlags{f, f << 1, f << 2, f << 3};
-}
+enum : unsigned { STAGE_CELL_LOW = 1u, STAGE_CELLS_NONFINITE = 2u, STAGE_POINT_LOW = 4u,
+                  STAGE_POINTS_NONFINITE = 8u };
+__device__ __forceinline__ int attempt_shift(int stage) { return kAttemptBit + kStageBits * stage; }
 // In 2D a stage of an attempt is one launch, and strips stop in the middle of it
 // once the attempt is rejected, which leaves out what the rest of it would have
 // raised: a NaN would be known by the inadmissible face beside it, that is met
@@ -431,9 +427,10 @@ inline unsigned first_flags(unsigned word, int dim) {
   if (word < (1u << kAttemptBit)) return word;
   unsigned f = word >> kAttemptBit;
   while (!(f & 15u)) f >>= kStageBits;
-  if (f & 1u) return FLAG_CELL_LOW;
-  if (f & 2u) return FLAG_NONFINITE;
-  return ((f & 4u) ? FLAG_POINT_LOW : 0u) | ((f & 8u) ? FLAG_NONFINITE : 0u);
+  if (f & STAGE_CELL_LOW) return FLAG_CELL_LOW;
+  if (f & STAGE_CELLS_NONFINITE) return FLAG_NONFINITE;
+  return ((f & STAGE_POINT_LOW) ? FLAG_POINT_LOW : 0u) |
+         ((f & STAGE_POINTS_NONFINITE) ? FLAG_NONFINITE : 0u);
 }
 
 // sticky flag word

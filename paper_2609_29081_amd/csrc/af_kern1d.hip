@@ -24,8 +24,8 @@
 // of a tile are its own in SSP-RK3, 61 - 16 in SSP-RK54.  That is 1.15 and 1.36
 // times the work, and one launch, one read and one write of the state instead
 // of three or five: a step of a run of 800 cells took 21.7 us with a launch per
-// stage and takes 15.0, one of SSP-RK54 at 160 cells (af_step) 62 and 36.4.  The
-// step kernel takes 197 VGPRs and spills 47 scalar registers (into lanes of
+// stage and takes 15.1, one of SSP-RK54 at 160 cells (af_step) 62 and 36.5.  The
+// step kernel takes 197 VGPRs and spills 49 scalar registers (into lanes of
 // vector ones, no memory): its arguments are held across the stages.
 #include "af_device.hpp"
 #include "af_internal.hpp"
@@ -206,11 +206,9 @@ __device__ __forceinline__ void cell_site(const G1& g, const Phys& ph, const Src
   for (int k = 0; k < 3; ++k) S.C[7 + k][t] = C0[k];
 }
 
-// limited flux of the face between ring cells a and a + 1, at lattice entry q; low
-// is added to the flags raised where a low-order state is inadmissible
+// limited flux of the face between ring cells a and a + 1, at lattice entry q
 __device__ __forceinline__ void face_flux(const G1& g, const Phys& ph, const Tile1& S, int a, int q,
-                                          double dt, unsigned low, unsigned& raised,
-                                          double* F) {
+                                          double dt, unsigned& raised, double* F) {
   const int b = a + 1;
   double FH[3];
   {
@@ -283,7 +281,7 @@ __device__ __forceinline__ void face_flux(const G1& g, const Phys& ph, const Til
                                theta_p1(ULm, pLm, Tm, mn(kPPEps, pLm), ph.gm1, ex));
           tpp = tr * tp;
         }
-        if (bad) raised |= low;
+        if (bad) raised |= STAGE_CELL_LOW;
       }
     }
     const double th = ts * tpp;
@@ -311,8 +309,8 @@ __device__ __forceinline__ void lo_site1(const Phys& ph, const double (&V)[5][3]
 // forward-Euler value of point k0 (lattice entry q, ring cells r0 and r0 + 1
 // at its sides) into out
 __device__ __forceinline__ void point_update(const G1& g, const Phys& ph, const Tile1& S, int k0,
-                                             int q, int r0, double dt, unsigned low,
-                                             unsigned& raised, double* out) {
+                                             int q, int r0, double dt, unsigned& raised,
+                                             double* out) {
   const int X = 2 * k0;
   const double i6h = 1.0 / (6.0 * g.dx);
   double Us[5][3], u[5], p[5], T[5];
@@ -392,7 +390,7 @@ __device__ __forceinline__ void point_update(const G1& g, const Phys& ph, const 
     bool lbad = false;
     double th = theta_pair1(UL, UH, ph.gm1, lbad, ph.lim & LIM_PEXACT);
     if (ph.lim & LIM_LOWONLY) th = 0.0;
-    if (lbad) raised |= low;
+    if (lbad) raised |= STAGE_POINT_LOW;
     if (th != 1.0) {
 #pragma unroll
       for (int k = 0; k < 3; ++k) out[k] = UL[k] + th * (UH[k] - UL[k]);
@@ -424,10 +422,8 @@ __global__ void __launch_bounds__(kThreads) k_stage1(G1 g, Phys ph, Stage1 st,
   // inside a step attempt: stop if a stage before this one raised a flag (the
   // attempt is rejected and the output never read); for one of this stage's own a
   // late tile does not, since its flags may come before
-  const StageFlags fl =
-      st.skip_flagged ? attempt_flags(st.stage)
-                      : StageFlags{FLAG_CELL_LOW, FLAG_NONFINITE, FLAG_POINT_LOW, FLAG_NONFINITE};
-  if (tid == 0) S.stop = st.skip_flagged ? peek_flags(st.flags) & (fl.cell_low - 1u) : 0u;
+  const int shift = attempt_shift(st.stage);
+  if (tid == 0) S.stop = st.skip_flagged ? peek_flags(st.flags) & ((1u << shift) - 1u) : 0u;
   // entry t of the tile's lattice is site 2 i0 - 2 + t; ring entry t is cell
   // i0 - 1 + t
   const Global1 U{Uk};
@@ -450,7 +446,7 @@ __global__ void __launch_bounds__(kThreads) k_stage1(G1 g, Phys ph, Stage1 st,
   };
   if (wave == 0) {
     double F[3] = {0.0, 0.0, 0.0};
-    if (nc > 0 && lane <= nc) face_flux(g, ph, S, lane, 2 * lane + 2, dt, fl.cell_low, raised, F);
+    if (nc > 0 && lane <= nc) face_flux(g, ph, S, lane, 2 * lane + 2, dt, raised, F);
     const double m = dt / g.dx;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
@@ -459,12 +455,17 @@ __global__ void __launch_bounds__(kThreads) k_stage1(G1 g, Phys ph, Stage1 st,
     }
   } else if (wave == 1 && lane < npt) {
     double out[3];
-    point_update(g, ph, S, i0 + lane, 2 * lane + 2, lane, dt, fl.point_low, raised, out);
+    point_update(g, ph, S, i0 + lane, 2 * lane + 2, lane, dt, raised, out);
 #pragma unroll
     for (int k = 0; k < 3; ++k) combine(g.off_pts + (long)k * g.np + i0 + lane, out[k]);
   }
-  if (!ok) raised |= wave == 0 ? fl.cells_nonfinite : fl.points_nonfinite;
-  if (raised) raise_flag(st.flags, raised);
+  if (!ok) raised |= wave == 0 ? STAGE_CELLS_NONFINITE : STAGE_POINTS_NONFINITE;
+  if (raised)
+    raise_flag(st.flags, st.skip_flagged
+                             ? raised << shift
+                             : ((raised & STAGE_CELL_LOW) ? FLAG_CELL_LOW : 0u) |
+                                   ((raised & STAGE_POINT_LOW) ? FLAG_POINT_LOW : 0u) |
+                                   (ok ? 0u : FLAG_NONFINITE));
 }
 
 // a whole step from U to Uout (other memory: neighbouring tiles read U)
@@ -542,7 +543,7 @@ __global__ void __launch_bounds__(kThreads) k_step1(G1 g, Phys ph, Step1 st,
     *st.x.t_out = dt0 > 0.0 ? t + dt0 : t;
     if (dt0 > 0.0) *st.x.steps = *st.x.steps + 1.0;
   }
-  unsigned raised = 0u;
+  unsigned all = 0u;
   // the lane's cell (wave 0) or point (wave 1): the step's first state, and
   // SSP-RK54's second stage, which its last one builds on
   double un[3], u2[3] = {0.0, 0.0, 0.0}, now[3];
@@ -568,7 +569,7 @@ __global__ void __launch_bounds__(kThreads) k_step1(G1 g, Phys ph, Step1 st,
     if (st.mul[s] != 1.0) dt = st.mul[s] * dt;
     const double ca = st.ca[s], cb = st.cb[s];
     const bool first = ca == 0.0, five = st.stages == 5;
-    const StageFlags fl = attempt_flags(s);
+    unsigned raised = 0u;
     bool ok = true;
     // the stage's combinations for the forward-Euler value fe of component k
     auto combine = [&](int k, double fe) {
@@ -585,7 +586,7 @@ __global__ void __launch_bounds__(kThreads) k_step1(G1 g, Phys ph, Step1 st,
     if (wave == 0) {
       double F[3] = {0.0, 0.0, 0.0};
       if (real_face && lane >= 2 * s && lane <= kCells - 2 * s)
-        face_flux(g, ph, S, lane, 2 * lane + 2, dt, fl.cell_low, raised, F);
+        face_flux(g, ph, S, lane, 2 * lane + 2, dt, raised, F);
       const double m = dt / g.dx;
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
@@ -597,14 +598,15 @@ __global__ void __launch_bounds__(kThreads) k_step1(G1 g, Phys ph, Step1 st,
       }
     } else if (wave == 1 && real_point && lane >= 2 * s && lane <= kCells - 2 * s) {
       double out[3];
-      point_update(g, ph, S, j, 2 * lane + 2, lane, dt, fl.point_low, raised, out);
+      point_update(g, ph, S, j, 2 * lane + 2, lane, dt, raised, out);
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
         combine(k, out[k]);
         H.P[k][lane + 1] = now[k];
       }
     }
-    if (!ok) raised |= wave == 0 ? fl.cells_nonfinite : fl.points_nonfinite;
+    if (!ok) raised |= wave == 0 ? STAGE_CELLS_NONFINITE : STAGE_POINTS_NONFINITE;
+    all |= raised << attempt_shift(s);
     __syncthreads();
   }
   if (lane >= halo && lane < halo + own) {
@@ -614,7 +616,7 @@ __global__ void __launch_bounds__(kThreads) k_step1(G1 g, Phys ph, Step1 st,
       if (wave == 1 && j < g.np) Uout[g.off_pts + (long)k * g.np + j] = now[k];
     }
   }
-  if (raised) raise_flag(st.flags, raised);
+  if (all) raise_flag(st.flags, all);
 }
 
 G1 geo1(const afi::Geo& geo) {

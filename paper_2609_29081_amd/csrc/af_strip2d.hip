@@ -30,8 +30,8 @@
 // stays in its registers.
 //
 // What bounds it: vector instructions and, in FP64, the power they take.  A step
-// of a strip takes 5,060 cycles (FP32 stencils: 4,020) for 2,990 (2,890) vector
-// instructions on four SIMDs, which are busy 62 % (74 %) of the time; LDS is
+// of a strip takes 5,110 cycles (FP32 stencils: 4,110) for 3,100 (3,010) vector
+// instructions on four SIMDs, which are busy 64 % (75 %) of the time; LDS is
 // busy 45 % and HBM a fifth.  An FP64 instruction takes 4.4 cycles of its SIMD
 // whatever it depends on, and under a stream of them the clock falls from 2.4
 // to about 2.05 GHz, so that large FP64 stages gain only from fewer
@@ -43,13 +43,13 @@
 //
 // Measured, stage of the shock tube (tile kernel, this; the card's clock under
 // this load differs from hour to hour, 87 to 101 us for the first):
-//   1000 x 500   FP64 210, 87 us    FP32 stencils 157, 70 us
-//   2048 x 1024  FP64 879, 341 us   FP32 stencils 671, 270 us
-//   400 x 200    FP64 41, 25 us     FP32 stencils 40, 21 us
-//   64 x 32      FP64 28, 12.8 us   FP32 stencils 42, 11.0 us
+//   1000 x 500   FP64 210, 88 us    FP32 stencils 157, 70 us
+//   2048 x 1024  FP64 878, 343 us   FP32 stencils 670, 269 us
+//   400 x 200    FP64 41, 26 us     FP32 stencils 40, 21 us
+//   64 x 32      FP64 28, 12.8 us   FP32 stencils 42, 11.2 us
 // On the way, at 1000 x 500 in FP64: 125 with eight waves (two per SIMD), 107
-// with twelve, 103 with shorter maxima, square roots, limiters and addresses,
-// 101 with fewer operations in the residuals.
+// with twelve, 103 with shorter maxima, square roots, limiters and addresses
+// (all on one day, at the slower clock).
 //
 // The arithmetic is the tile kernel's, expression by expression, so the two
 // give the same bits.  The tile kernel remains for batches (see strip_shapes, and
